@@ -43,9 +43,9 @@ int lq_test_orthonormalize(float* X, int l, int64_t m, int64_t ldx, double* scra
 /* Eigen-decomposition of the symmetric l x l fp64 matrix G (destroyed): eigenvalues descending in
  * lambda (l doubles), eigenvectors as rows of Ut (l x l fp32).  scratch: l * l doubles. */
 int lq_test_sym_eig(double* G, int l, float* Ut, double* lambda, double* scratch, void* stream);
-/* fp32 one-sided Jacobi variant used inside the decomposition for l <= 128 (multiple of 32): rows of Ut are
- * approximate eigenvectors of the symmetric fp64 G (left untouched), ordered by descending eigenvalue
- * estimate lambda (fp32 accuracy). */
+/* The eigen-solver used inside the decomposition for l <= 128 (multiple of 32): rows of Ut are the eigenvectors of the
+ * symmetric fp64 G (left untouched) rounded to fp32, ordered by descending eigenvalue lambda.  Uses a scratch array of the
+ * testing library: calls that overlap in time race. */
 int lq_test_sym_eig_fast(const double* G, int l, float* Ut, double* lambda, void* stream);
 /* The small kernels of the cold-start filter, one launch each on device arrays of l rows with leading dimension ldx
  * (a multiple of 4, m <= ldx):

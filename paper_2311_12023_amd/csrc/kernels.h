@@ -148,10 +148,11 @@ int launch_trsm(const double* Cfac, int l, float* X, int64_t m, int64_t ldx, siz
 // sorted by descending eigenvalue: lambda[z][l] and Ut[z] (l x l fp32, row j = j-th eigenvector).
 // `vt` holds batch * l * l doubles of scratch.
 int launch_jacobi_eig(double* G, int l, double* vt, float* Ut, double* lambda, int batch, hipStream_t st);
-// Approximate eigenvectors (fp32 one-sided Jacobi in LDS, l <= 128) of the symmetric G[z]: rows of Ut[z] ordered by
-// descending eigenvalue estimate (lambda[z], accurate to fp32 only).  G is not modified.
-bool jacobi_fast_supported(int l);
-int launch_jacobi_fast(const double* G, int l, float* Ut, double* lambda, int batch, hipStream_t st);
+// Eigen-decomposition of the symmetric G[z] (l x l fp64, l = 32, 64, 96 or 128; eig_kernels.hip): rows of Ut[z] ordered by
+// descending eigenvalue lambda[z].  G is not modified.  work: batch * sym_eig_work_doubles(l) doubles of scratch.
+bool sym_eig_supported(int l);
+constexpr size_t sym_eig_work_doubles(int l) { return (size_t)2 * l * l; }
+int launch_sym_eig(const double* G, int l, double* work, float* Ut, double* lambda, int batch, hipStream_t st);
 // lam[z][i] = squared norm of row i of the wide matrix X[z] (l x m), fp64.
 int launch_ritz_residual(const float* G, const float* Y, const double* lam, int rows, int64_t m, int64_t ldx, double* res,
                          hipStream_t st);

@@ -106,7 +106,7 @@ static void make_plan(int64_t d, int64_t k, int rank, const Params& prm, int bat
   const size_t ll = (size_t)l1 * l1;
   pl.gram_part = take((size_t)batch * GRAM_CHUNKS * ll * 8);
   pl.G = take((size_t)batch * ll * 8);
-  pl.Vt = take((size_t)batch * ll * 8);
+  pl.Vt = take((size_t)batch * std::max(ll, sym_eig_work_doubles(std::min(l1, 128))) * 8);
   pl.Ut = take((size_t)batch * ll * 4);
   pl.lam = take((size_t)batch * l1 * 8);
   pl.lam_cold = take((size_t)l1 * 8);
@@ -180,8 +180,8 @@ static int ritz_rotate(const Ctx& c, int l, const float* Y, float* Y2, size_t sY
   double* G = c.at<double>(pl.G);
   float* Ut = c.at<float>(pl.Ut);
   LQ_TRY(launch_gram(B, l, pl.k, pl.ldk, sB, c.at<double>(pl.gram_part), G, batch, c.st));
-  const bool fast = jacobi_fast_supported(l);
-  if (fast) LQ_TRY(launch_jacobi_fast(G, l, Ut, lambda, batch, c.st));
+  const bool fast = sym_eig_supported(l);
+  if (fast) LQ_TRY(launch_sym_eig(G, l, c.at<double>(pl.Vt), Ut, lambda, batch, c.st));
   else LQ_TRY(launch_jacobi_eig(G, l, c.at<double>(pl.Vt), Ut, lambda, batch, c.st));
   LQ_TRY(launch_wide_gemm(MODE_NN, l, pl.ldd, l, Ut, l, (size_t)l * l, Y, pl.ldd, sY, Y2, pl.ldd, sY, batch, nullptr, 0,
                           c.st));

@@ -20,6 +20,8 @@ Capture& capture() {
 
 using namespace lq;
 
+static __device__ double g_eig_work[lq::sym_eig_work_doubles(128)];
+
 extern "C" {
 
 int lq_test_capture_iterate(int cfg_index, int iter, float* Q_dense, double* sigma_next) {
@@ -81,8 +83,10 @@ int lq_test_sym_eig(double* G, int l, float* Ut, double* lambda, double* scratch
 
 int lq_test_sym_eig_fast(const double* G, int l, float* Ut, double* lambda, void* stream) {
   if (!G || !Ut || !lambda) return LQ_ERR_NULL;
-  if (!jacobi_fast_supported(l)) return LQ_ERR_ARG;
-  return launch_jacobi_fast(G, l, Ut, lambda, 1, (hipStream_t)stream);
+  if (!sym_eig_supported(l)) return LQ_ERR_ARG;
+  void* work = nullptr;
+  LQ_HIP_TRY(hipGetSymbolAddress(&work, HIP_SYMBOL(g_eig_work)));
+  return launch_sym_eig(G, l, static_cast<double*>(work), Ut, lambda, 1, (hipStream_t)stream);
 }
 
 int lq_test_lincomb3(float* X, float a, const float* Y, float b, const float* Z, float c, int l, int64_t ldx, void* stream) {

@@ -1,0 +1,74 @@
+"""The eigen-solver of the Rayleigh-Ritz step over the spectra that decide its route: separated eigenvalues (tridiagonal
+route), repeated, zero and nearly equal ones (one-sided Jacobi inside the same launch), graded and diagonal matrices.
+
+Tolerances: rows of fp32 numbers that are orthonormal to 2^-24 per entry, or to 1e-6 per pair on the Jacobi route and at
+the smallest gap the tridiagonal route accepts (2e-9 of the largest eigenvalue): 4e-6.  A Rayleigh quotient misses its
+eigenvalue by the square of the vector's error, or by the vector's rounding (2^-24 per entry, both factors, entries of G up
+to lambda_1): 4e-7 of the largest eigenvalue covers both."""
+import numpy as np
+import pytest
+
+from testing_lib import load
+
+pytestmark = pytest.mark.gpu
+
+
+def _spectrum(kind, l, rng):
+    if kind == "flat":                       # a bulk under a few dominant values, as a weight matrix has it
+        return np.concatenate([[900.0, 400.0, 120.0], 1.08 - 0.08 * np.sort(rng.random(l - 3))])
+    if kind == "geometric":
+        return 0.8 ** np.arange(l)
+    if kind == "repeated":
+        return np.repeat([7.0, 3.0], l // 2)
+    if kind == "low_rank":
+        return np.concatenate([np.linspace(2.0, 1.0, l // 4), np.zeros(l - l // 4)])
+    if kind == "one_pair":                   # two eigenvalues 1e-11 apart among separated ones
+        s = np.linspace(4.0, 1.0, l)
+        s[5] = s[4] * (1 - 1e-11)
+        return s
+    if kind == "smallest_gap":               # just above the line of the tridiagonal route
+        s = np.linspace(4.0, 1.0, l)
+        s[5] = s[4] - 1.0e-8 * 4.0
+        return s
+    raise ValueError(kind)
+
+
+def _solve(g):
+    import torch
+    L = load()
+    l = g.shape[0]
+    gt = torch.from_numpy(g.copy()).cuda()
+    ut = torch.full((l, l), float("nan"), dtype=torch.float32, device="cuda")
+    lam = torch.full((l,), float("nan"), dtype=torch.float64, device="cuda")
+    assert L.lq_test_sym_eig_fast(gt.data_ptr(), l, ut.data_ptr(), lam.data_ptr(), None) == 0
+    torch.cuda.synchronize()
+    return ut.cpu().numpy().astype(np.float64), lam.cpu().numpy()
+
+
+@pytest.mark.parametrize("l", [32, 64, 96, 128])
+@pytest.mark.parametrize("kind", ["flat", "geometric", "repeated", "low_rank", "one_pair", "smallest_gap"])
+@pytest.mark.parametrize("scale", [1.0, 1e-13, 1e11])
+def test_spectra(l, kind, scale):
+    rng = np.random.default_rng(l)
+    s = _spectrum(kind, l, rng)
+    q, _ = np.linalg.qr(rng.standard_normal((l, l)))
+    g = (q * s) @ q.T * scale
+    g = (g + g.T) / 2
+    u, lam = _solve(g)
+    ref = np.sort(s)[::-1] * scale
+    assert np.all(np.isfinite(u)) and np.all(np.diff(lam) <= 0)
+    assert np.max(np.abs(u @ u.T - np.eye(l))) < 4e-6
+    rq = np.einsum("ij,jk,ik->i", u, g, u)
+    assert np.max(np.abs(rq - ref)) < 4e-7 * ref[0]
+    assert np.max(np.abs(lam - ref)) < 1e-4 * ref[0]
+
+
+@pytest.mark.parametrize("l", [32, 64, 96, 128])
+def test_diagonal_and_zero_matrices(l):
+    d = np.arange(l, 0, -1.0)
+    perm = np.random.default_rng(l).permutation(l)
+    u, lam = _solve(np.diag(d[perm]))
+    assert np.allclose(lam, d, rtol=1e-6)
+    assert np.array_equal(np.abs(u), np.eye(l)[np.argsort(perm)])
+    u, lam = _solve(np.zeros((l, l)))
+    assert np.all(lam == 0) and np.max(np.abs(u @ u.T - np.eye(l))) == 0
