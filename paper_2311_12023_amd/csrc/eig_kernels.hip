@@ -1,57 +1,11 @@
 // The l x l symmetric eigenproblem of the Rayleigh-Ritz step (l = 32, 64, 96 or 128), one workgroup per problem.
-#include <type_traits>
-
+#include "dense_device.h"
 #include "kernels.h"
 #include "profiler.h"
 
 namespace lq {
 
 constexpr int EIG_THREADS = 256;
-
-// f(0), f(1), .. f(N - 1) (or downwards) with the index a compile-time constant, so that register arrays keep constant
-// subscripts however large the body is.
-template <int N, class F>
-__device__ __forceinline__ void for_each_block(F&& f) {
-  if constexpr (N > 0) { for_each_block<N - 1>(f); f(std::integral_constant<int, N - 1>{}); }
-}
-template <int N, class F>
-__device__ __forceinline__ void for_each_block_down(F&& f) {
-  if constexpr (N > 0) { f(std::integral_constant<int, N - 1>{}); for_each_block_down<N - 1>(f); }
-}
-
-template <int CTRL>
-__device__ __forceinline__ double dpp_move(double x) {
-  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(x), CTRL, 0xf, 0xf, false);
-  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(x), CTRL, 0xf, 0xf, false);
-  return __hiloint2double(hi, lo);
-}
-constexpr int XOR1 = 0xB1, XOR2 = 0x4E, XOR7 = 0x141, XOR15 = 0x140;   // quad_perm, quad_perm, row_half_mirror, row_mirror
-
-__device__ __forceinline__ double lane_value(double x, int lane) {
-  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(x), lane), __builtin_amdgcn_readlane(__double2loint(x), lane));
-}
-
-// Sum over the 64 lanes, the same in all of them.
-__device__ __forceinline__ double wave_sum(double x) {
-  x += dpp_move<XOR1>(x);
-  x += dpp_move<XOR2>(x);
-  x += dpp_move<XOR7>(x);
-  x += dpp_move<XOR15>(x);
-  return (lane_value(x, 0) + lane_value(x, 16)) + (lane_value(x, 32) + lane_value(x, 48));
-}
-
-// 1/x and 1/sqrt(x) for normal x: the hardware seeds (about 23 bits) and two Newton steps.
-__device__ __forceinline__ double rcp64(double x) {
-  double r = __builtin_amdgcn_rcp(x);
-  r = fma(r, fma(-x, r, 1.0), r);
-  return fma(r, fma(-x, r, 1.0), r);
-}
-__device__ __forceinline__ double rsqrt64(double x) {
-  double r = __builtin_amdgcn_rsq(x);
-  const double h = 0.5 * x;
-  r = fma(r, fma(-h * r, r, 0.5), r);
-  return fma(r, fma(-h * r, r, 0.5), r);
-}
 
 // Sums of N values over the 16 lanes of a DPP row with the values dealt out on the way: each of the first log2(N) steps
 // hands half of a lane's values to its partner, so a lane ends with the total of value row_sum_index<N>(lane) alone.

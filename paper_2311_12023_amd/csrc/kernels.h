@@ -126,12 +126,21 @@ int launch_range_sum_lowrank(const float* part, size_t pstride, int splits, cons
                              int64_t tld, int tsplits, int64_t m, int64_t N, int rank, const float* L2, int64_t ldl2,
                              float* Y, int64_t ldy, hipStream_t st);
 
+// ---- products of wide bases with l x l matrices (wide_kernels.hip) ------------------------------
+// C0[z] = U[z] A0[z] and, if A1 is given, C1[z] = U[z] A1[z] (U: l x l fp32 row-major, l = 32..128; A, C: l rows, leading
+// dimension ld, all ld columns are written), fp32 MFMA.  lower: U is lower triangular.
+bool rotate_supported(int l);
+int launch_rotate(int l, const float* U, size_t strideU, bool lower, const float* A0, float* C0, int64_t ld0, size_t stride0,
+                  const float* A1, float* C1, int64_t ld1, size_t stride1, int batch, hipStream_t st);
+// G[z] (l x l, fp64, row-major) = X[z] X[z]^T for wide X (l x m fp32, ldx at least m rounded up to 16).  `part`:
+// part_doubles doubles of scratch, at least batch * l * l; up to GRAM_CHUNKS_MAX times that lets a small batch use the
+// whole chip.
+constexpr int GRAM_CHUNKS = 16;                // what a batch gets room for, per problem
+constexpr int GRAM_CHUNKS_MAX = 128;
+int launch_gram(const float* X, int l, int64_t m, int64_t ldx, size_t strideX, double* part, size_t part_doubles, double* G,
+                int batch, hipStream_t st);
+
 // ---- small dense kernels (small_kernels.hip) --------------------------------------------------
-constexpr int GRAM_CHUNKS = 16;
-// G[z] (l x l, fp64, row-major) = X[z] X[z]^T for wide X (l x m, fp32).  `part` holds
-// batch * GRAM_CHUNKS * l * l doubles of scratch.
-int launch_gram(const float* X, int l, int64_t m, int64_t ldx, size_t strideX, double* part, double* G, int batch,
-                hipStream_t st);
 // In-place Cholesky G = C C^T (lower C, fp64; the strict upper triangle is left untouched).  A pivot that
 // is not positive relative to the largest diagonal entry marks a dependent direction: its diagonal entry
 // is stored as 0 and the triangular solve zeroes that row.

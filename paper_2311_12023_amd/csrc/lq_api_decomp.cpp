@@ -80,7 +80,7 @@ struct Plan {
   // shared
   size_t sr, sc, rsr, rsc;              // floats: d, k, d, k
   size_t Ya, Yb, Yc, Yd, Ba, Bb;        // cold-start wide bases (l1 rows)
-  size_t gpart, gram_part, G, Vt, Ut, lam, lam_cold, prob, errs;
+  size_t gpart, gram_part, gram_doubles, G, Vt, Ut, lam, lam_cold, prob, errs;
   // per problem (offset of problem 0, stride)
   size_t R, strideR;
   size_t Yw, Yw2, strideYw;             // floats
@@ -104,7 +104,8 @@ static void make_plan(int64_t d, int64_t k, int rank, const Params& prm, int bat
   pl.gpart_floats = std::max(gemm_part_floats(l1, 0), gemm_part_floats(lw, 0));
   pl.gpart = take(pl.gpart_floats * 4);
   const size_t ll = (size_t)l1 * l1;
-  pl.gram_part = take((size_t)batch * GRAM_CHUNKS * ll * 8);
+  pl.gram_doubles = std::max((size_t)batch * GRAM_CHUNKS, (size_t)GRAM_CHUNKS_MAX) * ll;
+  pl.gram_part = take(pl.gram_doubles * 8);
   pl.G = take((size_t)batch * ll * 8);
   pl.Vt = take((size_t)batch * std::max(ll, sym_eig_work_doubles(std::min(l1, 128))) * 8);
   pl.Ut = take((size_t)batch * ll * 4);
@@ -148,17 +149,16 @@ struct Ctx {
 };
 
 // Cholesky-QR: the rows of X (l x m) are replaced by an orthonormal basis of their span.  With the factor in
-// LDS the result is written to Xalt by the MFMA GEMM (C^-1 X) and the two pointers are exchanged; otherwise
+// registers the result is written to Xalt by rotate_kernel (C^-1 X) and the two pointers are exchanged; otherwise
 // X is solved in place.
 static int orthonormalize(const Ctx& c, float*& X, float*& Xalt, int l, int64_t m, int64_t ldx, size_t strideX,
                           int batch) {
   double* G = c.at<double>(c.pl.G);
-  LQ_TRY(launch_gram(X, l, m, ldx, strideX, c.at<double>(c.pl.gram_part), G, batch, c.st));
+  LQ_TRY(launch_gram(X, l, m, ldx, strideX, c.at<double>(c.pl.gram_part), c.pl.gram_doubles, G, batch, c.st));
   if (cholinv_supported(l)) {
     float* Cinv = c.at<float>(c.pl.Ut);
     LQ_TRY(launch_cholinv(G, l, Cinv, batch, c.st));
-    LQ_TRY(launch_wide_gemm(MODE_NN, l, ldx, l, Cinv, l, (size_t)l * l, X, ldx, strideX, Xalt, ldx, strideX, batch,
-                            nullptr, 0, c.st));
+    LQ_TRY(launch_rotate(l, Cinv, (size_t)l * l, true, X, Xalt, ldx, strideX, nullptr, nullptr, 0, 0, batch, c.st));
     std::swap(X, Xalt);
     return LQ_OK;
   }
@@ -179,14 +179,18 @@ static int ritz_rotate(const Ctx& c, int l, const float* Y, float* Y2, size_t sY
   const Plan& pl = c.pl;
   double* G = c.at<double>(pl.G);
   float* Ut = c.at<float>(pl.Ut);
-  LQ_TRY(launch_gram(B, l, pl.k, pl.ldk, sB, c.at<double>(pl.gram_part), G, batch, c.st));
+  LQ_TRY(launch_gram(B, l, pl.k, pl.ldk, sB, c.at<double>(pl.gram_part), pl.gram_doubles, G, batch, c.st));
   const bool fast = sym_eig_supported(l);
   if (fast) LQ_TRY(launch_sym_eig(G, l, c.at<double>(pl.Vt), Ut, lambda, batch, c.st));
   else LQ_TRY(launch_jacobi_eig(G, l, c.at<double>(pl.Vt), Ut, lambda, batch, c.st));
-  LQ_TRY(launch_wide_gemm(MODE_NN, l, pl.ldd, l, Ut, l, (size_t)l * l, Y, pl.ldd, sY, Y2, pl.ldd, sY, batch, nullptr, 0,
-                          c.st));
-  LQ_TRY(launch_wide_gemm(MODE_NN, l, pl.ldk, l, Ut, l, (size_t)l * l, B, pl.ldk, sB, B2, pl.ldk, sB, batch, nullptr, 0,
-                          c.st));
+  if (fast) {
+    LQ_TRY(launch_rotate(l, Ut, (size_t)l * l, false, Y, Y2, pl.ldd, sY, B, B2, pl.ldk, sB, batch, c.st));
+  } else {
+    LQ_TRY(launch_wide_gemm(MODE_NN, l, pl.ldd, l, Ut, l, (size_t)l * l, Y, pl.ldd, sY, Y2, pl.ldd, sY, batch, nullptr, 0,
+                            c.st));
+    LQ_TRY(launch_wide_gemm(MODE_NN, l, pl.ldk, l, Ut, l, (size_t)l * l, B, pl.ldk, sB, B2, pl.ldk, sB, batch, nullptr, 0,
+                            c.st));
+  }
   // Ritz values from the rotated projection itself: sigma_i^2 = |row i of B2|^2
   if (fast) LQ_TRY(launch_row_sumsq(B2, l, pl.k, pl.ldk, sB, lambda, batch, c.st));
   return LQ_OK;

@@ -63,11 +63,11 @@ int lq_test_orthonormalize(float* X, int l, int64_t m, int64_t ldx, double* scra
   if (l % 32 || l < 32 || l > 256) return LQ_ERR_ARG;
   double* G = scratch;
   double* part = scratch + (size_t)l * l;
-  LQ_TRY(launch_gram(X, l, m, ldx, 0, part, G, 1, (hipStream_t)stream));
+  LQ_TRY(launch_gram(X, l, m, ldx, 0, part, (size_t)16 * l * l, G, 1, (hipStream_t)stream));
   if (cholinv_supported(l) && alt) {
     float* Cinv = reinterpret_cast<float*>(part);       // the Gram partials are dead by now
     LQ_TRY(launch_cholinv(G, l, Cinv, 1, (hipStream_t)stream));
-    LQ_TRY(launch_wide_gemm(MODE_NN, l, ldx, l, Cinv, l, 0, X, ldx, 0, alt, ldx, 0, 1, nullptr, 0, (hipStream_t)stream));
+    LQ_TRY(launch_rotate(l, Cinv, 0, true, X, alt, ldx, 0, nullptr, nullptr, 0, 0, 1, (hipStream_t)stream));
     LQ_HIP_TRY(hipMemcpyAsync(X, alt, (size_t)l * ldx * sizeof(float), hipMemcpyDeviceToDevice, (hipStream_t)stream));
     return LQ_OK;
   }

@@ -25,7 +25,8 @@ enum Cls {
   SPLIT_PROJECT = 45,       // split_project_kernel (work = bytes)
   GEMM_F16_BASE = 46,       // + planes * 8 + mode * 4 + (l/32 - 1): wide_gemm_f16_kernel (work = flops of the product)
   ABSMAX = 62,
-  NUM_CLASSES = 63
+  ROTATE = 63,              // rotate_kernel (work = bytes)
+  NUM_CLASSES = 64
 };
 
 bool enabled();

@@ -1,85 +1,14 @@
-// Small dense kernels of the randomized SVD: Gram matrices in fp64, Cholesky-QR orthonormalisation,
+// Small dense kernels of the randomized SVD: Cholesky factors for the orthonormalisation,
 // the l x l symmetric eigenproblem of the Rayleigh-Ritz step (parallel Jacobi), sketch generation and
 // factor assembly (Algorithm 4).  These run on the ALUs with their working set in LDS when it fits;
 // they are latency-, not throughput-critical, and batched over the configurations of a sweep.
 #include <cmath>
 
+#include "dense_device.h"
 #include "kernels.h"
 #include "profiler.h"
 
 namespace lq {
-
-// ------------------------------------------------------------------------------------------------
-// Gram matrix: one workgroup per (column chunk, 32x32 output block of the lower triangle, problem).  Inputs are
-// fp32, products and sums fp64 (the Gram matrix of a basis whose singular values span two decades loses what the
-// SVD tolerance needs if it is accumulated in fp32), which makes the kernel fp64-FMA bound: only the blocks on and
-// below the diagonal are computed and gram_reduce_kernel mirrors them.
-__global__ __launch_bounds__(256) void gram_partial_kernel(const float* __restrict__ X, int l, int64_t m, int64_t ldx,
-                                                           size_t strideX, int64_t cols_per_chunk,
-                                                           double* __restrict__ part) {
-  __shared__ float xa[32][33];
-  __shared__ float xb[32][33];
-  const int chunk = blockIdx.x;
-  int bi = 0, bj = blockIdx.y;                    // blockIdx.y enumerates the pairs bj <= bi row by row
-  while (bj > bi) { bj -= bi + 1; ++bi; }
-  const int z = blockIdx.z;
-  const float* Xz = X + (size_t)z * strideX;
-  const int tid = threadIdx.x, ty = tid >> 4, tx = tid & 15;
-  const int64_t c0 = (int64_t)chunk * cols_per_chunk;
-  const int64_t c1 = c0 + cols_per_chunk < m ? c0 + cols_per_chunk : m;
-  double acc00 = 0, acc01 = 0, acc10 = 0, acc11 = 0;
-  for (int64_t cb = c0; cb < c1; cb += 32) {
-    __syncthreads();
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int idx = tid + q * 256;
-      const int r = idx >> 5, cc = idx & 31;
-      const int64_t col = cb + cc;
-      const bool ok = col < c1;
-      xa[r][cc] = ok ? Xz[(size_t)(32 * bi + r) * ldx + col] : 0.0f;
-      xb[r][cc] = ok ? Xz[(size_t)(32 * bj + r) * ldx + col] : 0.0f;
-    }
-    __syncthreads();
-#pragma unroll 8
-    for (int cc = 0; cc < 32; ++cc) {
-      const double a0 = xa[ty][cc], a1 = xa[ty + 16][cc], b0 = xb[tx][cc], b1 = xb[tx + 16][cc];
-      acc00 = fma(a0, b0, acc00); acc01 = fma(a0, b1, acc01);
-      acc10 = fma(a1, b0, acc10); acc11 = fma(a1, b1, acc11);
-    }
-  }
-  double* P = part + ((size_t)z * GRAM_CHUNKS + chunk) * (size_t)l * l;
-  const int r0 = 32 * bi + ty, q0 = 32 * bj + tx;
-  P[(size_t)r0 * l + q0] = acc00; P[(size_t)r0 * l + q0 + 16] = acc01;
-  P[(size_t)(r0 + 16) * l + q0] = acc10; P[(size_t)(r0 + 16) * l + q0 + 16] = acc11;
-}
-
-__global__ __launch_bounds__(256) void gram_reduce_kernel(const double* __restrict__ part, double* __restrict__ G,
-                                                          int l) {
-  const int z = blockIdx.y, ll = l * l;
-  const int i = blockIdx.x * 256 + threadIdx.x;
-  if (i >= ll) return;
-  const int r = i / l, q = i - r * l;
-  const int src = (r >> 5) >= (q >> 5) ? i : q * l + r;       // blocks above the diagonal: the transposed entry
-  const double* P = part + (size_t)z * GRAM_CHUNKS * ll;
-  double s = 0;
-  for (int c = 0; c < GRAM_CHUNKS; ++c) s += P[(size_t)c * ll + src];
-  G[(size_t)z * ll + i] = s;
-}
-
-int launch_gram(const float* X, int l, int64_t m, int64_t ldx, size_t strideX, double* part, double* G, int batch,
-                hipStream_t st) {
-  int64_t cpc = (m + GRAM_CHUNKS - 1) / GRAM_CHUNKS;
-  cpc = (cpc + 31) / 32 * 32;
-  const int nblk = l / 32;
-  prof::Scope ps(prof::GRAM, st, (double)l * m * 4.0 * batch);
-  hipLaunchKernelGGL(gram_partial_kernel, dim3(GRAM_CHUNKS, nblk * (nblk + 1) / 2, batch), dim3(256), 0, st, X, l, m, ldx,
-                     strideX, cpc, part);
-  LQ_HIP_TRY(hipGetLastError());
-  hipLaunchKernelGGL(gram_reduce_kernel, dim3((l * l + 255) / 256, batch), dim3(256), 0, st, (const double*)part, G,
-                     l);
-  LQ_HIP_TRY(hipGetLastError());
-  return LQ_OK;
-}
 
 // ------------------------------------------------------------------------------------------------
 // Cholesky, right-looking, one workgroup per problem.  PACKED: the lower triangle is worked on in LDS
@@ -153,99 +82,82 @@ int launch_cholesky(double* G, int l, int batch, hipStream_t st) {
 }
 
 // ------------------------------------------------------------------------------------------------
-// Cholesky factor and its inverse in one kernel (l = 32*NB <= 128), fp64.  G = C C^T; out = C^-1 as a
-// dense fp32 l x l matrix (zeros above the diagonal) that the MFMA GEMM then applies to the basis.
-// 1024 threads form a 32 x 32 grid; thread (ty, tx) keeps the elements (i, k) with i = ty (mod 32),
-// k = tx (mod 32) of both the matrix being factored and the inverse being built in registers.
-// Right-looking: step j broadcasts column j of the matrix and row j of the inverse through LDS
-// (double-buffered, one barrier per step) and every thread updates its own elements:
-//   a(i,k) -= c_ij c_kj,   T(i,k) -= c_ij T(j,k)   (Gauss-Jordan on [C | I]).
-// A non-positive pivot (dependent direction) zeroes that row of C^-1, which removes the direction.
-// 1 / sqrt(x) for positive finite x: fp32 seed on the mantissa (so that the seed exists whatever the magnitude of x),
-// three Newton steps in fp64, exponent put back.
-__device__ inline double fast_rsqrt(double x) {
-  int e;
-  double m = frexp(x, &e);                    // x = m 2^e, m in [0.5, 1)
-  if (e & 1) { m *= 2.0; e -= 1; }            // even exponent, m in [0.5, 2)
-  double r = (double)rsqrtf((float)m);
-  r = r * (1.5 - 0.5 * m * r * r);
-  r = r * (1.5 - 0.5 * m * r * r);
-  r = r * (1.5 - 0.5 * m * r * r);
-  return ldexp(r, -(e / 2));
-}
-
-template <int NB>
-__global__ __launch_bounds__(1024) void cholinv_kernel(const double* __restrict__ Gall, float* __restrict__ Cinvall) {
-  constexpr int l = 32 * NB;
-  __shared__ double colbuf[2][l];
-  __shared__ double rowbuf[2][l];
-  const int tid = threadIdx.x, ty = tid >> 5, tx = tid & 31;
-  const double* G = Gall + (size_t)blockIdx.x * l * l;
-  double a[NB][NB], t[NB][NB];
-#pragma unroll
-  for (int ei = 0; ei < NB; ++ei)
-#pragma unroll
-    for (int ek = 0; ek < NB; ++ek) {
-      const int i = ty + 32 * ei, k = tx + 32 * ek;
-      a[ei][ek] = G[(size_t)i * l + k];
-      t[ei][ek] = (i == k) ? 1.0 : 0.0;
-    }
-  // A pivot is compared with the row's own squared norm, not with the largest one (see cholesky_kernel).
+// Cholesky factor and its inverse in one kernel (l = 16 NE <= 128), fp64.  G = C C^T; out = C^-1 as a dense fp32 l x l
+// matrix (zeros above the diagonal) that the MFMA GEMM then applies to the basis.
+// 256 threads form a 16 x 16 grid; thread (ty, tx) keeps the elements (i, k) with i = ty, k = tx (mod 16) in registers.
+// Gauss-Jordan in place: at step j the columns k > j still hold the matrix A being factored and the columns k < j the
+// inverse T being built, and one vector serves both updates: r_k = a(k,j) / c_jj for k > j (which is c_kj, by symmetry),
+// t(j,k) / c_jj for k < j, 1 / c_jj for k = j; then element (i,k), i > j, loses c_ij r_k.  The vector goes through LDS
+// (double-buffered, one barrier per step).  A non-positive pivot (dependent direction) zeroes that row of C^-1, which
+// removes the direction.
+// The kernel is a serial chain of l steps, so what counts is the length of a step: four wavefronts that read 2 NE numbers
+// each per step, against sixteen with separate matrices for A and T that read 3 l / 32 each (l = 128: 101 -> 54 us,
+// l = 96: 69 -> 35 us, l = 64: 45 -> 20 us, l = 32: 20.5 -> 9 us, one problem).
+template <int NE>
+__global__ __launch_bounds__(256) void cholinv_kernel(const double* __restrict__ Gall, float* __restrict__ Cinvall) {
+  constexpr int l = 16 * NE;
+  __shared__ double s_vec[2][l];
   __shared__ double s_diag[l];
+  const int tid = threadIdx.x, ty = tid >> 4, tx = tid & 15;
+  const double* G = Gall + (size_t)blockIdx.x * l * l;
+  double a[NE][NE];
+#pragma unroll
+  for (int e = 0; e < NE; ++e)
+#pragma unroll
+    for (int f = 0; f < NE; ++f) a[e][f] = G[(size_t)(ty + 16 * e) * l + tx + 16 * f];
+  // A pivot is compared with the row's own squared norm, not with the largest one (see cholesky_kernel).
   if (ty == tx) {
 #pragma unroll
-    for (int e = 0; e < NB; ++e) s_diag[ty + 32 * e] = a[e][e];
+    for (int e = 0; e < NE; ++e) s_diag[ty + 16 * e] = a[e][e];
   }
-  __syncthreads();
-
+  for_each_block<NE>([&](auto block) {
+    constexpr int jb = decltype(block)::value;
+#pragma nounroll
+    for (int jt = 0; jt < 16; ++jt) {
+      const int j = 16 * jb + jt;
+      double* vec = s_vec[j & 1];
+      if (tx == jt) {                                    // column j from the diagonal down
 #pragma unroll
-  for (int jb = 0; jb < NB; ++jb) {
-    for (int jt = 0; jt < 32; ++jt) {
-      const int j = 32 * jb + jt, buf = j & 1;
-      if (tx == jt) {
-#pragma unroll
-        for (int ei = 0; ei < NB; ++ei) colbuf[buf][ty + 32 * ei] = a[ei][jb];
+        for (int e = jb; e < NE; ++e)
+          if (e > jb || ty >= jt) vec[ty + 16 * e] = a[e][jb];
       }
-      if (ty == jt) {
+      if (ty == jt) {                                    // row j of the inverse
 #pragma unroll
-        for (int ek = 0; ek < NB; ++ek) rowbuf[buf][tx + 32 * ek] = t[jb][ek];
+        for (int f = 0; f <= jb; ++f)
+          if (f < jb || tx < jt) vec[tx + 16 * f] = a[jb][f];
       }
       __syncthreads();
-      const double piv = colbuf[buf][j];
-      const bool ok = piv > 1e-12 * s_diag[j];
-      const double inv = ok ? fast_rsqrt(piv) : 0.0;
-      double ci[NB], ck[NB], tr[NB];
+      const double piv = vec[j];
+      double ci[NE], rk[NE];
 #pragma unroll
-      for (int e = 0; e < NB; ++e) {
-        const int i = ty + 32 * e, k = tx + 32 * e;
-        ci[e] = i > j ? colbuf[buf][i] * inv : 0.0;      // c_ij for this thread's rows
-        ck[e] = k > j ? colbuf[buf][k] * inv : 0.0;      // c_kj for this thread's columns
-        tr[e] = k <= j ? rowbuf[buf][k] * inv : 0.0;     // scaled row j of the inverse
+      for (int e = 0; e < NE; ++e) { rk[e] = vec[tx + 16 * e]; if (e >= jb) ci[e] = vec[ty + 16 * e]; }
+      const double inv = piv > 1e-12 * s_diag[j] ? rsqrt64(piv) : 0.0;
+#pragma unroll
+      for (int e = 0; e < NE; ++e) rk[e] *= inv;
+      if (tx == jt) {                                    // column j changes sides: it starts as column j of the identity
+        rk[jb] = inv;
+#pragma unroll
+        for (int e = jb; e < NE; ++e) a[e][jb] = 0.0;
       }
-      // only row blocks that reach below row j change; the matrix part needs columns > j, the inverse part
-      // columns <= j (uniform conditions: whole 32-wide blocks are skipped)
 #pragma unroll
-      for (int ei = 0; ei < NB; ++ei) {
-        if (32 * ei + 31 <= j) continue;
+      for (int e = jb; e < NE; ++e) {
+        ci[e] = e > jb || ty > jt ? ci[e] * inv : 0.0;
 #pragma unroll
-        for (int ek = 0; ek < NB; ++ek) {
-          if (32 * ek + 31 > j) a[ei][ek] = fma(-ci[ei], ck[ek], a[ei][ek]);
-          if (32 * ek <= j) t[ei][ek] = fma(-ci[ei], tr[ek], t[ei][ek]);
-        }
+        for (int f = 0; f <= e; ++f) a[e][f] = fma(-ci[e], rk[f], a[e][f]);   // blocks above the diagonal are never read
       }
       if (ty == jt) {
 #pragma unroll
-        for (int ek = 0; ek < NB; ++ek) t[jb][ek] = tr[ek];
+        for (int f = 0; f <= jb; ++f) a[jb][f] = rk[f];
       }
     }
-  }
+  });
   float* out = Cinvall + (size_t)blockIdx.x * l * l;
 #pragma unroll
-  for (int ei = 0; ei < NB; ++ei)
+  for (int e = 0; e < NE; ++e)
 #pragma unroll
-    for (int ek = 0; ek < NB; ++ek) {
-      const int i = ty + 32 * ei, k = tx + 32 * ek;
-      out[(size_t)i * l + k] = k <= i ? (float)t[ei][ek] : 0.0f;
+    for (int f = 0; f < NE; ++f) {
+      const int i = ty + 16 * e, k = tx + 16 * f;
+      out[(size_t)i * l + k] = k <= i ? (float)a[e][f] : 0.0f;
     }
 }
 
@@ -254,10 +166,10 @@ bool cholinv_supported(int l) { return l % 32 == 0 && l >= 32 && l <= 128; }
 int launch_cholinv(const double* G, int l, float* Cinv, int batch, hipStream_t st) {
   prof::Scope ps(prof::CHOLESKY, st, (double)l * l * 12.0 * batch);
   switch (l / 32) {
-    case 1: hipLaunchKernelGGL(cholinv_kernel<1>, dim3(batch), dim3(1024), 0, st, G, Cinv); break;
-    case 2: hipLaunchKernelGGL(cholinv_kernel<2>, dim3(batch), dim3(1024), 0, st, G, Cinv); break;
-    case 3: hipLaunchKernelGGL(cholinv_kernel<3>, dim3(batch), dim3(1024), 0, st, G, Cinv); break;
-    case 4: hipLaunchKernelGGL(cholinv_kernel<4>, dim3(batch), dim3(1024), 0, st, G, Cinv); break;
+    case 1: hipLaunchKernelGGL(cholinv_kernel<2>, dim3(batch), dim3(256), 0, st, G, Cinv); break;
+    case 2: hipLaunchKernelGGL(cholinv_kernel<4>, dim3(batch), dim3(256), 0, st, G, Cinv); break;
+    case 3: hipLaunchKernelGGL(cholinv_kernel<6>, dim3(batch), dim3(256), 0, st, G, Cinv); break;
+    case 4: hipLaunchKernelGGL(cholinv_kernel<8>, dim3(batch), dim3(256), 0, st, G, Cinv); break;
     default: return LQ_ERR_ARG;
   }
   LQ_HIP_TRY(hipGetLastError());
@@ -409,7 +321,14 @@ __global__ __launch_bounds__(256) void row_sumsq_kernel(const float* __restrict_
   const int row = blockIdx.x, z = blockIdx.y, tid = threadIdx.x;
   const float* x = X + (size_t)z * strideX + (size_t)row * ldx;
   double s = 0.0;
-  for (int64_t j = tid; j < m; j += 256) { const double v = x[j]; s = fma(v, v, s); }
+  const int64_t quads = m / 4;                 // rows start on 16-byte boundaries
+#pragma unroll 4
+  for (int64_t j = tid; j < quads; j += 256) {
+    const float4 v = reinterpret_cast<const float4*>(x)[j];
+    s = fma((double)v.x, (double)v.x, s); s = fma((double)v.y, (double)v.y, s);
+    s = fma((double)v.z, (double)v.z, s); s = fma((double)v.w, (double)v.w, s);
+  }
+  if (tid < m - 4 * quads) { const double v = x[4 * quads + tid]; s = fma(v, v, s); }
   for (int off = 1; off < 64; off <<= 1) s += __shfl_xor(s, off);
   if ((tid & 63) == 0) s_sum[tid >> 6] = s;
   __syncthreads();

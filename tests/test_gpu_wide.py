@@ -1,0 +1,32 @@
+"""Cholesky-QR (Gram matrix, factor and inverse, rotation) over every number of rows and at column counts around the 16
+columns of a Gram step and the 32 of a rotation tile, against what defines it: Q orthonormal, Q = C^-1 X with C lower
+triangular.  The Gram matrix is exact to fp64, so what is left is C^-1 rounded to fp32 and fp32 sums over l terms: at a
+condition of about 10 (rows drawn with 2 l columns or more), l * 2^-24 * 10 < 2e-4 for l <= 256."""
+import numpy as np
+import pytest
+
+from testing_lib import load
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("l", [32, 64, 96, 128, 160, 192, 224, 256])
+@pytest.mark.parametrize("extra", [0, 1, 15, 17, 31, 2049])
+def test_orthonormalize_ragged(l, extra):
+    import torch
+    L = load()
+    m = 2 * l + extra
+    ld = (m + 31) // 32 * 32
+    rng = np.random.default_rng(l + extra)
+    x = np.zeros((l, ld), np.float32)
+    x[:, :m] = rng.standard_normal((l, m))
+    xt = torch.from_numpy(x).cuda()
+    scratch = torch.full((17 * l * l,), float("nan"), dtype=torch.float64, device="cuda")
+    alt = torch.full((l, ld), float("nan"), dtype=torch.float32, device="cuda")
+    assert L.lq_test_orthonormalize(xt.data_ptr(), l, m, ld, scratch.data_ptr(), alt.data_ptr(), None) == 0
+    torch.cuda.synchronize()
+    q = xt.cpu().numpy().astype(np.float64)
+    assert np.all(q[:, m:] == 0)
+    assert np.max(np.abs(q @ q.T - np.eye(l))) < 2e-4
+    c = np.linalg.cholesky(x.astype(np.float64) @ x.T.astype(np.float64))
+    assert np.max(np.abs(c @ q - x)) < 2e-4 * np.max(np.abs(x)) * np.sqrt(l)
