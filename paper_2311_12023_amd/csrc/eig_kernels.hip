@@ -1,4 +1,6 @@
 // The l x l symmetric eigenproblem of the Rayleigh-Ritz step (l = 32, 64, 96 or 128), one workgroup per problem.
+#include <algorithm>
+
 #include "dense_device.h"
 #include "kernels.h"
 #include "profiler.h"
@@ -178,7 +180,9 @@ __device__ void jacobi_onesided(const double* __restrict__ G, double mscale, flo
 // per-wavefront work and the LDS reads of the vectors quadruple), two barriers per column, and scalar parts that every
 // wavefront computes for itself instead of waiting for one.
 // Eigenvectors computed one by one are orthogonal to about 1e-16 lambda_1 / gap.  Where a gap is below 2e-9 lambda_1 (so
-// that 1e-6 could be missed) the problem is solved by one-sided Jacobi instead, inside the same launch.
+// that 1e-6 could be missed; in a sweep the Ritz values of the quantization noise of 8-bit configurations, 1e-8 lambda_1
+// themselves, are such a cluster) the rows are orthonormalised together at the end, and where they have come out too
+// dependent for that (repeated eigenvalues, a singular matrix) the problem is solved by one-sided Jacobi, in the same launch.
 // Measured on a weight matrix's spectrum in a random basis (one problem, us): l = 32 98 -> 45, l = 64 297 -> 100,
 // l = 96 687 -> 192, l = 128 1491 -> 273 against one-sided Jacobi with 8 l threads, whose six to nine sweeps of l - 1
 // rounds are bound by LDS bandwidth (every round reads and writes X and V); Rayleigh quotients come out 10 to 70 times
@@ -204,6 +208,10 @@ __global__ __launch_bounds__(EIG_THREADS) void sym_eig_kernel(const double* __re
   double* Sm = Sp + l * l;
   float* Ut = Utall + (size_t)z * l * l;
   double* lam = lamall + (size_t)z * l;
+
+  // In a sweep the streaming kernels of other streams share the compute unit: this one is a serial chain that the next
+  // kernel of its stream waits for, they have thousands of wavefronts in flight.
+  __builtin_amdgcn_s_setprio(3);
 
   // unit scale by a power of two of the largest diagonal entry
   double a[NE][NE];
@@ -355,10 +363,7 @@ __global__ __launch_bounds__(EIG_THREADS) void sym_eig_kernel(const double* __re
   __syncthreads();
   bool close = false;
   if (tid < l - 1) close = !(s_lam[tid + 1] - s_lam[tid] > 2e-9 * bound);
-  if (__syncthreads_or(close)) {
-    jacobi_onesided<NE>(G, mscale, reinterpret_cast<float*>(lds), s_n2, s_vscale, s_rank, s_flags, Ut, lam);
-    return;
-  }
+  const bool clustered = __syncthreads_or(close);
   if (tid < l) lam[l - 1 - tid] = fmax(s_lam[tid], 0.0) / mscale;
 
   // Eigenvectors of the tridiagonal matrix: T - lambda = L D+ L^T from the top (lower half of the threads) and U D- U^T
@@ -456,13 +461,86 @@ __global__ __launch_bounds__(EIG_THREADS) void sym_eig_kernel(const double* __re
       }
     }
   });
+  if (!clustered) {
 #pragma unroll
-  for (int v = 0; v < NV; ++v) {
-    const int c = grp + 32 * v;
+    for (int v = 0; v < NV; ++v) {
+      const int c = grp + 32 * v;
+#pragma unroll
+      for (int m = 0; m < NE; ++m)
+        *reinterpret_cast<float2*>(Ut + (size_t)(l - 1 - c) * l + 16 * m + 2 * sub) =
+            make_float2((float)u[v][m][0], (float)u[v][m][1]);
+    }
+    return;
+  }
+
+  // Close eigenvalues: the rows are nearly orthonormal still, and steps U <- U + (I - U U^T) U / 2 make them so; the
+  // correction mixes only rows that overlap, which are those of close eigenvalues.  U lies in LDS (the reflectors are
+  // done with), thread (ty, tx) computes the elements (ty + 16 e, tx + 16 f) of both products.
+  constexpr int PU = l + 2;
+  double* Us = lds;
+  __syncthreads();
+#pragma unroll
+  for (int v = 0; v < NV; ++v)
 #pragma unroll
     for (int m = 0; m < NE; ++m)
-      *reinterpret_cast<float2*>(Ut + (size_t)(l - 1 - c) * l + 16 * m + 2 * sub) =
-          make_float2((float)u[v][m][0], (float)u[v][m][1]);
+      *reinterpret_cast<double2*>(Us + (grp + 32 * v) * PU + 16 * m + 2 * sub) = make_double2(u[v][m][0], u[v][m][1]);
+  for (int step = 0;; ++step) {
+    __syncthreads();
+    double s[NE][NE];
+#pragma unroll
+    for (int e = 0; e < NE; ++e)
+#pragma unroll
+      for (int f = 0; f < NE; ++f) s[e][f] = 0.0;
+    for (int i = 0; i < l; ++i) {
+      double p[NE], q[NE];
+#pragma unroll
+      for (int e = 0; e < NE; ++e) { p[e] = Us[(ty + 16 * e) * PU + i]; q[e] = Us[(tx + 16 * e) * PU + i]; }
+#pragma unroll
+      for (int e = 0; e < NE; ++e)
+#pragma unroll
+        for (int f = 0; f < NE; ++f) s[e][f] = fma(p[e], q[f], s[e][f]);
+    }
+    bool off = false, far = false;
+#pragma unroll
+    for (int e = 0; e < NE; ++e)
+#pragma unroll
+      for (int f = 0; f < NE; ++f) {
+        const double d = (e == f && ty == tx ? 1.0 : 0.0) - s[e][f];
+        off = off || !(fabs(d) < 1e-8);
+        far = far || !(fabs(d) < 0.02);
+        s[e][f] = 0.5 * d;
+      }
+    if (__syncthreads_or(far) || step == 4) {   // the vectors of a cluster came out too much alike (or not finite)
+      jacobi_onesided<NE>(G, mscale, reinterpret_cast<float*>(lds), s_n2, s_vscale, s_rank, s_flags, Ut, lam);
+      return;
+    }
+    if (!__syncthreads_or(off)) break;
+    double t[NE][NE];
+#pragma unroll
+    for (int e = 0; e < NE; ++e)
+#pragma unroll
+      for (int f = 0; f < NE; ++f) t[e][f] = Us[(ty + 16 * e) * PU + tx + 16 * f];
+    for_each_block<16 * NE>([&](auto column) {           // column 16 fb + b of s sits in lane b of the DPP row
+      constexpr int fb = decltype(column)::value / 16, b = decltype(column)::value % 16;
+      double q[NE];
+#pragma unroll
+      for (int f = 0; f < NE; ++f) q[f] = Us[(16 * fb + b) * PU + tx + 16 * f];
+#pragma unroll
+      for (int e = 0; e < NE; ++e) {
+        const double d = dpp_move<0x150 + b>(s[e][fb]);  // row_newbcast
+#pragma unroll
+        for (int f = 0; f < NE; ++f) t[e][f] = fma(d, q[f], t[e][f]);
+      }
+    });
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < NE; ++e)
+#pragma unroll
+      for (int f = 0; f < NE; ++f) Us[(ty + 16 * e) * PU + tx + 16 * f] = t[e][f];
+  }
+  for (int idx = tid; idx < l * l; idx += EIG_THREADS) {
+    const int c = idx / l, i = idx % l;
+    Ut[(size_t)(l - 1 - c) * l + i] = (float)Us[c * PU + i];
   }
 }
 
@@ -472,7 +550,8 @@ template <int NE>
 static int launch_eig(const double* G, double* work, float* Ut, double* lambda, int batch, hipStream_t st) {
   constexpr int l = 16 * NE;
   const size_t reflectors = (size_t)l * l * sizeof(double), jacobi = (size_t)2 * l * (l + 4) * sizeof(float);
-  const size_t need = reflectors > jacobi ? reflectors : jacobi;
+  const size_t rows = (size_t)l * (l + 2) * sizeof(double);
+  const size_t need = std::max(reflectors, std::max(jacobi, rows));
   static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(sym_eig_kernel<NE>),
                                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)need);
   LQ_HIP_TRY(attr);

@@ -100,6 +100,7 @@ __global__ __launch_bounds__(256) void cholinv_kernel(const double* __restrict__
   __shared__ double s_diag[l];
   const int tid = threadIdx.x, ty = tid >> 4, tx = tid & 15;
   const double* G = Gall + (size_t)blockIdx.x * l * l;
+  __builtin_amdgcn_s_setprio(3);               // a serial chain that shares the compute unit with streaming kernels
   double a[NE][NE];
 #pragma unroll
   for (int e = 0; e < NE; ++e)

@@ -1,5 +1,6 @@
 """The eigen-solver of the Rayleigh-Ritz step over the spectra that decide its route: separated eigenvalues (tridiagonal
-route), repeated, zero and nearly equal ones (one-sided Jacobi inside the same launch), graded and diagonal matrices.
+route), close ones (the same with a joint orthonormalisation), repeated and zero ones (one-sided Jacobi inside the same
+launch), graded and diagonal matrices.
 
 Tolerances: rows of fp32 numbers that are orthonormal to 2^-24 per entry, or to 1e-6 per pair on the Jacobi route and at
 the smallest gap the tridiagonal route accepts (2e-9 of the largest eigenvalue): 4e-6.  A Rayleigh quotient misses its
@@ -26,6 +27,8 @@ def _spectrum(kind, l, rng):
         s = np.linspace(4.0, 1.0, l)
         s[5] = s[4] * (1 - 1e-11)
         return s
+    if kind == "noise_floor":                # the residual of an 8-bit configuration: a cluster far below the rest
+        return np.concatenate([np.linspace(900.0, 1.0, l - l // 3), 1e-6 * (1.0 + 0.03 * np.sort(rng.random(l // 3)))])
     if kind == "smallest_gap":               # just above the line of the tridiagonal route
         s = np.linspace(4.0, 1.0, l)
         s[5] = s[4] - 1.0e-8 * 4.0
@@ -46,7 +49,7 @@ def _solve(g):
 
 
 @pytest.mark.parametrize("l", [32, 64, 96, 128])
-@pytest.mark.parametrize("kind", ["flat", "geometric", "repeated", "low_rank", "one_pair", "smallest_gap"])
+@pytest.mark.parametrize("kind", ["flat", "geometric", "repeated", "low_rank", "one_pair", "smallest_gap", "noise_floor"])
 @pytest.mark.parametrize("scale", [1.0, 1e-13, 1e11])
 def test_spectra(l, kind, scale):
     rng = np.random.default_rng(l)
