@@ -61,8 +61,6 @@ int launch_split_planes(const float* X, int64_t rows, int64_t K, int64_t ldx, in
 // SPLIT_PROJECT_MAX_RANK) as bf16 planes th / tl of rows_pad x Kd (Kd = 32 or 64, at least rank; columns beyond rank
 // and rows beyond `rows` are zero).  rows_pad is a multiple of 64.  precision 1 computes T from the hi halves alone
 // and leaves the lo plane of X unwritten.  `part`: split_project_part_floats(rows_pad, K) floats of scratch.
-// th == NULL: the planes of T are not formed; T stays as split_project_splits(rows_pad, K) partial results in `part`
-// (range z, row i at part + (z * rows_pad + i) * 64).
 // `bs`: block scales to reconstruct in the same launch (see launch_block_scales; nblocks == 0: none).
 constexpr int SPLIT_PROJECT_MAX_RANK = 64;
 struct BlockScales {
@@ -97,10 +95,8 @@ struct DensePart {
 // the machine without cutting the reduction).
 int qmatmul_splits(int64_t m, int64_t N, int nsteps);
 size_t qmatmul_part_floats(int64_t m, int64_t N, int nsteps);
-// splits_out: when given and the reduction was cut, the partial results stay in `part` (range z at part + z * m * N,
-// nothing is written to Y) and *splits_out is their number; otherwise *splits_out = 1 and Y holds the result.
 int launch_qmatmul(const QmmPart& q, const DensePart& dn, int64_t m, int64_t rows_pad, int64_t N, float* Y, int64_t ldy,
-                   float* part, size_t part_floats, int precision, hipStream_t st, int* splits_out = nullptr);
+                   float* part, size_t part_floats, int precision, hipStream_t st);
 
 // Y = sum of `splits` partial results (each m x N, contiguous, one after the other in `part`), in order.
 int launch_qmatmul_reduce(const float* part, int splits, int64_t m, int64_t N, float* Y, int64_t ldy, hipStream_t st);
@@ -125,6 +121,22 @@ int launch_qmatvec(const MvWeights& q, const float* X, int64_t ldx, int64_t K, c
 int launch_range_sum_lowrank(const float* part, size_t pstride, int splits, const float* tpart, size_t tstride,
                              int64_t tld, int tsplits, int64_t m, int64_t N, int rank, const float* L2, int64_t ldl2,
                              float* Y, int64_t ldy, hipStream_t st);
+// The same sum where column tiles have segments of their own number: the steps of all tiles (tile_cols columns of X Q
+// each, then tiles of ttile_cols columns of T), `steps` per tile, were dealt out in shares of per_wg; segment z of a tile
+// lies at part + z * m * N, at tpart + z * m * rank for T.
+int launch_segment_sum_lowrank(const float* part, const float* tpart, int64_t m, int64_t N, int rank, const float* L2,
+                               int64_t ldl2, float* Y, int64_t ldy, int steps, int per_wg, int tile_cols, int ttile_cols,
+                               hipStream_t st);
+
+// ---- forward product for a few dozen rows of X (rows_kernels.hip) ------------------------------------
+// As launch_qmatvec, for m <= QROWS_MAX_ROWS and rank <= QROWS_MAX_RANK, on bf16 MFMAs (precision as in launch_qmatmul):
+// K a multiple of 32, K * N below 2^31, X 16-byte aligned with ldx a multiple of 4.  part: qrows_part_floats floats.
+constexpr int64_t QROWS_MAX_ROWS = 128;
+constexpr int QROWS_MAX_RANK = 512;
+size_t qrows_part_floats(int64_t m, int64_t K, int64_t N, int rank);
+int launch_qrows(const MvWeights& q, const float* X, int64_t ldx, int64_t K, const float* L1, const float* L2, int64_t ldl2,
+                 int rank, int64_t m, int64_t N, int precision, float* Y, int64_t ldy, float* part, size_t part_floats,
+                 hipStream_t st);
 
 // ---- products of wide bases with l x l matrices (wide_kernels.hip) ------------------------------
 // C0[z] = U[z] A0[z] and, if A1 is given, C1[z] = U[z] A1[z] (U: l x l fp32 row-major, l = 32..128; A, C: l rows, leading

@@ -223,7 +223,13 @@ struct MvfArgs {
   int m; int64_t N; int rank;
   const float* L2; int64_t ldl2;
   float* Y; int64_t ldy;
+  // steps != 0: the number of ranges differs between column tiles (see launch_segment_sum_lowrank)
+  int steps, per_wg, tile_cols, ttile_cols;
 };
+// Ranges of a column tile: the workgroups that its steps were dealt to.
+__device__ __forceinline__ int mvf_segments(const MvfArgs& a, int64_t tile) {
+  return (int)(((tile + 1) * a.steps - 1) / a.per_wg - tile * a.steps / a.per_wg) + 1;
+}
 template <int M>
 __global__ __launch_bounds__(MVF_COLS * (M < 4 ? M : 4)) void qmatvec_finish_kernel(MvfArgs a) {
   constexpr int SLOTS = M < 4 ? M : 4, THREADS = MVF_COLS * SLOTS, RT = (M + SLOTS - 1) / SLOTS;
@@ -234,13 +240,15 @@ __global__ __launch_bounds__(MVF_COLS * (M < 4 ? M : 4)) void qmatvec_finish_ker
   const int m = a.m - row0 < M ? a.m - row0 : M;     // rows of this workgroup
   const bool live = col < a.N;
   const int64_t colc = live ? col : 0;
+  const int splits = a.steps ? mvf_segments(a, (int64_t)blockIdx.x * MVF_COLS / a.tile_cols) : a.splits;
+  const int64_t ttile0 = a.steps ? (a.N + a.tile_cols - 1) / a.tile_cols : 0;
   // the thread's rows of X Q
   float acc[RT];
 #pragma unroll
   for (int j = 0; j < RT; ++j) {
     const int i = slot + SLOTS * j;
     float s = 0.0f;
-    if (i < m) s = mvf_range_sum(a.part + (size_t)(row0 + i) * a.N + colc, a.pstride, a.splits);
+    if (i < m) s = mvf_range_sum(a.part + (size_t)(row0 + i) * a.N + colc, a.pstride, splits);
     acc[j] = s;
   }
   // T, with the tail up to a multiple of 32 zero
@@ -248,7 +256,8 @@ __global__ __launch_bounds__(MVF_COLS * (M < 4 ? M : 4)) void qmatvec_finish_ker
   for (int idx = tid; idx < m * rank32; idx += THREADS) {
     const int i = idx / rank32, p = idx % rank32;
     float t = 0.0f;
-    if (p < a.rank) t = mvf_range_sum(a.tpart + (size_t)(row0 + i) * a.tld + p, a.tstride, a.tsplits);
+    const int tsplits = a.steps ? mvf_segments(a, ttile0 + p / a.ttile_cols) : a.tsplits;
+    if (p < a.rank) t = mvf_range_sum(a.tpart + (size_t)(row0 + i) * a.tld + p, a.tstride, tsplits);
     s_t[i][p] = t;
   }
   __syncthreads();
@@ -272,19 +281,35 @@ __global__ __launch_bounds__(MVF_COLS * (M < 4 ? M : 4)) void qmatvec_finish_ker
   }
 }
 
-int launch_range_sum_lowrank(const float* part, size_t pstride, int splits, const float* tpart, size_t tstride,
-                             int64_t tld, int tsplits, int64_t m, int64_t N, int rank, const float* L2, int64_t ldl2,
-                             float* Y, int64_t ldy, hipStream_t st) {
-  if (m < 1 || N < 1 || splits < 1 || rank < 0 || rank > MVF_RANK_MAX || (rank > 0 && tsplits < 1)) return LQ_ERR_SHAPE;
-  const MvfArgs a{part, pstride, splits, tpart, tstride, tld, tsplits, (int)m, N, rank, L2, ldl2, Y, ldy};
-  prof::Scope ps(prof::MISC, st, 4.0 * ((double)splits * m * (double)N + (double)tsplits * m * rank + (double)rank * (double)N + m * (double)N));
-  const unsigned gx = (unsigned)((N + MVF_COLS - 1) / MVF_COLS);
+static int launch_finish(const MvfArgs& a, double bytes, hipStream_t st) {
+  const int64_t m = a.m;
+  prof::Scope ps(prof::MISC, st, bytes);
+  const unsigned gx = (unsigned)((a.N + MVF_COLS - 1) / MVF_COLS);
   if (m <= 1) hipLaunchKernelGGL((qmatvec_finish_kernel<1>), dim3(gx), dim3(MVF_COLS), 0, st, a);
   else if (m <= 2) hipLaunchKernelGGL((qmatvec_finish_kernel<2>), dim3(gx), dim3(2 * MVF_COLS), 0, st, a);
   else if (m <= 4) hipLaunchKernelGGL((qmatvec_finish_kernel<4>), dim3(gx), dim3(4 * MVF_COLS), 0, st, a);
   else hipLaunchKernelGGL((qmatvec_finish_kernel<8>), dim3(gx, (unsigned)((m + 7) / 8)), dim3(4 * MVF_COLS), 0, st, a);
   LQ_HIP_TRY(hipGetLastError());
   return LQ_OK;
+}
+
+int launch_range_sum_lowrank(const float* part, size_t pstride, int splits, const float* tpart, size_t tstride,
+                             int64_t tld, int tsplits, int64_t m, int64_t N, int rank, const float* L2, int64_t ldl2,
+                             float* Y, int64_t ldy, hipStream_t st) {
+  if (m < 1 || N < 1 || splits < 1 || rank < 0 || rank > MVF_RANK_MAX || (rank > 0 && tsplits < 1)) return LQ_ERR_SHAPE;
+  const MvfArgs a{part, pstride, splits, tpart, tstride, tld, tsplits, (int)m, N, rank, L2, ldl2, Y, ldy, 0, 1, 1, 1};
+  return launch_finish(a, 4.0 * ((double)splits * m * (double)N + (double)tsplits * m * rank + (double)rank * (double)N + m * (double)N), st);
+}
+
+int launch_segment_sum_lowrank(const float* part, const float* tpart, int64_t m, int64_t N, int rank, const float* L2,
+                               int64_t ldl2, float* Y, int64_t ldy, int steps, int per_wg, int tile_cols, int ttile_cols,
+                               hipStream_t st) {
+  if (m < 1 || N < 1 || rank < 0 || rank > MVF_RANK_MAX || steps < 1 || per_wg < 1 || tile_cols % MVF_COLS || ttile_cols < 1)
+    return LQ_ERR_SHAPE;
+  const MvfArgs a{part, (size_t)m * (size_t)N, 1, tpart, (size_t)m * (size_t)rank, rank, 1, (int)m, N, rank, L2, ldl2, Y, ldy,
+                  steps, per_wg, tile_cols, ttile_cols};
+  const double segments = 1.0 + (double)steps / per_wg;
+  return launch_finish(a, 4.0 * (segments * m * (double)(N + rank) + (double)rank * (double)N + m * (double)N), st);
 }
 
 // Reduction ranges for m rows against K x (N + rank) weights: at most 512 workgroups (with 8 rows two fit a CU, and a

@@ -56,7 +56,7 @@ static const char* const kNames[NUM_CLASSES] = {
     "wide_gemm_f16_kernel<1,1,1>", "wide_gemm_f16_kernel<2,1,1>", "wide_gemm_f16_kernel<3,1,1>", "wide_gemm_f16_kernel<4,1,1>",
     "wide_gemm_f16_kernel<1,0,2>", "wide_gemm_f16_kernel<2,0,2>", "wide_gemm_f16_kernel<3,0,2>", "wide_gemm_f16_kernel<4,0,2>",
     "wide_gemm_f16_kernel<1,1,2>", "wide_gemm_f16_kernel<2,1,2>", "wide_gemm_f16_kernel<3,1,2>", "wide_gemm_f16_kernel<4,1,2>",
-    "absmax_kernel", "rotate_kernel"};
+    "absmax_kernel", "rotate_kernel", "qrows_kernel"};
 
 }  // namespace prof
 }  // namespace lq

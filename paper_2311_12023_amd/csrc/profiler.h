@@ -26,7 +26,8 @@ enum Cls {
   GEMM_F16_BASE = 46,       // + planes * 8 + mode * 4 + (l/32 - 1): wide_gemm_f16_kernel (work = flops of the product)
   ABSMAX = 62,
   ROTATE = 63,              // rotate_kernel (work = bytes)
-  NUM_CLASSES = 64
+  QROWS = 64,               // qrows_kernel (work = flops of the product)
+  NUM_CLASSES = 65
 };
 
 bool enabled();

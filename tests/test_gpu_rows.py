@@ -1,0 +1,38 @@
+"""The forward product for 9 to 128 rows of X at the sizes where its kernel can go wrong: row tiles of 16 and groups of 48,
+column tiles of 128 in half runs of 8, reductions shorter than its eight wavefronts, shares that end inside a tile, ranks
+that are not multiples of 4 or of the 64 columns of a tile of L1.  Tolerances as in test_gpu_matmul.py: 4e-5 (precision 0)
+and 1e-2 (precision 1) of |X| (|Q| + |L1| |L2|)."""
+import numpy as np
+import pytest
+
+from paper_2311_12023_amd import gen
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("m,d,k,cfg,rank", [
+    (9, 32, 16, (2, 16, 16), 0), (16, 64, 48, (3, 16, 64), 1), (17, 256, 144, (8, 16, 16), 3), (48, 288, 128, (4, 64, 256), 64),
+    (49, 320, 272, (3, 16, 256), 65), (64, 1056, 528, (2, 16, 64), 33), (65, 512, 640, (8, 32, 16), 200), (97, 992, 384, (4, 128, 64), 62),
+    (127, 224, 1040, (3, 16, 16), 512), (128, 2080, 64, (2, 64, 16), 5), (128, 128, 2064, (4, 16, 256, 5, "fp16"), 16),
+    (9, 4096, 11008, (4, 64, 256, 8, "bf16"), 64),       # shares that end inside a tile
+])
+def test_rows_match_oracle(oracle, m, d, k, cfg, rank):
+    import torch
+    from paper_2311_12023_amd import lq
+    ocfg = oracle.config(*cfg)
+    w = gen.weight_matrix(d, k, 300 + m, 4, outlier_frac=0.01)
+    codes, sidx, v, _ = oracle.quantize(w.ravel(), ocfg)
+    l1, l2 = gen.low_rank_factors(d, k, rank, 301 + m) if rank > 0 else (None, None)
+    x = gen.activations(m, d, 302 + m)
+    ref, scale = oracle.matmul(x, codes, sidx, v, ocfg, k, l1, l2, want_abs=True)
+    t = lambda a: None if a is None else torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    args = (t(x), t(oracle.pack(codes, cfg[0])), t(sidx), t(v), lq.config(*cfg), k, t(l1), t(l2))
+    for precision, tol in ((0, 4e-5), (1, 1e-2)):
+        ws = lq.matmul_workspace(m, d, k, rank)
+        ws.fill_(0xff)                                   # NaN patterns: every partial sum that is read was written
+        y = lq.matmul(*args, precision=precision, workspace=ws)
+        again = lq.matmul(*args, precision=precision)
+        assert torch.equal(y, again)
+        y = y.cpu().numpy()
+        assert np.all(np.isfinite(y))
+        assert np.max(np.abs(y - ref) - tol * scale) <= 0, (precision, np.max(np.abs(y - ref) / scale))
