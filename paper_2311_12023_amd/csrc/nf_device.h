@@ -42,9 +42,15 @@ __device__ inline void load_tables_slot(const DevTables* __restrict__ tab, int s
   load_tables_slot_nosync(tab, slot, t);
   __syncthreads();
 }
+
+// The part of them that the bucket search reads.
 template <int BITS>
-__device__ inline void load_tables(const DevTables* __restrict__ tab, LdsTables& t) {
-  load_tables_slot(tab, Slot<BITS>::value, t);
+__device__ inline void load_search_tables(const DevTables* __restrict__ tab, LdsTables& t) {
+  constexpr int slot = Slot<BITS>::value;
+  for (int i = threadIdx.x; i < (1 << BITS) + 2; i += blockDim.x) t.thr[i] = tab->thr[slot][i];
+  for (int i = threadIdx.x; i < 128; i += blockDim.x)
+    reinterpret_cast<uint32_t*>(t.lut)[i] = reinterpret_cast<const uint32_t*>(tab->lut[slot])[i];
+  __syncthreads();
 }
 
 // Nearest code with ties to the lower index = number of thresholds <= x.
@@ -55,9 +61,9 @@ __device__ inline void load_tables(const DevTables* __restrict__ tab, LdsTables&
 template <int BITS>
 struct Thresholds {
   float r[(1 << BITS) - 1];
-  __device__ explicit Thresholds(const LdsTables& t) {
+  __device__ Thresholds(const LdsTables&, const DevTables* __restrict__ tab) {      // uniform: scalar loads
 #pragma unroll
-    for (int i = 0; i < (1 << BITS) - 1; ++i) r[i] = t.thr[i];
+    for (int i = 0; i < (1 << BITS) - 1; ++i) r[i] = tab->thr[Slot<BITS>::value][i];
   }
   __device__ inline uint32_t nearest(float x) const {
     uint32_t c = 0;
@@ -79,8 +85,8 @@ struct BucketSearch {
     return c;
   }
 };
-template <> struct Thresholds<4> : BucketSearch<1> { __device__ explicit Thresholds(const LdsTables& tt) : BucketSearch<1>(tt) {} };
-template <> struct Thresholds<8> : BucketSearch<2> { __device__ explicit Thresholds(const LdsTables& tt) : BucketSearch<2>(tt) {} };
+template <> struct Thresholds<4> : BucketSearch<1> { __device__ Thresholds(const LdsTables& tt, const DevTables*) : BucketSearch<1>(tt) {} };
+template <> struct Thresholds<8> : BucketSearch<2> { __device__ Thresholds(const LdsTables& tt, const DevTables*) : BucketSearch<2>(tt) {} };
 
 // ---- reductions over the QPB = 4, 8, 16 or 32 consecutive lanes that hold one block (aligned groups) ----
 // Cross-lane moves by DPP: quad_perm for the two steps inside a quad; after those every quad is uniform, so the
@@ -210,8 +216,8 @@ __device__ __forceinline__ float lanes_max(float x, int width) {
   return x;
 }
 
-// Maximum over the `width` consecutive lanes (power of two, 16..256, aligned) that hold one scale
-// group; the workgroup has 256 threads.  s_wave: 4 floats of LDS.  Contains barriers when
+// Maximum over the `width` consecutive lanes (power of two, 16 .. the workgroup's size, aligned) that hold one scale
+// group.  s_wave: one float of LDS per wavefront.  Contains barriers when
 // width > 64, so every thread of the workgroup must call it.
 __device__ inline float group_max(float x, int width, float* s_wave) {
   x = lanes_max(x, width < 64 ? width : 64);
@@ -219,7 +225,7 @@ __device__ inline float group_max(float x, int width, float* s_wave) {
     const int wave = threadIdx.x >> 6;
     if ((threadIdx.x & 63) == 0) s_wave[wave] = x;
     __syncthreads();
-    const int per = width >> 6;             // waves per group: 2 or 4
+    const int per = width >> 6;             // waves per group, a power of two
     const int base = wave & ~(per - 1);
     float m = s_wave[base];
     for (int i = 1; i < per; ++i) m = fmaxf(m, s_wave[base + i]);

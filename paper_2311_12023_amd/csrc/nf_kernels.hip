@@ -39,84 +39,53 @@ int ensure_device_tables() {
 }
 
 // ---------------------------------------------------------------------------------------------
-// Quantize(x, c) in one pass.  A workgroup of 256 lanes walks chunks of 4096*U weights that hold whole
-// scale groups (B0*B1 <= 4096*U); lane t owns runs t, t+256, ... of the chunk, so every load
-// instruction of a wavefront covers one contiguous 4 KB stretch.  Block absmax: cross-lane maxima over
-// B0/16 lanes.  Group absmax: cross-lane / LDS maxima over B0*B1/16 runs.  Nothing but the inputs and
-// outputs touches memory.
+// Quantize(x, c) in one pass.  A workgroup of T lanes takes a chunk of T runs that holds whole scale groups
+// (B0*B1 <= 16*T), one run per lane, so that the four loads of a wavefront cover one contiguous 4 KB stretch.  Block absmax:
+// cross-lane maxima over B0/16 lanes.  Group absmax: cross-lane / LDS maxima over B0*B1/16 lanes.  Nothing but the inputs
+// and outputs touches memory; the loads are on their way before the code search tables are fetched (2 and 3 bits: none, the
+// thresholds are scalars).
+// One run per lane with T from the group size, against 256 lanes that walked two or four runs each: a group of 16384
+// weights is one load latency instead of four (768 x 768, 3 bits 64/256: 11.3 -> below the 9 us that issuing a call takes),
+// and streaming gains too (8192 x 28672, 4 bits 64/256: 207 -> 190 us, 5.6 TB/s; 4096 x 11008: 44 -> 40 us).  HBM-bound there.
 
-template <int BITS, int U>
-__global__ __launch_bounds__(256) void quantize_fused_kernel(const float* __restrict__ x, int64_t nruns,
-                                                             int runs_per_block, int scale_block, int levels,
-                                                             int v_dtype, const DevTables* __restrict__ tab,
-                                                             uint8_t* __restrict__ codes, uint8_t* __restrict__ sidx,
-                                                             float* __restrict__ v) {
+template <int BITS, int T>
+__global__ __launch_bounds__(T) void quantize_fused_kernel(const float* __restrict__ x, int64_t nruns,
+                                                           int runs_per_block, int scale_block, int levels,
+                                                           int v_dtype, const DevTables* __restrict__ tab,
+                                                           uint8_t* __restrict__ codes, uint8_t* __restrict__ sidx,
+                                                           float* __restrict__ v) {
   __shared__ LdsTables s_tab;
-  __shared__ float s_wave[4];
-  load_tables<BITS>(tab, s_tab);
-  Thresholds<BITS> thr(s_tab);
+  __shared__ float s_wave[T / 64];
+  const int64_t run = (int64_t)blockIdx.x * T + threadIdx.x;
+  const bool live = run < nruns;
+  const float4* p = reinterpret_cast<const float4*>(x + (live ? run : nruns - 1) * 16);   // clamped, masked below
+  float4 in[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) in[q] = p[q];
+  if constexpr (BITS >= 4) load_search_tables<BITS>(tab, s_tab);
+  Thresholds<BITS> thr(s_tab, tab);
 
-  const int runs_per_group = runs_per_block * scale_block;          // 16 .. 256*U
-  const int slabs_per_group = runs_per_group > 256 ? runs_per_group / 256 : 1;
-  const int lane_width = runs_per_group > 256 ? 256 : runs_per_group;
+  const int runs_per_group = runs_per_block * scale_block;             // 16 .. T
   const int block_lanes = runs_per_block < 64 ? runs_per_block : 64;   // B0 <= 1024: a block never leaves a wavefront
-  const int64_t chunk_runs = 256 * U;
-  const int64_t nchunks = (nruns + chunk_runs - 1) / chunk_runs;
-
-  for (int64_t chunk = blockIdx.x; chunk < nchunks; chunk += gridDim.x) {
-    // Codes need the block absmax only, so each slab of 256 runs is searched and its codes stored as soon as it is
-    // loaded (the next slab's loads are already in flight); what waits for the whole chunk is the group absmax.
-    float amax[U];
-    int64_t run[U];
-    float4 nxt[4];
-    auto fetch = [&](int u) {
-      const int64_t r = chunk * chunk_runs + u * 256 + threadIdx.x;
-      const float4* p = reinterpret_cast<const float4*>(x + (r < nruns ? r : nruns - 1) * 16);   // clamped, masked below
+  float t[16];
 #pragma unroll
-      for (int q = 0; q < 4; ++q) nxt[q] = p[q];
-    };
-    fetch(0);
+  for (int q = 0; q < 4; ++q) {
+    t[4 * q] = live ? in[q].x : 0.0f; t[4 * q + 1] = live ? in[q].y : 0.0f;
+    t[4 * q + 2] = live ? in[q].z : 0.0f; t[4 * q + 3] = live ? in[q].w : 0.0f;
+  }
+  const float amax = lanes_max(run_absmax(t), block_lanes);
+  const float rcp = safe_reciprocal(amax);
+  uint32_t c[16];
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      run[u] = chunk * chunk_runs + u * 256 + threadIdx.x;
-      const bool live = run[u] < nruns;
-      float t[16];
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        t[4 * q] = live ? nxt[q].x : 0.0f; t[4 * q + 1] = live ? nxt[q].y : 0.0f;
-        t[4 * q + 2] = live ? nxt[q].z : 0.0f; t[4 * q + 3] = live ? nxt[q].w : 0.0f;
-      }
-      if (u + 1 < U) fetch(u + 1);
-      amax[u] = lanes_max(run_absmax(t), block_lanes);
-      const float rcp = safe_reciprocal(amax[u]);
-      uint32_t c[16];
-#pragma unroll
-      for (int j = 0; j < 16; ++j) c[j] = thr.nearest(t[j] * rcp);
-      if (live) store_codes<BITS>(codes, run[u], c);
+  for (int j = 0; j < 16; ++j) c[j] = thr.nearest(t[j] * rcp);
+  if (live) store_codes<BITS>(codes, run, c);
+  const float gmax = group_max(amax, runs_per_group, s_wave);
+  if (live) {
+    if ((run & (runs_per_block - 1)) == 0) {
+      const float sigma = gmax / (float)levels;
+      sidx[run / runs_per_block] = (uint8_t)scale_index(amax, sigma, levels);
     }
-    // group maxima: first across the slabs that belong to one group, then across lanes
-    float gmax[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      float m = amax[u];
-      const int g0 = u - (u % slabs_per_group);
-#pragma unroll
-      for (int w = 0; w < U; ++w)
-        if (w >= g0 && w < g0 + slabs_per_group) m = fmaxf(m, amax[w]);
-      gmax[u] = m;
-    }
-#pragma unroll
-    for (int u = 0; u < U; ++u) gmax[u] = group_max(gmax[u], lane_width, s_wave);
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      if (run[u] < nruns) {
-        if ((run[u] & (runs_per_block - 1)) == 0) {
-          const float sigma = gmax[u] / (float)levels;
-          sidx[run[u] / runs_per_block] = (uint8_t)scale_index(amax[u], sigma, levels);
-        }
-        if (run[u] % runs_per_group == 0) v[run[u] / runs_per_group] = cast_group_scale(gmax[u], v_dtype);
-      }
-    }
+    if (run % runs_per_group == 0) v[run / runs_per_group] = cast_group_scale(gmax, v_dtype);
   }
 }
 
@@ -214,17 +183,14 @@ static void launch_quantize_bits(const float* x, int64_t nruns, const lq_config&
                                  uint8_t* codes, uint8_t* sidx, float* v, hipStream_t st) {
   const int rpb = c.block / 16;
   const int lv = scale_levels(c);
-  const bool big = (int64_t)c.block * c.scale_block > 8192;
-  const int64_t chunk_runs = big ? 1024 : 512;
-  const int64_t nchunks = (nruns + chunk_runs - 1) / chunk_runs;
-  const int64_t cap = (int64_t)1 << 22;       // one chunk per workgroup: the loads of the many resident workgroups overlap
-  const dim3 grid((unsigned)(nchunks < cap ? nchunks : cap)), block(256);
-  if (big)
-    hipLaunchKernelGGL((quantize_fused_kernel<BITS, 4>), grid, block, 0, st, x, nruns, rpb, c.scale_block, lv,
-                       c.v_dtype, tab, codes, sidx, v);
-  else
-    hipLaunchKernelGGL((quantize_fused_kernel<BITS, 2>), grid, block, 0, st, x, nruns, rpb, c.scale_block, lv,
-                       c.v_dtype, tab, codes, sidx, v);
+  const int group_runs = rpb * c.scale_block;        // at most 1024: a workgroup holds whole groups
+#define LQ_QUANTIZE(T)                                                                                                   \
+  hipLaunchKernelGGL((quantize_fused_kernel<BITS, T>), dim3((unsigned)((nruns + (T) - 1) / (T))), dim3(T), 0, st, x,      \
+                     nruns, rpb, c.scale_block, lv, c.v_dtype, tab, codes, sidx, v)
+  if (group_runs > 512) LQ_QUANTIZE(1024);
+  else if (group_runs > 256) LQ_QUANTIZE(512);
+  else LQ_QUANTIZE(256);
+#undef LQ_QUANTIZE
 }
 
 int launch_quantize(const float* x, int64_t n, const lq_config& c, uint8_t* codes, uint8_t* sidx, float* v,
