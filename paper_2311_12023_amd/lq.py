@@ -107,7 +107,9 @@ def _dev(t, dtype, name):
 
 
 def _stream():
-    return torch.cuda.current_stream().cuda_stream
+    # the handle of torch.cuda.current_stream() without the Stream object around it (0.2 instead of 2.7 us, a quarter of what
+    # a small call takes on the host)
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def _pp(p):
