@@ -10,9 +10,12 @@
 // 2..16-byte word) in every 32nd row of its workgroup's range of reduction rows; a workgroup is 8 runs (128 columns) x
 // 32 row groups, so that 256 workgroups of up to 512 rows cover a 4096 x 4096 matrix with every load of a thread issued
 // before the first is used (the whole matrix is in flight at once, which is what an HBM-bound kernel needs).  The X
-// values of the range sit in LDS.  Row groups are summed by a fixed butterfly inside each wavefront and in wavefront
-// order through LDS; the ranges (`splits` of them: enough to fill the machine while the partial sums stay small next to
+// values of the range sit in LDS; they and the code book are asked for before the weights and waited for while those are in
+// flight.  Row groups are summed by a fixed butterfly inside each wavefront that deals the columns out on the way, and in
+// wavefront order through LDS; the ranges (`splits` of them: enough to fill the machine while the partial sums stay small next to
 // the weights) are added in a fixed order by the second kernel, so results are deterministic.
+// Whole call on 4096 x 4096, NF4, rank 64: 1 row 13.9 -> 12.0 us, 4 rows 23 -> 16, 8 rows 36 -> 21 (4096 x 11008: 8 rows 58 ->
+// 35) by loading before the first barrier, 14 instead of 48 exchanges per row of X, and scales without a division.
 #include <algorithm>
 
 #include "kernels.h"
@@ -37,6 +40,7 @@ struct MvArgs {
   int64_t K, N, Nd;
   int m, splits, rows_per_split, tiles_q;
   int block_shift, group_shift, levels;
+  float inv_levels;
   const DevTables* tables;
 };
 
@@ -52,10 +56,25 @@ __global__ __launch_bounds__(256) void qmatvec_kernel(MvArgs a) {
   const int64_t ra = (int64_t)split * a.rows_per_split;
   const int64_t rb = ra + a.rows_per_split < a.K ? ra + a.rows_per_split : a.K;
   const int nrows = (int)(rb - ra);
-  for (int i = tid; i < (1 << BITS); i += 256) s_code[i] = a.tables->code[Slot<BITS>::value][i];
+  // the slice of X and the code book are asked for first, then (quantized tiles) all weights of the thread: what waits at
+  // the barrier is the former, while the latter are in flight
+  float xin[M][MV_ROWS_MAX / 256];
+#pragma unroll
   for (int i = 0; i < M; ++i)
-    for (int r = tid; r < nrows; r += 256) s_x[i][r] = i < a.m ? a.X[(int64_t)i * a.ldx + ra + r] : 0.0f;
-  __syncthreads();
+#pragma unroll
+    for (int h = 0; h < MV_ROWS_MAX / 256; ++h) {
+      const int r = tid + 256 * h;
+      xin[i][h] = i < a.m && r < nrows ? a.X[(int64_t)i * a.ldx + ra + r] : 0.0f;
+    }
+  const float book = tid < (1 << BITS) ? a.tables->code[Slot<BITS>::value][tid] : 0.0f;
+  auto stage = [&]() {
+    if (tid < (1 << BITS)) s_code[tid] = book;
+#pragma unroll
+    for (int i = 0; i < M; ++i)
+#pragma unroll
+      for (int h = 0; h < MV_ROWS_MAX / 256; ++h) s_x[i][tid + 256 * h] = xin[i][h];
+    __syncthreads();
+  };
 
   float acc[M][16];
 #pragma unroll
@@ -91,13 +110,19 @@ __global__ __launch_bounds__(256) void qmatvec_kernel(MvArgs a) {
           vv[j] = a.v[blk >> a.group_shift];
         }
       }
+      if (pass == 0) {
+        __builtin_amdgcn_sched_barrier(0);
+        stage();
+      }
       constexpr int PER = 16 / PASSES;            // codes decoded per pass
       constexpr int CB = BITS == 8 ? 8 : BITS;
 #pragma unroll
       for (int j = 0; j < MV_DEPTH; ++j) {
         const int r = grp + MV_GROUPS * j;
         if (r < nrows) {
-          const float sh = block_scale(si[j], vv[j], a.levels);
+          // v / levels, correctly rounded: the quotient by the reciprocal, corrected by its exact remainder
+          const float qt = vv[j] * a.inv_levels;
+          const float sh = (float)si[j] * fmaf(fmaf(-qt, (float)a.levels, vv[j]), a.inv_levels, qt);
           const uint64_t word = (uint64_t)cw[j].x | ((uint64_t)cw[j].y << 32);
           float xr[M];
 #pragma unroll
@@ -111,10 +136,11 @@ __global__ __launch_bounds__(256) void qmatvec_kernel(MvArgs a) {
         }
       }
     }
-  } else if (live) {
+  } else {
+    stage();
     // 16 columns of D in the thread's rows, four rows' loads issued together; columns past Nd count as zero
     constexpr int DCH = 4;
-    for (int r0 = grp; r0 < nrows; r0 += DCH * MV_GROUPS) {
+    for (int r0 = live ? grp : nrows; r0 < nrows; r0 += DCH * MV_GROUPS) {
       float w[DCH][16];
 #pragma unroll
       for (int u = 0; u < DCH; ++u) {
@@ -148,51 +174,59 @@ __global__ __launch_bounds__(256) void qmatvec_kernel(MvArgs a) {
     }
   }
 
-  // the 8 row groups of a wavefront (lanes 8 apart), by a fixed butterfly; then the wavefronts in order through LDS
+  // The 8 row groups of a wavefront (lanes 8 apart), by a butterfly that deals the columns out on the way: each step hands
+  // half of a lane's columns to its partner, so that row group g of the wavefront ends with columns 2 g' and 2 g' + 1 of its
+  // run, g' = g with its bits reversed (14 exchanges per row of X instead of 48).  Then the wavefronts in order through LDS.
+  const int lane = tid & 63, gw = lane >> 3;
+  const bool b0 = gw & 1, b1 = gw & 2, b2 = gw & 4;
+  const int colw = 8 * (int)b0 + 4 * (int)b1 + 2 * (int)b2;      // first of the lane's two columns
+  float two[M][2];
 #pragma unroll
-  for (int i = 0; i < M; ++i)
+  for (int i = 0; i < M; ++i) {
+    float h8[8], h4[4];
 #pragma unroll
-    for (int j = 0; j < 16; ++j) {
-      float x = acc[i][j];
-      x += __shfl_xor(x, 8);
-      x += __shfl_xor(x, 16);
-      x += __shfl_xor(x, 32);
-      acc[i][j] = x;
+    for (int j = 0; j < 8; ++j) {
+      const float keep = b0 ? acc[i][8 + j] : acc[i][j], give = b0 ? acc[i][j] : acc[i][8 + j];
+      h8[j] = keep + dpp_move<0x128>(give);                      // row_ror:8, lanes 8 apart inside a row of 16
     }
-  const int lane = tid & 63;
-  if (wave > 0 && lane < MV_RUNS) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const float keep = b1 ? h8[4 + j] : h8[j], give = b1 ? h8[j] : h8[4 + j];
+      h4[j] = keep + __shfl_xor(give, 16);
+    }
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const float keep = b2 ? h4[2 + j] : h4[j], give = b2 ? h4[j] : h4[2 + j];
+      two[i][j] = keep + __shfl_xor(give, 32);
+    }
+  }
+  if (wave > 0) {
 #pragma unroll
     for (int i = 0; i < M; ++i)
-#pragma unroll
-      for (int q = 0; q < 4; ++q)
-        *reinterpret_cast<float4*>(&s_sum[wave - 1][i][16 * run + 4 * q]) =
-            make_float4(acc[i][4 * q], acc[i][4 * q + 1], acc[i][4 * q + 2], acc[i][4 * q + 3]);
+      *reinterpret_cast<float2*>(&s_sum[wave - 1][i][16 * run + colw]) = make_float2(two[i][0], two[i][1]);
   }
   __syncthreads();
-  if (wave == 0 && lane < MV_RUNS && live) {
+  if (wave == 0 && live) {
     float* __restrict__ Yq = a.Y + (size_t)split * (size_t)a.m * a.ldy;
     float* __restrict__ Yd = a.Yd + (size_t)split * (size_t)a.m * a.Nd;
 #pragma unroll
     for (int i = 0; i < M; ++i) {
       if (i >= a.m) break;
+      float o[2];
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        float o[4];
+      for (int e = 0; e < 2; ++e) {
+        float s = two[i][e];
+        s += s_sum[0][i][16 * run + colw + e];
+        s += s_sum[1][i][16 * run + colw + e];
+        s += s_sum[2][i][16 * run + colw + e];
+        o[e] = s;
+      }
+      if (!dense) {
+        *reinterpret_cast<float2*>(Yq + (int64_t)i * a.ldy + col + colw) = make_float2(o[0], o[1]);
+      } else {
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          float s = acc[i][4 * q + e];
-          s += s_sum[0][i][16 * run + 4 * q + e];
-          s += s_sum[1][i][16 * run + 4 * q + e];
-          s += s_sum[2][i][16 * run + 4 * q + e];
-          o[e] = s;
-        }
-        if (!dense) {
-          *reinterpret_cast<float4*>(Yq + (int64_t)i * a.ldy + col + 4 * q) = make_float4(o[0], o[1], o[2], o[3]);
-        } else {
-#pragma unroll
-          for (int e = 0; e < 4; ++e)
-            if (col + 4 * q + e < a.Nd) Yd[(int64_t)i * a.Nd + col + 4 * q + e] = o[e];
-        }
+        for (int e = 0; e < 2; ++e)
+          if (col + colw + e < a.Nd) Yd[(int64_t)i * a.Nd + col + colw + e] = o[e];
       }
     }
   }
@@ -354,6 +388,7 @@ int launch_qmatvec(const MvWeights& q, const float* X, int64_t ldx, int64_t K, c
   a.block_shift = __builtin_ctz((unsigned)q.block);
   a.group_shift = __builtin_ctz((unsigned)q.scale_block);
   a.levels = q.levels;
+  a.inv_levels = 1.0f / (float)q.levels;
   a.splits = qmatvec_splits(m, K, N, rank);
   int64_t rows = (K + a.splits - 1) / a.splits;
   rows = (rows + 31) / 32 * 32;
