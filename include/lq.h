@@ -258,13 +258,15 @@ int lq_fisher_row_col(const float* F, int64_t d, int64_t k, float* row_w, float*
  * inputs and quantized matrices with the matrix dequantized just in time):
  *     Y = X (Q + L1 L2)  computed as  X Q + (X L1) L2,
  * Q given in the quantized form that lq_decompose / lq_nf_quantize produce; its weights are decoded inside the
- * GEMM's load stage and never written to memory.
+ * GEMM's load stage (except as said under precision) and never written to the caller's memory.
  *   X        m x d fp32, 16-byte aligned          Y        m x k fp32, 16-byte aligned (so is L2)
  *   codes_packed, scale_idx, v    Quantize(Q, c) of the d x k matrix Q (row-major flattening); k % B0 == 0
  *   L1, L2   d x rank and rank x k fp32, or rank == 0 (then both may be NULL): Y = X Q
  *   precision  0: every operand is split into bf16 hi + lo and each product takes three bf16 MFMAs with fp32
  *                 accumulation (error of an output about 2^-16 of sum |x||w|);  1: bf16 operands, one MFMA
  *                 (about 2^-8), for callers that train in bf16
+ *              Up to 128 rows (rank <= 512) X is split on the fly and the workspace holds partial sums only.  Above 512
+ *              rows (rank <= 64) precision 1 decodes the weights into a bf16 plane in the workspace first.
  *              With m <= 8 and rank <= 512 the product is bound by reading the weights once; it then runs in plain
  *              fp32 on the vector ALU (exact products, fp32 accumulation) and `precision` is ignored.
  *   workspace  lq_matmul_workspace_bytes(m, d, k, rank) bytes: the bf16 hi / lo planes of X (rows padded to a

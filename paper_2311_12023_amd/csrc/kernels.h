@@ -138,6 +138,15 @@ int launch_qrows(const MvWeights& q, const float* X, int64_t ldx, int64_t K, con
                  int rank, int64_t m, int64_t N, int precision, float* Y, int64_t ldy, float* part, size_t part_floats,
                  hipStream_t st);
 
+// ---- forward product in bf16 for many rows of X (planes_kernels.hip) ---------------------------------
+// Y[m x N] = Xh dequant(q) + Th L2 with every operand in bf16: Xh (rows_pad x K) and Th (rows_pad x Kd, rank > 0) are planes,
+// rows_pad a multiple of 256; the weights and L2 (rank x N, contiguous, rank at most 64) are decoded into Wt
+// (weight_plane_elems(K, N) elements) and Lt (weight_plane_elems(Kd, N)) first.  part: qmatmul_part_floats floats.
+size_t weight_plane_elems(int64_t K, int64_t N);
+int launch_plane_product(const MvWeights& q, const uint16_t* Xh, int64_t K, const uint16_t* Th, int Kd, const float* L2,
+                         int rank, int64_t m, int64_t rows_pad, int64_t N, uint16_t* Wt, uint16_t* Lt, float* Y, int64_t ldy,
+                         float* part, size_t part_floats, hipStream_t st);
+
 // ---- products of wide bases with l x l matrices (wide_kernels.hip) ------------------------------
 // C0[z] = U[z] A0[z] and, if A1 is given, C1[z] = U[z] A1[z] (U: l x l fp32 row-major, l = 32..128; A, C: l rows, leading
 // dimension ld, all ld columns are written), fp32 MFMA.  lower: U is lower triangular.

@@ -14,12 +14,16 @@ static int64_t up32(int64_t x) { return (x + 31) & ~(int64_t)31; }
 // MFMA path up to 8 rows).
 constexpr int64_t SMALL_M = QMATVEC_MAX_ROWS;
 constexpr int SMALL_RANK = 512;
+// Above this many rows precision 1 decodes the weights into a bf16 plane first (see planes_kernels.hip for both sides).
+constexpr int64_t PLANE_M = 512;
+
 struct MatmulPlan {
   bool small;
   bool rows;       // a few dozen to a few hundred rows: rows_kernels.hip
   bool fused;      // T = X L1 comes out of the pass that splits X (rank up to SPLIT_PROJECT_MAX_RANK)
   int64_t r32, rows_pad;
   size_t x_plane, t_floats, t_plane, part_floats, scale_floats;   // elements
+  size_t w_plane, l_plane;   // the weights and L2 in bf16 (precision 1, ranks up to SPLIT_PROJECT_MAX_RANK)
 };
 static MatmulPlan plan_matmul(int64_t m, int64_t d, int64_t k, int rank) {
   MatmulPlan p{};
@@ -45,11 +49,15 @@ static MatmulPlan plan_matmul(int64_t m, int64_t d, int64_t k, int rank) {
   const size_t p2 = qmatmul_part_floats(m, k, (int)(d / 32 + p.r32 / 32));
   p.part_floats = p1 > p2 ? p1 : p2;
   p.scale_floats = (size_t)(d * k / 16);            // one scale per block, block size at least 16
+  if (m > PLANE_M && rank <= SPLIT_PROJECT_MAX_RANK) {
+    p.w_plane = weight_plane_elems(d, k);
+    p.l_plane = rank > 0 ? weight_plane_elems(p.r32, k) : 0;
+  }
   return p;
 }
 static size_t plan_bytes(const MatmulPlan& p) {
   return 2 * up256(p.x_plane * 2) + up256(p.t_floats * 4) + 2 * up256(p.t_plane * 2) + up256(p.part_floats * 4) +
-         up256(p.scale_floats * 4);
+         up256(p.scale_floats * 4) + up256(p.w_plane * 2) + up256(p.l_plane * 2);
 }
 
 // Scratch of lq_matmul_few_rows_static: a fixed array in device memory (every GPU the library runs on holds its own copy
@@ -125,8 +133,19 @@ int lq_matmul(const float* X, int64_t m, int64_t d, int64_t k, const uint8_t* co
   uint16_t* th = reinterpret_cast<uint16_t*>(w); w += up256(p.t_plane * 2);
   uint16_t* tl = reinterpret_cast<uint16_t*>(w); w += up256(p.t_plane * 2);
   float* part = reinterpret_cast<float*>(w); w += up256(p.part_floats * 4);
-  float* bscale = reinterpret_cast<float*>(w);
+  float* bscale = reinterpret_cast<float*>(w); w += up256(p.scale_floats * 4);
+  uint16_t* wt = reinterpret_cast<uint16_t*>(w); w += up256(p.w_plane * 2);
+  uint16_t* lt = reinterpret_cast<uint16_t*>(w);
 
+  if (precision == 1 && p.w_plane > 0) {
+    if (p.fused)
+      LQ_TRY(launch_split_project(X, m, d, d, p.rows_pad, L1, rank, precision, xh, xl, part, p.part_floats, th, tl,
+                                  (int)p.r32, BlockScales{}, st));
+    else
+      LQ_TRY(launch_split_planes(X, m, d, d, p.rows_pad, xh, xl, st));
+    const MvWeights q{codes_packed, scale_idx, v, c.bits, c.block, c.scale_block, scale_levels(c)};
+    return launch_plane_product(q, xh, d, th, (int)p.r32, L2, rank, m, p.rows_pad, k, wt, lt, Y, k, part, p.part_floats, st);
+  }
   QmmPart none{};
   if (p.fused) {    // planes of X and of T = X L1 from one pass over X, the block scales of Q in the same launch
     const BlockScales bs{scale_idx, v, d * k / c.block, c.scale_block, scale_levels(c), bscale};

@@ -1,0 +1,276 @@
+// Forward product with a decomposed weight in bf16 for many rows of X (lq_matmul, precision 1):  Y = X Q + (X L1) L2  with
+// every operand rounded to bf16 and fp32 accumulation.  The weights are decoded once per call into a bf16 plane that the
+// product then reads like any other operand, where qmatmul_kernel decodes a weight again for every 256 rows of X: with one
+// MFMA per product that decode cannot hide behind the matrix pipe.  4096 rows, rank 64, whole call: 4096 x 4096 242 -> 178 us
+// (4 bits; 271 -> 198 with 3), 4096 x 11008 640 -> 435, 11008 x 4096 599 -> 425; 1024 rows 98 -> 87, 200 -> 160, 195 -> 168.
+// At 512 rows the two are level (70, 131 against 125, 129) and below that the decode pass costs more than it saves (256
+// rows, 4096 x 11008: 81 against 98), so the line is drawn above 512.  The product runs at 0.9 PFLOP/s; what holds it there
+// is that reading operands from LDS and multiplying overlap poorly (without the MFMAs it takes 110 of its 156 us, without
+// the transfers 140).
+#include <algorithm>
+
+#include "kernels.h"
+#include "nf_device.h"
+#include "profiler.h"
+
+namespace lq {
+
+typedef float floatx16 __attribute__((ext_vector_type(16)));
+typedef float floatx2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+
+// ------------------------------------------------------------------------------------------------
+// Wt[n][k] = bf16(Q[k][n]) and, in the last row of the grid, Lt[n][p] = bf16(L2[p][n]) (p >= rank: zero): a workgroup decodes
+// 64 rows x 128 columns, turns them in LDS and writes runs of 64 along k.
+constexpr int WP_K = 64, WP_N = 128, WP_PITCH = 33;        // LDS pitch in pairs of bf16
+
+struct WpArgs {
+  const uint8_t* codes; const uint8_t* sidx; const float* v;
+  const float* L2; int rank, Kd;
+  uint16_t* Wt; uint16_t* Lt;
+  int64_t K, N;
+  int block_shift, group_shift, levels;
+  float inv_levels;
+  const DevTables* tables;
+};
+
+template <int BITS>
+__global__ __launch_bounds__(256) void weight_plane_kernel(WpArgs a) {
+  __shared__ float s_code[1 << BITS];
+  __shared__ uint32_t s_w[WP_N][WP_PITCH];
+  const int tid = threadIdx.x, run = tid & 7, pair = tid >> 3;      // two rows 2 pair, 2 pair + 1 of one 16-column run
+  const int64_t col = (int64_t)blockIdx.x * WP_N + 16 * run, k0 = (int64_t)blockIdx.y * WP_K;
+  const bool low_rank = k0 >= a.K;
+  const bool live = col < a.N;                                      // N is a multiple of 16
+  float w[2][16];
+#pragma unroll
+  for (int h = 0; h < 2; ++h)
+#pragma unroll
+    for (int j = 0; j < 16; ++j) w[h][j] = 0.0f;
+  if (!low_rank) {
+    for (int i = tid; i < (1 << BITS); i += 256) s_code[i] = a.tables->code[Slot<BITS>::value][i];
+    uint32_t c[2][16];
+    float scale[2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      int64_t k = k0 + 2 * pair + h;
+      k = k < a.K ? k : a.K - 1;                                    // past the end: loaded, never stored
+      const int64_t e = k * a.N + (live ? col : 0), blk = e >> a.block_shift;
+      load_codes<BITS>(a.codes, e >> 4, c[h]);
+      // v / levels, correctly rounded: the quotient by the reciprocal, corrected by its exact remainder
+      const float v = a.v[blk >> a.group_shift], qt = v * a.inv_levels;
+      scale[h] = (float)a.sidx[blk] * fmaf(fmaf(-qt, (float)a.levels, v), a.inv_levels, qt);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int j = 0; j < 16; ++j) w[h][j] = s_code[c[h][j]] * scale[h];
+  } else if (live) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int p = 2 * pair + h;
+      if (p < a.rank) {
+#pragma unroll
+        for (int j = 0; j < 16; ++j) w[h][j] = a.L2[(int64_t)p * a.N + col + j];
+      }
+    }
+  }
+#pragma unroll
+  for (int j = 0; j < 16; ++j)
+    s_w[16 * run + j][pair] = __builtin_bit_cast(uint32_t, __builtin_convertvector(floatx2{w[0][j], w[1][j]}, bf16x2));
+  __syncthreads();
+  uint32_t* out = reinterpret_cast<uint32_t*>(low_rank ? a.Lt : a.Wt);
+  const int64_t pitch = (low_rank ? a.Kd : a.K) / 2, at = low_rank ? 0 : k0 / 2;      // in pairs
+  const int p = tid & 31;
+  if (at + p < pitch) {
+    for (int n = tid >> 5; n < WP_N; n += 8) {
+      const int64_t row = (int64_t)blockIdx.x * WP_N + n;
+      if (row < a.N) out[row * pitch + at + p] = s_w[n][p];
+    }
+  }
+}
+
+// ------------------------------------------------------------------------------------------------
+// Y = A B^T for bf16 planes A (rows x K) and B (columns x K), both with K contiguous, plus a second pair with Kd.  A
+// 512-thread workgroup owns a 256 x 256 tile, a wavefront 128 x 64 of it (2 x 4).  Both tiles of a 32-deep step go from
+// global memory straight into LDS; four stages, one barrier per step, in the middle of its products: a wavefront waits for its
+// own transfers of the next step, the barrier makes that everyone's, and by then all have read the last operands of the
+// present stage, which is refilled.  So the operands of each half step are read while the other half multiplies (with the
+// barrier between the steps and reads before products the same tiles took 161 instead of 156 us at 4096^3; rows padded
+// to spread over the L2's channels changed nothing).  Rows are 64 bytes, unit u of a row stored at u ^ ((row / 2) % 4): conflict-free 128-bit operand reads.
+constexpr int PG_T = 256, PG_STAGES = 4, PG_THREADS = 512;
+constexpr uint32_t PG_TILE = PG_T * 64, PG_STAGE = 2 * PG_TILE;            // bytes
+
+struct PgArgs {
+  const uint16_t* A; const uint16_t* B; int64_t K;
+  const uint16_t* A2; const uint16_t* B2; int64_t K2;
+  float* Y; int64_t ldy;             // splits == 1: m x N; else range s at Y + s * m * ldy
+  int64_t m, N;
+  int nsteps1, nsteps, splits, tiles_m, tiles_n;
+};
+
+__device__ __forceinline__ void pg_transfer(const uint16_t* base, uint32_t voff, uint32_t lds) {
+  asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(voff), "s"(base) : "memory", "m0");
+}
+
+__global__ __launch_bounds__(PG_THREADS) void plane_gemm_kernel(PgArgs a) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char pg_lds[];
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+  const int ln = lane & 31, lh = lane >> 5;
+  // tiles are dealt to the 8 XCDs in contiguous stretches of an order that goes down four row tiles before the next column,
+  // so that the tiles an XCD works on at a time share operands in its L2
+  const int total = a.tiles_m * a.tiles_n, per = (total + 7) / 8;
+  const int t = (int)(blockIdx.x & 7) * per + (int)(blockIdx.x >> 3);
+  if ((int)(blockIdx.x >> 3) >= per || t >= total) return;
+  const int band = t / (4 * a.tiles_n), rows = a.tiles_m - 4 * band < 4 ? a.tiles_m - 4 * band : 4;
+  const int inside = t - band * 4 * a.tiles_n;
+  const int tm = 4 * band + inside % rows, tn = inside / rows;
+  const int s0 = (int)((int64_t)a.nsteps * blockIdx.y / a.splits), s1 = (int)((int64_t)a.nsteps * (blockIdx.y + 1) / a.splits);
+
+  // this wavefront's transfers: rows 16 wave .. + 15 and 128 further of both tiles; lane l brings unit l % 4 ^ swizzle of row l / 4
+  const int lrow = lane >> 2, unit = (lane & 3) ^ ((lrow >> 1) & 3);
+  const uint32_t voff1 = (uint32_t)(lrow * a.K * 2 + unit * 16), voff2 = (uint32_t)(lrow * a.K2 * 2 + unit * 16);
+  const int64_t arow = (int64_t)tm * PG_T + 16 * wave, brow = (int64_t)tn * PG_T + 16 * wave;
+  auto issue = [&](int s) {                      // past the end: the last step again, into a stage that nobody reads any more
+    const uint32_t lds = (uint32_t)((s - s0) % PG_STAGES) * PG_STAGE + (uint32_t)wave * 1024u;
+    s = s < s1 ? s : s1 - 1;
+    const bool second = s >= a.nsteps1;
+    const int64_t K = second ? a.K2 : a.K, k = 32 * (int64_t)(second ? s - a.nsteps1 : s);
+    const uint16_t* A = (second ? a.A2 : a.A) + arow * K + k;
+    const uint16_t* B = (second ? a.B2 : a.B) + brow * K + k;
+    const uint32_t voff = second ? voff2 : voff1;
+    pg_transfer(A, voff, lds);
+    pg_transfer(A + 128 * K, voff, lds + 8192u);
+    pg_transfer(B, voff, lds + PG_TILE);
+    pg_transfer(B + 128 * K, voff, lds + PG_TILE + 8192u);
+  };
+
+  floatx16 acc[4][2];
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.0f;
+  const int wm = wave >> 2, wn = wave & 3;
+  // operand addresses for the two 16-deep halves of a step; a row tile is 2 KB further
+  uint32_t aoff[2], boff[2];
+#pragma unroll
+  for (int g = 0; g < 2; ++g) {
+    const uint32_t u = (uint32_t)((2 * g + lh) ^ ((ln >> 1) & 3)) * 16u;
+    aoff[g] = (uint32_t)(128 * wm + ln) * 64u + u;
+    boff[g] = PG_TILE + (uint32_t)(64 * wn + ln) * 64u + u;
+  }
+
+  bf16x8 x[2][4], b[2][2];                       // operands of the two halves of a step
+  auto read = [&](int s, int g) {
+    const unsigned char* stage = pg_lds + (uint32_t)((s - s0) % PG_STAGES) * PG_STAGE;
+#pragma unroll
+    for (int j = 0; j < 2; ++j) b[g][j] = *reinterpret_cast<const bf16x8*>(stage + boff[g] + 2048u * j);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) x[g][i] = *reinterpret_cast<const bf16x8*>(stage + aoff[g] + 2048u * i);
+    __builtin_amdgcn_sched_barrier(0);           // the reads go out before the products of the other half
+  };
+  auto multiply = [&](int g) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[g][i], b[g][j], acc[i][j], 0, 0, 0);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+#pragma unroll
+  for (int p = 0; p < PG_STAGES; ++p) issue(s0 + p);
+  asm volatile("s_waitcnt vmcnt(12)\n\ts_barrier" ::: "memory");   // 4 transfers a step: the first step's are done
+  read(s0, 0);
+  for (int s = s0; s < s1; ++s) {
+    read(s, 1);
+    multiply(0);
+    // step s + 1 has arrived when at most the transfers of the two steps after it are outstanding; past the barrier that
+    // holds for every wavefront, and none reads stage s any more
+    asm volatile("s_waitcnt vmcnt(8) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    issue(s + PG_STAGES);
+    read(s + 1, 0);                              // past the end: never used (a branch here would cost exact waits)
+    multiply(1);
+  }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");                 // nothing lands in LDS after the workgroup is gone
+
+  float* __restrict__ Y = a.Y + (size_t)blockIdx.y * (size_t)a.m * (size_t)a.ldy;
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    const int64_t col = (int64_t)tn * PG_T + 64 * wn + 32 * j + ln;
+    if (col >= a.N) continue;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) {
+        const int64_t row = (int64_t)tm * PG_T + 128 * wm + 32 * i + 8 * (e >> 2) + 4 * lh + (e & 3);
+        if (row < a.m) Y[row * a.ldy + col] = acc[i][j][e];
+      }
+  }
+}
+
+size_t weight_plane_elems(int64_t K, int64_t N) { return (size_t)((N + PG_T - 1) / PG_T * PG_T) * (size_t)K; }
+
+template <int BITS>
+static void launch_weight_plane(const WpArgs& a, dim3 grid, hipStream_t st) {
+  hipLaunchKernelGGL(weight_plane_kernel<BITS>, grid, dim3(256), 0, st, a);
+}
+
+int launch_plane_product(const MvWeights& q, const uint16_t* Xh, int64_t K, const uint16_t* Th, int Kd, const float* L2,
+                         int rank, int64_t m, int64_t rows_pad, int64_t N, uint16_t* Wt, uint16_t* Lt, float* Y, int64_t ldy,
+                         float* part, size_t part_floats, hipStream_t st) {
+  if (m < 1 || rows_pad < m || rows_pad % PG_T || K < 32 || K % 32 || N < 16 || N % 16 || K * N >= (1ll << 31) ||
+      rows_pad * K >= (1ll << 31))
+    return LQ_ERR_SHAPE;
+  if (rank < 0 || (rank > 0 && (Kd < rank || Kd % 32 || Kd > WP_K))) return LQ_ERR_RANK;
+  if (q.block < 16 || (q.block & (q.block - 1)) || q.scale_block < 1 || (q.scale_block & (q.scale_block - 1)) || N % q.block)
+    return LQ_ERR_CONFIG;
+  WpArgs w{};
+  w.codes = q.codes; w.sidx = q.sidx; w.v = q.v; w.L2 = L2; w.rank = rank; w.Kd = Kd; w.Wt = Wt; w.Lt = Lt; w.K = K; w.N = N;
+  w.block_shift = __builtin_ctz((unsigned)q.block);
+  w.group_shift = __builtin_ctz((unsigned)q.scale_block);
+  w.levels = q.levels;
+  w.inv_levels = 1.0f / (float)q.levels;
+  LQ_TRY(device_tables(&w.tables));
+  const dim3 wgrid((unsigned)((N + WP_N - 1) / WP_N), (unsigned)((K + WP_K - 1) / WP_K + (rank > 0 ? 1 : 0)));
+  if (wgrid.y > 65535) return LQ_ERR_SHAPE;
+  {
+    prof::Scope ps(prof::MISC, st, (double)K * (double)N * (q.bits / 8.0 + 2.0));
+    switch (q.bits) {
+      case 2: launch_weight_plane<2>(w, wgrid, st); break;
+      case 3: launch_weight_plane<3>(w, wgrid, st); break;
+      case 4: launch_weight_plane<4>(w, wgrid, st); break;
+      case 8: launch_weight_plane<8>(w, wgrid, st); break;
+      default: return LQ_ERR_CONFIG;
+    }
+    LQ_HIP_TRY(hipGetLastError());
+  }
+  PgArgs a{};
+  a.A = Xh; a.B = Wt; a.K = K; a.A2 = Th; a.B2 = Lt; a.K2 = rank > 0 ? Kd : 0;
+  a.m = m; a.N = N;
+  a.nsteps1 = (int)(K / 32);
+  a.nsteps = a.nsteps1 + (int)(a.K2 / 32);
+  a.tiles_m = (int)((m + PG_T - 1) / PG_T);
+  a.tiles_n = (int)((N + PG_T - 1) / PG_T);
+  a.splits = qmatmul_splits(m, N, a.nsteps);
+  if (a.splits > 1 && part_floats < (size_t)a.splits * (size_t)m * (size_t)N) return LQ_ERR_WORKSPACE;
+  a.Y = a.splits > 1 ? part : Y;
+  a.ldy = a.splits > 1 ? N : ldy;
+  const int64_t tiles = (int64_t)a.tiles_m * a.tiles_n;
+  if (tiles >= (1ll << 28)) return LQ_ERR_SHAPE;
+  constexpr size_t lds = (size_t)PG_STAGES * PG_STAGE;
+  static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(plane_gemm_kernel),
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  LQ_HIP_TRY(attr);
+  {
+    prof::Scope ps(prof::QMATMUL, st, 2.0 * (double)m * (double)N * (double)(K + a.K2));
+    hipLaunchKernelGGL(plane_gemm_kernel, dim3((unsigned)((tiles + 7) / 8 * 8), (unsigned)a.splits), dim3(PG_THREADS), lds, st, a);
+    LQ_HIP_TRY(hipGetLastError());
+  }
+  if (a.splits > 1) return launch_qmatmul_reduce(part, a.splits, m, N, Y, ldy, st);
+  return LQ_OK;
+}
+
+}  // namespace lq
