@@ -193,6 +193,10 @@ int launch_absmax(const float* x, int64_t n, float* out, hipStream_t st);
 // X <- X - alpha * Y, both `count` floats (multiple of 4).
 constexpr int DEFLATE_ROWS_MAX = 16;
 int launch_deflate_rows(float* X, const float* L, int l, int locked, int64_t m, int64_t ldx, hipStream_t st);
+// Both in one pass: X <- a X + b Y + c Z (Y NULL: X as it is; Z NULL: no third term), then deflate_rows.  X, Y, Z: l rows with
+// leading dimension ldx, columns past m zero.
+int launch_filter_step(float* X, float a, const float* Y, float b, const float* Z, float c, const float* L, int l, int locked,
+                       int64_t m, int64_t ldx, hipStream_t st);
 int launch_lincomb3(float* X, float a, const float* Y, float b, const float* Z, float c, int64_t count, hipStream_t st);
 // Fills a wide matrix (l x m, padded ld) with N(0,1) draws from a counter-based generator; pads are zeroed.
 int launch_gaussian_fill(float* X, int l, int64_t m, int64_t ldx, uint64_t seed, hipStream_t st);

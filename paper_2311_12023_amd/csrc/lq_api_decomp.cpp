@@ -210,7 +210,7 @@ static int ritz_rotate(const Ctx& c, int l, const float* Y, float* Y2, size_t sY
 // limited so that this stays below `growth` = 1e5 (the leak stays a small part of the row).
 // Dominant directions that would hold the degree down are locked once converged (a direction theta_i has converged to
 // (b / theta_i)^it after `it` applications of M; 1e-5 is asked for): their rows stay as the last Rayleigh-Ritz left them
-// and every filter step ends by removing their components from the other rows (deflate_rows_kernel), so the recurrence
+// and every filter step ends by removing their components from the other rows (filter_step_kernel), so the recurrence
 // runs on the deflated operator and theta_1 above is the largest unlocked Ritz value.  Spectra with a dominant part
 // that is neither locked yet nor small get m = 1, which is subspace iteration on M - (b/2) I.  Before the first
 // Rayleigh-Ritz there is no b: plain power steps.
@@ -364,15 +364,14 @@ static int cold_factorize(const Ctx& c, const float* A, uint64_t seed, const flo
     m_prev = m;
     // step 1 (Ba = Y0 A is at hand)
     if (!have_g) LQ_TRY(gemm(c, MODE_NT, l, pl.d, pl.k, Ba, pl.ldk, 0, A, pl.k, 0, P[0], pl.ldd, 0, 1));
-    if (bcut > 0.0) LQ_TRY(launch_lincomb3(P[0], (float)(2.0 / bcut), Y0, -1.0f, nullptr, 0.0f, ycount, c.st));
-    LQ_TRY(launch_deflate_rows(P[0], Y0, l, locked, pl.d, pl.ldd, c.st));
+    LQ_TRY(launch_filter_step(P[0], bcut > 0.0 ? (float)(2.0 / bcut) : 1.0f, bcut > 0.0 ? Y0 : nullptr, -1.0f, nullptr, 0.0f, Y0, l,
+                              locked, pl.d, pl.ldd, c.st));
     // Y0 keeps the locked rows for the whole cycle: the recurrence rotates through the other three blocks
     float* Yj = P[0]; float* Yjm1 = Y0; float* Ynew = P[1]; float* third = P[2];
     for (int j = 1; j < m; ++j) {
       LQ_TRY(gemm(c, MODE_NN, l, pl.k, pl.d, Yj, pl.ldd, 0, A, pl.k, 0, Bb, pl.ldk, 0, 1));
       LQ_TRY(gemm(c, MODE_NT, l, pl.d, pl.k, Bb, pl.ldk, 0, A, pl.k, 0, Ynew, pl.ldd, 0, 1));
-      LQ_TRY(launch_lincomb3(Ynew, (float)(4.0 / bcut), Yj, -2.0f, Yjm1, -1.0f, ycount, c.st));
-      LQ_TRY(launch_deflate_rows(Ynew, Y0, l, locked, pl.d, pl.ldd, c.st));
+      LQ_TRY(launch_filter_step(Ynew, (float)(4.0 / bcut), Yj, -2.0f, Yjm1, -1.0f, Y0, l, locked, pl.d, pl.ldd, c.st));
       float* freed = Yjm1 == Y0 ? third : Yjm1;
       Yjm1 = Yj; Yj = Ynew; Ynew = freed;
     }

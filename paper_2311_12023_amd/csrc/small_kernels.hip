@@ -533,6 +533,97 @@ int launch_deflate_rows(float* X, const float* L, int l, int locked, int64_t m, 
   return LQ_OK;
 }
 
+// A filter step's lincomb3 and deflate_rows in one pass over the rows (one workgroup per row, the combined row in
+// registers): X is read and written once instead of three times and twice, and one launch waits for the other no more
+// (128 rows x 4096, four locked: 4.7 + 12.7 -> 5.9 us).  RC float4 per thread bound the row length; LB >= locked fixes the register arrays.
+constexpr int FS_THREADS = 512, FS_RC = 8;
+
+template <int LB>
+__global__ __launch_bounds__(FS_THREADS) void filter_step_kernel(float* __restrict__ X, float a, const float* __restrict__ Y,
+                                                                 float b, const float* __restrict__ Z, float c,
+                                                                 const float* __restrict__ L, int locked, int q4) {
+  __shared__ float s_part[FS_THREADS / 64][LB];
+  const int tid = threadIdx.x;
+  const int64_t row = blockIdx.x;
+  float4* x = reinterpret_cast<float4*>(X) + row * q4;
+  const float4* l4 = reinterpret_cast<const float4*>(L);
+  if (row < locked) {
+    for (int j = tid; j < q4; j += FS_THREADS) x[j] = l4[row * q4 + j];
+    return;
+  }
+  const float4* y = reinterpret_cast<const float4*>(Y) + row * q4;
+  const float4* z = Z ? reinterpret_cast<const float4*>(Z) + row * q4 : nullptr;
+  float4 v[FS_RC];
+  float dot[LB];
+#pragma unroll
+  for (int o = 0; o < LB; ++o) dot[o] = 0.f;
+#pragma unroll
+  for (int r = 0; r < FS_RC; ++r) {
+    const int j = tid + r * FS_THREADS;
+    v[r] = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (j < q4) {
+      float4 t = x[j];
+      if (Y) {
+        const float4 u = y[j];
+        t.x = fmaf(a, t.x, b * u.x); t.y = fmaf(a, t.y, b * u.y); t.z = fmaf(a, t.z, b * u.z); t.w = fmaf(a, t.w, b * u.w);
+        if (z) {
+          const float4 w = z[j];
+          t.x = fmaf(c, w.x, t.x); t.y = fmaf(c, w.y, t.y); t.z = fmaf(c, w.z, t.z); t.w = fmaf(c, w.w, t.w);
+        }
+      }
+      v[r] = t;
+#pragma unroll
+      for (int o = 0; o < LB; ++o) {
+        const float4 u = l4[(int64_t)(o < locked ? o : 0) * q4 + j];       // past the last one: a row again, its sum unused
+        dot[o] = fmaf(t.x, u.x, fmaf(t.y, u.y, fmaf(t.z, u.z, fmaf(t.w, u.w, dot[o]))));
+      }
+    }
+  }
+#pragma unroll
+  for (int o = 0; o < LB; ++o) {
+    float t = dot[o];
+    for (int off = 1; off < 64; off <<= 1) t += __shfl_xor(t, off);
+    if ((tid & 63) == 0) s_part[tid >> 6][o] = t;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int o = 0; o < LB; ++o) {
+    float t = 0.f;
+#pragma unroll
+    for (int w = 0; w < FS_THREADS / 64; ++w) t += s_part[w][o];
+    dot[o] = o < locked ? -t : 0.f;
+  }
+#pragma unroll
+  for (int r = 0; r < FS_RC; ++r) {
+    const int j = tid + r * FS_THREADS;
+    if (j < q4) {
+      float4 t = v[r];
+#pragma unroll
+      for (int o = 0; o < LB; ++o) {
+        const float4 u = l4[(int64_t)(o < locked ? o : 0) * q4 + j];
+        t.x = fmaf(dot[o], u.x, t.x); t.y = fmaf(dot[o], u.y, t.y); t.z = fmaf(dot[o], u.z, t.z); t.w = fmaf(dot[o], u.w, t.w);
+      }
+      x[j] = t;
+    }
+  }
+}
+
+int launch_filter_step(float* X, float a, const float* Y, float b, const float* Z, float c, const float* L, int l, int locked,
+                       int64_t m, int64_t ldx, hipStream_t st) {
+  if (locked < 0 || locked > DEFLATE_MAX || ldx % 4 != 0 || (Z && !Y)) return LQ_ERR_ARG;
+  if (locked == 0 || ldx > (int64_t)4 * FS_THREADS * FS_RC) {
+    if (Y) LQ_TRY(launch_lincomb3(X, a, Y, b, Z, c, (int64_t)l * ldx, st));
+    return launch_deflate_rows(X, L, l, locked, m, ldx, st);
+  }
+  prof::Scope ps(prof::MISC, st, (double)l * ldx * 4.0 * (2 + (Y ? 1 : 0) + (Z ? 1 : 0)));
+  const int q4 = (int)(ldx / 4);
+  if (locked <= 4) hipLaunchKernelGGL(filter_step_kernel<4>, dim3(l), dim3(FS_THREADS), 0, st, X, a, Y, b, Z, c, L, locked, q4);
+  else if (locked <= 8) hipLaunchKernelGGL(filter_step_kernel<8>, dim3(l), dim3(FS_THREADS), 0, st, X, a, Y, b, Z, c, L, locked, q4);
+  else hipLaunchKernelGGL(filter_step_kernel<16>, dim3(l), dim3(FS_THREADS), 0, st, X, a, Y, b, Z, c, L, locked, q4);
+  LQ_HIP_TRY(hipGetLastError());
+  return LQ_OK;
+}
+
 int launch_gaussian_fill(float* X, int l, int64_t m, int64_t ldx, uint64_t seed, hipStream_t st) {
   const int64_t total = (int64_t)l * ldx;
   const int64_t want = (total + 255) / 256;

@@ -30,3 +30,22 @@ def test_orthonormalize_ragged(l, extra):
     assert np.max(np.abs(q @ q.T - np.eye(l))) < 2e-4
     c = np.linalg.cholesky(x.astype(np.float64) @ x.T.astype(np.float64))
     assert np.max(np.abs(c @ q - x)) < 2e-4 * np.max(np.abs(x)) * np.sqrt(l)
+
+
+@pytest.mark.parametrize("d,k,rank", [(192, 256, 4), (1500, 640, 16), (640, 1504, 16)])
+def test_factorize_with_dominant_directions(d, k, rank):
+    """Dominant directions that the cold start locks (the filter step then removes them from every row), up to more than the
+    eight of its middle size: singular values against LAPACK at the 1e-4 of the decomposition's tests."""
+    import torch
+    from paper_2311_12023_amd import lq
+    rng = np.random.default_rng(d + rank)
+    for dominant in (1, 4, 7, 13):
+        n = min(d, k)
+        s = np.concatenate([40.0 * 0.9 ** np.arange(dominant), 1.0 + 0.1 * np.sort(rng.random(n - dominant))[::-1]])
+        u, _ = np.linalg.qr(rng.standard_normal((d, n)))
+        v, _ = np.linalg.qr(rng.standard_normal((k, n)))
+        a = ((u * s) @ v.T).astype(np.float32)
+        l1, l2, sigma = lq.factorize(torch.from_numpy(a).cuda(), rank, seed=3)
+        ref = np.linalg.svd(a.astype(np.float64), compute_uv=False)[:rank]
+        assert np.max(np.abs(sigma - ref) / ref) < 1e-4, dominant
+        assert torch.isfinite(l1).all() and torch.isfinite(l2).all()
