@@ -5,6 +5,7 @@ condition of about 10 (rows drawn with 2 l columns or more), l * 2^-24 * 10 < 2e
 import numpy as np
 import pytest
 
+from paper_2311_12023_amd import gen
 from testing_lib import load
 
 pytestmark = pytest.mark.gpu
@@ -49,3 +50,17 @@ def test_factorize_with_dominant_directions(d, k, rank):
         ref = np.linalg.svd(a.astype(np.float64), compute_uv=False)[:rank]
         assert np.max(np.abs(sigma - ref) / ref) < 1e-4, dominant
         assert torch.isfinite(l1).all() and torch.isfinite(l2).all()
+
+
+@pytest.mark.parametrize("d,k,rank", [(33, 48, 1), (65, 400, 15), (130, 144, 16), (96, 1040, 17), (192, 272, 97), (160, 256, 128)])
+def test_error_with_packed_factors(d, k, rank):
+    """The error that the decomposition reports comes from the factors packed as 16-bit pairs; it equals the error of the
+    factors returned.  An entry is off by at most 2^-17 of itself and the product of the two low parts is left out, so the
+    product is off by less than 2^-15 |L1| |L2|; 1e-6 covers the 32-bit subtraction."""
+    import torch
+    from paper_2311_12023_amd import lq
+    w = gen.weight_matrix(d, k, 700 + rank, min(rank, 8))
+    r = lq.decompose(torch.from_numpy(w).cuda(), rank, lq.config(4, 16, 16), 2, seed=5, want_dense=True)
+    l1, l2, q = (r[n].cpu().numpy().astype(np.float64) for n in ("L1", "L2", "Q"))
+    ref = np.linalg.norm(w - q - l1 @ l2)
+    assert abs(r["err"] - ref) <= 2.0 ** -15 * np.linalg.norm(np.abs(l1) @ np.abs(l2)) + 1e-6 * ref
