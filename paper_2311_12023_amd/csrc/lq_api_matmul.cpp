@@ -35,7 +35,8 @@ static MatmulPlan plan_matmul(int64_t m, int64_t d, int64_t k, int rank) {
   }
   p.rows = m <= QROWS_MAX_ROWS && rank <= QROWS_MAX_RANK;
   if (p.rows) {
-    p.part_floats = qrows_part_floats(m, d, k, rank);
+    // no less than the reduction ranges of the kernel for more rows, which callers know as this size's lower bound
+    p.part_floats = std::max(qrows_part_floats(m, d, k, rank), qmatmul_part_floats(m, k, (int)(d / 32 + up32(rank) / 32)));
     return p;
   }
   p.r32 = up32(rank);
