@@ -90,7 +90,7 @@ def measured_traffic(name: str, table: str | None = None):
     return tot / n if n else None
 
 
-# Kernel classes with a roofline of their own.  Everything else the library launches (Gram matrices, Cholesky, Jacobi,
+# Kernel classes with a roofline of their own.  Everything else the library launches (Gram matrices, Cholesky, eigen-solver,
 # fix-ups, packing) is a short or single-workgroup kernel bound by latency; those are listed with their time only.
 STREAMING = ("lowrank_blockquant_kernel", "residual_kernel", "scalequant_error_kernel", "quantize_fused_kernel",
              "dequant_kernel")
@@ -638,7 +638,7 @@ def main() -> int:
                     help="HIP hardware queues of this process (GPU_MAX_HW_QUEUES, 1..32).  Default 8 for the sweeps of "
                          "workloads 3 and 5, the runtime's own 4 otherwise.  Workload 3 keeps up to 14 streams busy (7 "
                          "matrices x 2 sub-batches); with 4 queues the streams share queues and a latency-bound "
-                         "single-workgroup kernel (Cholesky, Jacobi) of one stream holds back the machine-filling kernels "
+                         "single-workgroup kernel (Cholesky, eigen-solver) of one stream holds back the machine-filling kernels "
                          "of another in the same queue: 8 measured 4 %% faster, 14 no better.  Workload 2 (small "
                          "matrices, every kernel latency-bound) measured 16 %% slower with 8 than with 4")
     args = ap.parse_args()
