@@ -45,7 +45,8 @@ size_t packed_factor_elems(int64_t d, int64_t k, int rank) {
 
 // Bound by memory (both factors once in 32 bits, once out as two 16-bit planes).  A workgroup transposes PACK_ROWS rows
 // through LDS so that loads run along the factor's rows and stores are contiguous; a thread per row stored 16 bytes every
-// 2 RK bytes (12 problems of 4096 + 4096 rows, rank 64: 78 -> 46 us per launch).
+// 2 RK bytes (12 problems of 4096 + 4096 rows, rank 64,
+// beside two other streams: 78 -> 46 us per launch).
 constexpr int PACK_ROWS = 32, PACK_MAX_RANK = 128;
 static_assert(TM % PACK_ROWS == 0 && TN % PACK_ROWS == 0, "a workgroup's rows belong to one factor");
 __global__ __launch_bounds__(256) void pack_factors_kernel(PhaseArgs a, int64_t dpad, int64_t kpad, int rk) {
