@@ -30,6 +30,7 @@
 #include <algorithm>
 
 #include "kernels.h"
+#include "lds_transfer.h"
 #include "nf_device.h"
 #include "profiler.h"
 
@@ -195,15 +196,9 @@ __device__ __forceinline__ void qmm_dma(const uint16_t* hi, const uint16_t* lo, 
                                         uint32_t voff, uint32_t lds) {
 #pragma unroll
   for (int j = 0; j < 2; ++j) {
-    const uint16_t* ph = hi + k_elems + (int64_t)j * 128 * row_elems;    // wavefront-uniform
-    asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds + (uint32_t)j * 8192u), "v"(voff), "s"(ph)
-                 : "memory", "m0");
-    if constexpr (SPLIT) {
-      const uint16_t* pl = lo + k_elems + (int64_t)j * 128 * row_elems;
-      asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds + QmmLds::X_PLANE + (uint32_t)j * 8192u),
-                   "v"(voff), "s"(pl)
-                   : "memory", "m0");
-    }
+    const int64_t at = k_elems + (int64_t)j * 128 * row_elems;    // wavefront-uniform
+    transfer_to_lds(hi + at, voff, lds + (uint32_t)j * 8192u);
+    if constexpr (SPLIT) transfer_to_lds(lo + at, voff, lds + QmmLds::X_PLANE + (uint32_t)j * 8192u);
   }
 }
 

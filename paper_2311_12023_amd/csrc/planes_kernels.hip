@@ -10,6 +10,7 @@
 #include <algorithm>
 
 #include "kernels.h"
+#include "lds_transfer.h"
 #include "nf_device.h"
 #include "profiler.h"
 
@@ -111,10 +112,6 @@ struct PgArgs {
   int nsteps1, nsteps, splits, tiles_m, tiles_n;
 };
 
-__device__ __forceinline__ void pg_transfer(const uint16_t* base, uint32_t voff, uint32_t lds) {
-  asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(voff), "s"(base) : "memory", "m0");
-}
-
 __global__ __launch_bounds__(PG_THREADS) void plane_gemm_kernel(PgArgs a) {
   extern __shared__ __attribute__((aligned(16))) unsigned char pg_lds[];
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
@@ -141,10 +138,10 @@ __global__ __launch_bounds__(PG_THREADS) void plane_gemm_kernel(PgArgs a) {
     const uint16_t* A = (second ? a.A2 : a.A) + arow * K + k;
     const uint16_t* B = (second ? a.B2 : a.B) + brow * K + k;
     const uint32_t voff = second ? voff2 : voff1;
-    pg_transfer(A, voff, lds);
-    pg_transfer(A + 128 * K, voff, lds + 8192u);
-    pg_transfer(B, voff, lds + PG_TILE);
-    pg_transfer(B + 128 * K, voff, lds + PG_TILE + 8192u);
+    transfer_to_lds(A, voff, lds);
+    transfer_to_lds(A + 128 * K, voff, lds + 8192u);
+    transfer_to_lds(B, voff, lds + PG_TILE);
+    transfer_to_lds(B + 128 * K, voff, lds + PG_TILE + 8192u);
   };
 
   floatx16 acc[4][2];
