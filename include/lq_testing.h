@@ -61,6 +61,8 @@ int lq_test_ritz_residual(const float* G, const float* Y, const double* lam, int
  * plus two comparisons for 4 and 8 bits) on one normalised weight x; -1 for an unsupported bit width.
  * Needs no GPU. */
 int lq_test_bucket_code(int bits, float x);
+/* Host-side evaluation of the division-free v / levels of the forward product's kernels.  Needs no GPU. */
+float lq_test_sigma_by_reciprocal(float v, int levels);
 /* Largest LDS allocation per workgroup the device reports, in bytes. */
 size_t lq_test_lds_limit(void);
 /* Arms a capture for the next lq_error_table call of this host thread (of the testing library): after iteration `iter`

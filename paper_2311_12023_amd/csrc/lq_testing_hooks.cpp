@@ -122,6 +122,10 @@ int lq_test_bucket_code(int bits, float x) {
   return c0 + (x >= t.thr[slot][c0]) + (x >= t.thr[slot][c0 + 1]);
 }
 
+float lq_test_sigma_by_reciprocal(float v, int levels) {
+  return sigma_by_reciprocal(v, (float)levels, 1.0f / (float)levels);
+}
+
 size_t lq_test_lds_limit(void) { return lds_limit_for_tests(); }
 
 }  // extern "C"

@@ -120,9 +120,7 @@ __global__ __launch_bounds__(256) void qmatvec_kernel(MvArgs a) {
       for (int j = 0; j < MV_DEPTH; ++j) {
         const int r = grp + MV_GROUPS * j;
         if (r < nrows) {
-          // v / levels, correctly rounded: the quotient by the reciprocal, corrected by its exact remainder
-          const float qt = vv[j] * a.inv_levels;
-          const float sh = (float)si[j] * fmaf(fmaf(-qt, (float)a.levels, vv[j]), a.inv_levels, qt);
+          const float sh = block_scale_by_reciprocal(si[j], vv[j], a.levels, a.inv_levels);
           const uint64_t word = (uint64_t)cw[j].x | ((uint64_t)cw[j].y << 32);
           float xr[M];
 #pragma unroll

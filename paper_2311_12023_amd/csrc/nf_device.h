@@ -247,6 +247,20 @@ __device__ inline float block_scale(uint32_t idx, float v_stored, int levels) {
   return (float)idx * sigma;
 }
 
+// v / levels with inv = fl32(1 / levels), without a division: the quotient by the reciprocal, corrected by its remainder,
+// which the fused product leaves exact (Markstein, "Computation of elementary functions on the IBM RISC System/6000
+// processor", 1990).  Equal to the division for every v >= 0 and every `levels` that a configuration can have (all 2^31
+// bit patterns compared on the host).  The maximum is for v = infinity, where the remainder is inf - inf: what is added
+// to the infinite quotient then only has to be a number.
+__host__ __device__ inline float sigma_by_reciprocal(float v, float levels, float inv) {
+  const float q = v * inv;
+  return fmaf(fmaxf(fmaf(-q, levels, v), -3.402823466e38f), inv, q);
+}
+// block_scale for kernels whose inner loop it is in.
+__device__ __forceinline__ float block_scale_by_reciprocal(uint32_t idx, float v_stored, int levels, float inv) {
+  return (float)idx * sigma_by_reciprocal(v_stored, (float)levels, inv);
+}
+
 // cast(v, b2): round to nearest even into the storage type, returned as fp32.
 __device__ inline float cast_group_scale(float v, int v_dtype) {
   if (v_dtype == LQ_V_BF16) {

@@ -59,9 +59,7 @@ __global__ __launch_bounds__(256) void weight_plane_kernel(WpArgs a) {
       k = k < a.K ? k : a.K - 1;                                    // past the end: loaded, never stored
       const int64_t e = k * a.N + (live ? col : 0), blk = e >> a.block_shift;
       load_codes<BITS>(a.codes, e >> 4, c[h]);
-      // v / levels, correctly rounded: the quotient by the reciprocal, corrected by its exact remainder
-      const float v = a.v[blk >> a.group_shift], qt = v * a.inv_levels;
-      scale[h] = (float)a.sidx[blk] * fmaf(fmaf(-qt, (float)a.levels, v), a.inv_levels, qt);
+      scale[h] = block_scale_by_reciprocal(a.sidx[blk], a.v[blk >> a.group_shift], a.levels, a.inv_levels);
     }
     __syncthreads();
 #pragma unroll

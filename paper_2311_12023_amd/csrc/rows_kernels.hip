@@ -204,9 +204,7 @@ __global__ __launch_bounds__(64 * QR_WAVES, 2) void qrows_kernel(QrArgs a) {
         for (int i = 0; i < 8; ++i) {
           cur[i] = spread_half<BITS>(cw[i]);
           if constexpr (BITS == 4) asm("" : "+v"(cur[i].x), "+v"(cur[i].y));   // or the compiler undoes it
-          // v / levels, correctly rounded: the quotient by the reciprocal, corrected by its exact remainder
-          const float qt = vv[i] * a.inv_levels;
-          scale[i] = (float)si[i] * fmaf(fmaf(-qt, (float)a.levels, vv[i]), a.inv_levels, qt);
+          scale[i] = block_scale_by_reciprocal(si[i], vv[i], a.levels, a.inv_levels);
         }
         split_x();
         const int sn = s + QR_WAVES < s1 ? s + QR_WAVES : s;           // past the end: the same step again

@@ -198,3 +198,22 @@ def test_matmul_in_a_hip_graph(env, oracle, m):
         graph.replay()
         torch.cuda.synchronize()
         assert torch.equal(y, eager), rep
+
+
+@pytest.mark.parametrize("m,precision", [(1, 0), (8, 0), (24, 1), (300, 1), (600, 1)])
+def test_infinite_group_scale_is_infinite_weights(env, oracle, m, precision):
+    """A group scale of infinity (a maximum above 65504 stored in fp16) makes infinite weights, as Dequantize returns them:
+    the columns that hold one come out infinite, the others as ever."""
+    torch, lq = env
+    d, k, cfg = 64, 512, (4, 16, 16, 8, "fp16")
+    rng = np.random.default_rng(m)
+    ocfg = oracle.config(*cfg)
+    codes, sidx, v, _ = oracle.quantize(rng.uniform(0.5, 1.0, d * k).astype(np.float32), ocfg)
+    v[3] = np.inf                                            # row 1, columns 256 .. 511
+    x = rng.uniform(0.5, 1.0, (m, d)).astype(np.float32)
+    q = oracle.dequantize(codes, sidx, v, ocfg).reshape(d, k).astype(np.float64)
+    ref = x.astype(np.float64) @ q
+    assert np.all(np.isposinf(ref) == (np.arange(k) >= 256))
+    y = _gpu_product(env, oracle, x, codes, sidx, v, cfg, k, None, None, precision)
+    assert np.array_equal(np.isposinf(y), np.isposinf(ref))
+    assert np.max(np.abs(y[:, :256] / ref[:, :256] - 1)) < TOL_BF16

@@ -222,3 +222,20 @@ def test_code_search_equals_brute_force(L, oracle, bits):
     assert np.array_equal(got[inside], want[inside])
     assert L.lq_test_bucket_code(bits, float("nan")) == 0
     assert L.lq_test_bucket_code(5, 0.0) == -1
+
+
+@pytest.mark.parametrize("scale_bits", [2, 3, 4, 5, 6, 7, 8])
+def test_division_free_block_scale_equals_the_division(L, scale_bits):
+    """The forward product's kernels take v / levels from the reciprocal and a correction: equal to the division for normal
+    and subnormal v, for quotients that are subnormal, at both ends of the range, and for infinity."""
+    levels = 2 ** (scale_bits - 1) - 1
+    L = C.CDLL(TEST_LIB)
+    L.lq_test_sigma_by_reciprocal.restype = C.c_float
+    L.lq_test_sigma_by_reciprocal.argtypes = [C.c_float, C.c_int]
+    rng = np.random.default_rng(scale_bits)
+    bits = np.concatenate([rng.integers(0, 0x7F800000, 20000), np.arange(0, 2000), 0x00800000 + np.arange(-1000, 1000),
+                           (levels << 23) + np.arange(-500, 500), 0x7F7FFFFF - np.arange(1000), [0x7F800000]])
+    v = bits.astype(np.uint32).view(np.float32)
+    got = np.array([L.lq_test_sigma_by_reciprocal(float(x), levels) for x in v], np.float32)
+    assert np.array_equal(got, v / np.float32(levels))
+    assert np.isnan(L.lq_test_sigma_by_reciprocal(float("nan"), levels))

@@ -31,6 +31,8 @@ def load():
         L.lq_test_ritz_residual.argtypes = [vp, vp, vp, it, i64, i64, vp, vp]
         L.lq_test_lds_limit.restype = C.c_size_t
         L.lq_test_bucket_code.argtypes = [C.c_int, C.c_float]
+        L.lq_test_sigma_by_reciprocal.restype = C.c_float
+        L.lq_test_sigma_by_reciprocal.argtypes = [C.c_float, it]
         L.lq_test_capture_iterate.argtypes = [it, it, vp, vp]
         _lib = L
     return _lib
