@@ -552,9 +552,8 @@ static int launch_eig(const double* G, double* work, float* Ut, double* lambda, 
   const size_t reflectors = (size_t)l * l * sizeof(double), jacobi = (size_t)2 * l * (l + 4) * sizeof(float);
   const size_t rows = (size_t)l * (l + 2) * sizeof(double);
   const size_t need = std::max(reflectors, std::max(jacobi, rows));
-  static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(sym_eig_kernel<NE>),
-                                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)need);
-  LQ_HIP_TRY(attr);
+  static LdsLimit limit;
+  LQ_TRY(limit.raise(reinterpret_cast<const void*>(sym_eig_kernel<NE>), need));
   hipLaunchKernelGGL((sym_eig_kernel<NE>), dim3(batch), dim3(EIG_THREADS), need, st, G, work, Ut, lambda);
   LQ_HIP_TRY(hipGetLastError());
   return LQ_OK;

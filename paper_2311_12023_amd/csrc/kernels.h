@@ -3,9 +3,28 @@
 // a zero-padded leading dimension that is a multiple of 32.
 #pragma once
 
+#include <atomic>
+
 #include "lq_internal.h"
 
 namespace lq {
+
+// Raises a kernel's limit of dynamic LDS above the default 64 KB: once per device, since the limit belongs to the kernel as
+// loaded there; a call that failed is repeated by the next launch.  One static object per kernel.
+class LdsLimit {
+  std::atomic<bool> raised_[64] = {};
+
+ public:
+  int raise(const void* kernel, size_t bytes) {
+    int dev = 0;
+    LQ_HIP_TRY(hipGetDevice(&dev));
+    if (dev < 0 || dev >= 64) return LQ_ERR_HIP;
+    if (raised_[dev].load(std::memory_order_acquire)) return LQ_OK;
+    LQ_HIP_TRY(hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes));
+    raised_[dev].store(true, std::memory_order_release);
+    return LQ_OK;
+  }
+};
 
 typedef NfTables DevTables;
 

@@ -535,15 +535,8 @@ size_t qmatmul_part_floats(int64_t m, int64_t N, int nsteps) {
 
 template <int BITS, bool SPLIT>
 static int launch_variant(const QmmArgs& a, dim3 grid, hipStream_t st) {
-  static bool raised[64] = {};          // per device: the kernel uses more than the default 64 KB of LDS
-  int dev = 0;
-  LQ_HIP_TRY(hipGetDevice(&dev));
-  if (dev < 0 || dev >= 64) return LQ_ERR_HIP;
-  if (!raised[dev]) {
-    LQ_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(&qmatmul_kernel<BITS, SPLIT>),
-                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)QmmLds::BYTES));
-    raised[dev] = true;
-  }
+  static LdsLimit limit;
+  LQ_TRY(limit.raise(reinterpret_cast<const void*>(&qmatmul_kernel<BITS, SPLIT>), QmmLds::BYTES));
   hipLaunchKernelGGL((qmatmul_kernel<BITS, SPLIT>), grid, dim3(QM_THREADS), QmmLds::BYTES, st, a);
   LQ_HIP_TRY(hipGetLastError());
   return LQ_OK;

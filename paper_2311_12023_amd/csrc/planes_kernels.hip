@@ -256,9 +256,8 @@ int launch_plane_product(const MvWeights& q, const uint16_t* Xh, int64_t K, cons
   const int64_t tiles = (int64_t)a.tiles_m * a.tiles_n;
   if (tiles >= (1ll << 28)) return LQ_ERR_SHAPE;
   constexpr size_t lds = (size_t)PG_STAGES * PG_STAGE;
-  static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(plane_gemm_kernel),
-                                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-  LQ_HIP_TRY(attr);
+  static LdsLimit limit;
+  LQ_TRY(limit.raise(reinterpret_cast<const void*>(plane_gemm_kernel), lds));
   {
     prof::Scope ps(prof::QMATMUL, st, 2.0 * (double)m * (double)N * (double)(K + a.K2));
     hipLaunchKernelGGL(plane_gemm_kernel, dim3((unsigned)((tiles + 7) / 8 * 8), (unsigned)a.splits), dim3(PG_THREADS), lds, st, a);

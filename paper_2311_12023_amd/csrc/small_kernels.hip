@@ -374,14 +374,9 @@ int launch_jacobi_eig(double* G, int l, double* vt, float* Ut, double* lambda, i
   if (l > 256 || l % 2) return LQ_ERR_ARG;
   const size_t lim = max_lds_bytes() - 8192;          // static arrays of the kernel
   const size_t one = (size_t)l * (l + 1) * sizeof(double);
-  static bool attr_set = false;
-  if (!attr_set) {
-    LQ_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(jacobi_eig_kernel<1>),
-                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)lim));
-    LQ_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(jacobi_eig_kernel<2>),
-                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)lim));
-    attr_set = true;
-  }
+  static LdsLimit limit1, limit2;
+  LQ_TRY(limit1.raise(reinterpret_cast<const void*>(jacobi_eig_kernel<1>), lim));
+  LQ_TRY(limit2.raise(reinterpret_cast<const void*>(jacobi_eig_kernel<2>), lim));
   prof::Scope ps(prof::JACOBI, st, (double)l * l * 8.0 * batch);
   if (2 * one <= lim)
     hipLaunchKernelGGL(jacobi_eig_kernel<2>, dim3(batch), dim3(JT), 2 * one, st, G, l, vt, Ut, lambda);
