@@ -266,15 +266,23 @@ int lq_fisher_row_col(const float* F, int64_t d, int64_t k, float* row_w, float*
  *                 accumulation (error of an output about 2^-16 of sum |x||w|);  1: bf16 operands, one MFMA
  *                 (about 2^-8), for callers that train in bf16
  *              Up to 128 rows (rank <= 512) X is split on the fly and the workspace holds partial sums only.  Above 512
- *              rows (rank <= 64) precision 1 decodes the weights into a bf16 plane in the workspace first.
+ *              rows (rank <= 64) precision 1 decodes the weights into a bf16 plane in the workspace first.  A workspace
+ *              that is too small for either but holds what other sizes take (below) is used that way, and results then
+ *              differ by rounding.
  *              With m <= 8 and rank <= 512 the product is bound by reading the weights once; it then runs in plain
  *              fp32 on the vector ALU (exact products, fp32 accumulation) and `precision` is ignored.
- *   workspace  lq_matmul_workspace_bytes(m, d, k, rank) bytes: the bf16 hi / lo planes of X (rows padded to a
- *              multiple of 256), X L1 and its planes and, for small m, partial sums
+ *   workspace  lq_matmul_workspace_bytes(m, d, k, rank) bytes, which serve both precisions, or
+ *              lq_matmul_workspace_bytes_precision(..) bytes, which serve the one named (less where the other decodes the
+ *              weights, 2 bytes each).  For 9 to 128 rows (rank <= 512): partial sums, one size for all of them; it and
+ *              the sizes for more rows also serve every number of rows from 1 to 128.  Above 128 rows or rank 512: the
+ *              bf16 hi / lo planes of X (rows padded to a multiple of 256), X L1 and its planes, the block scales or the
+ *              plane of the weights, and partial sums where the reduction is cut, which more rows can need less of: ask
+ *              for each of these sizes.
  * d must be a multiple of 32 and ceil(m / 256) * 256 * d below 2^31 (LQ_ERR_SHAPE), rank <= 1024 (LQ_ERR_RANK).  Only enqueues work on `stream`; the
  * result is deterministic (partial sums are added in a fixed order).
  */
 size_t lq_matmul_workspace_bytes(int64_t m, int64_t d, int64_t k, int rank);
+size_t lq_matmul_workspace_bytes_precision(int64_t m, int64_t d, int64_t k, int rank, int precision);
 int lq_matmul(const float* X, int64_t m, int64_t d, int64_t k, const uint8_t* codes_packed, const uint8_t* scale_idx,
               const float* v, lq_config c, const float* L1, const float* L2, int rank, int precision, float* Y,
               void* workspace, size_t workspace_bytes, void* stream);

@@ -17,48 +17,72 @@ constexpr int SMALL_RANK = 512;
 // Above this many rows precision 1 decodes the weights into a bf16 plane first (see planes_kernels.hip for both sides).
 constexpr int64_t PLANE_M = 512;
 
+// The kernels a call can take.  Each needs a workspace of its own; where the one given is too small for the route that the
+// sizes call for but holds ROUTE_GENERAL, that one is taken.
+enum Route { ROUTE_FEW, ROUTE_ROWS, ROUTE_PLANE, ROUTE_GENERAL };
+static Route preferred_route(int64_t m, int rank, int precision) {
+  if (m <= SMALL_M && rank <= SMALL_RANK) return ROUTE_FEW;
+  if (m <= QROWS_MAX_ROWS && rank <= QROWS_MAX_RANK) return ROUTE_ROWS;
+  return precision == 1 && m > PLANE_M && rank <= SPLIT_PROJECT_MAX_RANK ? ROUTE_PLANE : ROUTE_GENERAL;
+}
+static int64_t padded_rows(int64_t m) { return (m + 255) / 256 * 256; }
+
 struct MatmulPlan {
-  bool small;
-  bool rows;       // a few dozen to a few hundred rows: rows_kernels.hip
   bool fused;      // T = X L1 comes out of the pass that splits X (rank up to SPLIT_PROJECT_MAX_RANK)
   int64_t r32, rows_pad;
-  size_t x_plane, t_floats, t_plane, part_floats, scale_floats;   // elements
-  size_t w_plane, l_plane;   // the weights and L2 in bf16 (precision 1, ranks up to SPLIT_PROJECT_MAX_RANK)
+  // elements of the regions, in the order in which they lie in the workspace
+  size_t xh, xl, t_floats, t_plane, part_floats, scale_floats;
+  size_t w_plane, l_plane;   // ROUTE_PLANE: the weights and L2 in bf16
 };
-static MatmulPlan plan_matmul(int64_t m, int64_t d, int64_t k, int rank) {
+static MatmulPlan plan_matmul(Route route, int64_t m, int64_t d, int64_t k, int rank) {
   MatmulPlan p{};
-  p.small = m <= SMALL_M && rank <= SMALL_RANK;
-  if (p.small) {
-    const int mc = (int)std::min<int64_t>(m, QMATVEC_MAX_ROWS);
-    p.part_floats = qmatvec_part_floats(mc, d, k, rank);
+  if (route == ROUTE_FEW) {
+    p.part_floats = qmatvec_part_floats((int)std::min<int64_t>(m, QMATVEC_MAX_ROWS), d, k, rank);
     return p;
   }
-  p.rows = m <= QROWS_MAX_ROWS && rank <= QROWS_MAX_RANK;
-  if (p.rows) {
-    // no less than the reduction ranges of the kernel for more rows, which callers know as this size's lower bound
-    p.part_floats = std::max(qrows_part_floats(m, d, k, rank), qmatmul_part_floats(m, k, (int)(d / 32 + up32(rank) / 32)));
+  if (route == ROUTE_ROWS) {
+    p.part_floats = qrows_part_floats(m, d, k, rank);
     return p;
   }
   p.r32 = up32(rank);
-  p.rows_pad = (m + 255) / 256 * 256;
-  p.x_plane = (size_t)p.rows_pad * (size_t)d;
+  p.rows_pad = padded_rows(m);
   p.fused = rank > 0 && rank <= SPLIT_PROJECT_MAX_RANK;
+  p.xh = (size_t)p.rows_pad * (size_t)d;
+  p.xl = route == ROUTE_PLANE && p.fused ? 0 : p.xh;   // split_project_kernel leaves it alone for bf16 operands
   p.t_floats = rank > 0 && !p.fused ? (size_t)m * (size_t)p.r32 : 0;
   p.t_plane = rank > 0 ? (size_t)p.rows_pad * (size_t)p.r32 : 0;
   const size_t p1 = p.fused ? split_project_part_floats(p.rows_pad, d)
                             : rank > 0 ? qmatmul_part_floats(m, p.r32, (int)(d / 32)) : 0;
   const size_t p2 = qmatmul_part_floats(m, k, (int)(d / 32 + p.r32 / 32));
   p.part_floats = p1 > p2 ? p1 : p2;
-  p.scale_floats = (size_t)(d * k / 16);            // one scale per block, block size at least 16
-  if (m > PLANE_M && rank <= SPLIT_PROJECT_MAX_RANK) {
+  if (route == ROUTE_PLANE) {
     p.w_plane = weight_plane_elems(d, k);
     p.l_plane = rank > 0 ? weight_plane_elems(p.r32, k) : 0;
+  } else {
+    p.scale_floats = (size_t)(d * k / 16);          // one scale per block, block size at least 16
   }
   return p;
 }
 static size_t plan_bytes(const MatmulPlan& p) {
-  return 2 * up256(p.x_plane * 2) + up256(p.t_floats * 4) + 2 * up256(p.t_plane * 2) + up256(p.part_floats * 4) +
-         up256(p.scale_floats * 4) + up256(p.w_plane * 2) + up256(p.l_plane * 2);
+  return up256(p.xh * 2) + up256(p.xl * 2) + up256(p.t_floats * 4) + 2 * up256(p.t_plane * 2) + up256(p.part_floats * 4) +
+         up256(p.scale_floats * 4) + up256(p.w_plane * 2) + up256(p.l_plane * 2) + 256;
+}
+static size_t route_bytes(Route route, int64_t m, int64_t d, int64_t k, int rank) {
+  return plan_bytes(plan_matmul(route, m, d, k, rank));
+}
+
+// What m rows need and, beyond the few, no less than any number of rows up to QROWS_MAX_ROWS needs: those sizes rise and fall
+// with m as reductions are cut less, and a caller sizes once for batches that come and go.  Among the rows of ROUTE_ROWS
+// only whole tiles of 16 have to be looked at, between which the cut stays the same.
+static size_t workspace_bytes_for(int64_t m, int64_t d, int64_t k, int rank, int precision) {
+  const Route route = preferred_route(m, rank, precision);
+  size_t need = route_bytes(route, m, d, k, rank);
+  if (route == ROUTE_FEW) return need;
+  if (rank <= SMALL_RANK)
+    for (int64_t r = 1; r <= SMALL_M; ++r) need = std::max(need, route_bytes(ROUTE_FEW, r, d, k, rank));
+  if (rank <= QROWS_MAX_RANK)
+    for (int64_t r = 16; r <= QROWS_MAX_ROWS; r += 16) need = std::max(need, route_bytes(ROUTE_ROWS, r, d, k, rank));
+  return need;
 }
 
 // Scratch of lq_matmul_few_rows_static: a fixed array in device memory (every GPU the library runs on holds its own copy
@@ -89,9 +113,14 @@ using namespace lq;
 
 extern "C" {
 
+size_t lq_matmul_workspace_bytes_precision(int64_t m, int64_t d, int64_t k, int rank, int precision) {
+  if (m <= 0 || d <= 0 || k <= 0 || rank < 0 || (d % 32) != 0 || (precision != 0 && precision != 1)) return 0;
+  return workspace_bytes_for(m, d, k, rank, precision);
+}
+
 size_t lq_matmul_workspace_bytes(int64_t m, int64_t d, int64_t k, int rank) {
-  if (m <= 0 || d <= 0 || k <= 0 || rank < 0 || (d % 32) != 0) return 0;
-  return plan_bytes(plan_matmul(m, d, k, rank)) + 256;
+  return std::max(lq_matmul_workspace_bytes_precision(m, d, k, rank, 0),
+                  m > PLANE_M ? lq_matmul_workspace_bytes_precision(m, d, k, rank, 1) : 0);
 }
 
 int lq_matmul(const float* X, int64_t m, int64_t d, int64_t k, const uint8_t* codes_packed, const uint8_t* scale_idx,
@@ -107,15 +136,18 @@ int lq_matmul(const float* X, int64_t m, int64_t d, int64_t k, const uint8_t* co
   if ((k % c.block) != 0) return LQ_ERR_SHAPE;
   if (precision != 0 && precision != 1) return LQ_ERR_ARG;
   if (((uintptr_t)X & 15) != 0 || ((uintptr_t)Y & 15) != 0 || (rank > 0 && ((uintptr_t)L2 & 15) != 0)) return LQ_ERR_ARG;
-  const MatmulPlan p = plan_matmul(m, d, k, rank);
-  if (std::max<int64_t>(p.rows_pad, p.rows ? 256 : 0) * d >= ((int64_t)1 << 31)) return LQ_ERR_SHAPE;   // 32-bit byte offsets
-  if (!p.small && d * k >= ((int64_t)1 << 31)) return LQ_ERR_SHAPE;   // and so are the codes
-  const size_t need = plan_bytes(p) + 256;
-  if (!workspace || ((uintptr_t)workspace & 255) != 0 || workspace_bytes < need) return LQ_ERR_WORKSPACE;
+  Route route = preferred_route(m, rank, precision);
+  // 32-bit byte offsets into the planes of X and into the codes
+  if (route != ROUTE_FEW && (padded_rows(m) * d >= ((int64_t)1 << 31) || d * k >= ((int64_t)1 << 31))) return LQ_ERR_SHAPE;
+  MatmulPlan p = plan_matmul(route, m, d, k, rank);
+  if (workspace_bytes < plan_bytes(p) && (route == ROUTE_ROWS || route == ROUTE_PLANE)) {
+    route = ROUTE_GENERAL;
+    p = plan_matmul(route, m, d, k, rank);
+  }
+  if (!workspace || ((uintptr_t)workspace & 255) != 0 || workspace_bytes < plan_bytes(p)) return LQ_ERR_WORKSPACE;
   char* w = reinterpret_cast<char*>(workspace);
   hipStream_t st = (hipStream_t)stream;
-  if (p.small) {
-    // plan_bytes lays the regions out in the same order with empty planes
+  if (route == ROUTE_FEW) {
     float* part = reinterpret_cast<float*>(w);           // the only region of the plan that is not empty
     const MvWeights q{codes_packed, scale_idx, v, c.bits, c.block, c.scale_block, scale_levels(c)};
     for (int64_t r0 = 0; r0 < m; r0 += QMATVEC_MAX_ROWS) {
@@ -124,12 +156,12 @@ int lq_matmul(const float* X, int64_t m, int64_t d, int64_t k, const uint8_t* co
     }
     return LQ_OK;
   }
-  if (p.rows) {
+  if (route == ROUTE_ROWS) {
     const MvWeights q{codes_packed, scale_idx, v, c.bits, c.block, c.scale_block, scale_levels(c)};
     return launch_qrows(q, X, d, d, L1, L2, k, rank, m, k, precision, Y, k, reinterpret_cast<float*>(w), p.part_floats, st);
   }
-  uint16_t* xh = reinterpret_cast<uint16_t*>(w); w += up256(p.x_plane * 2);
-  uint16_t* xl = reinterpret_cast<uint16_t*>(w); w += up256(p.x_plane * 2);
+  uint16_t* xh = reinterpret_cast<uint16_t*>(w); w += up256(p.xh * 2);
+  uint16_t* xl = reinterpret_cast<uint16_t*>(w); w += up256(p.xl * 2);
   float* T = reinterpret_cast<float*>(w); w += up256(p.t_floats * 4);
   uint16_t* th = reinterpret_cast<uint16_t*>(w); w += up256(p.t_plane * 2);
   uint16_t* tl = reinterpret_cast<uint16_t*>(w); w += up256(p.t_plane * 2);
@@ -138,7 +170,7 @@ int lq_matmul(const float* X, int64_t m, int64_t d, int64_t k, const uint8_t* co
   uint16_t* wt = reinterpret_cast<uint16_t*>(w); w += up256(p.w_plane * 2);
   uint16_t* lt = reinterpret_cast<uint16_t*>(w);
 
-  if (precision == 1 && p.w_plane > 0) {
+  if (route == ROUTE_PLANE) {
     if (p.fused)
       LQ_TRY(launch_split_project(X, m, d, d, p.rows_pad, L1, rank, precision, xh, xl, part, p.part_floats, th, tl,
                                   (int)p.r32, BlockScales{}, st));

@@ -83,6 +83,8 @@ _lib.lq_fisher_row_col_workspace_bytes.argtypes = [_i64, _i64]
 _lib.lq_fisher_row_col.argtypes = [_vp, _i64, _i64, _vp, _vp, _vp, _sz, _vp]
 _lib.lq_matmul_workspace_bytes.restype = _sz
 _lib.lq_matmul_workspace_bytes.argtypes = [_i64, _i64, _i64, _int]
+_lib.lq_matmul_workspace_bytes_precision.restype = _sz
+_lib.lq_matmul_workspace_bytes_precision.argtypes = [_i64, _i64, _i64, _int, _int]
 _lib.lq_matmul.argtypes = [_vp, _i64, _i64, _i64, _vp, _vp, _vp, Config, _vp, _vp, _int, _int, _vp, _vp, _sz, _vp]
 _lib.lq_matmul_few_rows_static_scratch_bytes.restype = _sz
 _lib.lq_matmul_few_rows_static.argtypes = [_vp, _i64, _i64, _i64, _vp, _vp, _vp, Config, _vp, _vp, _int, _vp, _vp]
@@ -302,7 +304,9 @@ def matmul(x: torch.Tensor, codes: torch.Tensor, scale_idx: torch.Tensor, v: tor
     rank = 0 if l1 is None else l1.shape[1]
     if out is None:
         out = torch.empty((m, k), dtype=torch.float32, device=x.device)
-    ws = workspace if workspace is not None else matmul_workspace(m, d, k, rank, x.device)
+    ws = workspace
+    if ws is None:
+        ws = _workspace(_lib.lq_matmul_workspace_bytes_precision(m, d, k, rank, precision), x.device)
     _check(_lib.lq_matmul(_dev(x, torch.float32, "x"), m, d, k, _dev(codes, torch.uint8, "codes"),
                           _dev(scale_idx, torch.uint8, "scale_idx"), _dev(v, torch.float32, "v"), cfg,
                           _dev(l1, torch.float32, "l1"), _dev(l2, torch.float32, "l2"), rank, precision,

@@ -1,0 +1,54 @@
+"""Runs a piece of Python with the testing build of the library in a process of its own whose HIP calls end in a stub: it is
+loaded before the library, so its symbols come first; it launches nothing and counts requests and launches."""
+import os
+import subprocess
+import sys
+
+from testing_lib import ROOT, TEST_LIB
+
+STUB = r"""
+#include <stddef.h>
+#include <stdlib.h>
+static int device = 0, refuse = 0, raised[8], launches = 0;
+void stub_set(int dev, int fail) { device = dev; refuse = fail; }
+int stub_raised(int dev) { return raised[dev]; }
+int stub_launches(void) { return launches; }
+int hipGetDevice(int* dev) { *dev = device; return 0; }
+int hipFuncSetAttribute(const void* f, int attr, int value) { if (refuse) return 1; ++raised[device]; return 0; }
+int hipDeviceGetAttribute(int* v, int attr, int dev) { *v = 160 * 1024; return 0; }
+int __hipPushCallConfiguration() { return 0; }
+int __hipPopCallConfiguration() { return 0; }
+int hipLaunchKernel() { ++launches; return 0; }
+int hipGetLastError(void) { return 0; }
+int hipGetSymbolAddress(void** p, const void* sym) { *p = malloc(1 << 20); return 0; }
+int hipMemcpy(void* d, const void* s, size_t n, int kind) { return 0; }
+"""
+
+PRELUDE = r"""
+import ctypes as C, sys
+stub = C.CDLL(sys.argv[1], mode=C.RTLD_GLOBAL)
+L = C.CDLL(sys.argv[2])
+args = sys.argv[3:]
+vp, i64, it = C.c_void_p, C.c_int64, C.c_int
+class Cfg(C.Structure):
+    _fields_ = [(n, C.c_int32) for n in ("bits", "block", "scale_block", "scale_bits", "v_dtype")]
+L.lq_matmul.argtypes = [vp, i64, i64, i64, vp, vp, vp, Cfg, vp, vp, it, it, vp, vp, C.c_size_t, vp]
+L.lq_matmul_workspace_bytes.restype = L.lq_matmul_workspace_bytes_precision.restype = C.c_size_t
+L.lq_matmul_workspace_bytes.argtypes = [i64, i64, i64, it]
+L.lq_matmul_workspace_bytes_precision.argtypes = [i64, i64, i64, it, it]
+L.lq_test_sym_eig_fast.argtypes = [vp, it, vp, vp, vp]
+L.lq_test_sym_eig.argtypes = [vp, it, vp, vp, vp, vp]
+"""
+
+
+def run(tmp_path, code, *args):
+    if not os.path.exists(TEST_LIB):
+        from paper_2311_12023_amd import build
+        build.build()
+    src, lib, script = tmp_path / "stub.c", tmp_path / "libstub.so", tmp_path / "run.py"
+    src.write_text(STUB)
+    script.write_text(PRELUDE + code)
+    subprocess.run(["gcc", "-shared", "-fPIC", "-w", "-o", str(lib), str(src)], check=True)
+    out = subprocess.run([sys.executable, str(script), str(lib), TEST_LIB, *map(str, args)], capture_output=True, text=True,
+                         cwd=ROOT)
+    assert out.returncode == 0, out.stderr

@@ -217,3 +217,25 @@ def test_infinite_group_scale_is_infinite_weights(env, oracle, m, precision):
     y = _gpu_product(env, oracle, x, codes, sidx, v, cfg, k, None, None, precision)
     assert np.array_equal(np.isposinf(y), np.isposinf(ref))
     assert np.max(np.abs(y[:, :256] / ref[:, :256] - 1)) < TOL_BF16
+
+
+@pytest.mark.parametrize("m,d,k,precision,nbytes", [
+    (128, 32, 2048, 0, 200_000), (128, 32, 2048, 1, 200_000),     # too small for the partial sums of 128 rows
+    (600, 512, 1024, 1, None),                                    # no room for the weights in bf16
+])
+def test_matmul_with_a_smaller_workspace(env, oracle, m, d, k, precision, nbytes):
+    """A workspace that only the general kernel can work with is accepted and the product is as good."""
+    torch, lq = env
+    cfg, rank = (4, 32, 64), 16
+    ocfg, codes, sidx, v, l1, l2 = _case(oracle, d, k, cfg, rank, 51)
+    x = gen.activations(m, d, 52)
+    ref, scale = oracle.matmul(x, codes, sidx, v, ocfg, k, l1, l2, want_abs=True)
+    nbytes = nbytes or lq._lib.lq_matmul_workspace_bytes_precision(m, d, k, rank, 0)
+    assert nbytes < lq._lib.lq_matmul_workspace_bytes_precision(m, d, k, rank, precision)
+    ws = torch.full((nbytes + 256,), 0xff, dtype=torch.uint8, device="cuda")
+    start = -ws.data_ptr() % 256
+    t = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    y = lq.matmul(t(x), t(oracle.pack(codes, cfg[0])), t(sidx), t(v), lq.config(*cfg), k, t(l1), t(l2), precision=precision,
+                  workspace=ws[start:start + nbytes]).cpu().numpy()
+    assert np.max(np.abs(y - ref) - (TOL_SPLIT, TOL_BF16)[precision] * scale) <= 0
+    assert torch.all(ws[start + nbytes:] == 0xff)                 # nothing is written past its end

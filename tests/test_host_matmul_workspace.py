@@ -1,0 +1,50 @@
+"""Workspaces of the forward product over row counts and precisions: what a size serves.  Needs no GPU (hip_stub.py)."""
+import pytest
+
+import hip_stub
+
+RUN = r"""
+d, k, rank = map(int, args)
+p = vp(4096)                                         # never dereferenced: nothing is launched
+def product(m, precision, size):
+    return L.lq_matmul(p, m, d, k, p, p, p, Cfg(4, 16, 16, 8, 0), p, p, rank, precision, p, p, size, None)
+# a workspace sized once for the largest batch serves every batch of 1 to 128 rows (ranks above 512 have no such kernels)
+for top in (9, 12, 16, 24, 49, 63, 100, 128, 129, 300, 513, 1000) if rank <= 512 else ():
+    size = L.lq_matmul_workspace_bytes(top, d, k, rank)
+    for m in range(1, min(top, 128) + 1):
+        for precision in (0, 1):
+            assert product(m, precision, size) == 0, (top, m, precision, size)
+for m in (1, 3, 8, 9, 40, 128, 129, 256, 400, 512, 513, 600, 1000, 4096):
+    both = L.lq_matmul_workspace_bytes(m, d, k, rank)
+    one = [L.lq_matmul_workspace_bytes_precision(m, d, k, rank, q) for q in (0, 1)]
+    assert both == max(one)
+    assert all(product(m, q, one[q]) == 0 for q in (0, 1))
+    assert product(m, 0, 255) == product(m, 1, 255) == -6
+    if m > 512:
+        # fp32-grade products bring no room for weights in bf16: two planes of X, T and its planes, partial sums of at most
+        # 256 tiles or 16 ranges, one scale for 16 weights
+        rows, r32 = -(-m // 256) * 256, -(-rank // 32) * 32
+        ranges = min(256 // max(1, -(-m // 256) * -(-k // 256)), 16)
+        bound = 4 * rows * (d + 2 * r32 + 64 * 16) + 4 * m * ranges * max(k, r32 if rank > 64 else 0) * (ranges > 1) + d * k // 4 + 4096
+        if rank <= 64:
+            assert one[0] <= bound, (m, one[0], bound)
+        # and a bf16 call takes such a workspace too
+        assert product(m, 1, one[0]) == 0
+"""
+
+
+@pytest.mark.parametrize("d,k", [(4096, 4096), (4096, 11008), (8192, 8192), (5120, 13824), (8192, 28672), (768, 768), (32, 16)])
+@pytest.mark.parametrize("rank", [0, 64, 200, 600])
+def test_workspace_serves_smaller_batches(tmp_path, d, k, rank):
+    hip_stub.run(tmp_path, RUN, d, k, rank)
+
+
+def test_sizes_of_the_precisions(tmp_path):
+    hip_stub.run(tmp_path, r"""
+size = L.lq_matmul_workspace_bytes_precision
+assert size(64, 250, 512, 8, 0) == size(64, 256, 512, 8, 2) == size(0, 256, 512, 8, 1) == 0
+assert size(1000, 4096, 11008, 64, 0) < 40e6 and size(1000, 4096, 11008, 64, 1) > 2 * 4096 * 11008
+assert L.lq_matmul_workspace_bytes(1000, 4096, 11008, 64) < 110e6          # nothing that a route leaves alone
+assert L.lq_matmul_workspace_bytes(4096, 11008, 4096, 64) == size(4096, 11008, 4096, 64, 0)   # the plane in place of the lo half of X
+assert L.lq_matmul_workspace_bytes(24, 4096, 11008, 64) == L.lq_matmul_workspace_bytes(9, 4096, 11008, 64) < 16e6
+""")
