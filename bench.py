@@ -299,6 +299,43 @@ def bench_quant(args, torch, gen, lq, dev) -> int:
 NF4_DOUBLE_QUANT = (4, 64, 256, 8, "bf16")
 
 
+# The product kernels of lq_matmul, by number of rows: 9 to 128 (qrows), bf16 operands above 512 (plane_gemm), the others
+# (qmatmul); up to 8 rows qmatvec.
+MATMUL_MFMA_KERNELS = ("qrows_kernel", "plane_gemm_kernel", "qmatmul_kernel")
+
+
+def matmul_roofline(prof: dict, precision: int, traffic: float | None) -> dict:
+    """Entries of the forward product's result line from the kernel classes {name: (ms, launches, work)} that ran."""
+    if not prof:
+        return {}
+    kernels = {n: {"ms": v[0], "launches": v[1]} for n, v in prof.items()}
+    timing = ("Kernel durations come from a second pass over the same steps with every launch bracketed by events on the "
+              "launch stream (an upper bound for short kernels); value and ms_per_step from the pass without brackets.")
+    name = next((n for n in MATMUL_MFMA_KERNELS if n in prof), None)
+    if name:
+        kms, launches, work = prof[name]
+        mult = 3.0 if precision == 0 else 1.0               # bf16 MFMAs executed per product
+        ach = mult * work / (kms * 1e-3) / 1e12
+        return {"roofline": {"kernel": name, "bound": "mfma", "achieved": ach, "peak": PEAK_BF16_MFMA_TFLOPS,
+                             "unit": "TFLOP/s", "frac": ach / PEAK_BF16_MFMA_TFLOPS,
+                             "traffic": traffic if name == "qmatmul_kernel" else None, "launches": launches,
+                             "avg_us": 1e3 * kms / launches, "algorithmic_tflops": work / (kms * 1e-3) / 1e12},
+                "roofline_note": "achieved counts the bf16 MFMA flops the kernel executes (3 per product at precision 0) "
+                                 "against the dense bf16 peak; algorithmic_tflops counts each product once.  " + timing,
+                "kernels": kernels}
+    if "qmatvec_kernel" in prof:                             # few tokens: bound by reading the weights once
+        kms, launches, work = prof["qmatvec_kernel"]
+        ach = work / (kms * 1e-3) / 1e9
+        return {"dtype": "f32",
+                "roofline": {"kernel": "qmatvec_kernel", "bound": "hbm", "achieved": ach, "peak": PEAK_HBM_GBS,
+                             "unit": "GB/s", "frac": ach / PEAK_HBM_GBS, "traffic": None, "launches": launches,
+                             "avg_us": 1e3 * kms / launches},
+                "roofline_note": "algorithmic bytes per launch: the packed codes and one scale index per block of the "
+                                 "d x k matrix, both low-rank factors, X and Y.  " + timing,
+                "kernels": kernels}
+    return {"kernels": kernels}
+
+
 def bench_matmul(args, torch, gen, lq, dev) -> int:
     """Forward products Y = X (Q + L1 L2) of one LLaMA-2-7B-shaped layer; one step = all 7 matrices."""
     RANK = 64
@@ -349,34 +386,10 @@ def bench_matmul(args, torch, gen, lq, dev) -> int:
            "dtype": "bf16x3" if args.precision == 0 else "bf16", "data": "synthetic",
            "config": {"workload": f"LLaMA-2-7B layer forward, {m} tokens, {len(items)} matrices, NF4 + double "
                                   f"quantization, rank {RANK}"}}
-    if "qmatmul_kernel" in prof:
-        kms, launches, work = prof["qmatmul_kernel"]
-        mult = 3.0 if args.precision == 0 else 1.0          # bf16 MFMAs executed per product
-        ach = mult * work / (kms * 1e-3) / 1e12
-        traffic = None
-        if m == 4096 and len(items) == 7 and args.precision == 0:      # the configuration the counter runs measured
-            traffic = measured_traffic("qmatmul_kernel", FORWARD_TRAFFIC_TABLE)
-        out["roofline"] = {"kernel": "qmatmul_kernel", "bound": "mfma", "achieved": ach, "peak": PEAK_BF16_MFMA_TFLOPS,
-                           "unit": "TFLOP/s", "frac": ach / PEAK_BF16_MFMA_TFLOPS, "traffic": traffic,
-                           "launches": launches, "avg_us": 1e3 * kms / launches,
-                           "algorithmic_tflops": work / (kms * 1e-3) / 1e12}
-        out["roofline_note"] = ("achieved counts the bf16 MFMA flops the kernel executes (3 per product at precision 0) "
-                                "against the dense bf16 peak; algorithmic_tflops counts each product once.  Kernel "
-                                "durations come from a second pass over the same steps with every launch bracketed by "
-                                "events on the launch stream; value and ms_per_step from the pass without brackets.")
-        out["kernels"] = {n: {"ms": v[0], "launches": v[1]} for n, v in prof.items()}
-    elif "qmatvec_kernel" in prof:                           # few tokens: bound by reading the weights once
-        kms, launches, work = prof["qmatvec_kernel"]
-        ach = work / (kms * 1e-3) / 1e9
-        out["dtype"] = "f32"
-        out["roofline"] = {"kernel": "qmatvec_kernel", "bound": "hbm", "achieved": ach, "peak": PEAK_HBM_GBS,
-                           "unit": "GB/s", "frac": ach / PEAK_HBM_GBS, "traffic": None, "launches": launches,
-                           "avg_us": 1e3 * kms / launches}
-        out["roofline_note"] = ("algorithmic bytes per launch: the packed codes and one scale index per block of the "
-                                "d x k matrix, both low-rank factors, X and Y.  Kernel durations come from a second pass "
-                                "over the same steps with every launch bracketed by events (an upper bound for kernels "
-                                "this short); value and ms_per_step from the pass without brackets.")
-        out["kernels"] = {n: {"ms": v[0], "launches": v[1]} for n, v in prof.items()}
+    traffic = None
+    if m == 4096 and len(items) == 7 and args.precision == 0:      # the configuration the counter runs measured
+        traffic = measured_traffic("qmatmul_kernel", FORWARD_TRAFFIC_TABLE)
+    out.update(matmul_roofline(prof, args.precision, traffic))
     if not args.no_cpu_baseline:
         from oracle import lq_oracle as O
         it = items[0]

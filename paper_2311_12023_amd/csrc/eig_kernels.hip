@@ -560,7 +560,7 @@ static int launch_eig(const double* G, double* work, float* Ut, double* lambda, 
 }
 
 int launch_sym_eig(const double* G, int l, double* work, float* Ut, double* lambda, int batch, hipStream_t st) {
-  prof::Scope ps(prof::JACOBI, st, (double)l * l * 8.0 * batch);
+  prof::Scope ps(prof::SYM_EIG, st, (double)l * l * 8.0 * batch);
   switch (l / 16) {
     case 2: return launch_eig<2>(G, work, Ut, lambda, batch, st);
     case 4: return launch_eig<4>(G, work, Ut, lambda, batch, st);

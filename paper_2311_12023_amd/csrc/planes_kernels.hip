@@ -232,7 +232,7 @@ int launch_plane_product(const MvWeights& q, const uint16_t* Xh, int64_t K, cons
   const dim3 wgrid((unsigned)((N + WP_N - 1) / WP_N), (unsigned)((K + WP_K - 1) / WP_K + (rank > 0 ? 1 : 0)));
   if (wgrid.y > 65535) return LQ_ERR_SHAPE;
   {
-    prof::Scope ps(prof::MISC, st, (double)K * (double)N * (q.bits / 8.0 + 2.0));
+    prof::Scope ps(prof::WEIGHT_PLANE, st, (double)K * (double)N * (q.bits / 8.0 + 2.0));
     switch (q.bits) {
       case 2: launch_weight_plane<2>(w, wgrid, st); break;
       case 3: launch_weight_plane<3>(w, wgrid, st); break;
@@ -259,7 +259,7 @@ int launch_plane_product(const MvWeights& q, const uint16_t* Xh, int64_t K, cons
   static LdsLimit limit;
   LQ_TRY(limit.raise(reinterpret_cast<const void*>(plane_gemm_kernel), lds));
   {
-    prof::Scope ps(prof::QMATMUL, st, 2.0 * (double)m * (double)N * (double)(K + a.K2));
+    prof::Scope ps(prof::PLANE_GEMM, st, 2.0 * (double)m * (double)N * (double)(K + a.K2));
     hipLaunchKernelGGL(plane_gemm_kernel, dim3((unsigned)((tiles + 7) / 8 * 8), (unsigned)a.splits), dim3(PG_THREADS), lds, st, a);
     LQ_HIP_TRY(hipGetLastError());
   }

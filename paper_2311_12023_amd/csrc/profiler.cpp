@@ -45,7 +45,7 @@ static const char* const kNames[NUM_CLASSES] = {
     "wide_gemm_kernel<1,1,2,0>", "wide_gemm_kernel<2,1,2,0>", "wide_gemm_kernel<3,1,2,0>", "wide_gemm_kernel<4,1,2,0>",
     "wide_gemm_kernel<5,1,1,0>", "wide_gemm_kernel<6,1,1,0>", "wide_gemm_kernel<7,1,1,0>", "wide_gemm_kernel<8,1,1,0>",
     "gemm_fixup_kernel", "gram_partial_kernel+gram_reduce_kernel", "cholesky_kernel", "trsm_kernel",
-    "sym_eig_kernel", "lowrank_blockquant_kernel", "scalequant_error_kernel+error_finalize_kernel",
+    "jacobi_eig_kernel", "lowrank_blockquant_kernel", "scalequant_error_kernel+error_finalize_kernel",
     "residual_kernel", "quantize_fused_kernel", "dequant_kernel", "misc",
     "wide_gemm_kernel<1,0,2,1>", "wide_gemm_kernel<2,0,2,1>", "wide_gemm_kernel<3,0,2,1>", "wide_gemm_kernel<4,0,2,1>",
     "wide_gemm_kernel<5,0,1,1>", "wide_gemm_kernel<6,0,1,1>", "wide_gemm_kernel<7,0,1,1>", "wide_gemm_kernel<8,0,1,1>",
@@ -56,7 +56,7 @@ static const char* const kNames[NUM_CLASSES] = {
     "wide_gemm_f16_kernel<1,1,1>", "wide_gemm_f16_kernel<2,1,1>", "wide_gemm_f16_kernel<3,1,1>", "wide_gemm_f16_kernel<4,1,1>",
     "wide_gemm_f16_kernel<1,0,2>", "wide_gemm_f16_kernel<2,0,2>", "wide_gemm_f16_kernel<3,0,2>", "wide_gemm_f16_kernel<4,0,2>",
     "wide_gemm_f16_kernel<1,1,2>", "wide_gemm_f16_kernel<2,1,2>", "wide_gemm_f16_kernel<3,1,2>", "wide_gemm_f16_kernel<4,1,2>",
-    "absmax_kernel", "rotate_kernel", "qrows_kernel"};
+    "absmax_kernel", "rotate_kernel", "qrows_kernel", "sym_eig_kernel", "plane_gemm_kernel", "weight_plane_kernel"};
 
 }  // namespace prof
 }  // namespace lq

@@ -27,7 +27,10 @@ enum Cls {
   ABSMAX = 62,
   ROTATE = 63,              // rotate_kernel (work = bytes)
   QROWS = 64,               // qrows_kernel (work = flops of the product)
-  NUM_CLASSES = 65
+  SYM_EIG = 65,             // sym_eig_kernel (work = bytes)
+  PLANE_GEMM = 66,          // plane_gemm_kernel (work = flops of the product)
+  WEIGHT_PLANE = 67,        // weight_plane_kernel (work = bytes)
+  NUM_CLASSES = 68
 };
 
 bool enabled();

@@ -21,6 +21,10 @@ int __hipPopCallConfiguration() { return 0; }
 int hipLaunchKernel() { ++launches; return 0; }
 int hipGetLastError(void) { return 0; }
 int hipGetSymbolAddress(void** p, const void* sym) { *p = malloc(1 << 20); return 0; }
+int hipEventCreate(void** e) { *e = malloc(1); return 0; }
+int hipEventRecord(void* e, void* st) { return 0; }
+int hipEventElapsedTime(float* ms, void* a, void* b) { *ms = 1.0f; return 0; }
+int hipDeviceSynchronize(void) { return 0; }
 int hipMemcpy(void* d, const void* s, size_t n, int kind) { return 0; }
 """
 
