@@ -38,7 +38,7 @@ int lq_test_wide_gemm_f16(int mode, int l, int64_t big, int64_t K, const float* 
 size_t lq_test_wide_gemm_part_floats(int l, int workgroups);
 /* Rows of X (l x m) are orthonormalised in place by Cholesky-QR (Gram in fp64).
  * scratch: at least 17 * l * l doubles.  alt: l * ldx floats of scratch, or NULL to force the
- * in-place triangular solve. */
+ * in-place triangular solve.  ldx at least m rounded up to 16; with alt and l <= 128 (the rotation) a multiple of 32. */
 int lq_test_orthonormalize(float* X, int l, int64_t m, int64_t ldx, double* scratch, float* alt, void* stream);
 /* Eigen-decomposition of the symmetric l x l fp64 matrix G (destroyed): eigenvalues descending in
  * lambda (l doubles), eigenvectors as rows of Ut (l x l fp32).  scratch: l * l doubles. */
@@ -47,14 +47,31 @@ int lq_test_sym_eig(double* G, int l, float* Ut, double* lambda, double* scratch
  * symmetric fp64 G (left untouched) rounded to fp32, ordered by descending eigenvalue lambda.  Uses a scratch array of the
  * testing library: calls that overlap in time race. */
 int lq_test_sym_eig_fast(const double* G, int l, float* Ut, double* lambda, void* stream);
+/* The same for `batch` problems in one launch, problem z at G + z l l, Ut + z l l, lambda + z l; work: 2 l l doubles of
+ * scratch per problem. */
+int lq_test_sym_eig_batch(const double* G, int l, int batch, double* work, float* Ut, double* lambda, void* stream);
+/* G[z] = X[z] X[z]^T in fp64 for `batch` problems (X: l x m each, leading dimension ldx as in lq_test_orthonormalize, stride
+ * floats apart; G: l x l each).  part: part_doubles doubles of scratch, at least batch * l * l; more lets the columns be
+ * cut into chunks. */
+int lq_test_gram(const float* X, int l, int64_t m, int64_t ldx, size_t stride, double* part, size_t part_doubles, double* G,
+                 int batch, void* stream);
+/* C0[z] = U[z] A0[z] and, with A1, C1[z] = U[z] A1[z] for `batch` problems stored strideU, stride0 and stride1 floats
+ * apart (U: l x l, l <= 128; A, C: l rows, leading dimensions ld0, ld1, multiples of 32, all of it is written); lower:
+ * U is lower triangular. */
+int lq_test_rotate(int l, const float* U, size_t strideU, int lower, const float* A0, float* C0, int64_t ld0, size_t stride0,
+                   const float* A1, float* C1, int64_t ld1, size_t stride1, int batch, void* stream);
 /* The small kernels of the cold-start filter, one launch each on device arrays of l rows with leading dimension ldx
  * (a multiple of 4, m <= ldx):
  *   lincomb3:       X <- a X + b Y + c Z over all l * ldx entries (Z may be NULL: no third term).
  *   deflate_rows:   rows i >= locked of X lose their components along the first `locked` (<= 16) rows of L, which are
  *                   orthonormal; rows i < locked of X become copies of those rows of L.
+ *   filter_step:    lincomb3 (Y may be NULL: X as it is; then Z is NULL too) followed by deflate_rows; the columns past m
+ *                   are zero in all operands.
  *   ritz_residual:  res[i] = |G_i - lam[i] Y_i|^2 for the first `rows` rows (lam, res: device doubles). */
 int lq_test_lincomb3(float* X, float a, const float* Y, float b, const float* Z, float c, int l, int64_t ldx, void* stream);
 int lq_test_deflate_rows(float* X, const float* L, int l, int locked, int64_t m, int64_t ldx, void* stream);
+int lq_test_filter_step(float* X, float a, const float* Y, float b, const float* Z, float c, const float* L, int l, int locked,
+                        int64_t m, int64_t ldx, void* stream);
 int lq_test_ritz_residual(const float* G, const float* Y, const double* lam, int rows, int64_t m, int64_t ldx, double* res,
                           void* stream);
 /* Host-side evaluation of the code search the kernels use (threshold count for 2 and 3 bits, bucket table

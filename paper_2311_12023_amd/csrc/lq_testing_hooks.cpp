@@ -89,6 +89,31 @@ int lq_test_sym_eig_fast(const double* G, int l, float* Ut, double* lambda, void
   return launch_sym_eig(G, l, static_cast<double*>(work), Ut, lambda, 1, (hipStream_t)stream);
 }
 
+int lq_test_sym_eig_batch(const double* G, int l, int batch, double* work, float* Ut, double* lambda, void* stream) {
+  if (!G || !work || !Ut || !lambda) return LQ_ERR_NULL;
+  if (!sym_eig_supported(l) || batch < 1) return LQ_ERR_ARG;
+  return launch_sym_eig(G, l, work, Ut, lambda, batch, (hipStream_t)stream);
+}
+
+int lq_test_gram(const float* X, int l, int64_t m, int64_t ldx, size_t stride, double* part, size_t part_doubles, double* G,
+                 int batch, void* stream) {
+  if (!X || !part || !G) return LQ_ERR_NULL;
+  return launch_gram(X, l, m, ldx, stride, part, part_doubles, G, batch, (hipStream_t)stream);
+}
+
+int lq_test_rotate(int l, const float* U, size_t strideU, int lower, const float* A0, float* C0, int64_t ld0, size_t stride0,
+                   const float* A1, float* C1, int64_t ld1, size_t stride1, int batch, void* stream) {
+  if (!U || !A0 || !C0 || (A1 && !C1)) return LQ_ERR_NULL;
+  return launch_rotate(l, U, strideU, lower != 0, A0, C0, ld0, stride0, A1, C1, ld1, stride1, batch, (hipStream_t)stream);
+}
+
+int lq_test_filter_step(float* X, float a, const float* Y, float b, const float* Z, float c, const float* L, int l, int locked,
+                        int64_t m, int64_t ldx, void* stream) {
+  if (!X || !L) return LQ_ERR_NULL;
+  if (l < 1 || locked > l || m < 1 || ldx < m) return LQ_ERR_ARG;
+  return launch_filter_step(X, a, Y, b, Z, c, L, l, locked, m, ldx, (hipStream_t)stream);
+}
+
 int lq_test_lincomb3(float* X, float a, const float* Y, float b, const float* Z, float c, int l, int64_t ldx, void* stream) {
   if (!X || !Y) return LQ_ERR_NULL;
   if (l < 1 || ldx < 4 || ldx % 4) return LQ_ERR_ARG;

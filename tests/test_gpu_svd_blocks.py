@@ -243,6 +243,47 @@ def test_filter_small_kernels(env):
     assert np.max(np.abs(got[:40] - ref[:40]) / ref[:40]) < 1e-10 and np.all(got[40:] == 0)
 
 
+# the leading dimension against the 2048 columns of one float4 per thread and the 16384 of eight; longer rows take the two
+# kernels the step was made of
+@pytest.mark.parametrize("m,ld", [(61, 64), (2047, 2048), (2050, 2112), (16381, 16384), (16387, 16448)])
+@pytest.mark.parametrize("locked", [0, 1, 4, 5, 8, 9, 16])     # register arrays of 4, 8 and 16
+def test_filter_step(env, m, ld, locked):
+    """One filter step against numpy in fp64: X <- a X + b Y + c Z, then the components along the first `locked` rows of L
+    taken out of the rows below and those rows replaced by L's.  With u = 2^-24, the combination is off by at most 3 u of
+    its terms; a dot product, whose terms pass through at most 32 + 6 + 8 additions, by 48 u of its terms' magnitudes and by
+    what the combination missed; the subtraction by u of every intermediate result."""
+    torch, lq, L = env
+    rng = np.random.default_rng(1000 * locked + ld)
+    l, u = 24, 2.0 ** -24
+
+    def rows(scale):
+        a = np.zeros((l, ld), np.float32)
+        a[:, :m] = scale * rng.standard_normal((l, m))
+        return a
+    x, y, z, low = rows(3.0), rows(1.0), rows(0.5), rows(0.0)
+    low[:, :m] = np.linalg.qr(rng.standard_normal((m, l)))[0].T
+    a, b, c = 1.75, -2.0, -1.0
+    put = lambda v: torch.from_numpy(v.copy()).cuda()
+    yt, zt, lt = put(y), put(z), put(low)
+    for ny, nz in ((0, 0), (1, 0), (1, 1)):
+        xt = put(x)
+        assert L.lq_test_filter_step(xt.data_ptr(), a, yt.data_ptr() if ny else None, b, zt.data_ptr() if nz else None, c,
+                                     lt.data_ptr(), l, locked, m, ld, None) == 0
+        torch.cuda.synchronize()
+        got = xt.cpu().numpy().astype(np.float64)
+        parts = [(a if ny else 1.0) * x.astype(np.float64)] + [b * y.astype(np.float64)] * ny + [c * z.astype(np.float64)] * nz
+        t, et = sum(parts), 3 * u * ny * sum(np.abs(p) for p in parts)
+        v = low[:locked].astype(np.float64)
+        dot = t @ v.T
+        ref = t - dot @ v
+        bound = (et + (48 * u * np.abs(t) + et) @ np.abs(v).T @ np.abs(v) +
+                 (locked + 1) * u * (np.abs(t) + np.abs(dot) @ np.abs(v))) * 1.001
+        assert np.all(np.abs(got - ref)[locked:] <= bound[locked:])
+        assert np.array_equal(got[:locked], low[:locked].astype(np.float64))
+        assert torch.equal(lt, put(low)) and torch.equal(yt, put(y)) and torch.equal(zt, put(z))
+    assert L.lq_test_filter_step(xt.data_ptr(), a, None, b, None, c, lt.data_ptr(), l, 17, m, ld, None) != 0
+
+
 @pytest.mark.parametrize("l", [32, 64, 96, 128, 256])
 def test_sym_eig(env, l):
     torch, lq, L = env

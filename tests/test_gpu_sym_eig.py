@@ -63,7 +63,10 @@ def test_spectra(l, kind, scale):
     assert np.max(np.abs(u @ u.T - np.eye(l))) < 4e-6
     rq = np.einsum("ij,jk,ik->i", u, g, u)
     assert np.max(np.abs(rq - ref)) < 4e-7 * ref[0]
-    assert np.max(np.abs(lam - ref)) < 1e-4 * ref[0]
+    # Eigenvalues of a route in fp64: the reduction and the multisection leave about l roundings of lambda_1.  The Jacobi
+    # route, in fp32, misses this by orders of magnitude, so it also says that the others were not left for it.
+    off_jacobi = kind not in ("repeated", "low_rank") and not (kind == "geometric" and l > 64)
+    assert np.max(np.abs(lam - ref)) < (1e-13 * l if off_jacobi else 1e-4) * ref[0]
 
 
 @pytest.mark.parametrize("l", [32, 64, 96, 128])
@@ -75,3 +78,28 @@ def test_diagonal_and_zero_matrices(l):
     assert np.array_equal(np.abs(u), np.eye(l)[np.argsort(perm)])
     u, lam = _solve(np.zeros((l, l)))
     assert np.all(lam == 0) and np.max(np.abs(u @ u.T - np.eye(l))) == 0
+
+
+@pytest.mark.parametrize("l", [32, 64, 96, 128])
+def test_problems_of_a_batch_are_independent(l):
+    """Problems of every route side by side in one launch, in scratch full of NaN: each comes out as it does alone."""
+    import torch
+    L = load()
+    kinds = ["flat", "repeated", "noise_floor", "geometric", "low_rank", "smallest_gap"]
+    rng = np.random.default_rng(l)
+    gs = []
+    for i, kind in enumerate(kinds):
+        q, _ = np.linalg.qr(rng.standard_normal((l, l)))
+        g = (q * _spectrum(kind, l, rng)) @ q.T * 10.0 ** (3 * i - 6)
+        gs.append((g + g.T) / 2)
+    n = len(kinds)
+    gt = torch.from_numpy(np.stack(gs)).cuda()
+    nan = lambda dtype, *shape: torch.full(shape, float("nan"), dtype=dtype, device="cuda")
+    work, ut, lam = nan(torch.float64, n * 2 * l * l), nan(torch.float32, n + 1, l, l), nan(torch.float64, n + 1, l)
+    assert L.lq_test_sym_eig_batch(gt.data_ptr(), l, n, work.data_ptr(), ut.data_ptr(), lam.data_ptr(), None) == 0
+    torch.cuda.synchronize()
+    assert torch.isnan(ut[n]).all() and torch.isnan(lam[n]).all()
+    for i in range(n):
+        u1, lam1 = _solve(gs[i])
+        assert np.array_equal(ut[i].cpu().numpy().astype(np.float64), u1), kinds[i]
+        assert np.array_equal(lam[i].cpu().numpy(), lam1), kinds[i]

@@ -33,6 +33,57 @@ def test_orthonormalize_ragged(l, extra):
     assert np.max(np.abs(c @ q - x)) < 2e-4 * np.max(np.abs(x)) * np.sqrt(l)
 
 
+@pytest.mark.parametrize("l,m,batch,chunks", [(32, 100, 3, 16), (64, 1000, 5, 1), (96, 333, 12, 16), (128, 2049, 2, 128),
+                                               (160, 500, 3, 7)])
+def test_gram_of_a_batch(l, m, batch, chunks):
+    """Problems a stride apart, scratch for one chunk of columns up to all of them.  A sum of m products of fp32 numbers in
+    fp64: m roundings of 2^-53."""
+    import torch
+    L = load()
+    ld, rng = (m + 15) // 16 * 16, np.random.default_rng(l)
+    stride = l * ld + 64
+    x = np.full((batch, stride), np.nan, np.float32)
+    xs = x[:, :l * ld].reshape(batch, l, ld)
+    xs[:, :, :m] = rng.standard_normal((batch, l, m)) * 10.0 ** np.arange(batch)[:, None, None]   # the padding stays NaN
+    xt = torch.from_numpy(x).cuda()
+    nd = batch * l * l * chunks
+    part = torch.full((nd + 1,), float("nan"), dtype=torch.float64, device="cuda")
+    g = torch.full((batch + 1, l, l), float("nan"), dtype=torch.float64, device="cuda")
+    assert L.lq_test_gram(xt.data_ptr(), l, m, ld, stride, part.data_ptr(), nd, g.data_ptr(), batch, None) == 0
+    torch.cuda.synchronize()
+    v = xs[:, :, :m].astype(np.float64)
+    assert np.all(np.abs(g[:batch].cpu().numpy() - v @ v.transpose(0, 2, 1)) <= 2.0 ** -52 * m * (np.abs(v) @ np.abs(v).transpose(0, 2, 1)))
+    assert torch.isnan(g[batch]).all() and torch.isnan(part[nd])
+
+
+@pytest.mark.parametrize("l", [32, 64, 96, 128])
+@pytest.mark.parametrize("lower", [False, True])
+@pytest.mark.parametrize("batch,ld0,ld1", [(1, 32, 0), (3, 96, 0), (4, 160, 64), (2, 1056, 2080)])
+def test_rotate_of_a_batch(l, lower, batch, ld0, ld1):
+    """One or two matrices per problem, a stride apart.  fp32 sums over l terms: l * 2^-24 of the terms' magnitudes."""
+    import torch
+    L = load()
+    rng = np.random.default_rng(l + ld0)
+    u = rng.standard_normal((batch, l, l)).astype(np.float32)
+    if lower:
+        u = np.tril(u)
+    put = lambda v: torch.from_numpy(v).cuda()
+    mats = []
+    for ld in (ld0, ld1):
+        if ld:
+            a = rng.standard_normal((batch, l + 1, ld)).astype(np.float32)        # a row between the problems
+            mats.append((ld, a, put(a), torch.full(a.shape, 7.0, dtype=torch.float32, device="cuda")))
+    ptr = lambda i, j: mats[i][j].data_ptr() if i < len(mats) else None
+    ut = put(u)
+    assert L.lq_test_rotate(l, ut.data_ptr(), l * l, int(lower), ptr(0, 2), ptr(0, 3), ld0, (l + 1) * ld0, ptr(1, 2), ptr(1, 3),
+                            ld1, (l + 1) * ld1, batch, None) == 0
+    torch.cuda.synchronize()
+    for ld, a, _, c in mats:
+        got, v = c.cpu().numpy(), a[:, :l].astype(np.float64)
+        assert np.all(np.abs(got[:, :l] - u @ v) <= 2.0 ** -24 * (l + 1) * (np.abs(u).astype(np.float64) @ np.abs(v)))
+        assert np.all(got[:, l] == 7.0)
+
+
 @pytest.mark.parametrize("d,k,rank", [(192, 256, 4), (1500, 640, 16), (640, 1504, 16)])
 def test_factorize_with_dominant_directions(d, k, rank):
     """Dominant directions that the cold start locks (the filter step then removes them from every row), up to more than the

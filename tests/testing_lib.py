@@ -29,6 +29,10 @@ def load():
         L.lq_test_lincomb3.argtypes = [vp, C.c_float, vp, C.c_float, vp, C.c_float, it, i64, vp]
         L.lq_test_deflate_rows.argtypes = [vp, vp, it, it, i64, i64, vp]
         L.lq_test_ritz_residual.argtypes = [vp, vp, vp, it, i64, i64, vp, vp]
+        L.lq_test_sym_eig_batch.argtypes = [vp, it, it, vp, vp, vp, vp]
+        L.lq_test_gram.argtypes = [vp, it, i64, i64, C.c_size_t, vp, C.c_size_t, vp, it, vp]
+        L.lq_test_rotate.argtypes = [it, vp, C.c_size_t, it, vp, vp, i64, C.c_size_t, vp, vp, i64, C.c_size_t, it, vp]
+        L.lq_test_filter_step.argtypes = [vp, C.c_float, vp, C.c_float, vp, C.c_float, vp, it, it, i64, i64, vp]
         L.lq_test_lds_limit.restype = C.c_size_t
         L.lq_test_bucket_code.argtypes = [C.c_int, C.c_float]
         L.lq_test_sigma_by_reciprocal.restype = C.c_float
