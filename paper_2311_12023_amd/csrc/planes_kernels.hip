@@ -114,15 +114,17 @@ __global__ __launch_bounds__(PG_THREADS) void plane_gemm_kernel(PgArgs a) {
   extern __shared__ __attribute__((aligned(16))) unsigned char pg_lds[];
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const int ln = lane & 31, lh = lane >> 5;
-  // tiles are dealt to the 8 XCDs in contiguous stretches of an order that goes down four row tiles before the next column,
-  // so that the tiles an XCD works on at a time share operands in its L2
-  const int total = a.tiles_m * a.tiles_n, per = (total + 7) / 8;
-  const int t = (int)(blockIdx.x & 7) * per + (int)(blockIdx.x >> 3);
-  if ((int)(blockIdx.x >> 3) >= per || t >= total) return;
+  // (tile, range) pairs are dealt to the 8 XCDs in contiguous stretches, tiles in an order that goes down four row tiles before
+  // the next column, so that the tiles an XCD works on at a time share operands in its L2.  Pairs and not tiles, or a few
+  // tiles of many ranges fill some XCDs twice and leave others idle (1025 rows x 4096 x 1024, 20 tiles of 12 ranges)
+  const int items = a.tiles_m * a.tiles_n * a.splits, per = (items + 7) / 8;
+  const int item = (int)(blockIdx.x & 7) * per + (int)(blockIdx.x >> 3);
+  if ((int)(blockIdx.x >> 3) >= per || item >= items) return;
+  const int t = item / a.splits, split = item - t * a.splits;
   const int band = t / (4 * a.tiles_n), rows = a.tiles_m - 4 * band < 4 ? a.tiles_m - 4 * band : 4;
   const int inside = t - band * 4 * a.tiles_n;
   const int tm = 4 * band + inside % rows, tn = inside / rows;
-  const int s0 = (int)((int64_t)a.nsteps * blockIdx.y / a.splits), s1 = (int)((int64_t)a.nsteps * (blockIdx.y + 1) / a.splits);
+  const int s0 = (int)((int64_t)a.nsteps * split / a.splits), s1 = (int)((int64_t)a.nsteps * (split + 1) / a.splits);
 
   // this wavefront's transfers: rows 16 wave .. + 15 and 128 further of both tiles; lane l brings unit l % 4 ^ swizzle of row l / 4
   const int lrow = lane >> 2, unit = (lane & 3) ^ ((lrow >> 1) & 3);
@@ -191,7 +193,7 @@ __global__ __launch_bounds__(PG_THREADS) void plane_gemm_kernel(PgArgs a) {
   }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");                 // nothing lands in LDS after the workgroup is gone
 
-  float* __restrict__ Y = a.Y + (size_t)blockIdx.y * (size_t)a.m * (size_t)a.ldy;
+  float* __restrict__ Y = a.Y + (size_t)split * (size_t)a.m * (size_t)a.ldy;
 #pragma unroll
   for (int j = 0; j < 2; ++j) {
     const int64_t col = (int64_t)tn * PG_T + 64 * wn + 32 * j + ln;
@@ -260,7 +262,7 @@ int launch_plane_product(const MvWeights& q, const uint16_t* Xh, int64_t K, cons
   LQ_TRY(limit.raise(reinterpret_cast<const void*>(plane_gemm_kernel), lds));
   {
     prof::Scope ps(prof::PLANE_GEMM, st, 2.0 * (double)m * (double)N * (double)(K + a.K2));
-    hipLaunchKernelGGL(plane_gemm_kernel, dim3((unsigned)((tiles + 7) / 8 * 8), (unsigned)a.splits), dim3(PG_THREADS), lds, st, a);
+    hipLaunchKernelGGL(plane_gemm_kernel, dim3((unsigned)((tiles * a.splits + 7) / 8 * 8)), dim3(PG_THREADS), lds, st, a);
     LQ_HIP_TRY(hipGetLastError());
   }
   if (a.splits > 1) return launch_qmatmul_reduce(part, a.splits, m, N, Y, ldy, st);
