@@ -265,16 +265,17 @@ int lq_fisher_row_col(const float* F, int64_t d, int64_t k, float* row_w, float*
  *   precision  0: every operand is split into bf16 hi + lo and each product takes three bf16 MFMAs with fp32
  *                 accumulation (error of an output about 2^-16 of sum |x||w|);  1: bf16 operands, one MFMA
  *                 (about 2^-8), for callers that train in bf16
- *              Up to 128 rows (rank <= 512) X is split on the fly and the workspace holds partial sums only.  Above 512
- *              rows (rank <= 64) precision 1 decodes the weights into a bf16 plane in the workspace first.  A workspace
- *              that is too small for either but holds what other sizes take (below) is used that way, and results then
- *              differ by rounding.
+ *              Up to 128 rows (rank <= 512; 64 for weights of 2^24 and more, where more depends on the sizes) X is split
+ *              on the fly and the workspace holds partial sums only.  Above 512 rows (rank <= 64) precision 1 decodes the
+ *              weights into a bf16 plane in the workspace first.  A workspace that is too small for the way that is taken
+ *              by size but holds what another needs is used that way, and results then differ by rounding.
  *              With m <= 8 and rank <= 512 the product is bound by reading the weights once; it then runs in plain
  *              fp32 on the vector ALU (exact products, fp32 accumulation) and `precision` is ignored.
  *   workspace  lq_matmul_workspace_bytes(m, d, k, rank) bytes, which serve both precisions, or
  *              lq_matmul_workspace_bytes_precision(..) bytes, which serve the one named (less where the other decodes the
- *              weights, 2 bytes each).  For 9 to 128 rows (rank <= 512): partial sums, one size for all of them; it and
- *              the sizes for more rows also serve every number of rows from 1 to 128.  Above 128 rows or rank 512: the
+ *              weights, 2 bytes each).  For 9 to 128 rows (rank <= 512): partial sums, one size that serves every number
+ *              of rows from 1 to 128 (so do the sizes for more rows).  Above 128 rows or rank 512, and where they are
+ *              faster above 64 rows: the
  *              bf16 hi / lo planes of X (rows padded to a multiple of 256), X L1 and its planes, the block scales or the
  *              plane of the weights, and partial sums where the reduction is cut, which more rows can need less of: ask
  *              for each of these sizes.

@@ -15,15 +15,41 @@ static int64_t up32(int64_t x) { return (x + 31) & ~(int64_t)31; }
 constexpr int64_t SMALL_M = QMATVEC_MAX_ROWS;
 constexpr int SMALL_RANK = 512;
 // Above this many rows precision 1 decodes the weights into a bf16 plane first (see planes_kernels.hip for both sides).
-constexpr int64_t PLANE_M = 512;
+// On small weights without a low-rank part of more than 32 the launch more costs what it gains up to 1024 rows (1024 x 1024, rank
+// 16, 640 rows: 37.8 us against 34.7 without a plane; rank 64: 37.3 against 38.7; 1500 rows, rank 16: level).
+constexpr int64_t PLANE_M = 512, PLANE_M_SMALL = 1024;
+
+// Between 9 and 128 rows: whether qrows_kernel is ahead of qmatmul_kernel, whose time is that of 256 rows whatever m is.
+// qrows_kernel decodes the weights once for every group of up to 48 rows, so it loses on large weights where it has three
+// groups (97 rows and more; qrows against qmatmul in us at 112 rows, whole calls, precision 0 / 1):
+//   3-bit codes, the dearest to decode        4096 x 11008, rank 64   112 / 89 against 98 / 75    (4096^2: 56 / 44 against 57 / 47)
+//   rows of L1 that cannot be read as float4  8192^2, rank 65         139 / 140 against 141 / 99
+//   T L2, on the vector ALU, for high ranks   4096 x 11008, rank 512  155 / 133 against 132 / 112  (11008 x 4096: 112 / 88 against 163 / 139)
+//   bf16 operands and the largest weights     8192^2, rank 64         - / 89 against - / 83
+// and elsewhere wins (4096 x 11008, 4 bits, rank 64: 82 / 61 against 86 / 67; rank 256: 110 / 89 against 125 / 104).
+static bool rows_kernel_ahead(int64_t m, int64_t d, int64_t k, int rank, int bits, int precision) {
+  const int64_t weights = d * k;
+  const bool wide = k > d, odd = rank % 4 != 0;
+  if (m <= 64 || weights < ((int64_t)1 << 24)) return true;
+  if (m <= 96)
+    return !(bits == 3 && rank >= 384 && wide && weights >= ((int64_t)1 << 25)) && !(odd && precision == 1 && weights >= ((int64_t)1 << 26));
+  if (bits == 3 && rank == 0) return false;
+  if (weights < ((int64_t)1 << 25)) return true;
+  if (bits == 3 && (rank <= SPLIT_PROJECT_MAX_RANK || d <= k)) return false;
+  if (rank >= 384 && wide) return false;
+  if (odd && (precision == 1 || (wide && weights >= ((int64_t)1 << 26)))) return false;
+  return !(weights >= ((int64_t)1 << 26) && rank <= SPLIT_PROJECT_MAX_RANK && (precision == 1 || rank == 0 || wide));
+}
 
 // The kernels a call can take.  Each needs a workspace of its own; where the one given is too small for the route that the
-// sizes call for but holds ROUTE_GENERAL, that one is taken.
+// sizes call for but holds the other that can serve the call, that one is taken.
 enum Route { ROUTE_FEW, ROUTE_ROWS, ROUTE_PLANE, ROUTE_GENERAL };
-static Route preferred_route(int64_t m, int rank, int precision) {
+static bool rows_route_serves(int64_t m, int rank) { return m <= QROWS_MAX_ROWS && rank <= QROWS_MAX_RANK; }
+static Route preferred_route(int64_t m, int64_t d, int64_t k, int rank, int bits, int precision) {
   if (m <= SMALL_M && rank <= SMALL_RANK) return ROUTE_FEW;
-  if (m <= QROWS_MAX_ROWS && rank <= QROWS_MAX_RANK) return ROUTE_ROWS;
-  return precision == 1 && m > PLANE_M && rank <= SPLIT_PROJECT_MAX_RANK ? ROUTE_PLANE : ROUTE_GENERAL;
+  if (rows_route_serves(m, rank)) return rows_kernel_ahead(m, d, k, rank, bits, precision) ? ROUTE_ROWS : ROUTE_GENERAL;
+  const int64_t from = d * k < ((int64_t)1 << 22) && rank <= 32 ? PLANE_M_SMALL : PLANE_M;
+  return precision == 1 && m > from && rank <= SPLIT_PROJECT_MAX_RANK ? ROUTE_PLANE : ROUTE_GENERAL;
 }
 static int64_t padded_rows(int64_t m) { return (m + 255) / 256 * 256; }
 
@@ -71,13 +97,13 @@ static size_t route_bytes(Route route, int64_t m, int64_t d, int64_t k, int rank
   return plan_bytes(plan_matmul(route, m, d, k, rank));
 }
 
-// What m rows need and, beyond the few, no less than any number of rows up to QROWS_MAX_ROWS needs: those sizes rise and fall
+// What m rows need, whatever the code width, and, beyond the few, no less than any number of rows up to QROWS_MAX_ROWS needs: those sizes rise and fall
 // with m as reductions are cut less, and a caller sizes once for batches that come and go.  Among the rows of ROUTE_ROWS
 // only whole tiles of 16 have to be looked at, between which the cut stays the same.
 static size_t workspace_bytes_for(int64_t m, int64_t d, int64_t k, int rank, int precision) {
-  const Route route = preferred_route(m, rank, precision);
-  size_t need = route_bytes(route, m, d, k, rank);
-  if (route == ROUTE_FEW) return need;
+  if (m <= SMALL_M && rank <= SMALL_RANK) return route_bytes(ROUTE_FEW, m, d, k, rank);
+  size_t need = 0;
+  for (int bits : {3, 4}) need = std::max(need, route_bytes(preferred_route(m, d, k, rank, bits, precision), m, d, k, rank));
   if (rank <= SMALL_RANK)
     for (int64_t r = 1; r <= SMALL_M; ++r) need = std::max(need, route_bytes(ROUTE_FEW, r, d, k, rank));
   if (rank <= QROWS_MAX_RANK)
@@ -120,7 +146,7 @@ size_t lq_matmul_workspace_bytes_precision(int64_t m, int64_t d, int64_t k, int 
 
 size_t lq_matmul_workspace_bytes(int64_t m, int64_t d, int64_t k, int rank) {
   return std::max(lq_matmul_workspace_bytes_precision(m, d, k, rank, 0),
-                  m > PLANE_M ? lq_matmul_workspace_bytes_precision(m, d, k, rank, 1) : 0);
+                  lq_matmul_workspace_bytes_precision(m, d, k, rank, 1));
 }
 
 int lq_matmul(const float* X, int64_t m, int64_t d, int64_t k, const uint8_t* codes_packed, const uint8_t* scale_idx,
@@ -136,12 +162,12 @@ int lq_matmul(const float* X, int64_t m, int64_t d, int64_t k, const uint8_t* co
   if ((k % c.block) != 0) return LQ_ERR_SHAPE;
   if (precision != 0 && precision != 1) return LQ_ERR_ARG;
   if (((uintptr_t)X & 15) != 0 || ((uintptr_t)Y & 15) != 0 || (rank > 0 && ((uintptr_t)L2 & 15) != 0)) return LQ_ERR_ARG;
-  Route route = preferred_route(m, rank, precision);
+  Route route = preferred_route(m, d, k, rank, c.bits, precision);
   // 32-bit byte offsets into the planes of X and into the codes
   if (route != ROUTE_FEW && (padded_rows(m) * d >= ((int64_t)1 << 31) || d * k >= ((int64_t)1 << 31))) return LQ_ERR_SHAPE;
   MatmulPlan p = plan_matmul(route, m, d, k, rank);
-  if (workspace_bytes < plan_bytes(p) && (route == ROUTE_ROWS || route == ROUTE_PLANE)) {
-    route = ROUTE_GENERAL;
+  if (workspace_bytes < plan_bytes(p) && route != ROUTE_FEW) {
+    route = route == ROUTE_GENERAL && rows_route_serves(m, rank) ? ROUTE_ROWS : ROUTE_GENERAL;
     p = plan_matmul(route, m, d, k, rank);
   }
   if (!workspace || ((uintptr_t)workspace & 255) != 0 || workspace_bytes < plan_bytes(p)) return LQ_ERR_WORKSPACE;

@@ -3,8 +3,9 @@
 // product then reads like any other operand, where qmatmul_kernel decodes a weight again for every 256 rows of X: with one
 // MFMA per product that decode cannot hide behind the matrix pipe.  4096 rows, rank 64, whole call: 4096 x 4096 242 -> 178 us
 // (4 bits; 271 -> 198 with 3), 4096 x 11008 640 -> 435, 11008 x 4096 599 -> 425; 1024 rows 98 -> 87, 200 -> 160, 195 -> 168.
-// At 512 rows the two are level (70, 131 against 125, 129) and below that the decode pass costs more than it saves (256
-// rows, 4096 x 11008: 81 against 98), so the line is drawn above 512.  The product runs at 0.9 PFLOP/s; what holds it there
+// The line is drawn above 512 rows: 513 rows, 4 bits, rank 64, with a plane 64, 137, 121 us (4096 x 4096, 4096 x 11008, 11008 x
+// 4096) against 72, 197, 138 without; 512 rows 65, 106, 110 against 66, 125, 110, but 8192 x 8192 146 against 132; 256 rows
+// 58, 80, 93 against 55, 74, 79.  Small weights: PLANE_M_SMALL in lq_api_matmul.cpp.  The product runs at 0.9 PFLOP/s; what holds it there
 // is that reading operands from LDS and multiplying overlap poorly (without the MFMAs it takes 110 of its 156 us, without
 // the transfers 140).
 #include <algorithm>

@@ -1,17 +1,19 @@
-// Forward product with a decomposed weight for a few dozen to a few hundred rows of X (decoding many sequences at once,
-// short prompts):  Y[m x N] = X dequant(codes) + (X L1) L2.  Two launches: the kernel below multiplies X with [Q | L1]
+// Forward product with a decomposed weight for 9 to 128 rows of X (decoding many sequences at once, short prompts):
+// Y[m x N] = X dequant(codes) + (X L1) L2.  Two launches: the kernel below multiplies X with [Q | L1]
 // over ranges of the reduction, qmatvec_finish_kernel adds the ranges and the product (X L1) L2.
 //
-// What bounds it: every weight is decoded (six vector instructions: extract, look up, scale, split into bf16 halves) for at
-// most 48 rows, where its matrix instructions take less time than the decode; the codes themselves are 0.25 to 1 byte per
-// weight.  So nothing is staged: a lane fetches half a 16-weight run of eight reduction rows, decodes them straight into the
+// Every weight is decoded (six vector instructions: extract, look up, scale, split into bf16 halves) for at most 48 rows,
+// where its matrix instructions take less time than the decode; the codes themselves are 0.25 to 1 byte per weight.  By
+// count the decode is a third of the kernel's 20 to 25 us at 24 rows x 4096 x 11008; what bounds it there is the latency of
+// loads one step ahead with two wavefronts per SIMD.  Nothing is staged: a lane fetches half a 16-weight run of eight reduction rows, decodes them straight into the
 // operand layout of v_mfma_f32_16x16x32_bf16 (8 column sets of 16 columns, column 8 c + j in set j) and multiplies them with
 // rows of X that it splits into bf16 halves on the way.  A workgroup owns 128 columns at a time; its eight wavefronts take
 // turns at the 32-deep reduction steps and their sums are added in order through LDS.
 // Whole call on 4096 x 11008, NF4, rank 64 (4096 x 4096): 24 rows 79 -> 32 us (45 -> 20), 64 rows 84 -> 50 us (47 -> 27),
 // 128 rows 94 -> 85 us (52 -> 42) against the kernel for large m, whose steps take 2 us whatever they multiply (256-row tiles
 // of X staged through LDS, a barrier per step).  At 192 rows that kernel is ahead on the wide matrix (95 against 111 us)
-// and level on the square one, so the line is drawn at 128.  What did not help: 256 columns per workgroup (twice the
+// and level on the square one, so the line is drawn at 128; rows_kernel_ahead in lq_api_matmul.cpp has the large weights
+// on which it is ahead from 65 or 97 rows on.  What did not help: 256 columns per workgroup (twice the
 // accumulators, half the wavefronts in flight: 37 us at 24 rows), four wavefronts per SIMD (registers spill: 80 us).
 #include <algorithm>
 #include <type_traits>
@@ -280,7 +282,8 @@ static int qrows_tiles(int64_t m) {
   return (int)((tiles + wgs - 1) / wgs);
 }
 
-// How the steps are dealt out to the 256 compute units.  Either every tile is cut into the same number of shares (the steps
+// How the steps are dealt out to the 256 compute units (a constant: it also sizes the workspace, which is asked for without
+// a device).  Either every tile is cut into the same number of shares (the steps
 // of a tile are counted up to a multiple of the share, so that no share reaches into the next tile), or the shares are
 // equal whatever the tiles and some workgroups have two segments, each with its own first fetch and sum: about one and a
 // half times a step of all wavefronts.  The smaller number of such steps is taken (4096 x 4096: 7 shares per tile and 3

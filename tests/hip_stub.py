@@ -28,7 +28,7 @@ int hipDeviceSynchronize(void) { return 0; }
 int hipMemcpy(void* d, const void* s, size_t n, int kind) { return 0; }
 """
 
-PRELUDE = r"""
+PRELUDE = r'''
 import ctypes as C, sys
 stub = C.CDLL(sys.argv[1], mode=C.RTLD_GLOBAL)
 L = C.CDLL(sys.argv[2])
@@ -42,7 +42,21 @@ L.lq_matmul_workspace_bytes.argtypes = [i64, i64, i64, it]
 L.lq_matmul_workspace_bytes_precision.argtypes = [i64, i64, i64, it, it]
 L.lq_test_sym_eig_fast.argtypes = [vp, it, vp, vp, vp]
 L.lq_test_sym_eig.argtypes = [vp, it, vp, vp, vp, vp]
-"""
+L.lq_profile_class_name.restype = C.c_char_p
+L.lq_profile_read.argtypes = [it, vp, vp, vp]
+def classes_of(call):
+    """Profile classes that the launches of call() are booked under: {name: work}."""
+    L.lq_profile_enable(1); L.lq_profile_reset()
+    assert call() == 0
+    ran = {}
+    for c in range(L.lq_profile_num_classes()):
+        ms, n, w = C.c_double(), C.c_int64(), C.c_double()
+        assert L.lq_profile_read(c, C.addressof(ms), C.addressof(n), C.addressof(w)) == 0
+        if n.value:
+            ran[L.lq_profile_class_name(c).decode()] = w.value
+    L.lq_profile_enable(0)
+    return ran
+'''
 
 
 def run(tmp_path, code, *args):

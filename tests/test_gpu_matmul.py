@@ -200,7 +200,7 @@ def test_matmul_in_a_hip_graph(env, oracle, m):
         assert torch.equal(y, eager), rep
 
 
-@pytest.mark.parametrize("m,precision", [(1, 0), (8, 0), (24, 1), (300, 1), (600, 1)])
+@pytest.mark.parametrize("m,precision", [(1, 0), (8, 0), (24, 1), (300, 1), (600, 1), (1100, 1)])
 def test_infinite_group_scale_is_infinite_weights(env, oracle, m, precision):
     """A group scale of infinity (a maximum above 65504 stored in fp16) makes infinite weights, as Dequantize returns them:
     the columns that hold one come out infinite, the others as ever."""
@@ -219,14 +219,14 @@ def test_infinite_group_scale_is_infinite_weights(env, oracle, m, precision):
     assert np.max(np.abs(y[:, :256] / ref[:, :256] - 1)) < TOL_BF16
 
 
-@pytest.mark.parametrize("m,d,k,precision,nbytes", [
-    (128, 32, 2048, 0, 200_000), (128, 32, 2048, 1, 200_000),     # too small for the partial sums of 128 rows
-    (600, 512, 1024, 1, None),                                    # no room for the weights in bf16
+@pytest.mark.parametrize("m,d,k,rank,precision,nbytes", [
+    (128, 32, 2048, 16, 0, 200_000), (128, 32, 2048, 16, 1, 200_000),     # too small for the partial sums of 128 rows
+    (600, 512, 1024, 40, 1, None),                                        # no room for the weights in bf16
 ])
-def test_matmul_with_a_smaller_workspace(env, oracle, m, d, k, precision, nbytes):
+def test_matmul_with_a_smaller_workspace(env, oracle, m, d, k, rank, precision, nbytes):
     """A workspace that only the general kernel can work with is accepted and the product is as good."""
     torch, lq = env
-    cfg, rank = (4, 32, 64), 16
+    cfg = (4, 32, 64)
     ocfg, codes, sidx, v, l1, l2 = _case(oracle, d, k, cfg, rank, 51)
     x = gen.activations(m, d, 52)
     ref, scale = oracle.matmul(x, codes, sidx, v, ocfg, k, l1, l2, want_abs=True)

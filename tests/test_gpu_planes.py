@@ -15,6 +15,8 @@ pytestmark = pytest.mark.gpu
     (768, 160, 256, (4, 64, 256), 33),        # whole tiles, an odd number of half decode tiles
     (1025, 416, 528, (8, 16, 16), 64),        # one row in the fifth row tile
     (600, 2080, 128, (4, 32, 16, 5, "fp16"), 32), (2100, 64, 144, (3, 16, 256), 17),
+    # the sizes above that go to the general kernel (small weights and ranks up to 32) at the rows from which they do not
+    (1281, 32, 16, (2, 16, 16), 0), (1032, 96, 272, (3, 16, 64), 1), (1112, 2080, 128, (4, 32, 16, 5, "fp16"), 32),
     (1100, 1024, 1008, (4, 16, 64), 16),      # 20 tiles of 8 ranges: pairs are dealt out across tiles
     # more than 128 tiles: the reduction is not cut, tiles go straight to Y
     (1030, 64, 6928, (3, 16, 256), 17),       # a second band of row tiles with a single one, 28 column tiles

@@ -26,17 +26,8 @@ ROUTES = [(1, 0, "qmatvec_kernel"), (8, 1, "qmatvec_kernel"), (9, 0, "qrows_kern
 def test_profile_names_the_kernel_that_runs(tmp_path, m, precision, kernel):
     hip_stub.run(tmp_path, r"""
 m, precision, kernel = int(args[0]), int(args[1]), args[2]
-L.lq_profile_class_name.restype = C.c_char_p
-L.lq_profile_read.argtypes = [it, vp, vp, vp]
 p = vp(4096)
-L.lq_profile_enable(1); L.lq_profile_reset()
-assert L.lq_matmul(p, m, 1024, 2048, p, p, p, Cfg(4, 16, 16, 8, 0), p, p, 64, precision, p, p, 1 << 40, None) == 0
-ran = {}
-for c in range(L.lq_profile_num_classes()):
-    ms, n, w = C.c_double(), C.c_int64(), C.c_double()
-    assert L.lq_profile_read(c, C.addressof(ms), C.addressof(n), C.addressof(w)) == 0
-    if n.value:
-        ran[L.lq_profile_class_name(c).decode()] = w.value
+ran = classes_of(lambda: L.lq_matmul(p, m, 1024, 2048, p, p, p, Cfg(4, 16, 16, 8, 0), p, p, 64, precision, p, p, 1 << 40, None))
 products = {"qmatvec_kernel", "qrows_kernel", "qmatmul_kernel", "plane_gemm_kernel"} & set(ran)
 assert products == {kernel}, ran
 if kernel not in ("qmatvec_kernel",):

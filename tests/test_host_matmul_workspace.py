@@ -48,3 +48,43 @@ assert L.lq_matmul_workspace_bytes(1000, 4096, 11008, 64) < 110e6          # not
 assert L.lq_matmul_workspace_bytes(4096, 11008, 4096, 64) == size(4096, 11008, 4096, 64, 0)   # the plane in place of the lo half of X
 assert L.lq_matmul_workspace_bytes(24, 4096, 11008, 64) == L.lq_matmul_workspace_bytes(9, 4096, 11008, 64) < 16e6
 """)
+
+
+# rows, weights, rank, bits -> the product kernel at precisions 0 and 1, as measured (us in lq_api_matmul.cpp)
+ROUTES = [
+    (64, 8192, 8192, 65, 3, "qrows qrows"), (96, 4096, 11008, 512, 4, "qrows qrows"), (96, 4096, 11008, 512, 3, "qmatmul qmatmul"),
+    (80, 8192, 8192, 62, 4, "qrows qmatmul"), (128, 4096, 4096, 64, 3, "qrows qrows"), (128, 4096, 4096, 0, 3, "qmatmul qmatmul"),
+    (128, 4096, 4096, 65, 4, "qrows qrows"), (97, 4096, 11008, 64, 3, "qmatmul qmatmul"), (97, 4096, 11008, 64, 4, "qrows qrows"),
+    (128, 11008, 4096, 128, 3, "qrows qrows"), (112, 4096, 11008, 128, 3, "qmatmul qmatmul"), (128, 4096, 11008, 256, 4, "qrows qrows"),
+    (128, 4096, 11008, 512, 8, "qmatmul qmatmul"), (128, 11008, 4096, 512, 8, "qrows qrows"), (100, 4096, 11008, 65, 4, "qrows qmatmul"),
+    (100, 5120, 13824, 65, 4, "qmatmul qmatmul"), (128, 8192, 8192, 64, 4, "qrows qmatmul"), (128, 8192, 8192, 0, 2, "qmatmul qmatmul"),
+    (128, 1024, 1024, 33, 3, "qrows qrows"),
+]
+
+
+@pytest.mark.parametrize("m,d,k,rank,bits,kernels", ROUTES)
+def test_kernel_for_65_to_128_rows(tmp_path, m, d, k, rank, bits, kernels):
+    """Large weights: the kernel that was measured to be the faster one runs when the workspace has the size that was asked
+    for, and the other where only that one fits."""
+    hip_stub.run(tmp_path, r"""
+m, d, k, rank, bits = map(int, args[:5])
+p = vp(4096)
+def ran(precision, size):
+    return [n.split("_")[0] for n in classes_of(lambda: L.lq_matmul(p, m, d, k, p, p, p, Cfg(bits, 16, 16, 8, 0), p, p, rank,
+            precision, p, p, size, None)) if n in ("qrows_kernel", "qmatmul_kernel")]
+for precision, kernel in enumerate(args[5].split()):
+    assert ran(precision, L.lq_matmul_workspace_bytes_precision(m, d, k, rank, precision)) == [kernel]
+    assert ran(precision, L.lq_matmul_workspace_bytes(9, d, k, rank)) == ["qrows"]
+""", m, d, k, rank, bits, kernels)
+
+
+@pytest.mark.parametrize("m,d,k,rank,kernel", [
+    (512, 4096, 4096, 64, "qmatmul"), (513, 4096, 4096, 64, "plane"), (513, 2048, 2048, 0, "plane"), (640, 1024, 1024, 16, "qmatmul"),
+    (640, 1024, 1024, 33, "plane"), (1024, 768, 3072, 32, "qmatmul"), (1025, 768, 3072, 32, "plane"), (600, 4096, 4096, 65, "qmatmul")])
+def test_kernel_for_bf16_rows(tmp_path, m, d, k, rank, kernel):
+    hip_stub.run(tmp_path, r"""
+m, d, k, rank = map(int, args[:4])
+p = vp(4096)
+ran = classes_of(lambda: L.lq_matmul(p, m, d, k, p, p, p, Cfg(4, 16, 16, 8, 0), p, p, rank, 1, p, p, 1 << 40, None))
+assert ("plane_gemm_kernel" in ran) == (args[4] == "plane") and ("qmatmul_kernel" in ran) == (args[4] == "qmatmul"), ran
+""", m, d, k, rank, kernel)
