@@ -766,8 +766,9 @@ static int resident_workgroups() {
 }
 
 // Workgroups that a launch aims at: all resident ones, one per CU for a single problem, whose every tile is cut into that
-// many partial results (a Fisher-weighted decomposition of 4096 x 11008 12.25 -> 11.68 ms; 4096 x 4096 and smaller: no
-// difference either way, what the longer shares cost the products the sum of the partial tiles gains).
+// many partial results.  Factorize of one matrix with two and with one per CU, rank 8 / 64 (ms): 11008 x 4096 4.22 -> 4.09 / 7.87
+// -> 6.57, 4096 x 11008 4.26 -> 4.10 / 8.51 -> 7.39, 8192 x 8192 5.38 -> 5.30 / 9.33 -> 8.97; 4096 x 4096, 1024 x 4096 and 768 x
+// 768 level to 0.4 % (what the longer shares cost the products the sum of the partial tiles gains), and so is rank 128.
 static int default_workgroups(int batch) { return batch == 1 ? resident_workgroups() / 2 : resident_workgroups(); }
 
 // Upper bound of the partial-tile scratch: two tiles per workgroup, at most twice the requested workgroups (plus the

@@ -184,13 +184,18 @@ static void launch_quantize_bits(const float* x, int64_t nruns, const lq_config&
   const int rpb = c.block / 16;
   const int lv = scale_levels(c);
   const int group_runs = rpb * c.scale_block;        // at most 1024: a workgroup holds whole groups
+  // a grid has fewer than 2^32 threads: more runs than 2^30 (whole groups) take several launches
+  constexpr int64_t MAX_RUNS = (int64_t)1 << 30;
+  for (int64_t r0 = 0; r0 < nruns; r0 += MAX_RUNS) {
+    const int64_t n = nruns - r0 < MAX_RUNS ? nruns - r0 : MAX_RUNS;
 #define LQ_QUANTIZE(T)                                                                                                   \
-  hipLaunchKernelGGL((quantize_fused_kernel<BITS, T>), dim3((unsigned)((nruns + (T) - 1) / (T))), dim3(T), 0, st, x,      \
-                     nruns, rpb, c.scale_block, lv, c.v_dtype, tab, codes, sidx, v)
-  if (group_runs > 512) LQ_QUANTIZE(1024);
-  else if (group_runs > 256) LQ_QUANTIZE(512);
-  else LQ_QUANTIZE(256);
+  hipLaunchKernelGGL((quantize_fused_kernel<BITS, T>), dim3((unsigned)((n + (T) - 1) / (T))), dim3(T), 0, st, x + 16 * r0, \
+                     n, rpb, c.scale_block, lv, c.v_dtype, tab, codes + 2 * BITS * r0, sidx + r0 / rpb, v + r0 / group_runs)
+    if (group_runs > 512) LQ_QUANTIZE(1024);
+    else if (group_runs > 256) LQ_QUANTIZE(512);
+    else LQ_QUANTIZE(256);
 #undef LQ_QUANTIZE
+  }
 }
 
 int launch_quantize(const float* x, int64_t n, const lq_config& c, uint8_t* codes, uint8_t* sidx, float* v,

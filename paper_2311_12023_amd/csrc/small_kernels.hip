@@ -1,7 +1,7 @@
-// Small dense kernels of the randomized SVD: Cholesky factors for the orthonormalisation,
-// the l x l symmetric eigenproblem of the Rayleigh-Ritz step (parallel Jacobi), sketch generation and
-// factor assembly (Algorithm 4).  These run on the ALUs with their working set in LDS when it fits;
-// they are latency-, not throughput-critical, and batched over the configurations of a sweep.
+// Small dense kernels of the randomized SVD: Cholesky factors for the orthonormalisation, the filter steps of the cold
+// start, a parallel Jacobi eigen-solver for blocks of more than 128 rows (eig_kernels.hip has the others), row norms, sketch
+// generation and factor assembly (Algorithm 4), Fisher weights.  They are latency-, not throughput-critical; the
+// factors and the solver keep their working set in registers or LDS where it fits.
 #include <cmath>
 
 #include "dense_device.h"

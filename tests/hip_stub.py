@@ -1,5 +1,6 @@
 """Runs a piece of Python with the testing build of the library in a process of its own whose HIP calls end in a stub: it is
-loaded before the library, so its symbols come first; it launches nothing and counts requests and launches."""
+loaded before the library, so its symbols come first; it launches nothing and counts requests, launches and their
+threads."""
 import os
 import subprocess
 import sys
@@ -9,14 +10,23 @@ from testing_lib import ROOT, TEST_LIB
 STUB = r"""
 #include <stddef.h>
 #include <stdlib.h>
+struct dim { unsigned x, y, z; };
 static int device = 0, refuse = 0, raised[8], launches = 0;
+static double most = 0, total = 0;
 void stub_set(int dev, int fail) { device = dev; refuse = fail; }
 int stub_raised(int dev) { return raised[dev]; }
 int stub_launches(void) { return launches; }
 int hipGetDevice(int* dev) { *dev = device; return 0; }
 int hipFuncSetAttribute(const void* f, int attr, int value) { if (refuse) return 1; ++raised[device]; return 0; }
 int hipDeviceGetAttribute(int* v, int attr, int dev) { *v = 160 * 1024; return 0; }
-int __hipPushCallConfiguration() { return 0; }
+double stub_most_threads(void) { return most; }
+double stub_all_threads(void) { return total; }
+int __hipPushCallConfiguration(struct dim g, struct dim b, size_t shm, void* st) {
+  double n = (double)g.x * g.y * g.z * b.x * b.y * b.z;
+  if (n > most) most = n;
+  total += n;
+  return 0;
+}
 int __hipPopCallConfiguration() { return 0; }
 int hipLaunchKernel() { ++launches; return 0; }
 int hipGetLastError(void) { return 0; }
@@ -33,9 +43,11 @@ import ctypes as C, sys
 stub = C.CDLL(sys.argv[1], mode=C.RTLD_GLOBAL)
 L = C.CDLL(sys.argv[2])
 args = sys.argv[3:]
+stub.stub_most_threads.restype = stub.stub_all_threads.restype = C.c_double
 vp, i64, it = C.c_void_p, C.c_int64, C.c_int
 class Cfg(C.Structure):
     _fields_ = [(n, C.c_int32) for n in ("bits", "block", "scale_block", "scale_bits", "v_dtype")]
+L.lq_nf_quantize.argtypes = [vp, i64, Cfg, vp, vp, vp, vp]
 L.lq_matmul.argtypes = [vp, i64, i64, i64, vp, vp, vp, Cfg, vp, vp, it, it, vp, vp, C.c_size_t, vp]
 L.lq_matmul_workspace_bytes.restype = L.lq_matmul_workspace_bytes_precision.restype = C.c_size_t
 L.lq_matmul_workspace_bytes.argtypes = [i64, i64, i64, it]
