@@ -1,4 +1,5 @@
-// Device helpers of the kernels that keep a small dense fp64 matrix in the registers of one workgroup.
+// Device helpers of the kernels that keep a small dense fp64 matrix in the registers of one workgroup, and of others that
+// index register arrays by compile-time constants.
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -15,6 +16,17 @@ __device__ __forceinline__ void for_each_block(F&& f) {
 template <int N, class F>
 __device__ __forceinline__ void for_each_block_down(F&& f) {
   if constexpr (N > 0) { f(std::integral_constant<int, N - 1>{}); for_each_block_down<N - 1>(f); }
+}
+
+// Pair a of a round of the parallel Jacobi method (circle method: round < n-1, a < n/2, so both sums stay below 2(n-1) and
+// one conditional subtraction replaces the modulo); p < q.
+__device__ inline void circle_pair(int a, int round, int n, int& p, int& q) {
+  if (a == 0) { p = n - 1; q = round; }
+  else {
+    p = round + a; if (p >= n - 1) p -= n - 1;
+    q = round - a + (n - 1); if (q >= n - 1) q -= n - 1;
+  }
+  if (p > q) { const int t = p; p = q; q = t; }
 }
 
 template <int CTRL>

@@ -44,16 +44,6 @@ __device__ __forceinline__ int row_sum_index(int tx) {
 }
 
 // ---- one-sided Jacobi, for matrices whose eigenvalues are not separated ------------------------------
-// Circle method: round < n-1, a < n/2.
-__device__ inline void circle_pair(int a, int round, int n, int& p, int& q) {
-  if (a == 0) { p = n - 1; q = round; }
-  else {
-    p = round + a; if (p >= n - 1) p -= n - 1;
-    q = round - a + (n - 1); if (q >= n - 1) q -= n - 1;
-  }
-  if (p > q) { const int t = p; p = q; q = t; }
-}
-
 __device__ __forceinline__ float row_sum16(float x) {
   x += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), XOR1, 0xf, 0xf, false));
   x += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), XOR2, 0xf, 0xf, false));

@@ -1,13 +1,14 @@
 // Forward product with a decomposed weight in bf16 for many rows of X (lq_matmul, precision 1):  Y = X Q + (X L1) L2  with
 // every operand rounded to bf16 and fp32 accumulation.  The weights are decoded once per call into a bf16 plane that the
 // product then reads like any other operand, where qmatmul_kernel decodes a weight again for every 256 rows of X: with one
-// MFMA per product that decode cannot hide behind the matrix pipe.  4096 rows, rank 64, whole call: 4096 x 4096 242 -> 178 us
-// (4 bits; 271 -> 198 with 3), 4096 x 11008 640 -> 435, 11008 x 4096 599 -> 425; 1024 rows 98 -> 87, 200 -> 160, 195 -> 168.
+// MFMA per product that decode cannot hide behind the matrix pipe.  4096 rows, rank 64, whole call without and with a plane:
+// 4096 x 4096 213 -> 163 us (4 bits; 239 -> 163 with 3), 4096 x 11008 592 -> 419, 11008 x 4096 595 -> 414; 1024 rows, 4 bits 87 ->
+// 79, 197 -> 140, 168 -> 158.
 // The line is drawn above 512 rows: 513 rows, 4 bits, rank 64, with a plane 64, 137, 121 us (4096 x 4096, 4096 x 11008, 11008 x
 // 4096) against 72, 197, 138 without; 512 rows 65, 106, 110 against 66, 125, 110, but 8192 x 8192 146 against 132; 256 rows
-// 58, 80, 93 against 55, 74, 79.  Small weights: PLANE_M_SMALL in lq_api_matmul.cpp.  The product runs at 0.9 PFLOP/s; what holds it there
-// is that reading operands from LDS and multiplying overlap poorly (without the MFMAs it takes 110 of its 156 us, without
-// the transfers 140).
+// 58, 80, 93 against 55, 74, 79.  Small weights: PLANE_M_SMALL in lq_api_matmul.cpp.  The product runs at 0.9 to 1.0 PFLOP/s
+// (138 us for 4096^3 in a trace); what holds it there is that reading operands from LDS and multiplying overlap poorly
+// (when it took 156 us: 110 without the MFMAs, 140 without the transfers).
 #include <algorithm>
 
 #include "kernels.h"

@@ -16,8 +16,8 @@
 // on which it is ahead from 65 or 97 rows on.  What did not help: 256 columns per workgroup (twice the
 // accumulators, half the wavefronts in flight: 37 us at 24 rows), four wavefronts per SIMD (registers spill: 80 us).
 #include <algorithm>
-#include <type_traits>
 
+#include "dense_device.h"
 #include "kernels.h"
 #include "nf_device.h"
 #include "profiler.h"
@@ -97,11 +97,6 @@ __device__ __forceinline__ uint32_t code_offset(uint2 r) {
   if constexpr (BITS == 8) return __builtin_amdgcn_ubfe(J < 4 ? r.x : r.y, 8 * (J % 4), 8) << 2;
   else if constexpr (BITS == 4) return __builtin_amdgcn_ubfe(J % 2 ? r.y : r.x, 8 * (J / 2), 8);
   else return (r.x >> (J * BITS)) & (((1u << BITS) - 1u) << 2);
-}
-
-template <int N, class F>
-__device__ __forceinline__ void each_column_set(F&& f) {
-  if constexpr (N > 0) { each_column_set<N - 1>(f); f(std::integral_constant<int, N - 1>{}); }
 }
 
 // The steps of all column tiles, in order (tile, step), are dealt out in equal contiguous shares, so that every compute unit
@@ -211,7 +206,7 @@ __global__ __launch_bounds__(64 * QR_WAVES, 2) void qrows_kernel(QrArgs a) {
         split_x();
         const int sn = s + QR_WAVES < s1 ? s + QR_WAVES : s;           // past the end: the same step again
         fetch_w(sn); fetch_x(sn);
-        each_column_set<QR_SETS>([&](auto set) {
+        for_each_block<QR_SETS>([&](auto set) {
           constexpr int j = decltype(set)::value;
           float w[8];
 #pragma unroll
@@ -236,7 +231,7 @@ __global__ __launch_bounds__(64 * QR_WAVES, 2) void qrows_kernel(QrArgs a) {
           }
         }
         split_x();
-        each_column_set<4>([&](auto set) {
+        for_each_block<4>([&](auto set) {
           constexpr int j = decltype(set)::value;
           const float w[8] = {d[0][j], d[1][j], d[2][j], d[3][j], d[4][j], d[5][j], d[6][j], d[7][j]};
           multiply(w, set);

@@ -212,17 +212,6 @@ int launch_trsm(const double* Cfac, int l, float* X, int64_t m, int64_t ldx, siz
 // l/2 disjoint rotations at once, M <- J^T M J as independent 2x2 blocks, Vt <- J^T Vt as row pairs.
 constexpr int JT = 512;
 
-__device__ inline void rr_pair(int a, int round, int n, int& p, int& q) {
-  // circle method: round < n-1, a < n/2, so both sums stay below 2(n-1) and one conditional subtraction
-  // replaces the modulo
-  if (a == 0) { p = n - 1; q = round; }
-  else {
-    p = round + a; if (p >= n - 1) p -= n - 1;
-    q = round - a + (n - 1); if (q >= n - 1) q -= n - 1;
-  }
-  if (p > q) { const int t = p; p = q; q = t; }
-}
-
 // STORE: 0 = M and Vt in global memory, 1 = M in LDS, 2 = M and Vt in LDS.
 template <int STORE>
 __global__ __launch_bounds__(JT) void jacobi_eig_kernel(double* __restrict__ Gall, int l, double* __restrict__ Vall,
@@ -251,7 +240,7 @@ __global__ __launch_bounds__(JT) void jacobi_eig_kernel(double* __restrict__ Gal
     for (int round = 0; round < l - 1; ++round) {
       if (tid < half) {
         int p, q;
-        rr_pair(tid, round, l, p, q);
+        circle_pair(tid, round, l, p, q);
         const double mpp = M[p * pm + p], mqq = M[q * pm + q], mpq = M[p * pm + q];
         double c = 1.0, s = 0.0;
         if (mpq != 0.0 && fabs(mpq) > 1e-10 * sqrt(fabs(mpp * mqq))) {
