@@ -82,102 +82,6 @@ int launch_cholesky(double* G, int l, int batch, hipStream_t st) {
 }
 
 // ------------------------------------------------------------------------------------------------
-// Cholesky factor and its inverse in one kernel (l = 16 NE <= 128), fp64.  G = C C^T; out = C^-1 as a dense fp32 l x l
-// matrix (zeros above the diagonal) that the MFMA GEMM then applies to the basis.
-// 256 threads form a 16 x 16 grid; thread (ty, tx) keeps the elements (i, k) with i = ty, k = tx (mod 16) in registers.
-// Gauss-Jordan in place: at step j the columns k > j still hold the matrix A being factored and the columns k < j the
-// inverse T being built, and one vector serves both updates: r_k = a(k,j) / c_jj for k > j (which is c_kj, by symmetry),
-// t(j,k) / c_jj for k < j, 1 / c_jj for k = j; then element (i,k), i > j, loses c_ij r_k.  The vector goes through LDS
-// (double-buffered, one barrier per step).  A non-positive pivot (dependent direction) zeroes that row of C^-1, which
-// removes the direction.
-// The kernel is a serial chain of l steps, so what counts is the length of a step: four wavefronts that read 2 NE numbers
-// each per step, against sixteen with separate matrices for A and T that read 3 l / 32 each (l = 128: 101 -> 54 us,
-// l = 96: 69 -> 35 us, l = 64: 45 -> 20 us, l = 32: 20.5 -> 9 us, one problem).
-template <int NE>
-__global__ __launch_bounds__(256) void cholinv_kernel(const double* __restrict__ Gall, float* __restrict__ Cinvall) {
-  constexpr int l = 16 * NE;
-  __shared__ double s_vec[2][l];
-  __shared__ double s_diag[l];
-  const int tid = threadIdx.x, ty = tid >> 4, tx = tid & 15;
-  const double* G = Gall + (size_t)blockIdx.x * l * l;
-  __builtin_amdgcn_s_setprio(3);               // a serial chain that shares the compute unit with streaming kernels
-  double a[NE][NE];
-#pragma unroll
-  for (int e = 0; e < NE; ++e)
-#pragma unroll
-    for (int f = 0; f < NE; ++f) a[e][f] = G[(size_t)(ty + 16 * e) * l + tx + 16 * f];
-  // A pivot is compared with the row's own squared norm, not with the largest one (see cholesky_kernel).
-  if (ty == tx) {
-#pragma unroll
-    for (int e = 0; e < NE; ++e) s_diag[ty + 16 * e] = a[e][e];
-  }
-  for_each_block<NE>([&](auto block) {
-    constexpr int jb = decltype(block)::value;
-#pragma nounroll
-    for (int jt = 0; jt < 16; ++jt) {
-      const int j = 16 * jb + jt;
-      double* vec = s_vec[j & 1];
-      if (tx == jt) {                                    // column j from the diagonal down
-#pragma unroll
-        for (int e = jb; e < NE; ++e)
-          if (e > jb || ty >= jt) vec[ty + 16 * e] = a[e][jb];
-      }
-      if (ty == jt) {                                    // row j of the inverse
-#pragma unroll
-        for (int f = 0; f <= jb; ++f)
-          if (f < jb || tx < jt) vec[tx + 16 * f] = a[jb][f];
-      }
-      __syncthreads();
-      const double piv = vec[j];
-      double ci[NE], rk[NE];
-#pragma unroll
-      for (int e = 0; e < NE; ++e) { rk[e] = vec[tx + 16 * e]; if (e >= jb) ci[e] = vec[ty + 16 * e]; }
-      const double inv = piv > 1e-12 * s_diag[j] ? rsqrt64(piv) : 0.0;
-#pragma unroll
-      for (int e = 0; e < NE; ++e) rk[e] *= inv;
-      if (tx == jt) {                                    // column j changes sides: it starts as column j of the identity
-        rk[jb] = inv;
-#pragma unroll
-        for (int e = jb; e < NE; ++e) a[e][jb] = 0.0;
-      }
-#pragma unroll
-      for (int e = jb; e < NE; ++e) {
-        ci[e] = e > jb || ty > jt ? ci[e] * inv : 0.0;
-#pragma unroll
-        for (int f = 0; f <= e; ++f) a[e][f] = fma(-ci[e], rk[f], a[e][f]);   // blocks above the diagonal are never read
-      }
-      if (ty == jt) {
-#pragma unroll
-        for (int f = 0; f <= jb; ++f) a[jb][f] = rk[f];
-      }
-    }
-  });
-  float* out = Cinvall + (size_t)blockIdx.x * l * l;
-#pragma unroll
-  for (int e = 0; e < NE; ++e)
-#pragma unroll
-    for (int f = 0; f < NE; ++f) {
-      const int i = ty + 16 * e, k = tx + 16 * f;
-      out[(size_t)i * l + k] = k <= i ? (float)a[e][f] : 0.0f;
-    }
-}
-
-bool cholinv_supported(int l) { return l % 32 == 0 && l >= 32 && l <= 128; }
-
-int launch_cholinv(const double* G, int l, float* Cinv, int batch, hipStream_t st) {
-  prof::Scope ps(prof::CHOLESKY, st, (double)l * l * 12.0 * batch);
-  switch (l / 32) {
-    case 1: hipLaunchKernelGGL(cholinv_kernel<2>, dim3(batch), dim3(256), 0, st, G, Cinv); break;
-    case 2: hipLaunchKernelGGL(cholinv_kernel<4>, dim3(batch), dim3(256), 0, st, G, Cinv); break;
-    case 3: hipLaunchKernelGGL(cholinv_kernel<6>, dim3(batch), dim3(256), 0, st, G, Cinv); break;
-    case 4: hipLaunchKernelGGL(cholinv_kernel<8>, dim3(batch), dim3(256), 0, st, G, Cinv); break;
-    default: return LQ_ERR_ARG;
-  }
-  LQ_HIP_TRY(hipGetLastError());
-  return LQ_OK;
-}
-
-// ------------------------------------------------------------------------------------------------
 // Forward substitution X <- C^-1 X, one lane per column of X, the column kept in LDS.
 __global__ __launch_bounds__(64) void trsm_kernel(const double* __restrict__ Call, int l, float* __restrict__ Xall,
                                                   int64_t m, int64_t ldx, size_t strideX) {

@@ -33,6 +33,33 @@ def test_orthonormalize_ragged(l, extra):
     assert np.max(np.abs(c @ q - x)) < 2e-4 * np.max(np.abs(x)) * np.sqrt(l)
 
 
+@pytest.mark.parametrize("l", [32, 64, 96, 128])
+@pytest.mark.parametrize("at", [1, 15, 16, 31])
+def test_orthonormalize_dependent_rows(l, at):
+    """Rows that are a multiple of an earlier one (a power of two, so exactly) or zero, at the edges of the 16-row blocks of
+    the factorisation and in the last row: they come out zero and the others orthonormal.  The pivot that remains of such a
+    row is rounding, l * 2^-53 of its squared norm, against the threshold of 1e-12."""
+    import torch
+    L = load()
+    m = ld = 4 * l
+    rng = np.random.default_rng(l + at)
+    x = rng.standard_normal((l, m)).astype(np.float32)
+    x[at], x[l - 1] = 4 * x[0], 0
+    if l > 32:
+        x[32 + at] = 0.5 * x[2]
+    dependent = [at, l - 1] + ([32 + at] if l > 32 else [])
+    xt = torch.from_numpy(x).cuda()
+    scratch = torch.full((17 * l * l,), float("nan"), dtype=torch.float64, device="cuda")
+    alt = torch.full((l, ld), float("nan"), dtype=torch.float32, device="cuda")
+    assert L.lq_test_orthonormalize(xt.data_ptr(), l, m, ld, scratch.data_ptr(), alt.data_ptr(), None) == 0
+    torch.cuda.synchronize()
+    q = xt.cpu().numpy().astype(np.float64)
+    assert np.all(q[dependent] == 0)
+    want = np.eye(l)
+    want[dependent, dependent] = 0
+    assert np.max(np.abs(q @ q.T - want)) < 2e-4
+
+
 @pytest.mark.parametrize("l,m,batch,chunks", [(32, 100, 3, 16), (64, 1000, 5, 1), (96, 333, 12, 16), (128, 2049, 2, 128),
                                                (160, 500, 3, 7)])
 def test_gram_of_a_batch(l, m, batch, chunks):
