@@ -24,11 +24,7 @@ typedef double doublex4 __attribute__((ext_vector_type(4)));
 // positive (dependent direction) zeroes that row of C^-1, which removes the direction.
 
 template <int J>
-__device__ __forceinline__ double row_broadcast(double x) {      // the value of lane J of each 16
-  const int lo = __builtin_amdgcn_mov_dpp(__double2loint(x), 0x150 + J, 0xf, 0xf, false);     // row_newbcast
-  const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(x), 0x150 + J, 0xf, 0xf, false);
-  return __hiloint2double(hi, lo);
-}
+__device__ __forceinline__ double row_broadcast(double x) { return dpp_move<0x150 + J>(x); }     // row_newbcast: lane J of each 16
 
 // x_m += f * (x_m of lane J of each 16), m < 5: the broadcast is part of the fp64 instruction, which the compiler, having only
 // the 32-bit move as a builtin, spells as two moves each.  The wait states are those between the instruction that wrote a
@@ -52,10 +48,7 @@ __device__ __forceinline__ void invert_block(double (&a)[16], double thr, int i)
   for_each_block<16>([&](auto step) {
     constexpr int j = decltype(step)::value;
     if (i == j) pivot = a[j];
-    const double x = a[j], seed = __builtin_amdgcn_rcp(x);
-    const double e = fma(-x, seed, 1.0);                       // 1/x = seed (1 + e + e^2 + ..), e of 2^-22
-    const double inverse = fma(seed, fma(e, e, e), seed);
-    const double r = row_broadcast<j>(x > thr ? inverse : 0.0);
+    const double x = a[j], r = row_broadcast<j>(x > thr ? rcp64(x) : 0.0);
     const double f = i > j ? -x * r : 0.0;
     for_each_block<3>([&](auto part) {                         // the next pivot's column first
       constexpr int k = j + 1 + 5 * decltype(part)::value;

@@ -31,8 +31,8 @@ __device__ inline void circle_pair(int a, int round, int n, int& p, int& q) {
 
 template <int CTRL>
 __device__ __forceinline__ double dpp_move(double x) {
-  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(x), CTRL, 0xf, 0xf, false);
-  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(x), CTRL, 0xf, 0xf, false);
+  const int lo = __builtin_amdgcn_mov_dpp(__double2loint(x), CTRL, 0xf, 0xf, false);     // every lane has a source: no old value
+  const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(x), CTRL, 0xf, 0xf, false);
   return __hiloint2double(hi, lo);
 }
 constexpr int XOR1 = 0xB1, XOR2 = 0x4E, XOR7 = 0x141, XOR15 = 0x140;   // quad_perm, quad_perm, row_half_mirror, row_mirror
@@ -50,11 +50,10 @@ __device__ __forceinline__ double wave_sum(double x) {
   return (lane_value(x, 0) + lane_value(x, 16)) + (lane_value(x, 32) + lane_value(x, 48));
 }
 
-// 1/x and 1/sqrt(x) for normal x: the hardware seeds (about 23 bits) and two Newton steps.
+// 1/x for normal x: the hardware seed (about 23 bits) times 1 + e + e^2, e = 1 - x seed.  1/sqrt(x): its seed and two Newton steps.
 __device__ __forceinline__ double rcp64(double x) {
-  double r = __builtin_amdgcn_rcp(x);
-  r = fma(r, fma(-x, r, 1.0), r);
-  return fma(r, fma(-x, r, 1.0), r);
+  const double r = __builtin_amdgcn_rcp(x), e = fma(-x, r, 1.0);
+  return fma(r, fma(e, e, e), r);
 }
 __device__ __forceinline__ double rsqrt64(double x) {
   double r = __builtin_amdgcn_rsq(x);

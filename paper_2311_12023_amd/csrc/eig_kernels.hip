@@ -163,8 +163,8 @@ __device__ void jacobi_onesided(const double* __restrict__ G, double mscale, flo
 }
 
 // ---- tridiagonal route ---------------------------------------------------------------------------------
-// Householder tridiagonalisation, eigenvalues by multisection on Sturm counts, eigenvectors by twisted factorisation,
-// back-transformation; all in fp64.  256 threads form a 16 x 16 grid, thread (ty, tx) keeps the elements (i, k) with
+// Householder tridiagonalisation, eigenvalues by Sturm counts (multisection until each is alone, then secant steps inside
+// the counts' brackets), eigenvectors by twisted factorisation, back-transformation; all in fp64.  256 threads form a 16 x 16 grid, thread (ty, tx) keeps the elements (i, k) with
 // i = ty, k = tx (mod 16) of the matrix in registers.  Every phase is a serial chain of l steps, so what bounds the
 // kernel is latency, and the layout is chosen for short steps: four wavefronts (one per SIMD; with 16 the redundant
 // per-wavefront work and the LDS reads of the vectors quadruple), two barriers per column, and scalar parts that every
@@ -173,28 +173,65 @@ __device__ void jacobi_onesided(const double* __restrict__ G, double mscale, flo
 // that 1e-6 could be missed; in a sweep the Ritz values of the quantization noise of 8-bit configurations, 1e-8 lambda_1
 // themselves, are such a cluster) the rows are orthonormalised together at the end, and where they have come out too
 // dependent for that (repeated eigenvalues, a singular matrix) the problem is solved by one-sided Jacobi, in the same launch.
-// Measured on a weight matrix's spectrum in a random basis (one problem, us): l = 32 98 -> 45, l = 64 297 -> 100,
-// l = 96 687 -> 192, l = 128 1491 -> 273 against one-sided Jacobi with 8 l threads, whose six to nine sweeps of l - 1
-// rounds are bound by LDS bandwidth (every round reads and writes X and V); Rayleigh quotients come out 10 to 70 times
-// closer, because the tridiagonal route keeps G in fp64.
+// Measured on a weight matrix's spectrum in a random basis (one problem, us): l = 32 98 -> 45 -> 35, l = 64 297 -> 99 -> 79,
+// l = 96 687 -> 193 -> 138, l = 128 1491 -> 275 -> 210: one-sided Jacobi with 8 l threads, whose six to nine sweeps of l - 1
+// rounds are bound by LDS bandwidth (every round reads and writes X and V); this route with a chain of two wavefront sums and
+// roots per column before anything else, 34 rounds of trisection and reciprocal pivots in memory behind branches; and as it
+// is.  Rayleigh quotients come out 10 to 70 times closer than Jacobi's, because G stays in fp64.  At l = 128 the phases take 275,
+// 61, 47 and 94 thousand cycles (tridiagonal form, eigenvalues, vectors, back-transformation): a column is 1400 cycles of
+// latency, by what it takes at l = 32, and its share of 3 l^2 fp64 operations.
+//
+// Eigenvalues below x of the tridiagonal matrix with {d_i, e_{i-1}^2} in de: the sign changes of p_i = (d_i - x) p_{i-1} -
+// e_{i-1}^2 p_{i-2}, which needs no division; sign bits are collected 32 at a time.  The pair is brought back to unit size every
+// 16 steps: with a norm of at most 2 l (a Gram matrix whose diagonal is below 2) and e^2 kept above 1e-36 of its square, a
+// step makes it no more than 2^17 larger and two steps no more than 1e-36 smaller.  p_l = f 2^e.
+template <int l>
+__device__ __forceinline__ int sturm(const double2* de, double x, double& f, int& e) {
+  double pa = 0.0, pb = 1.0;
+  int count = 0;
+  unsigned last = 0;
+  e = 0;
+  for (int i0 = 0; i0 < l; i0 += 32) {
+    unsigned bits = 0;
+#pragma unroll
+    for (int i1 = 0; i1 < 32; i1 += 16) {
+#pragma unroll
+      for (int i2 = 0; i2 < 16; ++i2) {
+        const double2 v = de[i0 + i1 + i2];
+        const double pn = fma(v.x - x, pb, -v.y * pa);
+        bits = __builtin_amdgcn_alignbit(bits, (unsigned)__double2hiint(pn), 31);
+        pa = pb; pb = pn;
+      }
+      const int ex = __builtin_amdgcn_frexp_exp(fmax(fabs(pa), fabs(pb)));
+      pa = ldexp(pa, -ex); pb = ldexp(pb, -ex);
+      e += ex;
+    }
+    count += __popc(bits ^ ((bits >> 1) | (last << 31)));
+    last = bits & 1u;
+  }
+  f = pb;
+  return count;
+}
+
 template <int NE>
 __global__ __launch_bounds__(EIG_THREADS) void sym_eig_kernel(const double* __restrict__ Gall, double* __restrict__ work,
                                                               float* __restrict__ Utall, double* __restrict__ lamall) {
-  constexpr int l = 16 * NE, NP = NE <= 2 ? 2 : (NE <= 4 ? 4 : 8);
-  constexpr int TPE = l > 64 ? 2 : (l > 32 ? 4 : 8);        // threads per eigenvalue in the multisection
-  constexpr int ROUNDS = TPE == 2 ? 34 : (TPE == 4 ? 23 : 17);   // (TPE + 1)^ROUNDS > 2^53
+  constexpr int l = 16 * NE;
   extern __shared__ __attribute__((aligned(16))) double lds[];   // reflectors [l][l]; the Jacobi route's X and V
   double* Vr = lds;
-  __shared__ double s_col[l], s_p[l], s_h[l], s_e[l], s_lam[l], s_inv[l];
+  __shared__ double s_col[l], s_next[l], s_p[l], s_h[l], s_e[l], s_lam[l], s_inv[l];
   __shared__ double2 s_de[l + 1];                            // {d_i, e_{i-1}^2}
   __shared__ double s_best[2][128], s_sum[2][128];
   __shared__ int s_at[2][128], s_k[128];
   __shared__ float s_n2[128], s_vscale[128];
   __shared__ int s_rank[128], s_flags[1];
-  __shared__ double s_wmax[4];
+  __shared__ double s_wmax[4], s_x[EIG_THREADS], s_f[EIG_THREADS];
+  __shared__ int s_cnt[EIG_THREADS], s_ex[EIG_THREADS];
   const int z = blockIdx.x, tid = threadIdx.x, lane = tid & 63, ty = tid >> 4, tx = tid & 15;
   const double* G = Gall + (size_t)z * l * l;
-  double* Sp = work + (size_t)z * 2 * l * l;
+  double* Sp;                                                // reciprocal pivots: in LDS where all three arrays fit
+  if constexpr (NE <= 4) Sp = lds + l * l;
+  else Sp = work + (size_t)z * 2 * l * l;
   double* Sm = Sp + l * l;
   float* Ut = Utall + (size_t)z * l * l;
   double* lam = lamall + (size_t)z * l;
@@ -223,70 +260,113 @@ __global__ __launch_bounds__(EIG_THREADS) void sym_eig_kernel(const double* __re
 #pragma unroll
     for (int f = 0; f < NE; ++f) a[e][f] *= mscale;
 
-  // Reduction of column j: x = A[j+1.., j], v = x - beta e_1, A <- H A H with H = I - h v v^T, as A -= v w^T + w v^T
+  // Reduction of column j: x = A[j+1.., j], v = x - beta e_1, A <- H A H with H = I - h v v^T, as A -= v w^T + w v^T with
+  // p = h A v, w = p - (h/2) (p^T v) v.  A step is two exchanges through LDS (x, p) and two short chains of dependent
+  // operations, the norm of x with its roots and reciprocals and then p^T v; every 16 lanes hold whole vectors (vk, wk, p), so
+  // sums take four cross-lane moves and no wavefront waits for another.  What else there is to do is dealt out between the
+  // links of the first chain: the last reflector's update, of which only the tile column that holds column j + 1 was done
+  // before that column went to LDS, and A x, which does not need beta (A v = A x - beta A e_1, and column j + 1 goes to LDS
+  // with column j).
+  double vi[NE], vk[NE], wi[NE], wk[NE];       // the last reflector, not yet applied to the tile columns past the current one
+#pragma unroll
+  for (int e = 0; e < NE; ++e) vi[e] = vk[e] = wi[e] = wk[e] = 0.0;
+  if (tx < 2) {
+#pragma unroll
+    for (int e = 0; e < NE; ++e) (tx ? s_next : s_col)[ty + 16 * e] = a[e][0];
+  }
   for_each_block<NE>([&](auto block) {
-    constexpr int jb = decltype(block)::value;
+    constexpr int jb = decltype(block)::value, LEFT = NE - jb, NP = LEFT <= 2 ? 2 : (LEFT <= 4 ? 4 : 8);
+    const int re = row_sum_index<NP>(tx), mine = ty + 16 * (jb + (re < LEFT ? re : 0));      // the row whose sum this lane ends up with
+#pragma nounroll
     for (int jt = 0; jt < 16; ++jt) {
       const int j = 16 * jb + jt;
-      if (tx == jt) {
-#pragma unroll
-        for (int e = jb; e < NE; ++e) s_col[ty + 16 * e] = a[e][jb];
-      }
       __syncthreads();
-      double x0 = lane > j && lane < l ? s_col[lane < l ? lane : 0] : 0.0;
-      double x1 = 0.0;
-      if constexpr (l > 64) x1 = lane + 64 > j && lane + 64 < l ? s_col[lane + 64 < l ? lane + 64 : 0] : 0.0;
-      const double alpha = j + 1 < l ? s_col[j + 1 < l ? j + 1 : j] : 0.0;
-      const double s2 = wave_sum((lane == j + 1 ? 0.0 : x0 * x0) + (lane + 64 == j + 1 ? 0.0 : x1 * x1));
+      double xi[NE], xk[NE], part[NP];
+#pragma unroll
+      for (int e = jb; e < NE; ++e) { xk[e] = s_col[tx + 16 * e]; xi[e] = s_col[ty + 16 * e]; }
+      const double alpha = s_col[j + 1 < l ? j + 1 : j], next = s_next[mine];
+      if (tid < l && tid != j + 1) Vr[j * l + tid] = tid > j ? s_col[tid] : 0.0;
+      if (tid == 0) s_de[j].x = s_col[j];
+      xk[jb] = tx > jt ? xk[jb] : 0.0;
+      auto piece = [&](auto row) __attribute__((always_inline)) {   // row e of the pending update and of A x
+        constexpr int e = jb + decltype(row)::value;
+        if constexpr (e - jb < NP) part[e - jb] = 0.0;
+        if constexpr (e < NE) {
+          part[e - jb] = a[e][jb] * xk[jb];
+#pragma unroll
+          for (int f = jb + 1; f < NE; ++f) {
+            a[e][f] = fma(-vi[e], wk[f], fma(-wi[e], vk[f], a[e][f]));
+            part[e - jb] = fma(a[e][f], xk[f], part[e - jb]);
+          }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      };
+#define LQ_PIECE(E) piece(std::integral_constant<int, E>{})
+      __builtin_amdgcn_sched_barrier(0);
+      double s2 = 0.0;                         // squares of x past its first element
+#pragma unroll
+      for (int e = jb; e < NE; ++e) s2 = fma(e <= jb + 1 && tx + 16 * e == j + 1 ? 0.0 : xk[e], xk[e], s2);
+      LQ_PIECE(0);
+      s2 += dpp_move<XOR1>(s2);
+      LQ_PIECE(1);
+      s2 += dpp_move<XOR2>(s2);
+      LQ_PIECE(2);
+      s2 += dpp_move<XOR7>(s2);
+      LQ_PIECE(3);
+      s2 += dpp_move<XOR15>(s2);
+      LQ_PIECE(4);
       const double n2 = fma(alpha, alpha, s2);
       const bool reflect = s2 > 1e-280;
-      const double norm = reflect ? n2 * rsqrt64(n2) : 0.0;
+      LQ_PIECE(5);
+      const double root = n2 * rsqrt64(n2);
+      LQ_PIECE(6);
+      const double norm = reflect ? root : 0.0;
       const double beta = reflect ? -copysign(norm, alpha) : alpha;
       const double h = reflect ? rcp64(fma(fabs(alpha), norm, n2)) : 0.0;     // 2 / v^T v
       const double v1 = reflect ? alpha - beta : 0.0;
-      if (lane == j + 1) x0 = v1;
-      if (lane + 64 == j + 1) x1 = v1;
-      double vi[NE], vk[NE];
+      LQ_PIECE(7);
+#undef LQ_PIECE
+      const double total = row_sum_dealt<NP>(part, tx);
+      if (re < LEFT) s_p[mine] = mine > j ? fma(-beta, next, total) * h : 0.0;
+      if (tid == 0) { s_h[j] = h; s_e[j] = beta; if (j + 1 < l) Vr[j * l + j + 1] = v1; }
 #pragma unroll
       for (int e = jb; e < NE; ++e) {
-        const int i = ty + 16 * e, k = tx + 16 * e;
-        vi[e] = s_col[i]; vk[e] = s_col[k];
-        if (e <= jb + 1) {
-          vi[e] = i > j + 1 ? vi[e] : (i == j + 1 ? v1 : 0.0);
-          vk[e] = k > j + 1 ? vk[e] : (k == j + 1 ? v1 : 0.0);
-        }
-      }
-      if (tid < l) Vr[j * l + tid] = tid > j + 1 ? s_col[tid] : (tid == j + 1 ? v1 : 0.0);
-      if (tid == 0) { s_h[j] = h; s_e[j] = beta; s_de[j].x = s_col[j]; }
-      double part[NP];
-#pragma unroll
-      for (int e = 0; e < NP; ++e) {
-        part[e] = 0.0;
-        if (e >= jb && e < NE) {
-#pragma unroll
-          for (int f = jb; f < NE; ++f) part[e] = fma(a[e][f], vk[f], part[e]);
-        }
-      }
-      const double total = row_sum_dealt<NP>(part, tx);
-      const int re = row_sum_index<NP>(tx);
-      if (re < NE) {
-        const int i = ty + 16 * re;
-        s_p[i] = i > j ? total * h : 0.0;
+        vi[e] = e <= jb + 1 && ty + 16 * e == j + 1 ? v1 : (e > jb || ty > jt ? xi[e] : 0.0);
+        vk[e] = e <= jb + 1 && tx + 16 * e == j + 1 ? v1 : xk[e];
       }
       __syncthreads();
-      double pv = x0 * (lane < l ? s_p[lane < l ? lane : 0] : 0.0);
-      if constexpr (l > 64) pv = fma(x1, lane + 64 < l ? s_p[lane + 64 < l ? lane + 64 : 0] : 0.0, pv);
-      const double K = 0.5 * h * wave_sum(pv);
-      double wi[NE], wk[NE];
+      double pv = 0.0;
 #pragma unroll
-      for (int e = jb; e < NE; ++e) {
-        wi[e] = fma(-K, vi[e], s_p[ty + 16 * e]);
-        wk[e] = fma(-K, vk[e], s_p[tx + 16 * e]);
+      for (int e = jb; e < NE; ++e) { wk[e] = s_p[tx + 16 * e]; wi[e] = s_p[ty + 16 * e]; pv = fma(vk[e], wk[e], pv); }
+      pv += dpp_move<XOR1>(pv);
+      pv += dpp_move<XOR2>(pv);
+      pv += dpp_move<XOR7>(pv);
+      pv += dpp_move<XOR15>(pv);
+      const double K = 0.5 * h * pv;
+#pragma unroll
+      for (int e = jb; e < NE; ++e) { wi[e] = fma(-K, vi[e], wi[e]); wk[e] = fma(-K, vk[e], wk[e]); }
+      // the tile column that holds column j + 1 (and, at its edge, j + 2)
+      if (jt < 15) {
+#pragma unroll
+        for (int e = jb; e < NE; ++e) a[e][jb] = fma(-vi[e], wk[jb], fma(-wi[e], vk[jb], a[e][jb]));
+        if (tx == jt + 1 || tx == jt + 2) {
+#pragma unroll
+          for (int e = jb; e < NE; ++e) (tx == jt + 1 ? s_col : s_next)[ty + 16 * e] = a[e][jb];
+        }
+        if constexpr (jb + 1 < NE) {
+          if (jt == 14 && tx == 0) {           // not yet updated there: the piece of the next step does that
+#pragma unroll
+            for (int e = jb; e < NE; ++e)
+              s_next[ty + 16 * e] = fma(-vi[e], wk[jb + 1], fma(-wi[e], vk[jb + 1], a[e][jb + 1]));
+          }
+        }
+      } else if constexpr (jb + 1 < NE) {
+#pragma unroll
+        for (int e = jb + 1; e < NE; ++e) {
+          a[e][jb + 1] = fma(-vi[e], wk[jb + 1], fma(-wi[e], vk[jb + 1], a[e][jb + 1]));
+          if (tx < 2) (tx ? s_next : s_col)[ty + 16 * e] = a[e][jb + 1];
+        }
       }
-#pragma unroll
-      for (int e = jb; e < NE; ++e)
-#pragma unroll
-        for (int f = jb; f < NE; ++f) a[e][f] = fma(-vi[e], wk[f], fma(-wi[e], vk[f], a[e][f]));
     }
   });
   __syncthreads();
@@ -312,42 +392,88 @@ __global__ __launch_bounds__(EIG_THREADS) void sym_eig_kernel(const double* __re
   if (tid == 0) { s_de[l].x = 0.0; s_de[l].y = 0.0; }
   __syncthreads();
 
-  // Eigenvalue g (ascending): TPE threads count the eigenvalues below the inner points of its interval.  The count is the
-  // number of sign changes of p_i = (d_i - x) p_{i-1} - e_{i-1}^2 p_{i-2}, which needs no division; sign bits are
-  // collected 32 at a time and the pair is brought back to unit size every eight steps.
-  {
+  if constexpr (NE <= 2) {
+    // Eigenvalue g (ascending): eight threads count the eigenvalues below the inner points of its interval.  (Sequences this
+    // short cost less than the bookkeeping of fewer rounds: l = 32 14 against 22 thousand cycles, l = 64 36 against 34.)
+    constexpr int TPE = 8;
     const int g = tid / TPE, sub = tid % TPE;
-    if (g < l) {
-      for (int round = 0; round < ROUNDS; ++round) {
-        const double x = fma(hi - lo, (sub + 1) * (1.0 / (TPE + 1)), lo);
-        double pa = 0.0, pb = 1.0;
-        int count = 0;
-        unsigned last = 0;
-        for (int i0 = 0; i0 < l; i0 += 32) {
-          unsigned bits = 0;
-#pragma unroll
-          for (int i1 = 0; i1 < 32; i1 += 8) {
-#pragma unroll
-            for (int i2 = 0; i2 < 8; ++i2) {
-              const double2 de = s_de[i0 + i1 + i2];
-              const double pn = fma(de.x - x, pb, -de.y * pa);
-              bits = __builtin_amdgcn_alignbit(bits, (unsigned)__double2hiint(pn), 31);
-              pa = pb; pb = pn;
-            }
-            const int ex = __builtin_amdgcn_frexp_exp(fmax(fabs(pa), fabs(pb)));
-            pa = ldexp(pa, -ex); pb = ldexp(pb, -ex);
-          }
-          count += __popc(bits ^ ((bits >> 1) | (last << 31)));
-          last = bits & 1u;
-        }
-        const bool below = count <= g;                   // the eigenvalue is at x or above
-        double nlo = below ? x : lo, nhi = below ? hi : x;
-        nlo = fmax(nlo, dpp_move<XOR1>(nlo)); nhi = fmin(nhi, dpp_move<XOR1>(nhi));
-        if constexpr (TPE >= 4) { nlo = fmax(nlo, dpp_move<XOR2>(nlo)); nhi = fmin(nhi, dpp_move<XOR2>(nhi)); }
-        if constexpr (TPE >= 8) { nlo = fmax(nlo, dpp_move<XOR7>(nlo)); nhi = fmin(nhi, dpp_move<XOR7>(nhi)); }
-        lo = nlo; hi = nhi;
+    for (int round = 0; round < 17; ++round) {               // 9^17 > 2^53
+      const double x = fma(hi - lo, (sub + 1) * (1.0 / (TPE + 1)), lo);
+      double f; int e;
+      const bool over = sturm<l>(s_de, x, f, e) <= g;        // the eigenvalue is at x or above
+      double nlo = over ? x : lo, nhi = over ? hi : x;
+      nlo = fmax(nlo, dpp_move<XOR1>(nlo)); nhi = fmin(nhi, dpp_move<XOR1>(nhi));
+      nlo = fmax(nlo, dpp_move<XOR2>(nlo)); nhi = fmin(nhi, dpp_move<XOR2>(nhi));
+      lo = fmax(nlo, dpp_move<XOR7>(nlo)); hi = fmin(nhi, dpp_move<XOR7>(nhi));
+    }
+    if (sub == 0) s_lam[g] = 0.5 * (lo + hi);
+  } else {
+    // Eigenvalue g (ascending) lies in [lo, hi), with clo <= g eigenvalues below lo and chi > g below hi.
+    double xlo = lo, xhi = hi, flo = 0.0, fhi = 0.0;        // the sequence's last value at both ends, f 2^e (0: not known)
+    int elo = 0, ehi = 0, clo = 0, chi = l;
+    // First every thread takes a point of its own: the eigenvalues that still share an interval share their threads' points,
+    // so that a round cuts it 256 / l times as often as it holds eigenvalues.  (A pair of a point and its count is true for any
+    // eigenvalue: what a thread reads of another group, should rounding make counts disagree, narrows no interval wrongly.)
+    constexpr int TPE = EIG_THREADS / l;
+    for (int round = 0; round < 3; ++round) {
+      const int g = tid / TPE;
+      if (g < l) {
+        const int t = tid - clo * TPE + 1, m = (chi - clo) * TPE + 1;
+        const double x = fma(xhi - xlo, (double)t / (double)m, xlo);
+        double f; int e;
+        s_cnt[tid] = sturm<l>(s_de, x, f, e);
+        s_x[tid] = x; s_f[tid] = f; s_ex[tid] = e;
       }
-      if (sub == 0) s_lam[g] = 0.5 * (lo + hi);
+      __syncthreads();
+      if (g < l) {
+        int below = clo * TPE - 1, above = chi * TPE;        // points of the group at or below eigenvalue g, and above it
+        while (above - below > 1) {
+          const int mid = (below + above) >> 1;
+          if (s_cnt[mid] <= g) below = mid; else above = mid;
+        }
+        const bool up = below >= clo * TPE && s_x[below < 0 ? 0 : below] >= xlo, dn = above < chi * TPE && s_x[above < l * TPE ? above : 0] <= xhi;
+        if (up) { xlo = s_x[below]; flo = s_f[below]; elo = s_ex[below]; clo = s_cnt[below]; }
+        if (dn) { xhi = s_x[above]; fhi = s_f[above]; ehi = s_ex[above]; chi = s_cnt[above]; }
+      }
+      __syncthreads();
+    }
+    if (tid % TPE == 0 && tid / TPE < l) {                   // handed to pairs of threads
+      const int g = tid / TPE;
+      s_x[2 * g] = xlo; s_f[2 * g] = flo; s_ex[2 * g] = elo; s_cnt[2 * g] = clo;
+      s_x[2 * g + 1] = xhi; s_f[2 * g + 1] = fhi; s_ex[2 * g + 1] = ehi; s_cnt[2 * g + 1] = chi;
+    }
+    __syncthreads();
+    // Then two threads per eigenvalue.  Once it is alone in its interval the two points stand q of the width to either side of
+    // the secant's zero; the secant's error shrinks with the square of the width, so q -> 2 q^2 where the eigenvalue was
+    // between them, and thirds after a miss.
+    const int g = tid >> 1, sub = tid & 1;
+    if (g < l) {
+      xlo = s_x[2 * g]; flo = s_f[2 * g]; elo = s_ex[2 * g]; clo = s_cnt[2 * g];
+      xhi = s_x[2 * g + 1]; fhi = s_f[2 * g + 1]; ehi = s_ex[2 * g + 1]; chi = s_cnt[2 * g + 1];
+      const double tol = 2.3e-16 * bound;
+      double q = 0.125;
+      bool missed = false;
+      for (int round = 0; round < 64 && __any(xhi - xlo > tol); ++round) {
+        const double ratio = ldexp(flo * rcp64(fhi), elo - ehi), at = ratio * rcp64(ratio - 1.0);
+        const bool secant = !missed && chi - clo == 1 && fhi != 0.0 && at >= 0.0 && at <= 1.0;     // false for NaN
+        const double pa = secant ? fmax(at - q, 0.5 * at) : 1.0 / 3, pb = secant ? fmin(at + q, 0.5 + 0.5 * at) : 2.0 / 3;
+        const double x = fma(xhi - xlo, sub ? pb : pa, xlo);
+        double f; int e;
+        const int c = sturm<l>(s_de, x, f, e);
+        const double x2 = dpp_move<XOR1>(x), f2 = dpp_move<XOR1>(f);
+        const int e2 = __builtin_amdgcn_mov_dpp(e, XOR1, 0xf, 0xf, false), c2 = __builtin_amdgcn_mov_dpp(c, XOR1, 0xf, 0xf, false);
+        const double xa = sub ? x2 : x, fa = sub ? f2 : f, xb = sub ? x : x2, fb = sub ? f : f2;
+        const int ea = sub ? e2 : e, ca = sub ? c2 : c, eb = sub ? e : e2, cb = sub ? c : c2;
+        const bool over_a = ca <= g, over_b = cb <= g;       // the eigenvalue is at the point or above it
+        const bool between = over_a != over_b;
+        if (over_b) { xlo = xb; flo = fb; elo = eb; clo = cb; }
+        else if (over_a) { xlo = xa; flo = fa; elo = ea; clo = ca; }
+        if (!over_a) { xhi = xa; fhi = fa; ehi = ea; chi = ca; }
+        else if (!over_b) { xhi = xb; fhi = fb; ehi = eb; chi = cb; }
+        if (secant) q = between ? fmax(2.0 * q * q, 1e-9) : 0.125;
+        missed = secant && !between;
+      }
+      if (sub == 0) s_lam[g] = 0.5 * (xlo + xhi);
     }
   }
   __syncthreads();
@@ -359,30 +485,29 @@ __global__ __launch_bounds__(EIG_THREADS) void sym_eig_kernel(const double* __re
   // Eigenvectors of the tridiagonal matrix: T - lambda = L D+ L^T from the top (lower half of the threads) and U D- U^T
   // from the bottom (upper half), joined at the index k where |gamma_k| is smallest.  The reciprocal pivots go through
   // the scratch in memory, one eigenvector per lane.
-  const int half = tid >> 7, g = tid & 127;
+  const int half = __builtin_amdgcn_readfirstlane(tid >> 7), g = tid & 127;
   const bool has = g < l;
   const double lg = has ? s_lam[g] : 0.0;
   const double tiny = 1e-30 * bound;
   if (has) {
-    double* S = half == 0 ? Sp : Sm;
+    auto pivot = [&](double D) { return rcp64(fabs(D) > tiny ? D : copysign(tiny, D)); };
     double r = 0.0;
-#pragma unroll 4
-    for (int s = 0; s < l; ++s) {
-      const int i = half == 0 ? s : l - 1 - s;
-      double D = (s_de[i].x - lg) - (half == 0 ? s_de[i].y : s_de[i + 1].y) * r;
-      if (!(fabs(D) > tiny)) D = copysign(tiny, D);
-      r = rcp64(D);
-      S[i * l + g] = r;
+    if (half == 0) {
+#pragma unroll 16
+      for (int i = 0; i < l; ++i) Sp[i * l + g] = r = pivot(fma(-s_de[i].y, r, s_de[i].x - lg));
+    } else {
+#pragma unroll 16
+      for (int i = l - 1; i >= 0; --i) Sm[i * l + g] = r = pivot(fma(-s_de[i + 1].y, r, s_de[i].x - lg));
     }
   }
   __syncthreads();
   if (has) {
     double best = INFINITY;
     int at = half * (l / 2);
-#pragma unroll 8
+#pragma unroll 32
     for (int s = 0; s < l / 2; ++s) {
       const int i = half * (l / 2) + s;
-      const double up = i > 0 ? Sp[(i - 1) * l + g] : 0.0, dn = i + 1 < l ? Sm[(i + 1) * l + g] : 0.0;
+      const double up = i > 0 ? Sp[(i > 0 ? i - 1 : 0) * l + g] : 0.0, dn = i + 1 < l ? Sm[(i + 1 < l ? i + 1 : i) * l + g] : 0.0;
       const double ga = fabs((s_de[i].x - lg) - s_de[i].y * up - s_de[i + 1].y * dn);
       if (ga < best) { best = ga; at = i; }
     }
@@ -392,25 +517,34 @@ __global__ __launch_bounds__(EIG_THREADS) void sym_eig_kernel(const double* __re
   if (has) {
     const int k = s_best[1][g] < s_best[0][g] ? s_at[1][g] : s_at[0][g];
     double zz = 1.0, sum = half == 0 ? 1.0 : 0.0;
-    if (half == 0) {
-      s_k[g] = k;
-#pragma unroll 8
+    if (half == 0) {                           // every element is stored (those of the other half's vector as they were): no
+      s_k[g] = k;                              // branch keeps the loads from being issued ahead
+#pragma unroll 32
       for (int i = l - 1; i >= 0; --i) {
         const double r = Sp[i * l + g];
-        if (i < k) { zz *= -s_e[i] * r; sum = fma(zz, zz, sum); }
-        if (i <= k) Sp[i * l + g] = zz;
+        double m = -s_e[i] * r;
+        asm("" : "+v"(m));                     // computed whether needed or not
+        zz *= i < k ? m : 1.0;
+        const double t = i < k ? zz : 0.0;
+        sum = fma(t, t, sum);
+        Sp[i * l + g] = i <= k ? zz : r;
       }
     } else {
-#pragma unroll 8
+#pragma unroll 32
       for (int i = 1; i < l; ++i) {
         const double r = Sm[i * l + g];
-        if (i > k) { zz *= -s_e[i - 1] * r; sum = fma(zz, zz, sum); Sm[i * l + g] = zz; }
+        double m = -s_e[i - 1] * r;
+        asm("" : "+v"(m));
+        zz *= i > k ? m : 1.0;
+        const double t = i > k ? zz : 0.0;
+        sum = fma(t, t, sum);
+        Sm[i * l + g] = i > k ? zz : r;
       }
     }
     s_sum[half][g] = sum;
   }
   __syncthreads();
-  if (tid < l) s_inv[tid] = 1.0 / sqrt(s_sum[0][tid] + s_sum[1][tid]);
+  if (tid < l) s_inv[tid] = rsqrt64(s_sum[0][tid] + s_sum[1][tid]);
   __syncthreads();
 
   // Back-transformation: 8 lanes per eigenvector, l/32 eigenvectors per lane group, entries 16 m + 2 sub + {0, 1}
@@ -431,23 +565,39 @@ __global__ __launch_bounds__(EIG_THREADS) void sym_eig_kernel(const double* __re
   }
   for_each_block_down<NE>([&](auto block) {
     constexpr int jb = decltype(block)::value;
-    for (int jt = 15; jt >= 0; --jt) {
+#pragma nounroll
+    for (int jt = 15; jt >= 1; jt -= 2) {      // H_j, then H_{j-1}: their sums over a vector are taken together
       const int j = 16 * jb + jt;
-      const double h = s_h[j];
-      double2 w[NE];
+      const double h1 = s_h[j], h0 = s_h[j - 1];
+      double2 w1[NE], w0[NE];
 #pragma unroll
-      for (int m = jb; m < NE; ++m) w[m] = *reinterpret_cast<const double2*>(Vr + j * l + 16 * m + 2 * sub);
+      for (int m = jb; m < NE; ++m) {
+        w1[m] = *reinterpret_cast<const double2*>(Vr + j * l + 16 * m + 2 * sub);
+        w0[m] = *reinterpret_cast<const double2*>(Vr + (j - 1) * l + 16 * m + 2 * sub);
+      }
+      double d1[NV], d0[NV], c = 0.0;
+#pragma unroll
+      for (int m = jb; m < NE; ++m) c = fma(w1[m].x, w0[m].x, fma(w1[m].y, w0[m].y, c));
 #pragma unroll
       for (int v = 0; v < NV; ++v) {
-        double dot = 0.0;
+        d1[v] = d0[v] = 0.0;
 #pragma unroll
-        for (int m = jb; m < NE; ++m) dot = fma(w[m].x, u[v][m][0], fma(w[m].y, u[v][m][1], dot));
-        dot += dpp_move<XOR1>(dot);
-        dot += dpp_move<XOR2>(dot);
-        dot += dpp_move<XOR7>(dot);
-        dot *= -h;
+        for (int m = jb; m < NE; ++m) {
+          d1[v] = fma(w1[m].x, u[v][m][0], fma(w1[m].y, u[v][m][1], d1[v]));
+          d0[v] = fma(w0[m].x, u[v][m][0], fma(w0[m].y, u[v][m][1], d0[v]));
+        }
+      }
+      auto sum8 = [](double x) { x += dpp_move<XOR1>(x); x += dpp_move<XOR2>(x); return x + dpp_move<XOR7>(x); };
+      c = sum8(c);
 #pragma unroll
-        for (int m = jb; m < NE; ++m) { u[v][m][0] = fma(dot, w[m].x, u[v][m][0]); u[v][m][1] = fma(dot, w[m].y, u[v][m][1]); }
+      for (int v = 0; v < NV; ++v) {
+        d1[v] = -h1 * sum8(d1[v]);
+        d0[v] = -h0 * fma(d1[v], c, sum8(d0[v]));
+#pragma unroll
+        for (int m = jb; m < NE; ++m) {
+          u[v][m][0] = fma(d0[v], w0[m].x, fma(d1[v], w1[m].x, u[v][m][0]));
+          u[v][m][1] = fma(d0[v], w0[m].y, fma(d1[v], w1[m].y, u[v][m][1]));
+        }
       }
     }
   });
@@ -539,7 +689,7 @@ bool sym_eig_supported(int l) { return l % 32 == 0 && l >= 32 && l <= 128; }
 template <int NE>
 static int launch_eig(const double* G, double* work, float* Ut, double* lambda, int batch, hipStream_t st) {
   constexpr int l = 16 * NE;
-  const size_t reflectors = (size_t)l * l * sizeof(double), jacobi = (size_t)2 * l * (l + 4) * sizeof(float);
+  const size_t reflectors = (size_t)l * l * (NE <= 4 ? 3 : 1) * sizeof(double), jacobi = (size_t)2 * l * (l + 4) * sizeof(float);
   const size_t rows = (size_t)l * (l + 2) * sizeof(double);
   const size_t need = std::max(reflectors, std::max(jacobi, rows));
   static LdsLimit limit;

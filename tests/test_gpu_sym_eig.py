@@ -103,3 +103,31 @@ def test_problems_of_a_batch_are_independent(l):
         u1, lam1 = _solve(gs[i])
         assert np.array_equal(ut[i].cpu().numpy().astype(np.float64), u1), kinds[i]
         assert np.array_equal(lam[i].cpu().numpy(), lam1), kinds[i]
+
+
+@pytest.mark.parametrize("l", [32, 64, 96, 128])
+@pytest.mark.parametrize("seed", range(4))
+def test_eigenvalues_of_nested_clusters(l, seed):
+    """Clusters within clusters, 1e-8 and 1e-4 of the largest eigenvalue apart and of odd sizes, and eigenvalues on the
+    points of a uniform grid: groups of every size share an interval of the eigenvalue search for a while.  The reduction and
+    the search leave about l roundings of lambda_1."""
+    rng = np.random.default_rng(100 * l + seed)
+    s = np.zeros(l)
+    n = 0
+    while n < l:
+        m = min(int(rng.integers(1, 8)), l - n)
+        step = 10.0 ** -float(rng.choice([2, 4, 7]))
+        s[n:n + m] = round(float(rng.uniform(0.05, 1.0)) * 64) / 64 - step * np.arange(m) * rng.uniform(0.8, 1.2, m)
+        n += m
+    s[0] = 1.0
+    q, _ = np.linalg.qr(rng.standard_normal((l, l)))
+    g = (q * np.abs(s)) @ q.T
+    g = (g + g.T) / 2
+    u, lam = _solve(g)
+    assert np.max(np.abs(lam - np.linalg.eigvalsh(g)[::-1])) < (1e-13 * l if _tridiagonal(s) else 1e-4)
+    assert np.max(np.abs(u @ u.T - np.eye(l))) < 4e-6
+
+
+def _tridiagonal(s):
+    """Whether no two eigenvalues coincide (to 1e-9): otherwise the Jacobi route, in fp32, may have been taken."""
+    return np.min(np.diff(np.sort(np.abs(s)))) > 1e-9
