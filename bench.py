@@ -112,8 +112,9 @@ def roofline_of(name: str, ms: float, launches: int, work: float) -> dict | None
         return {**common, "bound": "hbm", "achieved": ach, "peak": PEAK_HBM_GBS, "unit": "GB/s", "frac": ach / PEAK_HBM_GBS,
                 "algorithmic_tflops": work / sec / 1e12,
                 "executed_f16_mfma_frac": (1.0 if planes == 1 else 3.0) * work / sec / 1e12 / PEAK_BF16_MFMA_TFLOPS}
-    if name.startswith("wide_gemm_kernel"):
-        lt, _, _, prec = (int(t) for t in name[name.index("<") + 1:name.index(">")].split(","))
+    if name.startswith(("wide_gemm_kernel", "column_gemm_kernel")):
+        args = [int(t) for t in name[name.index("<") + 1:name.index(">")].split(",")]
+        lt, prec = (args[0] / 2, 1) if name.startswith("column") else (args[0], args[3])
         if prec == 0:      # fp32 MFMA: work is flops
             ach = work / sec / 1e12
             return {**common, "bound": "mfma", "achieved": ach, "peak": PEAK_FP32_MFMA_TFLOPS, "unit": "TFLOP/s",

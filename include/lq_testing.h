@@ -36,6 +36,19 @@ int lq_test_wide_gemm_f16(int mode, int l, int64_t big, int64_t K, const float* 
                           const uint8_t* A_lo, int64_t lda, float* C, int64_t ldc, int batch, int workgroups, float* part, size_t part_floats,
                           float x_scale, const double* lam0, float out_scale, void* stream);
 size_t lq_test_wide_gemm_part_floats(int l, int workgroups);
+/* The large products of one problem (precision 1 of lq_test_wide_gemm; l <= 128), X given as fp32: C as there, and C_packed
+ * (NULL: not wanted) the result in operand layout, 2 * l * ldc 16-bit numbers, ldc the width rounded up to 64.  nt: tiles of 16 nt
+ * columns (1, 2, 4; 0: the library's choice of both), ranges: parts of the reduction (1..8).  scratch: l * (ldx + ranges * ldc)
+ * floats, ranges as 8 where the library chooses. */
+int lq_test_column_gemm(int mode, int l, int64_t big, int64_t K, const float* X, int64_t ldx, const float* A, int64_t lda,
+                        float* C, int64_t ldc, uint16_t* C_packed, int nt, int ranges, float* scratch, void* stream);
+/* Splits X (l x ldx, ldx a multiple of 64) into the operand layout of the above: 2 * l * ldx 16-bit numbers. */
+int lq_test_pack(int l, const float* X, int64_t ldx, uint16_t* packed, void* stream);
+/* lq_test_filter_step with X read as the sum of `ranges` l x ldx matrices at `part` (NULL: X itself) and the result also in
+ * operand layout (NULL: not wanted; ldx a multiple of 64). */
+int lq_test_filter_step_packed(float* X, float a, const float* Y, float b, const float* Z, float c, const float* L, int l,
+                               int locked, int64_t m, int64_t ldx, const float* part, int ranges, uint16_t* packed,
+                               void* stream);
 /* Rows of X (l x m) are orthonormalised in place by Cholesky-QR (Gram in fp64).
  * scratch: at least 17 * l * l doubles.  alt: l * ldx floats of scratch, or NULL to force the
  * in-place triangular solve.  ldx at least m rounded up to 16; with alt and l <= 128 (the rotation) a multiple of 32. */

@@ -18,27 +18,14 @@
 #include <cstdlib>
 
 #include "kernels.h"
+#include "mfma_device.h"
 #include "profiler.h"
 
 namespace lq {
 
-typedef float floatx16 __attribute__((ext_vector_type(16)));
-typedef float floatx4 __attribute__((ext_vector_type(4)));   // native vector: arrays of it stay in registers
-typedef float floatx2 __attribute__((ext_vector_type(2)));
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-
 constexpr int PREC_FP32 = 0;     // v_mfma_f32_32x32x2_f32
 constexpr int PREC_BF16X3 = 1;   // operands split into bf16 hi + lo, three v_mfma_f32_32x32x16_bf16 per product
 constexpr int HPITCH = 40;       // LDS row pitch of the split X tile in bf16 elements (80 B: conflict-free b128 reads)
-
-// a = hi + lo + O(2^-17 a) with hi, lo in bf16.
-__device__ __forceinline__ void split_bf16(floatx2 v, bf16x2& hi, bf16x2& lo) {
-  hi = __builtin_convertvector(v, bf16x2);
-  const floatx2 back = __builtin_convertvector(hi, floatx2);
-  lo = __builtin_convertvector(v - back, bf16x2);
-}
 
 constexpr int BK = 32;           // K chunk staged per step
 constexpr int XPITCH = BK + 4;   // LDS row pitch in floats: 16-byte aligned rows, conflict-free b128 reads
@@ -387,10 +374,6 @@ __global__ __launch_bounds__(256) void gemm_fixup_kernel(GemmArgs g, int l, int 
 // fp16 would show in the result to first order.  The result is multiplied by out_scale (a power of two) when stored.
 // Same work decomposition, tile shapes and fix-up as wide_gemm_kernel; the reduction is cut into steps of 64 (one
 // plane) or 32 (two planes), and both operands keep the natural order of the reduction index.
-typedef _Float16 halfx8 __attribute__((ext_vector_type(8)));
-typedef _Float16 halfx4 __attribute__((ext_vector_type(4)));
-typedef uint32_t uintx4 __attribute__((ext_vector_type(4)));
-
 constexpr int HP16 = 64 + 8;     // LDS row pitch of the X halves in fp16 elements (144 B: conflict-free b128 reads)
 
 // X tile: L x (16 G) floats, LT * G / 2 float4 per thread.  The leading dimension of X is a multiple of 64.
@@ -493,11 +476,8 @@ __device__ __forceinline__ void operands16(const uintx4 (&cur)[G][2], int g, hal
   }
 }
 
-// The lo plane of the residual: one byte per element, the upper byte of the fp16 number 2^11 (a - hi) (sign, five exponent
-// bits, two fraction bits).  NN mode only: ring[g][e / 4][e % 4] = the 16 bits holding columns col, col + 1 of reduction
+// The lo plane of the residual (LO8_SCALE).  NN mode only: ring[g][e / 4][e % 4] = the 16 bits holding columns col, col + 1 of reduction
 // row k0 + 16 g + 8 h + e; off is the lane's byte offset in the fp16 plane, i.e. twice the one here.
-constexpr float LO8_SCALE = 2048.0f;
-
 template <int G, bool GUARD>
 __device__ __forceinline__ void fetch_a8(const uint8_t* __restrict__ A, int64_t lda, uint32_t off, int lh, int64_t k0,
                                          int64_t kend, uintx4 (&ring)[G][2]) {
@@ -597,13 +577,6 @@ __device__ __forceinline__ void multiply_chunk16(const _Float16* xh, const _Floa
       }
     }
   }
-}
-
-// Power of two xs with |x| xs <= 2^13 for the rows of a wide matrix whose largest squared row norm is lam0.
-__device__ __forceinline__ float x_scale_from(double lam0) {
-  const float s = (float)lam0;
-  if (!(s > 0.0f) || !(s < 3.0e38f)) return 1.0f;
-  return exp2f(13.0f - ceilf(0.5f * log2f(s)));
 }
 
 template <int LT, int MODE, int PLANES, int STAGES>

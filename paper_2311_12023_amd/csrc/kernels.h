@@ -65,6 +65,21 @@ int launch_wide_gemm_f16(int mode, int l, int64_t big, int64_t K, const float* X
                          size_t strideC, int batch, float* part, size_t part_floats, float x_scale, const double* lam0,
                          size_t strideLam, float out_scale, hipStream_t st, int workgroups = 0);
 
+// ---- large products of one problem, precision 1 of the above (column_gemm_kernels.hip) --------------------------
+// X comes in operand layout (launch_column_sum; l * K elements, K rounded up to 64, two 16-bit halves each); A 16-byte aligned, lda
+// (NT mode: and K; NN mode: and big) a multiple of 4.  The reduction is cut into split.ranges ranges.  One range: the
+// product goes to C (columns big and beyond are not written) and, in operand layout, to packed; either may be NULL.  More:
+// range r goes to part + r * l * ldp, ldp = big rounded up to 64 with zeros past big, and C and packed are not written.
+struct ColumnSplit { int nt, ranges; };
+bool column_gemm_supported(int l);
+ColumnSplit column_gemm_split(int l, int64_t big, int64_t K);
+int launch_column_gemm(int mode, int l, int64_t big, int64_t K, const uint16_t* X, const float* A, int64_t lda, ColumnSplit split,
+                       float* C, int64_t ldc, uint16_t* packed, float* part, hipStream_t st);
+// Sum of `ranges` matrices of l rows (leading dimension ld, a multiple of 64, one after the other), in order: as fp32 to C and in
+// operand layout to packed; either may be NULL.
+int launch_column_sum(int l, const float* src, int64_t ld, int ranges, int64_t big, float* C, int64_t ldc, uint16_t* packed,
+                      hipStream_t st);
+
 // Row and column Fisher weights from a full Fisher matrix (Section 3.3): row_w = a^2, col_w = (b / mean(sqrt F))^2
 // with a, b the row / column means of sqrt(F), accumulated in fp64.  scratch: fisher_scratch_doubles(d, k) doubles.
 size_t fisher_scratch_doubles(int64_t d, int64_t k);
@@ -212,11 +227,12 @@ int launch_absmax(const float* x, int64_t n, float* out, hipStream_t st);
 // X <- X - alpha * Y, both `count` floats (multiple of 4).
 constexpr int DEFLATE_ROWS_MAX = 16;
 int launch_deflate_rows(float* X, const float* L, int l, int locked, int64_t m, int64_t ldx, hipStream_t st);
-// Both in one pass: X <- a X + b Y + c Z (Y NULL: X as it is; Z NULL: no third term), then deflate_rows.  X, Y, Z: l rows with
-// leading dimension ldx, columns past m zero.
+// A filter step in one pass: X <- a X + b Y + c Z (Y NULL: X as it is; Z NULL: no third term), then deflate_rows.  X, Y, Z: l rows
+// with leading dimension ldx, columns past m zero.  With `part` the X that is read is the sum of `ranges` matrices of l x ldx
+// there (launch_column_gemm); with `packed` the result is also written in operand layout (ldx a multiple of 64).
 int launch_filter_step(float* X, float a, const float* Y, float b, const float* Z, float c, const float* L, int l, int locked,
-                       int64_t m, int64_t ldx, hipStream_t st);
-int launch_lincomb3(float* X, float a, const float* Y, float b, const float* Z, float c, int64_t count, hipStream_t st);
+                       int64_t m, int64_t ldx, hipStream_t st, const float* part = nullptr, int ranges = 1,
+                       uint16_t* packed = nullptr);
 // Fills a wide matrix (l x m, padded ld) with N(0,1) draws from a counter-based generator; pads are zeroed.
 int launch_gaussian_fill(float* X, int l, int64_t m, int64_t ldx, uint64_t seed, hipStream_t st);
 // out[i][j] = sr[i] * A[i][j] * sc[j]  (sr = sqrt(row_w), sc = sqrt(col_w): D_row A D_col of Eq. 5).

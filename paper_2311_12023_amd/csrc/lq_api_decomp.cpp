@@ -228,10 +228,41 @@ static int cold_factorize(const Ctx& c, const float* A, uint64_t seed, const flo
   float* Ba = c.at<float>(pl.Ba); float* Bb = c.at<float>(pl.Bb);
   double* lam = c.at<double>(pl.lam_cold);
   const int64_t ycount = (int64_t)l * pl.ldd;
+  // Products of one problem with split operands: X goes in operand layout from the kernel that made it to the product (pY: rows
+  // of Y, pB: rows of B), and partial sums from the product to the kernel that reads it.  All three lie in the scratch of the
+  // other kernel's partial tiles; a matrix so long that they do not fit there keeps that kernel.
+  const ColumnSplit by_k = column_gemm_split(l, pl.k, pl.d), by_d = column_gemm_split(l, pl.d, pl.k);   // Y A, B A^T
+  const size_t packed_floats = (size_t)l * (pl.ldd + pl.ldk);
+  const size_t part_floats = (size_t)l * std::max(by_k.ranges * pl.ldk, by_d.ranges * pl.ldd);
+  const bool columns = pl.prm.prec != 0 && column_gemm_supported(l) && packed_floats + part_floats <= pl.gpart_floats;
+  float* const part = c.at<float>(pl.gpart);
+  uint16_t* const pY = reinterpret_cast<uint16_t*>(part + part_floats);
+  uint16_t* const pB = pY + (size_t)2 * l * pl.ldd;
+  // Ba = Y A from Y (in pY): fp32 to B, operand layout to packed
+  auto project = [&](const float* Y, float* B, bool want_b, bool want_packed) -> int {
+    if (!columns) return gemm(c, MODE_NN, l, pl.k, pl.d, Y, pl.ldd, 0, A, pl.k, 0, B, pl.ldk, 0, 1);
+    uint16_t* packed = want_packed ? pB : nullptr;
+    if (!want_b) B = nullptr;
+    LQ_TRY(launch_column_gemm(MODE_NN, l, pl.k, pl.d, pY, A, pl.k, by_k, B, pl.ldk, packed, part, c.st));
+    return by_k.ranges > 1 ? launch_column_sum(l, part, pl.ldk, by_k.ranges, pl.k, B, pl.ldk, packed, c.st) : LQ_OK;
+  };
+  // Y = B A^T from B (in pB); *sum: NULL, or the ranges that the caller adds up
+  auto apply_transpose = [&](const float* B, float* Y, const float** sum) -> int {
+    if (sum) *sum = nullptr;
+    if (!columns) return gemm(c, MODE_NT, l, pl.d, pl.k, B, pl.ldk, 0, A, pl.k, 0, Y, pl.ldd, 0, 1);
+    LQ_TRY(launch_column_gemm(MODE_NT, l, pl.d, pl.k, pB, A, pl.k, by_d, Y, pl.ldd, nullptr, part, c.st));
+    if (by_d.ranges == 1) return LQ_OK;
+    if (sum) { *sum = part; return LQ_OK; }
+    return launch_column_sum(l, part, pl.ldd, by_d.ranges, pl.d, Y, pl.ldd, nullptr, c.st);
+  };
+  auto pack = [&](const float* X, int64_t ldx, uint16_t* packed) -> int {
+    return columns ? launch_column_sum(l, X, ldx, 1, ldx, nullptr, 0, packed, c.st) : LQ_OK;
+  };
   for (float* p : all) LQ_HIP_TRY(hipMemsetAsync(p, 0, ycount * 4, c.st));
   LQ_HIP_TRY(hipMemsetAsync(Bb, 0, (size_t)l * pl.ldk * 4, c.st));
   LQ_TRY(launch_gaussian_fill(Ba, l, pl.k, pl.ldk, seed, c.st));
-  LQ_TRY(gemm(c, MODE_NT, l, pl.d, pl.k, Ba, pl.ldk, 0, A, pl.k, 0, Y0, pl.ldd, 0, 1));
+  LQ_TRY(pack(Ba, pl.ldk, pB));
+  LQ_TRY(apply_transpose(Ba, Y0, nullptr));
   LQ_TRY(orthonormalize(c, Y0, P[0], l, pl.d, pl.ldd, 0, 1));
   std::vector<double> prev(r, 0.0), cur(l, 0.0);
   bool have_prev = false;
@@ -273,14 +304,18 @@ static int cold_factorize(const Ctx& c, const float* A, uint64_t seed, const flo
   std::vector<double> res(r, 0.0);
   double last_est = 0.0;      // residual-based error estimate of the previous Rayleigh-Ritz (valid when rate_ok)
   for (int it = 0;;) {        // it: applications of M so far
-    LQ_TRY(gemm(c, MODE_NN, l, pl.k, pl.d, Y0, pl.ldd, 0, A, pl.k, 0, Ba, pl.ldk, 0, 1));
+    const bool check = it >= next_check || it >= pl.prm.maxit;
+    LQ_TRY(pack(Y0, pl.ldd, pY));
+    LQ_TRY(project(Y0, Ba, check, !check));
     bool have_g = false;      // P[0] = Ba A^T = Y0 M already computed (by the residual check)
-    if (it >= next_check || it >= pl.prm.maxit) {
+    const float* sum = nullptr;        // where its ranges are, if they are still to be added
+    if (check) {
       LQ_TRY(ritz_rotate(c, l, Y0, P[0], 0, Ba, Bb, 0, lam, 1));
       std::swap(Y0, P[0]); std::swap(Ba, Bb);
       // residuals of the top-r Ritz pairs, |y_j M - theta_j y_j|: y_j M = (y_j A) A^T is the first product of the next
       // cycle anyway
-      LQ_TRY(gemm(c, MODE_NT, l, pl.d, pl.k, Ba, pl.ldk, 0, A, pl.k, 0, P[0], pl.ldd, 0, 1));
+      LQ_TRY(pack(Ba, pl.ldk, pB));
+      LQ_TRY(apply_transpose(Ba, P[0], nullptr));
       LQ_TRY(launch_ritz_residual(P[0], Y0, lam, r, pl.d, pl.ldd, res_dev, c.st));
       have_g = true;
       LQ_HIP_TRY(hipMemcpyAsync(cur.data(), lam, sizeof(double) * l, hipMemcpyDeviceToHost, c.st));
@@ -363,15 +398,17 @@ static int cold_factorize(const Ctx& c, const float* A, uint64_t seed, const flo
     m = std::max(1, std::min(m, std::min(next_check, pl.prm.maxit) - it));
     m_prev = m;
     // step 1 (Ba = Y0 A is at hand)
-    if (!have_g) LQ_TRY(gemm(c, MODE_NT, l, pl.d, pl.k, Ba, pl.ldk, 0, A, pl.k, 0, P[0], pl.ldd, 0, 1));
+    if (!have_g) LQ_TRY(apply_transpose(Ba, P[0], &sum));
+    uint16_t* const packed = columns ? pY : nullptr;
     LQ_TRY(launch_filter_step(P[0], bcut > 0.0 ? (float)(2.0 / bcut) : 1.0f, bcut > 0.0 ? Y0 : nullptr, -1.0f, nullptr, 0.0f, Y0, l,
-                              locked, pl.d, pl.ldd, c.st));
+                              locked, pl.d, pl.ldd, c.st, sum, by_d.ranges, m > 1 ? packed : nullptr));
     // Y0 keeps the locked rows for the whole cycle: the recurrence rotates through the other three blocks
     float* Yj = P[0]; float* Yjm1 = Y0; float* Ynew = P[1]; float* third = P[2];
     for (int j = 1; j < m; ++j) {
-      LQ_TRY(gemm(c, MODE_NN, l, pl.k, pl.d, Yj, pl.ldd, 0, A, pl.k, 0, Bb, pl.ldk, 0, 1));
-      LQ_TRY(gemm(c, MODE_NT, l, pl.d, pl.k, Bb, pl.ldk, 0, A, pl.k, 0, Ynew, pl.ldd, 0, 1));
-      LQ_TRY(launch_filter_step(Ynew, (float)(4.0 / bcut), Yj, -2.0f, Yjm1, -1.0f, Y0, l, locked, pl.d, pl.ldd, c.st));
+      LQ_TRY(project(Yj, Bb, false, true));
+      LQ_TRY(apply_transpose(Bb, Ynew, &sum));
+      LQ_TRY(launch_filter_step(Ynew, (float)(4.0 / bcut), Yj, -2.0f, Yjm1, -1.0f, Y0, l, locked, pl.d, pl.ldd, c.st, sum,
+                                by_d.ranges, j + 1 < m ? packed : nullptr));
       float* freed = Yjm1 == Y0 ? third : Yjm1;
       Yjm1 = Yj; Yj = Ynew; Ynew = freed;
     }

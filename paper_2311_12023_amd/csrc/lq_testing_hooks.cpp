@@ -114,10 +114,37 @@ int lq_test_filter_step(float* X, float a, const float* Y, float b, const float*
   return launch_filter_step(X, a, Y, b, Z, c, L, l, locked, m, ldx, (hipStream_t)stream);
 }
 
+int lq_test_filter_step_packed(float* X, float a, const float* Y, float b, const float* Z, float c, const float* L, int l,
+                               int locked, int64_t m, int64_t ldx, const float* part, int ranges, uint16_t* packed,
+                               void* stream) {
+  if (!X || !L) return LQ_ERR_NULL;
+  if (l < 1 || locked > l || m < 1 || ldx < m) return LQ_ERR_ARG;
+  return launch_filter_step(X, a, Y, b, Z, c, L, l, locked, m, ldx, (hipStream_t)stream, part, ranges, packed);
+}
+
+int lq_test_pack(int l, const float* X, int64_t ldx, uint16_t* packed, void* stream) {
+  if (!X || !packed) return LQ_ERR_NULL;
+  return launch_column_sum(l, X, ldx, 1, ldx, nullptr, 0, packed, (hipStream_t)stream);
+}
+
+int lq_test_column_gemm(int mode, int l, int64_t big, int64_t K, const float* X, int64_t ldx, const float* A, int64_t lda,
+                        float* C, int64_t ldc, uint16_t* C_packed, int nt, int ranges, float* scratch, void* stream) {
+  if (!X || !A || !C || !scratch) return LQ_ERR_NULL;
+  if (big < 1 || ldc < (big + 63) / 64 * 64 || ldx < K || !column_gemm_supported(l)) return LQ_ERR_ARG;
+  hipStream_t st = (hipStream_t)stream;
+  const ColumnSplit split = nt ? ColumnSplit{nt, ranges} : column_gemm_split(l, big, K);
+  uint16_t* xp = reinterpret_cast<uint16_t*>(scratch);
+  float* part = scratch + (size_t)l * ldx;
+  LQ_TRY(launch_column_sum(l, X, ldx, 1, ldx, nullptr, 0, xp, st));
+  LQ_TRY(launch_column_gemm(mode, l, big, K, xp, A, lda, split, C, ldc, C_packed, part, st));
+  if (split.ranges == 1) return LQ_OK;
+  return launch_column_sum(l, part, (big + 63) / 64 * 64, split.ranges, big, C, ldc, C_packed, st);
+}
+
 int lq_test_lincomb3(float* X, float a, const float* Y, float b, const float* Z, float c, int l, int64_t ldx, void* stream) {
   if (!X || !Y) return LQ_ERR_NULL;
   if (l < 1 || ldx < 4 || ldx % 4) return LQ_ERR_ARG;
-  return launch_lincomb3(X, a, Y, b, Z, c, (int64_t)l * ldx, (hipStream_t)stream);
+  return launch_filter_step(X, a, Y, b, Z, c, nullptr, l, 0, ldx, ldx, (hipStream_t)stream);
 }
 
 int lq_test_deflate_rows(float* X, const float* L, int l, int locked, int64_t m, int64_t ldx, void* stream) {

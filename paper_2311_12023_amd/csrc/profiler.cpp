@@ -56,7 +56,9 @@ static const char* const kNames[NUM_CLASSES] = {
     "wide_gemm_f16_kernel<1,1,1>", "wide_gemm_f16_kernel<2,1,1>", "wide_gemm_f16_kernel<3,1,1>", "wide_gemm_f16_kernel<4,1,1>",
     "wide_gemm_f16_kernel<1,0,2>", "wide_gemm_f16_kernel<2,0,2>", "wide_gemm_f16_kernel<3,0,2>", "wide_gemm_f16_kernel<4,0,2>",
     "wide_gemm_f16_kernel<1,1,2>", "wide_gemm_f16_kernel<2,1,2>", "wide_gemm_f16_kernel<3,1,2>", "wide_gemm_f16_kernel<4,1,2>",
-    "absmax_kernel", "rotate_kernel", "qrows_kernel", "sym_eig_kernel", "plane_gemm_kernel", "weight_plane_kernel"};
+    "absmax_kernel", "rotate_kernel", "qrows_kernel", "sym_eig_kernel", "plane_gemm_kernel", "weight_plane_kernel",
+    "column_gemm_kernel<2,0>", "column_gemm_kernel<4,0>", "column_gemm_kernel<6,0>", "column_gemm_kernel<8,0>",
+    "column_gemm_kernel<2,1>", "column_gemm_kernel<4,1>", "column_gemm_kernel<6,1>", "column_gemm_kernel<8,1>", "column_sum_kernel"};
 
 }  // namespace prof
 }  // namespace lq

@@ -30,7 +30,9 @@ enum Cls {
   SYM_EIG = 65,             // sym_eig_kernel (work = bytes)
   PLANE_GEMM = 66,          // plane_gemm_kernel (work = flops of the product)
   WEIGHT_PLANE = 67,        // weight_plane_kernel (work = bytes)
-  NUM_CLASSES = 68
+  COLUMN_GEMM_BASE = 68,    // + mode * 4 + (l/32 - 1): column_gemm_kernel (work = flops of the product)
+  COLUMN_SUM = 76,          // column_sum_kernel (work = bytes)
+  NUM_CLASSES = 77
 };
 
 bool enabled();

@@ -6,6 +6,7 @@
 
 #include "dense_device.h"
 #include "kernels.h"
+#include "mfma_device.h"
 #include "profiler.h"
 
 namespace lq {
@@ -338,30 +339,6 @@ int launch_absmax(const float* x, int64_t n, float* out, hipStream_t st) {
   return LQ_OK;
 }
 
-// X <- a X + b Y + c Z over `count` floats (count a multiple of 4; Z may be NULL: no third term).
-__global__ __launch_bounds__(256) void lincomb3_kernel(float* __restrict__ X, float a, const float* __restrict__ Y, float b,
-                                                       const float* __restrict__ Z, float c, int64_t count4) {
-  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < count4; i += (int64_t)gridDim.x * 256) {
-    float4 x = reinterpret_cast<float4*>(X)[i];
-    const float4 y = reinterpret_cast<const float4*>(Y)[i];
-    x.x = fmaf(a, x.x, b * y.x); x.y = fmaf(a, x.y, b * y.y); x.z = fmaf(a, x.z, b * y.z); x.w = fmaf(a, x.w, b * y.w);
-    if (Z != nullptr) {
-      const float4 z = reinterpret_cast<const float4*>(Z)[i];
-      x.x = fmaf(c, z.x, x.x); x.y = fmaf(c, z.y, x.y); x.z = fmaf(c, z.z, x.z); x.w = fmaf(c, z.w, x.w);
-    }
-    reinterpret_cast<float4*>(X)[i] = x;
-  }
-}
-
-int launch_lincomb3(float* X, float a, const float* Y, float b, const float* Z, float c, int64_t count, hipStream_t st) {
-  const int64_t count4 = count / 4;
-  const int64_t want = (count4 + 255) / 256;
-  prof::Scope ps(prof::MISC, st, (double)count * (Z ? 16.0 : 12.0));
-  hipLaunchKernelGGL(lincomb3_kernel, dim3((unsigned)(want < 2048 ? want : 2048)), dim3(256), 0, st, X, a, Y, b, Z, c, count4);
-  LQ_HIP_TRY(hipGetLastError());
-  return LQ_OK;
-}
-
 // Rows of X against the first `locked` rows of L (orthonormal): rows i >= locked lose their components along them,
 // x_i <- x_i - sum_o (x_i . l_o) l_o; rows i < locked become copies of l_i.  One workgroup per row; inner products in
 // fp32 with a fixed summation order.  locked <= DEFLATE_MAX.
@@ -421,26 +398,68 @@ int launch_deflate_rows(float* X, const float* L, int l, int locked, int64_t m, 
   return LQ_OK;
 }
 
-// A filter step's lincomb3 and deflate_rows in one pass over the rows (one workgroup per row, the combined row in
-// registers): X is read and written once instead of three times and twice, and one launch waits for the other no more
-// (128 rows x 4096, four locked: 4.7 + 12.7 -> 5.9 us).  RC float4 per thread bound the row length; LB >= locked fixes the register arrays.
+// A filter step.  X is read as it is or as the sum of the ranges that launch_column_gemm left, and the result is also written in
+// the operand layout of the next product: neither takes a launch of its own.  A workgroup's rows are those of a 16-row tile that
+// its XCD has, so that the 8-byte pieces of the operand layout meet in one L2.
+struct FilterArgs {
+  float* X; const float* part; int ranges; size_t next;       // part NULL: X itself
+  float a, b, c;
+  const float* Y; const float* Z; const float* L;
+  int locked, q4, row_tiles;
+  uintx2* packed;
+};
+
+__device__ __forceinline__ float4 filter_combine(const FilterArgs& g, int64_t row, int j) {
+  const int64_t at = row * g.q4 + j;
+  float4 t;
+  if (g.part) {
+    const float* p = g.part + 4 * at;
+    t = *reinterpret_cast<const float4*>(p);
+    for (int r = 1; r < g.ranges; ++r) {
+      const float4 u = *reinterpret_cast<const float4*>(p + r * g.next);
+      t.x += u.x; t.y += u.y; t.z += u.z; t.w += u.w;
+    }
+  } else {
+    t = reinterpret_cast<const float4*>(g.X)[at];
+  }
+  if (g.Y) {
+    const float4 u = reinterpret_cast<const float4*>(g.Y)[at];
+    t.x = fmaf(g.a, t.x, g.b * u.x); t.y = fmaf(g.a, t.y, g.b * u.y); t.z = fmaf(g.a, t.z, g.b * u.z); t.w = fmaf(g.a, t.w, g.b * u.w);
+    if (g.Z) {
+      const float4 w = reinterpret_cast<const float4*>(g.Z)[at];
+      t.x = fmaf(g.c, w.x, t.x); t.y = fmaf(g.c, w.y, t.y); t.z = fmaf(g.c, w.z, t.z); t.w = fmaf(g.c, w.w, t.w);
+    }
+  }
+  return t;
+}
+
+__device__ __forceinline__ void filter_store(const FilterArgs& g, int64_t row, int j, float4 t) {
+  reinterpret_cast<float4*>(g.X)[row * g.q4 + j] = t;
+  if (g.packed) store_packed(g.packed, g.row_tiles, (int)row, 4 * (int64_t)j, floatx4{t.x, t.y, t.z, t.w});
+}
+
+// Nothing locked: elementwise.  gridDim = (rows, quads / 256).
+__global__ __launch_bounds__(256) void filter_combine_kernel(FilterArgs g) {
+  const int64_t row = (int64_t)(blockIdx.x % 8) * (gridDim.x / 8) + blockIdx.x / 8;
+  const int j = blockIdx.y * 256 + threadIdx.x;
+  if (j < g.q4) filter_store(g, row, j, filter_combine(g, row, j));
+}
+
+// The combination and deflate_rows in one pass over the rows (one workgroup per row, the combined row in registers; 128 rows x
+// 4096, four locked: two launches 17.4, this 5.9 us).  RC float4 per thread bound the row length; LB >= locked fixes the register
+// arrays.
 constexpr int FS_THREADS = 512, FS_RC = 8;
 
 template <int LB>
-__global__ __launch_bounds__(FS_THREADS) void filter_step_kernel(float* __restrict__ X, float a, const float* __restrict__ Y,
-                                                                 float b, const float* __restrict__ Z, float c,
-                                                                 const float* __restrict__ L, int locked, int q4) {
+__global__ __launch_bounds__(FS_THREADS) void filter_step_kernel(FilterArgs g) {
   __shared__ float s_part[FS_THREADS / 64][LB];
-  const int tid = threadIdx.x;
-  const int64_t row = blockIdx.x;
-  float4* x = reinterpret_cast<float4*>(X) + row * q4;
-  const float4* l4 = reinterpret_cast<const float4*>(L);
+  const int tid = threadIdx.x, locked = g.locked, q4 = g.q4;
+  const int64_t row = (int64_t)(blockIdx.x % 8) * (gridDim.x / 8) + blockIdx.x / 8;
+  const float4* l4 = reinterpret_cast<const float4*>(g.L);
   if (row < locked) {
-    for (int j = tid; j < q4; j += FS_THREADS) x[j] = l4[row * q4 + j];
+    for (int j = tid; j < q4; j += FS_THREADS) filter_store(g, row, j, l4[row * q4 + j]);
     return;
   }
-  const float4* y = reinterpret_cast<const float4*>(Y) + row * q4;
-  const float4* z = Z ? reinterpret_cast<const float4*>(Z) + row * q4 : nullptr;
   float4 v[FS_RC];
   float dot[LB];
 #pragma unroll
@@ -450,15 +469,7 @@ __global__ __launch_bounds__(FS_THREADS) void filter_step_kernel(float* __restri
     const int j = tid + r * FS_THREADS;
     v[r] = make_float4(0.f, 0.f, 0.f, 0.f);
     if (j < q4) {
-      float4 t = x[j];
-      if (Y) {
-        const float4 u = y[j];
-        t.x = fmaf(a, t.x, b * u.x); t.y = fmaf(a, t.y, b * u.y); t.z = fmaf(a, t.z, b * u.z); t.w = fmaf(a, t.w, b * u.w);
-        if (z) {
-          const float4 w = z[j];
-          t.x = fmaf(c, w.x, t.x); t.y = fmaf(c, w.y, t.y); t.z = fmaf(c, w.z, t.z); t.w = fmaf(c, w.w, t.w);
-        }
-      }
+      const float4 t = filter_combine(g, row, j);
       v[r] = t;
 #pragma unroll
       for (int o = 0; o < LB; ++o) {
@@ -491,25 +502,33 @@ __global__ __launch_bounds__(FS_THREADS) void filter_step_kernel(float* __restri
         const float4 u = l4[(int64_t)(o < locked ? o : 0) * q4 + j];
         t.x = fmaf(dot[o], u.x, t.x); t.y = fmaf(dot[o], u.y, t.y); t.z = fmaf(dot[o], u.z, t.z); t.w = fmaf(dot[o], u.w, t.w);
       }
-      x[j] = t;
+      filter_store(g, row, j, t);
     }
   }
 }
 
 int launch_filter_step(float* X, float a, const float* Y, float b, const float* Z, float c, const float* L, int l, int locked,
-                       int64_t m, int64_t ldx, hipStream_t st) {
-  if (locked < 0 || locked > DEFLATE_MAX || ldx % 4 != 0 || (Z && !Y)) return LQ_ERR_ARG;
-  if (locked == 0 || ldx > (int64_t)4 * FS_THREADS * FS_RC) {
-    if (Y) LQ_TRY(launch_lincomb3(X, a, Y, b, Z, c, (int64_t)l * ldx, st));
-    return launch_deflate_rows(X, L, l, locked, m, ldx, st);
+                       int64_t m, int64_t ldx, hipStream_t st, const float* part, int ranges, uint16_t* packed) {
+  if (l < 8 || l % 8 || locked < 0 || locked > DEFLATE_MAX || ldx % 4 != 0 || ldx > (1ll << 31) || (Z && !Y)) return LQ_ERR_ARG;
+  if (packed && (l % 16 || ldx % 64)) return LQ_ERR_ARG;
+  const bool whole = locked > 0 && ldx <= (int64_t)4 * FS_THREADS * FS_RC;      // a row fits the registers of a workgroup
+  if (locked == 0 && !Y && !part && !packed) return LQ_OK;
+  FilterArgs g;
+  g.X = X; g.part = part; g.ranges = ranges; g.next = (size_t)l * ldx;
+  g.a = a; g.b = b; g.c = c; g.Y = Y; g.Z = Z; g.L = L;
+  g.locked = locked; g.q4 = (int)(ldx / 4); g.row_tiles = l / 16;
+  g.packed = whole || locked == 0 ? reinterpret_cast<uintx2*>(packed) : nullptr;
+  if (whole || locked == 0 || Y || part) {
+    prof::Scope ps(prof::MISC, st, (double)l * ldx * 4.0 * (1 + (part ? ranges : 1) + (Y ? 1 : 0) + (Z ? 1 : 0)));
+    if (!whole) hipLaunchKernelGGL(filter_combine_kernel, dim3(l, (unsigned)((g.q4 + 255) / 256)), dim3(256), 0, st, g);
+    else if (locked <= 4) hipLaunchKernelGGL(filter_step_kernel<4>, dim3(l), dim3(FS_THREADS), 0, st, g);
+    else if (locked <= 8) hipLaunchKernelGGL(filter_step_kernel<8>, dim3(l), dim3(FS_THREADS), 0, st, g);
+    else hipLaunchKernelGGL(filter_step_kernel<16>, dim3(l), dim3(FS_THREADS), 0, st, g);
+    LQ_HIP_TRY(hipGetLastError());
   }
-  prof::Scope ps(prof::MISC, st, (double)l * ldx * 4.0 * (2 + (Y ? 1 : 0) + (Z ? 1 : 0)));
-  const int q4 = (int)(ldx / 4);
-  if (locked <= 4) hipLaunchKernelGGL(filter_step_kernel<4>, dim3(l), dim3(FS_THREADS), 0, st, X, a, Y, b, Z, c, L, locked, q4);
-  else if (locked <= 8) hipLaunchKernelGGL(filter_step_kernel<8>, dim3(l), dim3(FS_THREADS), 0, st, X, a, Y, b, Z, c, L, locked, q4);
-  else hipLaunchKernelGGL(filter_step_kernel<16>, dim3(l), dim3(FS_THREADS), 0, st, X, a, Y, b, Z, c, L, locked, q4);
-  LQ_HIP_TRY(hipGetLastError());
-  return LQ_OK;
+  if (whole || locked == 0) return LQ_OK;
+  LQ_TRY(launch_deflate_rows(X, L, l, locked, m, ldx, st));
+  return packed ? launch_column_sum(l, X, ldx, 1, ldx, nullptr, 0, packed, st) : LQ_OK;
 }
 
 int launch_gaussian_fill(float* X, int l, int64_t m, int64_t ldx, uint64_t seed, hipStream_t st) {

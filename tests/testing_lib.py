@@ -33,6 +33,9 @@ def load():
         L.lq_test_gram.argtypes = [vp, it, i64, i64, C.c_size_t, vp, C.c_size_t, vp, it, vp]
         L.lq_test_rotate.argtypes = [it, vp, C.c_size_t, it, vp, vp, i64, C.c_size_t, vp, vp, i64, C.c_size_t, it, vp]
         L.lq_test_filter_step.argtypes = [vp, C.c_float, vp, C.c_float, vp, C.c_float, vp, it, it, i64, i64, vp]
+        L.lq_test_column_gemm.argtypes = [it, it, i64, i64, vp, i64, vp, i64, vp, i64, vp, it, it, vp, vp]
+        L.lq_test_pack.argtypes = [it, vp, i64, vp, vp]
+        L.lq_test_filter_step_packed.argtypes = [vp, C.c_float, vp, C.c_float, vp, C.c_float, vp, it, it, i64, i64, vp, it, vp, vp]
         L.lq_test_lds_limit.restype = C.c_size_t
         L.lq_test_bucket_code.argtypes = [C.c_int, C.c_float]
         L.lq_test_sigma_by_reciprocal.restype = C.c_float
