@@ -16,6 +16,8 @@
 // the weights) are added in a fixed order by the second kernel, so results are deterministic.
 // Whole call on 4096 x 4096, NF4, rank 64: 1 row 13.9 -> 12.0 us, 4 rows 23 -> 16, 8 rows 36 -> 21 (4096 x 11008: 8 rows 58 ->
 // 35) by loading before the first barrier, 14 instead of 48 exchanges per row of X, and scales without a division.
+// 1 row 13.0 -> 11.2, 8 rows 20.7 -> 18.1 (rank 512: 32.4 -> 21.9 and 49.7 -> 36) by asking for all that the second launch
+// reads before it uses any of it.
 #include <algorithm>
 
 #include "kernels.h"
@@ -231,24 +233,37 @@ __global__ __launch_bounds__(256) void qmatvec_kernel(MvArgs a) {
 }
 
 // Second kernel: Y = sum of the ranges of X Q (in range order) + T L2 with T = sum of the ranges of X L1.  A workgroup
-// owns 64 columns and M rows (blockIdx.y picks the rows); thread (column, slot) takes rows slot, slot + 4 of them
-// (SLOTS = min(M, 4) slots, one wavefront each).  The workgroup first sums the rank values of T per row into LDS; the
-// loads of a column of L2 are issued 32 at a time.  Both sets of partial sums are described by the distance between
-// ranges and (for T) the row pitch, so the kernel also finishes the MFMA path's products of a few dozen rows.
+// owns 64 columns and M rows (blockIdx.y picks the rows).  What bounds it is the chain of memory round trips, so everything
+// that a rank of 64 needs is asked for before anything is used: the ranges of T and of X Q (thread = (column, slot), rows slot
+// and slot + 4; a lane's column is its rank in T), and the rows of L2, of which each of the four slots (one wavefront each) takes a
+// quarter for all M rows.  T then goes through LDS to every slot, and the slots' products back to the thread that has the ranges,
+// which adds them in slot order.  Both sets of partial sums are described by the distance between ranges and (for T) the
+// row pitch, so the kernel also finishes the MFMA path's products of a few dozen rows.
 constexpr int MVF_COLS = 64;
+constexpr int MVF_SLOTS = 4;
+constexpr int MVF_THREADS = MVF_COLS * MVF_SLOTS;
 constexpr int MVF_RANK_MAX = 512;
-// p[0] + p[stride] + ... (n terms, in this order), the loads issued eight at a time.
-__device__ __forceinline__ float mvf_range_sum(const float* __restrict__ p, size_t stride, int n) {
-  float s = 0.0f;
-  for (int z0 = 0; z0 < n; z0 += 8) {
-    float v[8];
+// p[0], p[stride], ...: the first W of n terms, asked for together (past the last: that one again) and added in order.
+template <int W>
+struct MvfRanges {
+  float v[W];
+  __device__ __forceinline__ void load(const float* __restrict__ p, size_t stride, int n) {
 #pragma unroll
-    for (int u = 0; u < 8; ++u) v[u] = z0 + u < n ? p[(size_t)(z0 + u) * stride] : 0.0f;
-#pragma unroll
-    for (int u = 0; u < 8; ++u) s += v[u];
+    for (int u = 0; u < W; ++u) v[u] = p[(size_t)(u < n ? u : n - 1) * stride];
   }
-  return s;
-}
+  __device__ __forceinline__ float sum(const float* __restrict__ p, size_t stride, int n) const {
+    float s = 0.0f;
+#pragma unroll
+    for (int u = 0; u < W; ++u) s += u < n ? v[u] : 0.0f;
+    for (int z0 = W; z0 < n; z0 += W) {
+      MvfRanges more;
+      more.load(p + (size_t)z0 * stride, stride, n - z0);
+#pragma unroll
+      for (int u = 0; u < W; ++u) s += z0 + u < n ? more.v[u] : 0.0f;
+    }
+    return s;
+  }
+};
 struct MvfArgs {
   const float* part; size_t pstride; int splits;               // ranges of X Q: range z, row i at part + z * pstride + i * N
   const float* tpart; size_t tstride; int64_t tld; int tsplits;  // ranges of T: row i at tpart + z * tstride + i * tld
@@ -262,9 +277,113 @@ struct MvfArgs {
 __device__ __forceinline__ int mvf_segments(const MvfArgs& a, int64_t tile) {
   return (int)(((tile + 1) * a.steps - 1) / a.per_wg - tile * a.steps / a.per_wg) + 1;
 }
-template <int M>
-__global__ __launch_bounds__(MVF_COLS * (M < 4 ? M : 4)) void qmatvec_finish_kernel(MvfArgs a) {
-  constexpr int SLOTS = M < 4 ? M : 4, THREADS = MVF_COLS * SLOTS, RT = (M + SLOTS - 1) / SLOTS;
+// RANKS: what LDS holds of T.  Ranks are in flight CHUNK at a time (a lane each).
+template <int M, int W, int RANKS>
+__global__ __launch_bounds__(MVF_THREADS) void qmatvec_finish_kernel(MvfArgs a) {
+  constexpr int CHUNK = RANKS < MVF_COLS ? RANKS : MVF_COLS, PER_SLOT = CHUNK / MVF_SLOTS;
+  constexpr int RT = (M + MVF_SLOTS - 1) / MVF_SLOTS;           // rows of a thread
+  __shared__ __attribute__((aligned(16))) float s_t[M][RANKS];
+  __shared__ float s_sum[MVF_SLOTS][M][MVF_COLS];
+  const int tid = threadIdx.x, c = tid % MVF_COLS, slot = __builtin_amdgcn_readfirstlane(tid / MVF_COLS);
+  const int64_t col = (int64_t)blockIdx.x * MVF_COLS + c;
+  const int row0 = (int)blockIdx.y * M;
+  const int m = a.m - row0 < M ? a.m - row0 : M;     // rows of this workgroup
+  const bool live = col < a.N;
+  const int64_t colc = live ? col : 0;
+  const int splits = a.steps ? mvf_segments(a, (int64_t)blockIdx.x * MVF_COLS / a.tile_cols) : a.splits;
+  const int64_t ttile0 = a.steps ? (a.N + a.tile_cols - 1) / a.tile_cols : 0;
+
+  // T, with the tail up to a multiple of a chunk zero: a wavefront has the same rows of it as of X Q, a lane one rank of a chunk
+  MvfRanges<W> tv[RT];
+  const auto t_from = [&](int i, int p) {
+    return a.tpart + (size_t)(row0 + (i < m ? i : m - 1)) * a.tld + (p < a.rank ? p : a.rank - 1);
+  };
+  const auto t_splits = [&](int p0) { return a.steps ? mvf_segments(a, ttile0 + p0 / a.ttile_cols) : a.tsplits; };
+  const auto t_load = [&](int p0) {
+#pragma unroll
+    for (int j = 0; j < RT; ++j)
+      if (slot + MVF_SLOTS * j < M) tv[j].load(t_from(slot + MVF_SLOTS * j, p0 + c), a.tstride, t_splits(p0));
+  };
+  const auto t_store = [&](int p0) {
+#pragma unroll
+    for (int j = 0; j < RT; ++j) {
+      const int i = slot + MVF_SLOTS * j;
+      if (i >= M) continue;
+      const float t = tv[j].sum(t_from(i, p0 + c), a.tstride, t_splits(p0));
+      if (c < CHUNK) s_t[i][p0 + c] = p0 + c < a.rank ? t : 0.0f;
+    }
+  };
+  float w[PER_SLOT];
+  const auto w_load = [&](int p0) {
+#pragma unroll
+    for (int u = 0; u < PER_SLOT; ++u) {
+      const int q = p0 + PER_SLOT * slot + u;
+      w[u] = a.L2[(int64_t)(q < a.rank ? q : a.rank - 1) * a.ldl2 + colc];
+    }
+  };
+
+  if (a.rank > 0) t_load(0);
+  MvfRanges<W> pv[RT];
+  const float* prow[RT];
+#pragma unroll
+  for (int j = 0; j < RT; ++j) {
+    const int i = slot + MVF_SLOTS * j;
+    prow[j] = a.part + (size_t)(row0 + (i < m ? i : m - 1)) * a.N + colc;
+    if (i < M) pv[j].load(prow[j], a.pstride, splits);
+  }
+  if (a.rank > 0) {
+    w_load(0);
+    __builtin_amdgcn_sched_barrier(0);
+    t_store(0);
+    for (int p0 = CHUNK; p0 < a.rank; p0 += CHUNK) { t_load(p0); t_store(p0); }
+    __syncthreads();
+    float acc[M];
+#pragma unroll
+    for (int i = 0; i < M; ++i) acc[i] = 0.0f;
+    for (int p0 = 0; p0 < a.rank; p0 += CHUNK) {
+      float cur[PER_SLOT];
+#pragma unroll
+      for (int u = 0; u < PER_SLOT; ++u)       // (a row of L2 past the rank counts as zero, whatever was read for it)
+        cur[u] = p0 + PER_SLOT * slot + u < a.rank ? w[u] : 0.0f;
+      if (p0 + CHUNK < a.rank) w_load(p0 + CHUNK);
+#pragma unroll
+      for (int i = 0; i < M; ++i)
+#pragma unroll
+        for (int u = 0; u < PER_SLOT; ++u) acc[i] = fmaf(s_t[i][p0 + PER_SLOT * slot + u], cur[u], acc[i]);
+    }
+#pragma unroll
+    for (int i = 0; i < M; ++i) s_sum[slot][i][c] = acc[i];
+    __syncthreads();
+  }
+#pragma unroll
+  for (int j = 0; j < RT; ++j) {
+    const int i = slot + MVF_SLOTS * j;
+    if (i >= m) continue;
+    float y = pv[j].sum(prow[j], a.pstride, splits);
+    if (a.rank > 0) {
+#pragma unroll
+      for (int u = 0; u < MVF_SLOTS; ++u) y += s_sum[u][i][c];
+    }
+    if (live) a.Y[(int64_t)(row0 + i) * a.ldy + col] = y;
+  }
+}
+
+// The same for many rows, where the machine is full and instructions count instead of round trips: a thread takes rows slot and
+// slot + 4 through all ranks, 32 loads of a column of L2 at a time, and nothing is exchanged at the end.
+// p[0] + p[stride] + ... (n terms, in this order), the loads issued eight at a time.
+__device__ __forceinline__ float mvf_range_sum(const float* __restrict__ p, size_t stride, int n) {
+  float s = 0.0f;
+  for (int z0 = 0; z0 < n; z0 += 8) {
+    float v[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) v[u] = z0 + u < n ? p[(size_t)(z0 + u) * stride] : 0.0f;
+#pragma unroll
+    for (int u = 0; u < 8; ++u) s += v[u];
+  }
+  return s;
+}
+__global__ __launch_bounds__(MVF_THREADS) void rows_finish_kernel(MvfArgs a) {
+  constexpr int M = 8, RT = M / MVF_SLOTS;
   __shared__ float s_t[M][MVF_RANK_MAX];
   const int tid = threadIdx.x, slot = tid / MVF_COLS;
   const int64_t col = (int64_t)blockIdx.x * MVF_COLS + (tid % MVF_COLS);
@@ -278,14 +397,14 @@ __global__ __launch_bounds__(MVF_COLS * (M < 4 ? M : 4)) void qmatvec_finish_ker
   float acc[RT];
 #pragma unroll
   for (int j = 0; j < RT; ++j) {
-    const int i = slot + SLOTS * j;
+    const int i = slot + MVF_SLOTS * j;
     float s = 0.0f;
     if (i < m) s = mvf_range_sum(a.part + (size_t)(row0 + i) * a.N + colc, a.pstride, splits);
     acc[j] = s;
   }
   // T, with the tail up to a multiple of 32 zero
   const int rank32 = (a.rank + 31) & ~31;
-  for (int idx = tid; idx < m * rank32; idx += THREADS) {
+  for (int idx = tid; idx < m * rank32; idx += MVF_THREADS) {
     const int i = idx / rank32, p = idx % rank32;
     float t = 0.0f;
     const int tsplits = a.steps ? mvf_segments(a, ttile0 + p / a.ttile_cols) : a.tsplits;
@@ -299,28 +418,44 @@ __global__ __launch_bounds__(MVF_COLS * (M < 4 ? M : 4)) void qmatvec_finish_ker
     for (int u = 0; u < 32; ++u) w[u] = p0 + u < a.rank ? a.L2[(int64_t)(p0 + u) * a.ldl2 + colc] : 0.0f;
 #pragma unroll
     for (int j = 0; j < RT; ++j) {
-      const int i = slot + SLOTS * j;
-      if (i < M) {
+      const int i = slot + MVF_SLOTS * j;
 #pragma unroll
-        for (int u = 0; u < 32; ++u) acc[j] = fmaf(s_t[i][p0 + u], w[u], acc[j]);
-      }
+      for (int u = 0; u < 32; ++u) acc[j] = fmaf(s_t[i][p0 + u], w[u], acc[j]);
     }
   }
 #pragma unroll
   for (int j = 0; j < RT; ++j) {
-    const int i = slot + SLOTS * j;
+    const int i = slot + MVF_SLOTS * j;
     if (live && i < m) a.Y[(int64_t)(row0 + i) * a.ldy + col] = acc[j];
   }
 }
 
-static int launch_finish(const MvfArgs& a, double bytes, hipStream_t st) {
-  const int64_t m = a.m;
+template <int M, int W>
+static void launch_finish_w(const MvfArgs& a, hipStream_t st) {
+  const dim3 grid((unsigned)((a.N + MVF_COLS - 1) / MVF_COLS), (unsigned)((a.m + M - 1) / M));
+  if (a.rank <= 16) hipLaunchKernelGGL((qmatvec_finish_kernel<M, W, 16>), grid, dim3(MVF_THREADS), 0, st, a);
+  else if (a.rank <= 64) hipLaunchKernelGGL((qmatvec_finish_kernel<M, W, 64>), grid, dim3(MVF_THREADS), 0, st, a);
+  else hipLaunchKernelGGL((qmatvec_finish_kernel<M, W, MVF_RANK_MAX>), grid, dim3(MVF_THREADS), 0, st, a);
+}
+// `ranges`: the most that a value of X Q or of T has.
+template <int M>
+static void launch_finish_m(const MvfArgs& a, int ranges, hipStream_t st) {
+  if (ranges <= 4) launch_finish_w<M, 4>(a, st);
+  else if (ranges <= 8) launch_finish_w<M, 8>(a, st);
+  else launch_finish_w<M, 16>(a, st);
+}
+// Which kernel, in us of whole calls (rows_finish_kernel / qmatvec_finish_kernel): the second up to 8 rows (4096 x 4096, 4 bits,
+// rank 64: 1 row 13.0 / 11.2, 8 rows 20.7 / 18.2; rank 512: 32.4 / 21.9, 49.7 / 35.9) and, the more ranks there are, for more rows
+// (24 rows: rank 8 12.1 / 12.3, rank 33 16.2 / 15.7, rank 64 19.1 / 17.6; 48 rows: rank 33 21.8 / 22.5, rank 64 23.6 / 23.1 or,
+// 4096 x 11008, level, rank 512 49.5 / 47.5; 128 rows: rank 16 41.1 / 42.3, rank 512 71.0 / 75.7).
+static int launch_finish(const MvfArgs& a, int ranges, double bytes, hipStream_t st) {
   prof::Scope ps(prof::MISC, st, bytes);
-  const unsigned gx = (unsigned)((a.N + MVF_COLS - 1) / MVF_COLS);
-  if (m <= 1) hipLaunchKernelGGL((qmatvec_finish_kernel<1>), dim3(gx), dim3(MVF_COLS), 0, st, a);
-  else if (m <= 2) hipLaunchKernelGGL((qmatvec_finish_kernel<2>), dim3(gx), dim3(2 * MVF_COLS), 0, st, a);
-  else if (m <= 4) hipLaunchKernelGGL((qmatvec_finish_kernel<4>), dim3(gx), dim3(4 * MVF_COLS), 0, st, a);
-  else hipLaunchKernelGGL((qmatvec_finish_kernel<8>), dim3(gx, (unsigned)((m + 7) / 8)), dim3(4 * MVF_COLS), 0, st, a);
+  if (a.m <= 1) launch_finish_m<1>(a, ranges, st);
+  else if (a.m <= 2) launch_finish_m<2>(a, ranges, st);
+  else if (a.m <= 4) launch_finish_m<4>(a, ranges, st);
+  else if (a.m <= 8 || (a.m <= 32 && a.rank > 16) || (a.m <= 64 && a.rank > 64)) launch_finish_m<8>(a, ranges, st);
+  else hipLaunchKernelGGL(rows_finish_kernel, dim3((unsigned)((a.N + MVF_COLS - 1) / MVF_COLS), (unsigned)((a.m + 7) / 8)),
+                          dim3(MVF_THREADS), 0, st, a);
   LQ_HIP_TRY(hipGetLastError());
   return LQ_OK;
 }
@@ -330,18 +465,19 @@ int launch_range_sum_lowrank(const float* part, size_t pstride, int splits, cons
                              float* Y, int64_t ldy, hipStream_t st) {
   if (m < 1 || N < 1 || splits < 1 || rank < 0 || rank > MVF_RANK_MAX || (rank > 0 && tsplits < 1)) return LQ_ERR_SHAPE;
   const MvfArgs a{part, pstride, splits, tpart, tstride, tld, tsplits, (int)m, N, rank, L2, ldl2, Y, ldy, 0, 1, 1, 1};
-  return launch_finish(a, 4.0 * ((double)splits * m * (double)N + (double)tsplits * m * rank + (double)rank * (double)N + m * (double)N), st);
+  return launch_finish(a, std::max(splits, tsplits), 4.0 * ((double)splits * m * (double)N + (double)tsplits * m * rank + (double)rank * (double)N + m * (double)N), st);
 }
 
 int launch_segment_sum_lowrank(const float* part, const float* tpart, int64_t m, int64_t N, int rank, const float* L2,
                                int64_t ldl2, float* Y, int64_t ldy, int steps, int per_wg, int tile_cols, int ttile_cols,
                                hipStream_t st) {
-  if (m < 1 || N < 1 || rank < 0 || rank > MVF_RANK_MAX || steps < 1 || per_wg < 1 || tile_cols % MVF_COLS || ttile_cols < 1)
+  if (m < 1 || N < 1 || rank < 0 || rank > MVF_RANK_MAX || steps < 1 || per_wg < 1 || tile_cols % MVF_COLS || ttile_cols % MVF_COLS ||
+      ttile_cols < 1)
     return LQ_ERR_SHAPE;
   const MvfArgs a{part, (size_t)m * (size_t)N, 1, tpart, (size_t)m * (size_t)rank, rank, 1, (int)m, N, rank, L2, ldl2, Y, ldy,
                   steps, per_wg, tile_cols, ttile_cols};
   const double segments = 1.0 + (double)steps / per_wg;
-  return launch_finish(a, 4.0 * (segments * m * (double)(N + rank) + (double)rank * (double)N + m * (double)N), st);
+  return launch_finish(a, (steps + per_wg - 2) / per_wg + 1, 4.0 * (segments * m * (double)(N + rank) + (double)rank * (double)N + m * (double)N), st);
 }
 
 // Reduction ranges for m rows against K x (N + rank) weights: at most 512 workgroups (with 8 rows two fit a CU, and a
