@@ -180,18 +180,37 @@ __global__ __launch_bounds__(64 * gram_waves(NT)) void gram_partial_kernel(const
 #undef LQ_GRAM_WAVE
 }
 
-// G = sum of the chunks in order; the tiles above the diagonal are mirrored.  One workgroup per tile pair and problem;
-// accumulator register r of a lane is row 4 r + lane / 16, column lane % 16.
-__global__ __launch_bounds__(256) void gram_reduce_kernel(const double* __restrict__ part, double* __restrict__ G, int l,
-                                                          int chunks) {
-  const int pair = blockIdx.x, z = blockIdx.y, tid = threadIdx.x;
+// G = sum of the chunks, the tiles above the diagonal mirrored.  One workgroup per accumulator register of a tile pair and
+// problem; register r of a lane is row 4 r + lane / 16, column lane % 16.  Bound by memory round trips: each of the up to
+// eight wavefronts adds a contiguous range of the chunks, GRAM_REDUCE_DEPTH in flight at a time, and the ranges are added in
+// order through LDS (one problem of 4096 columns, l = 128: 6.8 -> 4.5 us against one thread for all chunks of an element, l = 32:
+// 4.6 -> 3.3).
+constexpr int GRAM_REDUCE_DEPTH = 16, GRAM_REDUCE_WAVES = 8;
+__global__ __launch_bounds__(64 * GRAM_REDUCE_WAVES) void gram_reduce_kernel(const double* __restrict__ part, double* __restrict__ G,
+                                                                             int l, int chunks, int per_wave) {
+  __shared__ double s_sum[GRAM_REDUCE_WAVES][64];
+  const int pair = blockIdx.x >> 2, r = blockIdx.x & 3, pairs = gridDim.x >> 2, z = blockIdx.y;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), waves = blockDim.x >> 6;
   int ti = 0, tj = pair;
   while (tj > ti) { tj -= ti + 1; ++ti; }
-  const double* P = part + ((size_t)z * chunks * gridDim.x + pair) * 256 + tid;
+  const size_t pitch = (size_t)pairs * 256;
+  const double* P = part + ((size_t)z * chunks * pairs + pair) * 256 + 64 * r + lane;
+  const int c1 = (wave + 1) * per_wave < chunks ? (wave + 1) * per_wave : chunks;
   double s = 0.0;
-#pragma unroll 16
-  for (int c = 0; c < chunks; ++c) s += P[(size_t)c * gridDim.x * 256];
-  const int i = 16 * ti + 4 * (tid >> 6) + ((tid & 63) >> 4), j = 16 * tj + (tid & 15);
+  for (int c = wave * per_wave; c < c1; c += GRAM_REDUCE_DEPTH) {
+    double v[GRAM_REDUCE_DEPTH];
+#pragma unroll
+    for (int u = 0; u < GRAM_REDUCE_DEPTH; ++u) v[u] = P[(size_t)(c + u < c1 ? c + u : c1 - 1) * pitch];
+#pragma unroll
+    for (int u = 0; u < GRAM_REDUCE_DEPTH; ++u) s += c + u < c1 ? v[u] : 0.0;
+  }
+  if (waves > 1) {
+    s_sum[wave][lane] = s;
+    __syncthreads();
+    if (wave > 0) return;
+    for (int w = 1; w < waves; ++w) s += s_sum[w][lane];
+  }
+  const int i = 16 * ti + 4 * r + (lane >> 4), j = 16 * tj + (lane & 15);
   double* Gz = G + (size_t)z * l * l;
   Gz[(size_t)i * l + j] = s;
   if (ti != tj) Gz[(size_t)j * l + i] = s;
@@ -232,7 +251,9 @@ int launch_gram(const float* X, int l, int64_t m, int64_t ldx, size_t strideX, d
     default: return LQ_ERR_ARG;
   }
   LQ_HIP_TRY(hipGetLastError());
-  hipLaunchKernelGGL(gram_reduce_kernel, dim3(pairs, batch), dim3(256), 0, st, (const double*)part, G, l, (int)chunks);
+  const int waves = (int)std::min<int64_t>(GRAM_REDUCE_WAVES, (chunks + GRAM_REDUCE_DEPTH - 1) / GRAM_REDUCE_DEPTH);
+  hipLaunchKernelGGL(gram_reduce_kernel, dim3(4 * pairs, batch), dim3(64 * waves), 0, st, (const double*)part, G, l, (int)chunks,
+                     ((int)chunks + waves - 1) / waves);
   LQ_HIP_TRY(hipGetLastError());
   return LQ_OK;
 }

@@ -83,6 +83,25 @@ def test_gram_of_a_batch(l, m, batch, chunks):
     assert torch.isnan(g[batch]).all() and torch.isnan(part[nd])
 
 
+@pytest.mark.parametrize("l", [32, 96])
+@pytest.mark.parametrize("chunks", [1, 2, 15, 16, 17, 32, 33, 113, 127, 128])
+def test_gram_adds_every_chunk(l, chunks):
+    """Chunks of two groups of 16 columns, one to eight wavefronts that add them, the last range shorter than the others.
+    Tolerance as for a batch."""
+    import torch
+    L = load()
+    m, ld = 32 * chunks - 5, 32 * chunks
+    x = torch.full((l, ld), float("nan"), device="cuda")
+    x[:, :m] = torch.from_numpy(np.random.default_rng(chunks).standard_normal((l, m)).astype(np.float32)).cuda()
+    nd = l * l * 128
+    part = torch.full((nd,), float("nan"), dtype=torch.float64, device="cuda")
+    g = torch.empty((l, l), dtype=torch.float64, device="cuda")
+    assert L.lq_test_gram(x.data_ptr(), l, m, ld, 0, part.data_ptr(), nd, g.data_ptr(), 1, None) == 0
+    torch.cuda.synchronize()
+    v = x[:, :m].double().cpu().numpy()
+    assert np.all(np.abs(g.cpu().numpy() - v @ v.T) <= 2.0 ** -52 * m * (np.abs(v) @ np.abs(v).T))
+
+
 @pytest.mark.parametrize("l", [32, 64, 96, 128])
 @pytest.mark.parametrize("lower", [False, True])
 @pytest.mark.parametrize("batch,ld0,ld1", [(1, 32, 0), (3, 96, 0), (4, 160, 64), (2, 1056, 2080)])
