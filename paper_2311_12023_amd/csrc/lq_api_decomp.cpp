@@ -300,8 +300,10 @@ static int cold_factorize(const Ctx& c, const float* A, uint64_t seed, const flo
     }
     return m;
   };
-  double* res_dev = c.at<double>(pl.lam);     // squared residual norms of the top-r Ritz pairs (free until the warm passes)
-  std::vector<double> res(r, 0.0);
+  // squared residual norms of the top-r Ritz pairs: right before the Ritz values, so that both come to the host in one copy (the
+  // end of a region that is free until the warm passes)
+  double* res_dev = lam - r;
+  std::vector<double> res(r, 0.0), fetched(r + l);
   double last_est = 0.0;      // residual-based error estimate of the previous Rayleigh-Ritz (valid when rate_ok)
   for (int it = 0;;) {        // it: applications of M so far
     const bool check = it >= next_check || it >= pl.prm.maxit;
@@ -318,9 +320,10 @@ static int cold_factorize(const Ctx& c, const float* A, uint64_t seed, const flo
       LQ_TRY(apply_transpose(Ba, P[0], nullptr));
       LQ_TRY(launch_ritz_residual(P[0], Y0, lam, r, pl.d, pl.ldd, res_dev, c.st));
       have_g = true;
-      LQ_HIP_TRY(hipMemcpyAsync(cur.data(), lam, sizeof(double) * l, hipMemcpyDeviceToHost, c.st));
-      LQ_HIP_TRY(hipMemcpyAsync(res.data(), res_dev, sizeof(double) * r, hipMemcpyDeviceToHost, c.st));
+      LQ_HIP_TRY(hipMemcpyAsync(fetched.data(), res_dev, sizeof(double) * (r + l), hipMemcpyDeviceToHost, c.st));
       LQ_HIP_TRY(hipStreamSynchronize(c.st));
+      std::copy_n(fetched.begin(), r, res.begin());
+      std::copy_n(fetched.begin() + r, l, cur.begin());
       double delta = 0.0;
       for (int j = 0; j < r; ++j) {
         const double a = std::sqrt(cur[j]), b = std::sqrt(prev[j]);
@@ -502,19 +505,18 @@ static int residual_scale(Ctx& c) {
   const Plan& pl = c.pl;
   if (pl.prm.prec != 2) return LQ_OK;
   float* scratch = c.at<float>(pl.gram_part);
-  LQ_TRY(launch_absmax(c.W, pl.n, scratch, c.st));
+  // A launch leaves its result in element 1024, behind its partial maxima.  Each starts one element before the last one, on
+  // whose partial maxima, done with, its own lie: the results are neighbours and come to the host in one copy.
+  LQ_TRY(launch_absmax(c.W, pl.n, scratch + 2, c.st));
   if (c.weighted) {
-    LQ_TRY(launch_absmax(c.sr, pl.d, scratch + 1056, c.st));
-    LQ_TRY(launch_absmax(c.sc, pl.k, scratch + 2112, c.st));
+    LQ_TRY(launch_absmax(c.sr, pl.d, scratch + 1, c.st));
+    LQ_TRY(launch_absmax(c.sc, pl.k, scratch, c.st));
   }
-  float m[3] = {0.f, 1.f, 1.f};
-  LQ_HIP_TRY(hipMemcpyAsync(&m[0], scratch + 1024, sizeof(float), hipMemcpyDeviceToHost, c.st));
-  if (c.weighted) {
-    LQ_HIP_TRY(hipMemcpyAsync(&m[1], scratch + 1056 + 1024, sizeof(float), hipMemcpyDeviceToHost, c.st));
-    LQ_HIP_TRY(hipMemcpyAsync(&m[2], scratch + 2112 + 1024, sizeof(float), hipMemcpyDeviceToHost, c.st));
-  }
+  float m[3] = {1.f, 1.f, 0.f};
+  const int first = c.weighted ? 0 : 2;
+  LQ_HIP_TRY(hipMemcpyAsync(m + first, scratch + 1024 + first, sizeof(float) * (3 - first), hipMemcpyDeviceToHost, c.st));
   LQ_HIP_TRY(hipStreamSynchronize(c.st));
-  const double top = (double)m[0] * m[1] * m[2];
+  const double top = (double)m[2] * m[1] * m[0];
   c.a_scale = (top > 0.0 && std::isfinite(top)) ? (float)std::ldexp(1.0, 9 - std::ilogb(top)) : 1.0f;
   if (!(c.a_scale > 0.0f) || !std::isfinite(c.a_scale)) c.a_scale = 1.0f;
   return LQ_OK;
@@ -633,7 +635,7 @@ struct Loop {
     a.blk = c->at<BlockRec>(pl.blk); a.strideBlk = pl.strideBlk;
     a.err_part = c->at<double>(pl.epart); a.strideErrPart = pl.strideEpart;
     errs = c->at<double>(pl.errs);
-    a.strideErrOut = MAX_ITERS;
+    a.strideErrOut = iters;
     set_first(Y1, B1);
     return LQ_OK;
   }
@@ -772,17 +774,17 @@ struct Loop {
       a.R = nullptr; a.Qd = direct->Qd; a.strideQd = 0;
       LQ_TRY(launch_residual(a, c->st));
     }
-    host_err.assign((size_t)batch * MAX_ITERS, 0.0);
-    for (int b = 0; b < batch; ++b)   // only the used prefix of every row
-      LQ_HIP_TRY(hipMemcpyAsync(host_err.data() + (size_t)b * MAX_ITERS, errs + (size_t)b * MAX_ITERS,
-                                sizeof(double) * done, hipMemcpyDeviceToHost, c->st));
+    host_err.assign((size_t)batch * iters, 0.0);
+    if (done > 0)
+      LQ_HIP_TRY(hipMemcpyAsync(host_err.data(), errs, sizeof(double) * ((size_t)(batch - 1) * iters + done),
+                                hipMemcpyDeviceToHost, c->st));
     LQ_HIP_TRY(hipStreamSynchronize(c->st));
     for (int b = 0; b < batch; ++b) {
       int nd = done;
       int best = done;
       if (early_stop && batch > 1) {         // lock-step batches apply the rule after the fact
         for (int t = 1; t < done; ++t)
-          if (host_err[(size_t)b * MAX_ITERS + t] > host_err[(size_t)b * MAX_ITERS + t - 1]) {
+          if (host_err[(size_t)b * iters + t] > host_err[(size_t)b * iters + t - 1]) {
             nd = t + 1;
             best = early_stop == 2 ? t : t + 1;
             break;
@@ -795,7 +797,7 @@ struct Loop {
       if (trace)
         for (int t = 0; t < iters; ++t)
           trace[(size_t)b * iters + t] =
-              (t < nd && (want_trace || early_stop || t == iters - 1)) ? host_err[(size_t)b * MAX_ITERS + t] : NAN;
+              (t < nd && (want_trace || early_stop || t == iters - 1)) ? host_err[(size_t)b * iters + t] : NAN;
     }
     return LQ_OK;
   }
@@ -840,17 +842,24 @@ struct StreamLease {            // also owns the event the sub-batches wait for
   }
 };
 
-static int emit_factors(const Ctx& c, const float* Y, const float* B, const double* lam, float* L1, float* L2,
-                        double* sigma_host) {
+static int assemble_factors(const Ctx& c, const float* Y, const float* B, const double* lam, float* L1, float* L2) {
   const Plan& pl = c.pl;
-  LQ_TRY(launch_assemble_factors(Y, pl.ldd, B, pl.ldk, lam, pl.rank, pl.d, pl.k,
-                                 c.rsr, c.rsc, L1, L2, c.st));
+  return launch_assemble_factors(Y, pl.ldd, B, pl.ldk, lam, pl.rank, pl.d, pl.k, c.rsr, c.rsc, L1, L2, c.st);
+}
+// The singular values, on the host (synchronizes the stream).
+static int fetch_sigma(const Ctx& c, const double* lam, double* sigma_host) {
+  const Plan& pl = c.pl;
   std::vector<double> lamh(pl.rank);
   LQ_HIP_TRY(hipMemcpyAsync(lamh.data(), lam, sizeof(double) * pl.rank, hipMemcpyDeviceToHost, c.st));
   LQ_HIP_TRY(hipStreamSynchronize(c.st));
   if (sigma_host)
     for (int j = 0; j < pl.rank; ++j) sigma_host[j] = std::sqrt(lamh[j]);
   return LQ_OK;
+}
+static int emit_factors(const Ctx& c, const float* Y, const float* B, const double* lam, float* L1, float* L2,
+                        double* sigma_host) {
+  LQ_TRY(assemble_factors(c, Y, B, lam, L1, L2));
+  return fetch_sigma(c, lam, sigma_host);
 }
 
 static bool aligned16(const void* p) { return ((uintptr_t)p & 15) == 0; }
@@ -940,8 +949,9 @@ int lq_decompose(const float* W, int64_t d, int64_t k, int rank, lq_config cfg, 
   lp.set_first(Y1, B1);
   for (int t = 1; t <= iters; ++t) LQ_TRY(lp.step(t));
   int32_t best = 0;
+  if (!lp.keep_best()) LQ_TRY(assemble_factors(c, lp.Ycur, lp.Bcur, lp.lamcur, L1, L2));    // before finish() waits for the stream
   LQ_TRY(lp.finish(trace.data(), &done, &best));
-  if (!lp.keep_best()) LQ_TRY(emit_factors(c, lp.Ycur, lp.Bcur, lp.lamcur, L1, L2, sigma));
+  if (!lp.keep_best()) LQ_TRY(fetch_sigma(c, lp.lamcur, sigma));
   if (err) *err = trace[best - 1];
   if (err_trace) std::memcpy(err_trace, trace.data(), sizeof(double) * iters);
   if (iters_done) *iters_done = done;
