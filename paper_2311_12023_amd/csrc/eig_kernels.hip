@@ -8,6 +8,7 @@
 namespace lq {
 
 constexpr int EIG_THREADS = 256;
+typedef double doublex2 __attribute__((ext_vector_type(2)));   // native vector: arrays of it stay in registers
 
 // Sums of N values over the 16 lanes of a DPP row with the values dealt out on the way: each of the first log2(N) steps
 // hands half of a lane's values to its partner, so a lane ends with the total of value row_sum_index<N>(lane) alone.
@@ -177,7 +178,7 @@ __device__ void jacobi_onesided(const double* __restrict__ G, double mscale, flo
 // l = 96 687 -> 193 -> 138, l = 128 1491 -> 275 -> 210: one-sided Jacobi with 8 l threads, whose six to nine sweeps of l - 1
 // rounds are bound by LDS bandwidth (every round reads and writes X and V); this route with a chain of two wavefront sums and
 // roots per column before anything else, 34 rounds of trisection and reciprocal pivots in memory behind branches; and as it
-// is.  Rayleigh quotients come out 10 to 70 times closer than Jacobi's, because G stays in fp64.  At l = 128 the phases take 275,
+// was with the vectors in the same launch (EIG_HANDS_ON has them now).  Rayleigh quotients come out 10 to 70 times closer than Jacobi's, because G stays in fp64.  At l = 128 the phases take 275,
 // 61, 47 and 94 thousand cycles (tridiagonal form, eigenvalues, vectors, back-transformation): a column is 1400 cycles of
 // latency, by what it takes at l = 32, and its share of 3 l^2 fp64 operations.
 //
@@ -212,6 +213,18 @@ __device__ __forceinline__ int sturm(const double2* de, double x, double& f, int
   f = pb;
   return count;
 }
+
+// From l = 96 on the vectors of separated eigenvalues take a launch of their own with a workgroup for every 16 of them: one
+// workgroup's pivots do not fit LDS beside the reflectors, and its l / 32 vectors per 8 lanes are a third of its time (one problem, as
+// traced beside the rest of a call: l = 128 212 -> 149 + 36 us, l = 96 147 -> 110 + 27; at l = 64 and below everything is in LDS
+// and the whole solve takes 80 us).  What is handed on lies in the scratch: the reflectors from the diagonal block on (block row jb: 16 rows of l - 16 jb), then this.
+template <int NE> constexpr bool EIG_HANDS_ON = NE > 4;
+template <int NE> constexpr __host__ __device__ int packed_block(int jb) { return 256 * (jb * NE - jb * (jb - 1) / 2); }
+template <int NE>
+struct EigHandOn { double2 de[16 * NE + 1]; double e[16 * NE], h[16 * NE], lam[16 * NE], bound; };
+// Stands in the first element of row l - 1 - 16 b of Ut until workgroup b of the second launch has read it (a quiet NaN that no
+// arithmetic here makes); where the first launch has written the rows itself, the second leaves them.
+constexpr unsigned EIG_HANDED_ON = 0x7fc5e16eu;
 
 template <int NE>
 __global__ __launch_bounds__(EIG_THREADS) void sym_eig_kernel(const double* __restrict__ Gall, double* __restrict__ work,
@@ -481,6 +494,21 @@ __global__ __launch_bounds__(EIG_THREADS) void sym_eig_kernel(const double* __re
   if (tid < l - 1) close = !(s_lam[tid + 1] - s_lam[tid] > 2e-9 * bound);
   const bool clustered = __syncthreads_or(close);
   if (tid < l) lam[l - 1 - tid] = fmax(s_lam[tid], 0.0) / mscale;
+  if constexpr (EIG_HANDS_ON<NE>) {
+    if (!clustered) {                          // the vectors are eig_vectors_kernel's
+      double* const out = work + (size_t)z * 2 * l * l;
+      for_each_block<NE>([&](auto block) {
+        constexpr int jb = decltype(block)::value, W = l - 16 * jb;
+        for (int i = tid; i < 16 * W; i += EIG_THREADS) out[packed_block<NE>(jb) + i] = Vr[(16 * jb + i / W) * l + 16 * jb + i % W];
+      });
+      EigHandOn<NE>& on = *reinterpret_cast<EigHandOn<NE>*>(out + packed_block<NE>(NE));
+      if (tid <= l) on.de[tid] = s_de[tid];
+      if (tid < l) { on.e[tid] = s_e[tid]; on.h[tid] = s_h[tid]; on.lam[tid] = s_lam[tid]; }
+      if (tid == 0) on.bound = bound;
+      if (tid < NE) reinterpret_cast<unsigned*>(Ut)[(l - 1 - 16 * tid) * l] = EIG_HANDED_ON;
+      return;
+    }
+  }
 
   // Eigenvectors of the tridiagonal matrix: T - lambda = L D+ L^T from the top (lower half of the threads) and U D- U^T
   // from the bottom (upper half), joined at the index k where |gamma_k| is smallest.  The reciprocal pivots go through
@@ -684,6 +712,172 @@ __global__ __launch_bounds__(EIG_THREADS) void sym_eig_kernel(const double* __re
   }
 }
 
+// Eigenvectors 16 b .. 16 b + 15 (ascending) of a problem whose tridiagonal form and eigenvalues sym_eig_kernel has handed on:
+// the same twisted factorisation, two lanes of the first wavefront per vector, with the pivots in LDS, while the reflectors are on their way;
+// then 16 lanes per vector apply those, entries 32 m + 2 tx + {0, 1}.
+template <int NE>
+__global__ __launch_bounds__(EIG_THREADS, 2) void eig_vectors_kernel(const double* __restrict__ work, float* __restrict__ Utall) {
+  constexpr int l = 16 * NE, PK = packed_block<NE>(NE);
+  extern __shared__ __attribute__((aligned(16))) double lds[];
+  double* piv = lds;                                         // pivots, [2][l][16]
+  double* Vp = lds;                                          // then the packed reflectors
+  __shared__ double2 s_de[l + 1];
+  __shared__ double s_e[l], s_h[l], s_best[16][16], s_sum[2][16];
+  __shared__ int s_at[16][16], s_k[16];
+  const int b = blockIdx.x, z = blockIdx.y, tid = threadIdx.x, ty = tid >> 4, tx = tid & 15;
+  float* Ut = Utall + (size_t)z * l * l;
+  const unsigned mark = reinterpret_cast<const unsigned*>(Ut)[(l - 1 - 16 * b) * l];
+  if (mark != EIG_HANDED_ON) return;                         // the same word for all of the workgroup
+  __builtin_amdgcn_s_setprio(3);
+  const double* in = work + (size_t)z * 2 * l * l;
+  const EigHandOn<NE>& on = *reinterpret_cast<const EigHandOn<NE>*>(in + PK);
+  if (tid <= l) s_de[tid] = on.de[tid];
+  if (tid < l) { s_e[tid] = on.e[tid]; s_h[tid] = on.h[tid]; }
+  const double bound = on.bound, tiny = 1e-30 * bound, lg = on.lam[16 * b + tx];
+  constexpr int PIECES = (PK / 2 + EIG_THREADS - 1) / EIG_THREADS;
+  doublex2 held[PIECES];                                     // in flight behind the factorisation, whose LDS they take over
+#pragma unroll
+  for (int i = 0; i < PIECES; ++i) {
+    const int at = tid + EIG_THREADS * i;
+    held[i] = reinterpret_cast<const doublex2*>(in)[at < PK / 2 ? at : 0];
+  }
+  __syncthreads();
+  const int half = ty & 1;                                   // 0: from the top, 1: from the bottom
+  if (tid < 32) {
+    auto pivot = [&](double D) { return rcp64(fabs(D) > tiny ? D : copysign(tiny, D)); };
+    const int step = half ? -1 : 1, first = half ? l - 1 : 0;
+    double r = 0.0;
+#pragma nounroll
+    for (int s0 = 0; s0 < l; s0 += 16) {       // loads by hand in front of stores that they might alias for all the compiler knows
+      const int i0 = first + step * s0;
+      double x[16], y[16];
+#pragma unroll
+      for (int s = 0; s < 16; ++s) { x[s] = s_de[i0 + step * s].x - lg; y[s] = -s_de[i0 + step * s + half].y; }
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int s = 0; s < 16; ++s) {
+        r = pivot(fma(y[s], r, x[s]));
+        piv[(half * l + i0 + step * s) * 16 + tx] = r;
+      }
+    }
+  }
+  __syncthreads();
+  {
+    double best = INFINITY;
+    int at = ty;
+#pragma unroll
+    for (int s = 0; s < NE; ++s) {
+      const int i = ty + 16 * s;
+      const double up = i > 0 ? piv[(i > 0 ? i - 1 : 0) * 16 + tx] : 0.0, dn = i + 1 < l ? piv[(l + (i + 1 < l ? i + 1 : i)) * 16 + tx] : 0.0;
+      const double ga = fabs((s_de[i].x - lg) - s_de[i].y * up - s_de[i + 1].y * dn);
+      if (ga < best) { best = ga; at = i; }
+    }
+    s_best[ty][tx] = best; s_at[ty][tx] = at;
+  }
+  __syncthreads();
+  if (tid < 32) {
+    double best = s_best[0][tx];
+    int k = s_at[0][tx];
+#pragma unroll
+    for (int p = 1; p < 16; ++p)
+      if (s_best[p][tx] < best) { best = s_best[p][tx]; k = s_at[p][tx]; }
+    if (half == 0) s_k[tx] = k;
+    double zz = 1.0, sum = half == 0 ? 1.0 : 0.0;
+    const int step = half ? 1 : -1, first = half ? 0 : l - 1;
+#pragma nounroll
+    for (int s0 = 0; s0 < l; s0 += 16) {       // away from k; every element is stored, those of the other half as they were
+      const int i0 = first + step * s0;
+      double* at = piv + (half * l + i0) * 16 + tx;
+      double r[16], m[16];
+#pragma unroll
+      for (int s = 0; s < 16; ++s) {
+        const int ie = i0 + step * s - half;
+        r[s] = at[16 * step * s];
+        m[s] = -s_e[ie > 0 ? ie : 0] * r[s];
+      }
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int s = 0; s < 16; ++s) {
+        const int i = i0 + step * s;
+        const bool mine = half ? i > k : i < k;
+        zz *= mine ? m[s] : 1.0;
+        const double t = mine ? zz : 0.0;
+        sum = fma(t, t, sum);
+        at[16 * step * s] = mine || i == k ? zz : r[s];
+      }
+    }
+    s_sum[half][tx] = sum;
+  }
+  __syncthreads();
+  const int k = s_k[ty], M = NE / 2;
+  const double inv = rsqrt64(s_sum[0][ty] + s_sum[1][ty]);
+  double u[NE / 2][2];
+#pragma unroll
+  for (int m = 0; m < M; ++m)
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      const int i = 32 * m + 2 * tx + q;
+      u[m][q] = piv[((i <= k ? 0 : l) + i) * 16 + ty] * inv;
+    }
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < PIECES; ++i) {
+    const int at = tid + EIG_THREADS * i;
+    if (at < PK / 2) reinterpret_cast<doublex2*>(Vp)[at] = held[i];
+  }
+  __syncthreads();
+  for_each_block_down<NE>([&](auto block) {
+    constexpr int jb = decltype(block)::value, W = l - 16 * jb, M0 = jb / 2;
+    const double* rows = Vp + packed_block<NE>(jb);
+    double h1, h0, n1, n0;
+    double2 w1[NE / 2], w0[NE / 2], next1[NE / 2], next0[NE / 2];
+    auto fetch = [&](int jt) {
+      n1 = s_h[16 * jb + jt]; n0 = s_h[16 * jb + jt - 1];
+#pragma unroll
+      for (int m = M0; m < NE / 2; ++m) {
+        const int at = (jb & 1) && m == M0 && tx < 8 ? 0 : 32 * m + 2 * tx - 16 * jb;
+        next1[m] = *reinterpret_cast<const double2*>(rows + jt * W + at);
+        next0[m] = *reinterpret_cast<const double2*>(rows + (jt - 1) * W + at);
+      }
+    };
+    fetch(15);
+#pragma nounroll
+    for (int jt = 15; jt >= 1; jt -= 2) {      // H_j, then H_{j-1}: their sums over a vector are taken together
+      h1 = n1; h0 = n0;
+#pragma unroll
+      for (int m = M0; m < NE / 2; ++m) {
+        const bool before = (jb & 1) && m == M0 && tx < 8;                 // columns in front of the block row
+        w1[m] = before ? make_double2(0.0, 0.0) : next1[m];
+        w0[m] = before ? make_double2(0.0, 0.0) : next0[m];
+      }
+      fetch(jt > 2 ? jt - 2 : 1);
+      __builtin_amdgcn_sched_barrier(0);
+      double c = 0.0, d1 = 0.0, d0 = 0.0;
+#pragma unroll
+      for (int m = M0; m < NE / 2; ++m) {
+        c = fma(w1[m].x, w0[m].x, fma(w1[m].y, w0[m].y, c));
+        d1 = fma(w1[m].x, u[m][0], fma(w1[m].y, u[m][1], d1));
+        d0 = fma(w0[m].x, u[m][0], fma(w0[m].y, u[m][1], d0));
+      }
+      auto sum16 = [](double x) {
+        x += dpp_move<XOR1>(x); x += dpp_move<XOR2>(x); x += dpp_move<XOR7>(x);
+        return x + dpp_move<XOR15>(x);
+      };
+      c = sum16(c);
+      d1 = -h1 * sum16(d1);
+      d0 = -h0 * fma(d1, c, sum16(d0));
+#pragma unroll
+      for (int m = M0; m < NE / 2; ++m) {
+        u[m][0] = fma(d0, w0[m].x, fma(d1, w1[m].x, u[m][0]));
+        u[m][1] = fma(d0, w0[m].y, fma(d1, w1[m].y, u[m][1]));
+      }
+    }
+  });
+#pragma unroll
+  for (int m = 0; m < M; ++m)
+    *reinterpret_cast<float2*>(Ut + (size_t)(l - 1 - 16 * b - ty) * l + 32 * m + 2 * tx) = make_float2((float)u[m][0], (float)u[m][1]);
+}
+
 bool sym_eig_supported(int l) { return l % 32 == 0 && l >= 32 && l <= 128; }
 
 template <int NE>
@@ -696,6 +890,15 @@ static int launch_eig(const double* G, double* work, float* Ut, double* lambda, 
   LQ_TRY(limit.raise(reinterpret_cast<const void*>(sym_eig_kernel<NE>), need));
   hipLaunchKernelGGL((sym_eig_kernel<NE>), dim3(batch), dim3(EIG_THREADS), need, st, G, work, Ut, lambda);
   LQ_HIP_TRY(hipGetLastError());
+  if constexpr (EIG_HANDS_ON<NE>) {
+    constexpr size_t lds = (size_t)std::max(packed_block<NE>(NE), 32 * l) * sizeof(double);
+    if constexpr (lds > 57344) {               // beside what the kernel has without asking
+      static LdsLimit vectors;
+      LQ_TRY(vectors.raise(reinterpret_cast<const void*>(eig_vectors_kernel<NE>), lds));
+    }
+    hipLaunchKernelGGL((eig_vectors_kernel<NE>), dim3(NE, batch), dim3(EIG_THREADS), lds, st, work, Ut);
+    LQ_HIP_TRY(hipGetLastError());
+  }
   return LQ_OK;
 }
 
