@@ -1,6 +1,6 @@
 // Forward product with a decomposed weight for 9 to 128 rows of X (decoding many sequences at once, short prompts):
 // Y[m x N] = X dequant(codes) + (X L1) L2.  Two launches: the kernel below multiplies X with [Q | L1]
-// over ranges of the reduction, qmatvec_finish_kernel adds the ranges and the product (X L1) L2.
+// over ranges of the reduction, qmatvec_finish_kernel or rows_finish_kernel adds the ranges and the product (X L1) L2.
 //
 // Every weight is decoded (six vector instructions: extract, look up, scale, split into bf16 halves) for at most 48 rows,
 // where its matrix instructions take less time than the decode; the codes themselves are 0.25 to 1 byte per weight.  By
