@@ -221,10 +221,9 @@ __device__ __forceinline__ int sturm(const double2* de, double x, double& f, int
 template <int NE> constexpr bool EIG_HANDS_ON = NE > 4;
 template <int NE> constexpr __host__ __device__ int packed_block(int jb) { return 256 * (jb * NE - jb * (jb - 1) / 2); }
 template <int NE>
-struct EigHandOn { double2 de[16 * NE + 1]; double e[16 * NE], h[16 * NE], lam[16 * NE], bound; };
-// Stands in the first element of row l - 1 - 16 b of Ut until workgroup b of the second launch has read it (a quiet NaN that no
-// arithmetic here makes); where the first launch has written the rows itself, the second leaves them.
-constexpr unsigned EIG_HANDED_ON = 0x7fc5e16eu;
+struct EigHandOn { double2 de[16 * NE + 1]; double e[16 * NE], h[16 * NE], lam[16 * NE], bound; int vectors_wanted; };
+// vectors_wanted is written by the first launch for every problem, whatever the scratch held: 0 where that launch has made the
+// vectors itself (which it says once it is done with the pivots, whose place this is).
 
 template <int NE>
 __global__ __launch_bounds__(EIG_THREADS) void sym_eig_kernel(const double* __restrict__ Gall, double* __restrict__ work,
@@ -504,8 +503,7 @@ __global__ __launch_bounds__(EIG_THREADS) void sym_eig_kernel(const double* __re
       EigHandOn<NE>& on = *reinterpret_cast<EigHandOn<NE>*>(out + packed_block<NE>(NE));
       if (tid <= l) on.de[tid] = s_de[tid];
       if (tid < l) { on.e[tid] = s_e[tid]; on.h[tid] = s_h[tid]; on.lam[tid] = s_lam[tid]; }
-      if (tid == 0) on.bound = bound;
-      if (tid < NE) reinterpret_cast<unsigned*>(Ut)[(l - 1 - 16 * tid) * l] = EIG_HANDED_ON;
+      if (tid == 0) { on.bound = bound; on.vectors_wanted = 1; }
       return;
     }
   }
@@ -647,6 +645,9 @@ __global__ __launch_bounds__(EIG_THREADS) void sym_eig_kernel(const double* __re
   constexpr int PU = l + 2;
   double* Us = lds;
   __syncthreads();
+  if constexpr (EIG_HANDS_ON<NE>) {
+    if (tid == 0) reinterpret_cast<EigHandOn<NE>*>(work + (size_t)z * 2 * l * l + packed_block<NE>(NE))->vectors_wanted = 0;
+  }
 #pragma unroll
   for (int v = 0; v < NV; ++v)
 #pragma unroll
@@ -726,11 +727,10 @@ __global__ __launch_bounds__(EIG_THREADS, 2) void eig_vectors_kernel(const doubl
   __shared__ int s_at[16][16], s_k[16];
   const int b = blockIdx.x, z = blockIdx.y, tid = threadIdx.x, ty = tid >> 4, tx = tid & 15;
   float* Ut = Utall + (size_t)z * l * l;
-  const unsigned mark = reinterpret_cast<const unsigned*>(Ut)[(l - 1 - 16 * b) * l];
-  if (mark != EIG_HANDED_ON) return;                         // the same word for all of the workgroup
-  __builtin_amdgcn_s_setprio(3);
   const double* in = work + (size_t)z * 2 * l * l;
   const EigHandOn<NE>& on = *reinterpret_cast<const EigHandOn<NE>*>(in + PK);
+  if (on.vectors_wanted != 1) return;                        // the same for all of the problem's workgroups
+  __builtin_amdgcn_s_setprio(3);
   if (tid <= l) s_de[tid] = on.de[tid];
   if (tid < l) { s_e[tid] = on.e[tid]; s_h[tid] = on.h[tid]; }
   const double bound = on.bound, tiny = 1e-30 * bound, lg = on.lam[16 * b + tx];

@@ -105,6 +105,31 @@ def test_problems_of_a_batch_are_independent(l):
         assert np.array_equal(lam[i].cpu().numpy(), lam1), kinds[i]
 
 
+@pytest.mark.parametrize("l", [96, 128])
+def test_which_launch_makes_the_vectors(l):
+    """From l = 96 on the vectors of separated eigenvalues come from a second launch.  Whether a problem has left them to it is
+    said by a word of the scratch, which is written for every problem, and not by what stood in Ut before."""
+    import torch
+    L = load()
+    rng = np.random.default_rng(l)
+    q, _ = np.linalg.qr(rng.standard_normal((l, l)))
+    work = torch.full((2 * l * l,), float("nan"), dtype=torch.float64, device="cuda")
+    lam = torch.empty(l, dtype=torch.float64, device="cuda")
+    ne = l // 16                             # behind the packed reflectors, {d, e^2}, e, h, the eigenvalues and their bound
+    at = 8 * 256 * (ne * ne - ne * (ne - 1) // 2) + 16 * (l + 1) + 3 * 8 * l + 8
+    wanted = work.view(torch.int32)[at // 4]
+    for kind, second in (("flat", 1), ("noise_floor", 0), ("smallest_gap", 1), ("repeated", 0)):
+        g = (q * _spectrum(kind, l, rng)) @ q.T
+        g = (g + g.T) / 2
+        gt = torch.from_numpy(g.copy()).cuda()
+        wanted.fill_(7)
+        ut = torch.full((l, l), float("nan"), dtype=torch.float32, device="cuda")
+        assert L.lq_test_sym_eig_batch(gt.data_ptr(), l, 1, work.data_ptr(), ut.data_ptr(), lam.data_ptr(), None) == 0
+        assert wanted.item() == second, kind
+        u = ut.cpu().numpy().astype(np.float64)
+        assert np.max(np.abs(u @ u.T - np.eye(l))) < 4e-6, kind
+
+
 @pytest.mark.parametrize("l", [32, 64, 96, 128])
 @pytest.mark.parametrize("seed", range(4))
 def test_eigenvalues_of_nested_clusters(l, seed):
