@@ -93,6 +93,9 @@ int lq_test_ritz_residual(const float* G, const float* Y, const double* lam, int
 int lq_test_bucket_code(int bits, float x);
 /* Host-side evaluation of the division-free v / levels of the forward product's kernels.  Needs no GPU. */
 float lq_test_sigma_by_reciprocal(float v, int levels);
+/* 1 where the launch that adds a forward product's ranges for m rows and N columns is rows_finish_kernel, 0 where it is
+ * qmatvec_finish_kernel.  Needs no GPU. */
+int lq_test_rows_finish(int64_t m, int64_t N, int rank);
 /* Largest LDS allocation per workgroup the device reports, in bytes. */
 size_t lq_test_lds_limit(void);
 /* Arms a capture for the next lq_error_table call of this host thread (of the testing library): after iteration `iter`

@@ -155,6 +155,8 @@ int launch_qmatvec(const MvWeights& q, const float* X, int64_t ldx, int64_t K, c
 int launch_range_sum_lowrank(const float* part, size_t pstride, int splits, const float* tpart, size_t tstride,
                              int64_t tld, int tsplits, int64_t m, int64_t N, int rank, const float* L2, int64_t ldl2,
                              float* Y, int64_t ldy, hipStream_t st);
+// Which of two kernels takes that sum for m rows (the same results up to the order of the rank's products).
+bool rows_finish_preferred(int64_t m, int64_t N, int rank);
 // The same sum where column tiles have segments of their own number: the steps of all tiles (tile_cols columns of X Q
 // each, then tiles of ttile_cols columns of T), `steps` per tile, were dealt out in shares of per_wg; segment z of a tile
 // lies at part + z * m * N, at tpart + z * m * rank for T.

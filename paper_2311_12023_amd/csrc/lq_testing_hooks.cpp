@@ -178,6 +178,8 @@ float lq_test_sigma_by_reciprocal(float v, int levels) {
   return sigma_by_reciprocal(v, (float)levels, 1.0f / (float)levels);
 }
 
+int lq_test_rows_finish(int64_t m, int64_t N, int rank) { return rows_finish_preferred(m, N, rank); }
+
 size_t lq_test_lds_limit(void) { return lds_limit_for_tests(); }
 
 }  // extern "C"

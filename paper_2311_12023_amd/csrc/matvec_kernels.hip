@@ -430,6 +430,8 @@ __global__ __launch_bounds__(MVF_THREADS) void rows_finish_kernel(MvfArgs a) {
   }
 }
 
+// Three sizes of T in LDS: with room for 512 ranks where 16 or 64 would do a call takes up to 4 % longer (4096 x 4096, rank 16,
+// 8 rows 16.0 -> 16.7 us; rank 64, 1 row 11.1 -> 11.5).
 template <int M, int W>
 static void launch_finish_w(const MvfArgs& a, hipStream_t st) {
   const dim3 grid((unsigned)((a.N + MVF_COLS - 1) / MVF_COLS), (unsigned)((a.m + M - 1) / M));
@@ -437,25 +439,39 @@ static void launch_finish_w(const MvfArgs& a, hipStream_t st) {
   else if (a.rank <= 64) hipLaunchKernelGGL((qmatvec_finish_kernel<M, W, 64>), grid, dim3(MVF_THREADS), 0, st, a);
   else hipLaunchKernelGGL((qmatvec_finish_kernel<M, W, MVF_RANK_MAX>), grid, dim3(MVF_THREADS), 0, st, a);
 }
-// `ranges`: the most that a value of X Q or of T has.
+// `ranges`: the most that a value of X Q or of T has.  As many in flight as there are, up to 16: with 8 where there are 16 or more
+// a call takes 4 to 26 % longer (4096 x 4096, rank 512, 1 row 21.0 -> 24.4 us; rank 64, 8 rows 16.7 -> 18.0), with 16 where there
+// are 3 or 4 up to 19 % (2048 x 28672, rank 64, 8 rows 35.1 -> 36.6, rank 512 50.4 -> 60.2).
 template <int M>
 static void launch_finish_m(const MvfArgs& a, int ranges, hipStream_t st) {
   if (ranges <= 4) launch_finish_w<M, 4>(a, st);
   else if (ranges <= 8) launch_finish_w<M, 8>(a, st);
   else launch_finish_w<M, 16>(a, st);
 }
-// Which kernel, in us of whole calls (rows_finish_kernel / qmatvec_finish_kernel): the second up to 8 rows (4096 x 4096, 4 bits,
-// rank 64: 1 row 13.0 / 11.2, 8 rows 20.7 / 18.2; rank 512: 32.4 / 21.9, 49.7 / 35.9) and, the more ranks there are, for more rows
-// (24 rows: rank 8 12.1 / 12.3, rank 33 16.2 / 15.7, rank 64 19.1 / 17.6; 48 rows: rank 33 21.8 / 22.5, rank 64 23.6 / 23.1 or,
-// 4096 x 11008, level, rank 512 49.5 / 47.5; 128 rows: rank 16 41.1 / 42.3, rank 512 71.0 / 75.7).
+// Whether rows_finish_kernel is the faster one.  qmatvec_finish_kernel saves round trips, which count while the machine is not
+// full, and pays for them with work on ranks past the last (it takes them 64 at a time, the other 32), which counts once it is.
+// Measured as whole calls of 9 to 64 rows x 768 to 28672 columns x reductions of 1024 to 8192 x ranks of 8 to 512, 4 bits, by the
+// number of workgroups of 8 rows x 64 columns: with the last 64 ranks more than half full and no more of them it is 7 % faster
+// up to 256 workgroups, 3 % up to 512, 1.5 % up to 768 and 1 to 4 % slower beyond; with more ranks 8 to 20 %, 3 to 7 %, level, and
+// up to 22 % slower; with the last 64 less than half full 1 to 8 % faster up to 256 and slower beyond (ranks above 64), 3 to 6 %
+// slower everywhere (17 to 32) or level and slower (up to 16).  Up to 8 rows it is the faster one throughout (4096 x 4096, rank 64,
+// 1 row 13.0 -> 11.2 us, 8 rows 20.7 -> 18.2; rank 512 32.4 -> 21.9, 49.7 -> 35.9); what it costs there past 1024 workgroups, at
+// one or two rows and ranks just above a multiple of 64, is up to 5 % (1024 x 131072, rank 17, 1 row: 31.7 -> 33.0).
+bool rows_finish_preferred(int64_t m, int64_t N, int rank) {
+  if (m <= 8) return false;
+  if (m > 64 || rank <= 32) return true;
+  const int64_t workgroups = (N + MVF_COLS - 1) / MVF_COLS * ((m + 7) / 8);
+  return workgroups > ((rank - 1) % 64 < 32 ? 256 : rank <= 64 ? 768 : 512);
+}
 static int launch_finish(const MvfArgs& a, int ranges, double bytes, hipStream_t st) {
   prof::Scope ps(prof::MISC, st, bytes);
-  if (a.m <= 1) launch_finish_m<1>(a, ranges, st);
+  if (rows_finish_preferred(a.m, a.N, a.rank))
+    hipLaunchKernelGGL(rows_finish_kernel, dim3((unsigned)((a.N + MVF_COLS - 1) / MVF_COLS), (unsigned)((a.m + 7) / 8)),
+                       dim3(MVF_THREADS), 0, st, a);
+  else if (a.m <= 1) launch_finish_m<1>(a, ranges, st);
   else if (a.m <= 2) launch_finish_m<2>(a, ranges, st);
   else if (a.m <= 4) launch_finish_m<4>(a, ranges, st);
-  else if (a.m <= 8 || (a.m <= 32 && a.rank > 16) || (a.m <= 64 && a.rank > 64)) launch_finish_m<8>(a, ranges, st);
-  else hipLaunchKernelGGL(rows_finish_kernel, dim3((unsigned)((a.N + MVF_COLS - 1) / MVF_COLS), (unsigned)((a.m + 7) / 8)),
-                          dim3(MVF_THREADS), 0, st, a);
+  else launch_finish_m<8>(a, ranges, st);
   LQ_HIP_TRY(hipGetLastError());
   return LQ_OK;
 }

@@ -2,6 +2,7 @@
 import pytest
 
 import hip_stub
+from testing_lib import load
 
 RUN = r"""
 d, k, rank = map(int, args)
@@ -88,3 +89,20 @@ p = vp(4096)
 ran = classes_of(lambda: L.lq_matmul(p, m, d, k, p, p, p, Cfg(4, 16, 16, 8, 0), p, p, rank, 1, p, p, 1 << 40, None))
 assert ("plane_gemm_kernel" in ran) == (args[4] == "plane") and ("qmatmul_kernel" in ran) == (args[4] == "qmatmul"), ran
 """, m, d, k, rank, kernel)
+
+
+# columns, rows, rank -> us of the whole call with rows_finish_kernel and with qmatvec_finish_kernel, at K of 2048 (28672 columns),
+# 1024 (1024 columns) or 4096
+FINISH = [
+    (28672, 16, 17, 36.6, 38.9), (28672, 32, 17, 42.8, 46.6), (28672, 24, 64, 37.3, 38.3), (28672, 16, 65, 46.6, 50.1),
+    (28672, 48, 65, 65.1, 75.1), (28672, 24, 256, 53.0, 58.5), (28672, 64, 512, 151.2, 176.6), (11008, 32, 17, 33.6, 34.9),
+    (11008, 24, 65, 39.8, 41.6), (11008, 48, 256, 56.0, 59.3), (11008, 64, 512, 88.7, 98.3), (1024, 24, 17, 11.9, 12.6),
+    (28672, 8, 64, 36.7, 35.3), (28672, 8, 512, 65.6, 53.0), (11008, 24, 64, 30.5, 29.8), (11008, 32, 64, 31.5, 30.8),
+    (11008, 16, 256, 40.6, 38.0), (11008, 16, 512, 56.3, 51.4), (1024, 24, 64, 13.5, 12.4), (1024, 64, 512, 36.8, 30.2),
+    (1024, 4, 256, 17.0, 13.3),
+]
+
+
+@pytest.mark.parametrize("k,m,rank,rows_us,few_us", FINISH)
+def test_finishing_kernel(k, m, rank, rows_us, few_us):
+    assert load().lq_test_rows_finish(m, k, rank) == (rows_us < few_us)
