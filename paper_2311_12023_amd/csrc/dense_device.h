@@ -29,6 +29,13 @@ __device__ inline void circle_pair(int a, int round, int n, int& p, int& q) {
   if (p > q) { const int t = p; p = q; q = t; }
 }
 
+// Descending order of the values, NaN last, equal ones by index: a total order, so that counting what stands before each gives
+// every rank once.
+template <typename T>
+__device__ __forceinline__ bool sorts_before(T a, int ia, T b, int ib) {
+  return a == b || (a != a && b != b) ? ia < ib : a > b || b != b;
+}
+
 template <int CTRL>
 __device__ __forceinline__ double dpp_move(double x) {
   const int lo = __builtin_amdgcn_mov_dpp(__double2loint(x), CTRL, 0xf, 0xf, false);     // every lane has a source: no old value

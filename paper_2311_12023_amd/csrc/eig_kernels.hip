@@ -152,7 +152,7 @@ __device__ void jacobi_onesided(const double* __restrict__ G, double mscale, flo
   for (int c = tid; c < l; c += EIG_THREADS) {
     const float li = s_n2[c];
     int r = 0;
-    for (int j = 0; j < l; ++j) r += (s_n2[j] > li || (s_n2[j] == li && j < c)) ? 1 : 0;
+    for (int j = 0; j < l; ++j) r += sorts_before(s_n2[j], j, li, c) ? 1 : 0;
     s_rank[c] = r;
     lam[r] = (double)li / mscale;
   }

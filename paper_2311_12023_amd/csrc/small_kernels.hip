@@ -193,10 +193,7 @@ __global__ __launch_bounds__(JT) void jacobi_eig_kernel(double* __restrict__ Gal
   for (int i = tid; i < l; i += JT) {
     const double li = M[i * pm + i];
     int r = 0;
-    for (int j = 0; j < l; ++j) {
-      const double lj = M[j * pm + j];
-      r += (lj > li || (lj == li && j < i)) ? 1 : 0;
-    }
+    for (int j = 0; j < l; ++j) r += sorts_before(M[j * pm + j], j, li, i) ? 1 : 0;
     s_rank[i] = r;
     lamall[(size_t)z * l + r] = li > 0.0 ? li : 0.0;
   }

@@ -130,6 +130,36 @@ def test_which_launch_makes_the_vectors(l):
         assert np.max(np.abs(u @ u.T - np.eye(l))) < 4e-6, kind
 
 
+@pytest.mark.parametrize("l", [32, 64, 96, 128, 160])
+@pytest.mark.parametrize("kind", ["nan", "one_nan", "inf"])
+def test_every_row_is_written_for_a_matrix_that_is_not_finite(l, kind):
+    """Nothing of what the outputs held before is left, so the result does not depend on it."""
+    import torch
+    L = load()
+    g = np.random.default_rng(l).standard_normal((l, l))
+    g = g @ g.T
+    if kind == "nan":
+        g[:] = np.nan
+    elif kind == "one_nan":
+        g[3, 17] = g[17, 3] = np.nan
+    else:
+        g[5, 5] = np.inf
+    results = []
+    for before in (7.0, -3.0):
+        gt = torch.from_numpy(g.copy()).cuda()
+        work = torch.full((2 * l * l,), before, dtype=torch.float64, device="cuda")
+        ut = torch.full((l, l), before, dtype=torch.float32, device="cuda")
+        lam = torch.full((l,), before, dtype=torch.float64, device="cuda")
+        if l <= 128:
+            assert L.lq_test_sym_eig_batch(gt.data_ptr(), l, 1, work.data_ptr(), ut.data_ptr(), lam.data_ptr(), None) == 0
+        else:
+            assert L.lq_test_sym_eig(gt.data_ptr(), l, ut.data_ptr(), lam.data_ptr(), work.data_ptr(), None) == 0
+        assert not (ut == before).any() and not (lam == before).any()
+        results.append((ut.cpu().numpy(), lam.cpu().numpy()))
+    for a, b in zip(*results):
+        assert np.array_equal(a, b, equal_nan=True)
+
+
 @pytest.mark.parametrize("l", [32, 64, 96, 128])
 @pytest.mark.parametrize("seed", range(4))
 def test_eigenvalues_of_nested_clusters(l, seed):
