@@ -93,6 +93,10 @@ int lq_test_ritz_residual(const float* G, const float* Y, const double* lam, int
 int lq_test_bucket_code(int bits, float x);
 /* Host-side evaluation of the division-free v / levels of the forward product's kernels.  Needs no GPU. */
 float lq_test_sigma_by_reciprocal(float v, int levels);
+/* Host-side evaluation of where the eigenvalue search looks next: points[0], points[1] as parts of the interval whose ends
+ * have the values flo 2^elo and fhi 2^ehi (0: not known); wanted: whether one eigenvalue is left in it.  1: around the secant's
+ * zero, q to either side; 0: thirds.  Needs no GPU. */
+int lq_test_search_points(double flo, int elo, double fhi, int ehi, int wanted, double q, double* points);
 /* 1 where the launch that adds a forward product's ranges for m rows and N columns is rows_finish_kernel, 0 where it is
  * qmatvec_finish_kernel.  Needs no GPU. */
 int lq_test_rows_finish(int64_t m, int64_t N, int rank);

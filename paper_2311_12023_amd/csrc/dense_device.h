@@ -58,15 +58,29 @@ __device__ __forceinline__ double wave_sum(double x) {
 }
 
 // 1/x for normal x: the hardware seed (about 23 bits) times 1 + e + e^2, e = 1 - x seed.  1/sqrt(x): its seed and two Newton steps.
-__device__ __forceinline__ double rcp64(double x) {
+__host__ __device__ __forceinline__ double rcp64(double x) {
+#ifdef __HIP_DEVICE_COMPILE__
   const double r = __builtin_amdgcn_rcp(x), e = fma(-x, r, 1.0);
   return fma(r, fma(e, e, e), r);
+#else
+  return 1.0 / x;
+#endif
 }
 __device__ __forceinline__ double rsqrt64(double x) {
   double r = __builtin_amdgcn_rsq(x);
   const double h = 0.5 * x;
   r = fma(r, fma(-h * r, r, 0.5), r);
   return fma(r, fma(-h * r, r, 0.5), r);
+}
+
+// The two points of the next round of the eigenvalue search, as parts of the interval: around the zero of the secant through
+// the ends' values flo 2^elo and fhi 2^ehi, q to either side, or thirds where there is no secant to take (not wanted, an end's
+// value not known, which 0 says, or a zero outside).
+struct SearchPoints { double a, b; bool secant; };
+__host__ __device__ __forceinline__ SearchPoints search_points(double flo, int elo, double fhi, int ehi, bool wanted, double q) {
+  const double ratio = ldexp(flo * rcp64(fhi), elo - ehi), at = ratio * rcp64(ratio - 1.0);
+  const bool secant = wanted && flo != 0.0 && fhi != 0.0 && at >= 0.0 && at <= 1.0;     // false for NaN
+  return {secant ? fmax(at - q, 0.5 * at) : 1.0 / 3, secant ? fmin(at + q, 0.5 + 0.5 * at) : 2.0 / 3, secant};
 }
 
 }  // namespace lq

@@ -466,10 +466,8 @@ __global__ __launch_bounds__(EIG_THREADS) void sym_eig_kernel(const double* __re
       double q = 0.125;
       bool missed = false;
       for (int round = 0; round < 64 && __any(xhi - xlo > tol); ++round) {
-        const double ratio = ldexp(flo * rcp64(fhi), elo - ehi), at = ratio * rcp64(ratio - 1.0);
-        const bool secant = !missed && chi - clo == 1 && fhi != 0.0 && at >= 0.0 && at <= 1.0;     // false for NaN
-        const double pa = secant ? fmax(at - q, 0.5 * at) : 1.0 / 3, pb = secant ? fmin(at + q, 0.5 + 0.5 * at) : 2.0 / 3;
-        const double x = fma(xhi - xlo, sub ? pb : pa, xlo);
+        const SearchPoints at = search_points(flo, elo, fhi, ehi, !missed && chi - clo == 1, q);
+        const double x = fma(xhi - xlo, sub ? at.b : at.a, xlo);
         double f; int e;
         const int c = sturm<l>(s_de, x, f, e);
         const double x2 = dpp_move<XOR1>(x), f2 = dpp_move<XOR1>(f);
@@ -482,8 +480,8 @@ __global__ __launch_bounds__(EIG_THREADS) void sym_eig_kernel(const double* __re
         else if (over_a) { xlo = xa; flo = fa; elo = ea; clo = ca; }
         if (!over_a) { xhi = xa; fhi = fa; ehi = ea; chi = ca; }
         else if (!over_b) { xhi = xb; fhi = fb; ehi = eb; chi = cb; }
-        if (secant) q = between ? fmax(2.0 * q * q, 1e-9) : 0.125;
-        missed = secant && !between;
+        if (at.secant) q = between ? fmax(2.0 * q * q, 1e-9) : 0.125;
+        missed = at.secant && !between;
       }
       if (sub == 0) s_lam[g] = 0.5 * (xlo + xhi);
     }

@@ -4,6 +4,7 @@
 #include <cmath>
 
 #include "../../include/lq_testing.h"
+#include "dense_device.h"
 #include "kernels.h"
 #include "nf_device.h"
 #include "testing_capture.h"
@@ -176,6 +177,12 @@ int lq_test_bucket_code(int bits, float x) {
 
 float lq_test_sigma_by_reciprocal(float v, int levels) {
   return sigma_by_reciprocal(v, (float)levels, 1.0f / (float)levels);
+}
+
+int lq_test_search_points(double flo, int elo, double fhi, int ehi, int wanted, double q, double* points) {
+  const SearchPoints at = search_points(flo, elo, fhi, ehi, wanted != 0, q);
+  points[0] = at.a; points[1] = at.b;
+  return at.secant;
 }
 
 int lq_test_rows_finish(int64_t m, int64_t N, int rank) { return rows_finish_preferred(m, N, rank); }

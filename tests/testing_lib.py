@@ -36,6 +36,7 @@ def load():
         L.lq_test_column_gemm.argtypes = [it, it, i64, i64, vp, i64, vp, i64, vp, i64, vp, it, it, vp, vp]
         L.lq_test_pack.argtypes = [it, vp, i64, vp, vp]
         L.lq_test_filter_step_packed.argtypes = [vp, C.c_float, vp, C.c_float, vp, C.c_float, vp, it, it, i64, i64, vp, it, vp, vp]
+        L.lq_test_search_points.argtypes = [C.c_double, it, C.c_double, it, it, C.c_double, vp]
         L.lq_test_rows_finish.argtypes = [i64, i64, it]
         L.lq_test_lds_limit.restype = C.c_size_t
         L.lq_test_bucket_code.argtypes = [C.c_int, C.c_float]
