@@ -80,7 +80,7 @@ struct Plan {
   // shared
   size_t sr, sc, rsr, rsc;              // floats: d, k, d, k
   size_t Ya, Yb, Yc, Yd, Ba, Bb;        // cold-start wide bases (l1 rows)
-  size_t gpart, gram_part, gram_doubles, G, Vt, Ut, lam, lam_cold, prob, errs;
+  size_t gpart, gram_part, gram_doubles, G, Vt, Ut, lam, lam_cold, res_cold, prob, errs;
   // per problem (offset of problem 0, stride)
   size_t R, strideR;
   size_t Yw, Yw2, strideYw;             // floats
@@ -109,8 +109,12 @@ static void make_plan(int64_t d, int64_t k, int rank, const Params& prm, int bat
   pl.G = take((size_t)batch * ll * 8);
   pl.Vt = take((size_t)batch * std::max(ll, sym_eig_work_doubles(std::min(l1, 128))) * 8);
   pl.Ut = take((size_t)batch * ll * 4);
-  pl.lam = take((size_t)batch * l1 * 8);
-  pl.lam_cold = take((size_t)l1 * 8);
+  // One region: Ritz values of the warm passes, then those of the cold start, whose residuals (rank < l1 of them) come right
+  // before them, on the end of the former, which are not there yet.
+  const size_t lam_bytes = up256((size_t)batch * l1 * 8);
+  pl.lam = take(lam_bytes + (size_t)l1 * 8);
+  pl.lam_cold = pl.lam + lam_bytes;
+  pl.res_cold = pl.lam_cold - (size_t)rank * 8;
   pl.prob = take((size_t)batch * sizeof(LoopProblem));
   pl.errs = take((size_t)batch * MAX_ITERS * 8);
   const size_t n = (size_t)pl.n;
@@ -300,9 +304,8 @@ static int cold_factorize(const Ctx& c, const float* A, uint64_t seed, const flo
     }
     return m;
   };
-  // squared residual norms of the top-r Ritz pairs: right before the Ritz values, so that both come to the host in one copy (the
-  // end of a region that is free until the warm passes)
-  double* res_dev = lam - r;
+  // squared residual norms of the top-r Ritz pairs: right before the Ritz values, so that both come to the host in one copy
+  double* res_dev = c.at<double>(pl.res_cold);
   std::vector<double> res(r, 0.0), fetched(r + l);
   double last_est = 0.0;      // residual-based error estimate of the previous Rayleigh-Ritz (valid when rate_ok)
   for (int it = 0;;) {        // it: applications of M so far
