@@ -63,6 +63,36 @@ def test_column_gemm(l, mode, big, K, nt, ranges):
     assert L.lq_test_column_gemm(*args[:8], again.data_ptr(), *args[9:]) == 0 and torch.equal(ct, again)
 
 
+@pytest.mark.parametrize("bad", [float("nan"), float("inf"), -float("inf")])
+@pytest.mark.parametrize("mode,big,K", [(0, 65, 48), (0, 515, 752), (1, 64, 33), (1, 528, 769)])
+@pytest.mark.parametrize("nt,ranges", [(0, 0), (1, 3), (4, 2)])
+def test_column_gemm_keeps_what_is_not_finite_where_it_belongs(mode, big, K, nt, ranges, bad):
+    """An entry of A reaches its own column of the product (every row: X has no zeros), one of X its own row, also where they lie
+    at the end of a ragged reduction or in the last column of a tile, whose neighbours past the edge are read in its place."""
+    import torch
+    L = load()
+    l, rng, ldx, ldc = 64, np.random.default_rng(big), up64(K), up64(big)
+    x = np.zeros((l, ldx), np.float32)
+    x[:, :K] = rng.standard_normal((l, K))
+    a = rng.standard_normal((big, K)).astype(np.float32)
+    a[big - 1, K - 1] = a[3, 0] = bad
+    x[17, K - 1] = x[40, 5] = bad
+    at = torch.from_numpy(np.ascontiguousarray(a if mode == 0 else a.T)).cuda()
+    xt, ct = torch.from_numpy(x).cuda(), torch.full((l, ldc), 7.0, device="cuda")
+    packed = torch.full((2 * l * ldc,), -1, dtype=torch.int16, device="cuda")
+    scratch = torch.full((l * (ldx + 8 * ldc),), float("nan"), device="cuda")
+    assert L.lq_test_column_gemm(mode, l, big, K, xt.data_ptr(), ldx, at.data_ptr(), at.shape[1], ct.data_ptr(), ldc, packed.data_ptr(),
+                                 nt, ranges, scratch.data_ptr(), None) == 0
+    got = ct.cpu().numpy()[:, :big]
+    hit = np.zeros((l, big), bool)
+    hit[[17, 40]] = True
+    hit[:, [3, big - 1]] = True
+    assert np.array_equal(~np.isfinite(got), hit)
+    with np.errstate(invalid="ignore"):
+        ref = x[:, :K].astype(np.float64) @ a.T.astype(np.float64)
+    assert np.max(np.abs(got - ref)[~hit]) < 1.5e-4 * np.sqrt(K)
+
+
 @pytest.mark.parametrize("l,m", [(32, 100), (96, 1003), (128, 16400)])
 @pytest.mark.parametrize("locked", [0, 3, 16])
 @pytest.mark.parametrize("ranges", [0, 1, 4])

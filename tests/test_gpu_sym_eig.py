@@ -160,29 +160,40 @@ def test_every_row_is_written_for_a_matrix_that_is_not_finite(l, kind):
         assert np.array_equal(a, b, equal_nan=True)
 
 
+def _nested_clusters(l, seed):
+    """Clusters of 1 to 7 eigenvalues that start on points of a grid of 1/64, each point once, 1e-2, 1e-4 or 1e-7 apart inside;
+    the largest is 1 and no two are within 1e-8, which leaves them all to the tridiagonal route (its line: 2e-9 of a bound below 3)."""
+    rng = np.random.default_rng(100 * l + seed)
+    s, tops = [1.0], iter(rng.permutation(np.arange(8, 64)) / 64)
+    while len(s) < l:
+        m = min(int(rng.integers(1, 8)), l - len(s))
+        s += list(next(tops) - 10.0 ** -float(rng.choice([2, 4, 7])) * (np.arange(m) + 0.3 * rng.random(m)))
+    s = np.array(s)
+    assert np.min(np.diff(np.sort(s))) > 1e-8 and np.min(s) > 0
+    q, _ = np.linalg.qr(rng.standard_normal((l, l)))
+    return s, q
+
+
 @pytest.mark.parametrize("l", [32, 64, 96, 128])
 @pytest.mark.parametrize("seed", range(4))
 def test_eigenvalues_of_nested_clusters(l, seed):
-    """Clusters within clusters, 1e-8 and 1e-4 of the largest eigenvalue apart and of odd sizes, and eigenvalues on the
-    points of a uniform grid: groups of every size share an interval of the eigenvalue search for a while.  The reduction and
-    the search leave about l roundings of lambda_1."""
-    rng = np.random.default_rng(100 * l + seed)
-    s = np.zeros(l)
-    n = 0
-    while n < l:
-        m = min(int(rng.integers(1, 8)), l - n)
-        step = 10.0 ** -float(rng.choice([2, 4, 7]))
-        s[n:n + m] = round(float(rng.uniform(0.05, 1.0)) * 64) / 64 - step * np.arange(m) * rng.uniform(0.8, 1.2, m)
-        n += m
-    s[0] = 1.0
-    q, _ = np.linalg.qr(rng.standard_normal((l, l)))
-    g = (q * np.abs(s)) @ q.T
+    """Groups of every size share an interval of the eigenvalue search for a while, also on the points of a uniform grid.  The
+    reduction and the search leave about l roundings of lambda_1."""
+    s, q = _nested_clusters(l, seed)
+    g = (q * s) @ q.T
     g = (g + g.T) / 2
     u, lam = _solve(g)
-    assert np.max(np.abs(lam - np.linalg.eigvalsh(g)[::-1])) < (1e-13 * l if _tridiagonal(s) else 1e-4)
+    assert np.max(np.abs(lam - np.linalg.eigvalsh(g)[::-1])) < 1e-13 * l
     assert np.max(np.abs(u @ u.T - np.eye(l))) < 4e-6
 
 
-def _tridiagonal(s):
-    """Whether no two eigenvalues coincide (to 1e-9): otherwise the Jacobi route, in fp32, may have been taken."""
-    return np.min(np.diff(np.sort(np.abs(s)))) > 1e-9
+@pytest.mark.parametrize("l", [32, 64, 96, 128])
+def test_eigenvalues_of_repeated_clusters(l):
+    """The same with eigenvalues that coincide, which may end on the Jacobi route (fp32: 1e-4 as in test_spectra)."""
+    s, q = _nested_clusters(l, 0)
+    s[l // 2:] = s[:l // 2]
+    g = (q * s) @ q.T
+    g = (g + g.T) / 2
+    u, lam = _solve(g)
+    assert np.max(np.abs(lam - np.linalg.eigvalsh(g)[::-1])) < 1e-4
+    assert np.max(np.abs(u @ u.T - np.eye(l))) < 4e-6

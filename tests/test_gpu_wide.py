@@ -60,6 +60,45 @@ def test_orthonormalize_dependent_rows(l, at):
     assert np.max(np.abs(q @ q.T - want)) < 2e-4
 
 
+@pytest.mark.parametrize("l", [64, 96, 128])
+@pytest.mark.parametrize("bad", [float("nan"), float("inf")])
+def test_orthonormalize_of_a_row_that_is_not_finite(l, bad):
+    """A row of Q is a sum over the rows of X up to its own, taken 32 rows at a time: what is not finite reaches its own 32 rows and
+    those after them, and the rows before are what they are without it."""
+    import torch
+    L = load()
+    m = ld = 4 * l
+    x = np.random.default_rng(l).standard_normal((l, m)).astype(np.float32)
+    results = []
+    for value in (1.0, bad):
+        x[l - 20, 5] = value
+        xt = torch.from_numpy(x).cuda()
+        scratch = torch.full((17 * l * l,), float("nan"), dtype=torch.float64, device="cuda")
+        alt = torch.full((l, ld), float("nan"), dtype=torch.float32, device="cuda")
+        assert L.lq_test_orthonormalize(xt.data_ptr(), l, m, ld, scratch.data_ptr(), alt.data_ptr(), None) == 0
+        results.append(xt.cpu().numpy())
+    assert np.array_equal(results[0][:l - 32], results[1][:l - 32])
+    assert not np.isfinite(results[1][l - 20]).any()
+
+
+@pytest.mark.parametrize("bad", [float("nan"), float("inf")])
+@pytest.mark.parametrize("d,k,rank", [(96, 160, 4), (300, 272, 40)])
+def test_factorize_of_a_matrix_that_is_not_finite(d, k, rank, bad):
+    """It comes back, says so in its results, and they do not depend on what the workspace held."""
+    import torch
+    from paper_2311_12023_amd import lq
+    w = torch.from_numpy(np.random.default_rng(d).standard_normal((d, k)).astype(np.float32)).cuda()
+    w[7, 11] = bad
+    results = []
+    for fill in (0, 0x5b):
+        ws = torch.full((lq._lib.lq_factorize_workspace_bytes(d, k, rank, None) + 256,), fill, dtype=torch.uint8, device="cuda")
+        l1, l2, sigma = lq.factorize(w, rank, seed=3, workspace=ws)
+        assert not np.isfinite(sigma).all() or not torch.isfinite(l1).all() or not torch.isfinite(l2).all()
+        results.append((l1.cpu().numpy(), l2.cpu().numpy(), sigma))
+    for a, b in zip(*results):
+        assert np.array_equal(a, b, equal_nan=True)
+
+
 @pytest.mark.parametrize("l,m,batch,chunks", [(32, 100, 3, 16), (64, 1000, 5, 1), (96, 333, 12, 16), (128, 2049, 2, 128),
                                                (160, 500, 3, 7)])
 def test_gram_of_a_batch(l, m, batch, chunks):
