@@ -23,7 +23,10 @@ namespace lq {
 // compute unit), and below that the length of a single pass through memory.  Measured with the launches
 // that split X and add the ranges, against the kernel for batches and its fix-up (us, X A^T / X A): l = 64, 768 x 768 20.0 /
 // 17.5 -> 8.7 / 8.5; l = 96, 2500 x 4096 27.9 / 26.3 -> 23 / 22; l = 128, 4096 x 4096 40.2 / 38.5 -> 34.7 / 31.9, 4096 x 11008
-// 76.5 / 67.3 -> 71.5 / 59.8; where the neighbouring kernels split and add, 4 to 8 us less.
+// 76.5 / 67.3 -> 71.5 / 59.8; where the neighbouring kernels split and add, 4 to 8 us less.  As the cold start runs them: l = 128,
+// 8192 x 8192 97 / 86 -> 69 / 69, 8192 x 28672 308 / 259 -> 257 / 255, 28672 x 8192 312 / 264 -> 279 / 227; l = 32, 512 x 512 17.3 / 14.4 ->
+// 4.3 / 4.2, 4096 x 4096 23.6 / 22.3 -> 18.6 / 22.4, 8192 x 28672 229 / 181 -> 173 / 193 (the one loss, less than its other product
+// gains: factorizations there take 0.93 of the time).  Twenty shapes of factorizations take 0.53 to 0.93 of the time.
 constexpr int COL_THREADS = 256, COL_BK = 32;
 
 struct ColArgs {
@@ -255,8 +258,8 @@ bool column_gemm_supported(int l) { return l % 32 == 0 && l >= 32 && l <= 128; }
 
 // Width of the tiles (16 nt columns) and number of ranges by what a launch is estimated to take, in us: per round of 256
 // workgroups what each reads (X out of L2 at 88 bytes per ns, A at 24, the share of one compute unit when all of them stream),
-// and with more than one range the partial sums, written and read at 2.5 TB/s, and 5 us for whoever adds them.  Of 84 shapes
-// from 512 x 512 to 8192 x 8192 (l = 64, 96, 128) the choice is within 10 % of the fastest of all everywhere, 5 % in most.
+// and with more than one range the partial sums, written and read at 2.5 TB/s, and 5 us for whoever adds them.  Compared with
+// all other choices on 84 shapes from 512 x 512 to 8192 x 8192 (l = 64, 96, 128): within 10 % of the fastest of them everywhere, 5 % in most.
 ColumnSplit column_gemm_split(int l, int64_t big, int64_t K) {
   const int64_t ns = (K + COL_BK - 1) / COL_BK;
   ColumnSplit best{1, 1};

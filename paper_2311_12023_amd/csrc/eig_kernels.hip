@@ -165,8 +165,8 @@ __device__ void jacobi_onesided(const double* __restrict__ G, double mscale, flo
 
 // ---- tridiagonal route ---------------------------------------------------------------------------------
 // Householder tridiagonalisation, eigenvalues by Sturm counts (multisection until each is alone, then secant steps inside
-// the counts' brackets), eigenvectors by twisted factorisation, back-transformation; all in fp64.  256 threads form a 16 x 16 grid, thread (ty, tx) keeps the elements (i, k) with
-// i = ty, k = tx (mod 16) of the matrix in registers.  Every phase is a serial chain of l steps, so what bounds the
+// the counts' brackets), eigenvectors by twisted factorisation, back-transformation; all in fp64.  256 threads form a 16 x 16 grid,
+// thread (ty, tx) keeps the elements (i, k) with i = ty, k = tx (mod 16) of the matrix in registers.  Every phase is a serial chain of l steps, so what bounds the
 // kernel is latency, and the layout is chosen for short steps: four wavefronts (one per SIMD; with 16 the redundant
 // per-wavefront work and the LDS reads of the vectors quadruple), two barriers per column, and scalar parts that every
 // wavefront computes for itself instead of waiting for one.
@@ -174,13 +174,17 @@ __device__ void jacobi_onesided(const double* __restrict__ G, double mscale, flo
 // that 1e-6 could be missed; in a sweep the Ritz values of the quantization noise of 8-bit configurations, 1e-8 lambda_1
 // themselves, are such a cluster) the rows are orthonormalised together at the end, and where they have come out too
 // dependent for that (repeated eigenvalues, a singular matrix) the problem is solved by one-sided Jacobi, in the same launch.
-// Measured on a weight matrix's spectrum in a random basis (one problem, us): l = 32 98 -> 45 -> 35, l = 64 297 -> 99 -> 79,
-// l = 96 687 -> 193 -> 138, l = 128 1491 -> 275 -> 210: one-sided Jacobi with 8 l threads, whose six to nine sweeps of l - 1
-// rounds are bound by LDS bandwidth (every round reads and writes X and V); this route with a chain of two wavefront sums and
-// roots per column before anything else, 34 rounds of trisection and reciprocal pivots in memory behind branches; and as it
-// was with the vectors in the same launch (EIG_HANDS_ON has them now).  Rayleigh quotients come out 10 to 70 times closer than Jacobi's, because G stays in fp64.  At l = 128 the phases take 275,
-// 61, 47 and 94 thousand cycles (tridiagonal form, eigenvalues, vectors, back-transformation): a column is 1400 cycles of
-// latency, by what it takes at l = 32, and its share of 3 l^2 fp64 operations.
+// Measured on a weight matrix's spectrum in a random basis (one problem, us), with one-sided Jacobi (8 l threads, six to nine
+// sweeps of l - 1 rounds bound by LDS bandwidth, every one of which reads and writes X and V), with a first form of this route (a
+// chain of two wavefront sums and roots per column before anything else, 34 rounds of trisection, reciprocal pivots in memory
+// behind branches), with this one and the vectors in the same launch, and as it is: l = 32 98, 45, 35, 35; l = 64 297, 99, 79, 78;
+// l = 96 687, 193, 138, 131; l = 128 1491, 275, 210, 184.  Rayleigh quotients come out 10 to 70 times closer than Jacobi's, because G
+// stays in fp64.  In the one launch of l = 128 the phases took 275, 61, 47 and 94 thousand cycles (tridiagonal form, eigenvalues,
+// vectors, back-transformation); the first launch keeps the first two.  A column of the form is 1400 cycles of latency, by
+// what it takes at l = 32, and its share of 3 l^2 fp64 operations.
+// The pivots of l = 64 beside the reflectors make 96 KB of LDS, which leaves room for one workgroup of a kernel with 64 KB on
+// the compute unit: sweeps that solve l = 64 in batches gain all the same (36 configurations of 4096 x 4096, rank 16, 32 and 40: 25.8 ->
+// 24.5, 26.4 -> 25.2, 26.8 -> 25.6 ms; nine of 1024 x 4096, rank 16: 6.0 -> 4.7).
 //
 // Eigenvalues below x of the tridiagonal matrix with {d_i, e_{i-1}^2} in de: the sign changes of p_i = (d_i - x) p_{i-1} -
 // e_{i-1}^2 p_{i-2}, which needs no division; sign bits are collected 32 at a time.  The pair is brought back to unit size every

@@ -396,8 +396,9 @@ int launch_deflate_rows(float* X, const float* L, int l, int locked, int64_t m, 
 }
 
 // A filter step.  X is read as it is or as the sum of the ranges that launch_column_gemm left, and the result is also written in
-// the operand layout of the next product: neither takes a launch of its own.  A workgroup's rows are those of a 16-row tile that
-// its XCD has, so that the 8-byte pieces of the operand layout meet in one L2.
+// the operand layout of the next product: neither takes a launch of its own.  An XCD's workgroups have l / 8 neighbouring rows: at
+// l = 64 and 128 whole lines of the operand layout (8 rows of 16 bytes) come out of one L2; at l = 32 and 96 some lines are written
+// in two parts by two XCDs.
 struct FilterArgs {
   float* X; const float* part; int ranges; size_t next;       // part NULL: X itself
   float a, b, c;
