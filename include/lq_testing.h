@@ -91,6 +91,8 @@ int lq_test_ritz_residual(const float* G, const float* Y, const double* lam, int
  * plus two comparisons for 4 and 8 bits) on one normalised weight x; -1 for an unsupported bit width.
  * Needs no GPU. */
 int lq_test_bucket_code(int bits, float x);
+/* The same for the search of the decomposition's quantize pass; -2 where x would leave its table. */
+int lq_test_search_code(int bits, float x);
 /* Host-side evaluation of the division-free v / levels of the forward product's kernels.  Needs no GPU. */
 float lq_test_sigma_by_reciprocal(float v, int levels);
 /* Host-side evaluation of where the eigenvalue search looks next: points[0], points[1] as parts of the interval whose ends

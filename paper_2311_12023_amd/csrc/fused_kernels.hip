@@ -117,33 +117,16 @@ __device__ __forceinline__ void store_quad_codes(uint8_t* __restrict__ base, uin
   }
 }
 
-// Code search of phase 1.  One 16-byte LDS entry per bucket j = floor((x + 1) * 256), j = 0..513 (x lies in
-// [-1, 1] up to rounding; the index is clamped all the same): {thr[c0], c0, thr[c0 + 1]} with c0 = the number of
-// thresholds safely below the bucket.  The code of x is c0 + (x >= thr[c0]) (+ (x >= thr[c0 + 1]) for 8 bits, where two
-// thresholds can fall into one bucket): one LDS read and one or two comparisons per weight for every bit width.
-struct SearchEntry { float ta; uint32_t c0; float tb; uint32_t pad; };
-constexpr int SEARCH_ENTRIES = 514;
-
-__device__ __forceinline__ void build_search_nosync(const DevTables* __restrict__ tab, int slot, SearchEntry* s_search) {
-  for (int j = threadIdx.x; j < SEARCH_ENTRIES; j += blockDim.x) {
-    const uint32_t c0 = tab->lut[slot][j < 511 ? j : 511];
-    SearchEntry e;
-    e.ta = tab->thr[slot][c0]; e.c0 = c0; e.tb = tab->thr[slot][c0 + 1]; e.pad = 0;
-    s_search[j] = e;
-  }
+// Copies the search table of phase 1 to LDS.
+__device__ __forceinline__ void load_search_nosync(const DevTables* __restrict__ tab, int slot, SearchEntry* s_search) {
+  const int n = slot == Slot<8>::value ? search_entries(8) : search_entries(4);
+  for (int j = threadIdx.x; j < n; j += blockDim.x) s_search[j] = tab->search[slot][j];
 }
 
 template <int BITS>
 __device__ __forceinline__ uint32_t search_code(const SearchEntry* s_search, float x) {
-  int j = (int)fmaf(x, 256.0f, 256.0f);                         // NaN -> 0
-  j = j < 0 ? 0 : (j > SEARCH_ENTRIES - 1 ? SEARCH_ENTRIES - 1 : j);
-  if constexpr (BITS == 8) {
-    const float4 e = *reinterpret_cast<const float4*>(s_search + j);
-    return __float_as_uint(e.y) + ((x >= e.x) ? 1u : 0u) + ((x >= e.z) ? 1u : 0u);
-  } else {
-    const float2 e = *reinterpret_cast<const float2*>(s_search + j);
-    return __float_as_uint(e.y) + ((x >= e.x) ? 1u : 0u);
-  }
+  const SearchEntry e = *reinterpret_cast<const SearchEntry*>(reinterpret_cast<const char*>(s_search) + search_offset<BITS>(x));
+  return e.below + ((x >= e.thr) ? 1u : 0u);
 }
 
 // max |t| of a quad, as the bit pattern of a non-negative float (unsigned order = numeric order).
@@ -152,117 +135,171 @@ __device__ __forceinline__ uint32_t quad_absmax_bits(const float (&t)[4]) {
   asm("v_max3_f32 %0, |%1|, |%2|, |%3|\n\tv_max_f32 %0, |%4|, %0" : "=&v"(m) : "v"(t[0]), "v"(t[1]), "v"(t[2]), "v"(t[3]));
   return __float_as_uint(m);
 }
-template <int CTRL>
-__device__ __forceinline__ uint32_t umax_dpp(uint32_t x) {
-  const uint32_t y = (uint32_t)__builtin_amdgcn_update_dpp((int)x, (int)x, CTRL, 0xf, 0xf, false);
-  return x > y ? x : y;
-}
-// Maximum over the QPB consecutive lanes that hold one block (see group_max_lanes), on bit patterns.
-template <int QPB>
-__device__ __forceinline__ uint32_t block_umax(uint32_t x) {
-  x = umax_dpp<DPP_QUAD_XOR1>(x);
-  x = umax_dpp<DPP_QUAD_XOR2>(x);
-  if constexpr (QPB >= 8) x = umax_dpp<DPP_ROW_HALF_MIRROR>(x);
-  if constexpr (QPB >= 16) x = umax_dpp<DPP_ROW_MIRROR>(x);
-  if constexpr (QPB >= 32) { const uint32_t y = (uint32_t)__shfl_xor((int)x, 16); x = x > y ? x : y; }
+// Reductions over the QPB = 4, 8, 16 or 32 lanes that hold a block, for the four quads of a lane at once (lane i of every
+// hardware quad, 4 consecutive lanes, ends with the result of quad i): the two steps inside a hardware quad hand half of the
+// values to the partner, so four results take the moves of less than two.  Beyond it lanes meet others of the same i: the
+// half-row mirror with the quads' order put back is xor 4, a rotation of a row by 8 is xor 8.
+constexpr int DPP_QUAD_REVERSE = 0x1B, DPP_ROW_ROR8 = 0x128;
+template <int QPB, typename T, typename Op>
+__device__ __forceinline__ T block_reduce_dealt(const T (&v)[4], bool odd, bool high, Op op) {
+  auto move = [](T x, auto ctrl) __attribute__((always_inline)) {
+    return __builtin_bit_cast(T, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, x), decltype(ctrl)::value, 0xf, 0xf, true));
+  };
+#define LQ_MOVE(X, CTRL) move(X, std::integral_constant<int, CTRL>{})
+  const T a = op(odd ? v[1] : v[0], LQ_MOVE(odd ? v[0] : v[1], DPP_QUAD_XOR1));
+  const T b = op(odd ? v[3] : v[2], LQ_MOVE(odd ? v[2] : v[3], DPP_QUAD_XOR1));
+  T x = op(high ? b : a, LQ_MOVE(high ? a : b, DPP_QUAD_XOR2));
+  if constexpr (QPB >= 8) x = op(x, LQ_MOVE(LQ_MOVE(x, DPP_ROW_HALF_MIRROR), DPP_QUAD_REVERSE));
+  if constexpr (QPB >= 16) x = op(x, LQ_MOVE(x, DPP_ROW_ROR8));
+  if constexpr (QPB >= 32) x = op(x, __builtin_bit_cast(T, __shfl_xor(__builtin_bit_cast(int, x), 16)));
+#undef LQ_MOVE
   return x;
 }
+// Value of lane I of each hardware quad.
+template <int I>
+__device__ __forceinline__ float quad_lane(float x) {
+  return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), 0x55 * I, 0xf, 0xf, true));
+}
+
+// What a lane of phase 1 holds of W and of the Fisher scales beside its product tile: its four quads (rows tid / 32 + 16 u),
+// 1/sqrt(row_w) of their rows, 1/sqrt(col_w) and col_w of their columns.
+struct PhaseQuads { float4 w[4]; float rs[4]; float4 rc, cw; };
 
 // Epilogue of phase 1 in quad layout: lane `tid` handles quads tid, tid+512, ... of the 64 x 128 tile (32 quads
 // per row), so W loads, LDS reads of the product and code stores are all contiguous across lanes.  QPB = B0/4
 // lanes hold one block.  The four quads of a lane lie in four different blocks; their block maxima are found first,
-// then one division serves all four (lane i of every hardware quad divides for quad i, the quotients go back by quad
-// broadcasts: the four lanes of a hardware quad always share their blocks), then the codes.
-template <int BITS, int QPB, bool WITH_ERR>
+// then one division serves all four (lane i of every hardware quad has the maximum of quad i and divides, the quotients go back
+// by quad broadcasts: the four lanes of a hardware quad always share their blocks), then the codes.  Blocks lie
+// inside the matrix or outside it, so whatever the quads past its edge hold stays there and is never stored.
+template <int BITS, int QPB, bool WITH_ERR, bool WEIGHTED>
 __device__ __forceinline__ void phase1_epilogue(const PhaseArgs& a, int z, const float* pt, const SearchEntry* s_search,
-                                                const float* s_code, int64_t r0, int64_t c0, const float4 (&wreg)[4]) {
-  const int tid = threadIdx.x;
+                                                const float* s_code, int64_t r0, int64_t c0, const PhaseQuads& in) {
+  const int tid = threadIdx.x, sub = tid & 3;
+  const bool odd = sub & 1, high = sub & 2;
   uint8_t* codes = a.codes + (size_t)z * a.strideCodes;
   BlockRec* blk = a.blk + (size_t)z * a.strideBlk;
   // quad indices: a uniform part per quad u (first quad of the tile, NTHR1 / 32 rows further down for each u) plus a
   // 32-bit lane part; both are multiples of QPB where a block starts, so block indices split the same way
   const int cq = tid & 31;
-  const int64_t col = c0 + 4 * cq;
-  const int64_t tq0 = (r0 * a.k + c0) >> 2, quad_step = (NTHR1 / 32) * (a.k >> 2);
+  const int64_t tq0 = (r0 * a.k + c0) >> 2;
+  const uint32_t quad_step = (uint32_t)((NTHR1 / 32) * (a.k >> 2));
   const uint32_t lq = (uint32_t)((tid >> 5) * (a.k >> 2) + cq);
   constexpr int CODE_BYTES_X2 = BITS;            // bytes per quad = BITS / 2
-  const bool col_live = col < a.k;
-  float4 rc = make_float4(1.f, 1.f, 1.f, 1.f), cw = make_float4(1.f, 1.f, 1.f, 1.f);
-  if (a.rsc && col_live) {
-    rc = *reinterpret_cast<const float4*>(a.rsc + col);
-    if (WITH_ERR) cw = *reinterpret_cast<const float4*>(a.col_w + col);
-  }
+  const bool col_live = c0 + 4 * cq < a.k;
+  const int rows_left = (int)(a.d - r0 < TM ? a.d - r0 : TM) - (tid >> 5);
   float t[4][4];
-  uint32_t mbits[4];
-  bool live[4];
+  uint32_t qmax[4];
 #pragma unroll
   for (int u = 0; u < 4; ++u) {
     const int lr = (tid >> 5) + (NTHR1 / 32) * u;
-    const int64_t row = r0 + lr;
-    live[u] = row < a.d && col_live;
     const float4 p = *reinterpret_cast<const float4*>(pt + lr * PP + 4 * cq);
     float pv[4] = {p.x, p.y, p.z, p.w};
-    const float fv[4] = {wreg[u].x, wreg[u].y, wreg[u].z, wreg[u].w};
-    if (a.rsc) {
-      const float rs = live[u] ? a.rsr[row] : 0.0f;
-      pv[0] *= rs * rc.x; pv[1] *= rs * rc.y; pv[2] *= rs * rc.z; pv[3] *= rs * rc.w;
+    const float fv[4] = {in.w[u].x, in.w[u].y, in.w[u].z, in.w[u].w};
+    if constexpr (WEIGHTED) {
+      const float rs = in.rs[u];
+      pv[0] *= rs * in.rc.x; pv[1] *= rs * in.rc.y; pv[2] *= rs * in.rc.z; pv[3] *= rs * in.rc.w;
     }
 #pragma unroll
-    for (int e = 0; e < 4; ++e) t[u][e] = live[u] ? fv[e] - pv[e] : 0.0f;
-    mbits[u] = block_umax<QPB>(quad_absmax_bits(t[u]));
+    for (int e = 0; e < 4; ++e) t[u][e] = fv[e] - pv[e];
+    qmax[u] = quad_absmax_bits(t[u]);
   }
-  // lane i of each hardware quad divides for quad i
-  const int sub = tid & 3;
-  const uint32_t mine = sub == 0 ? mbits[0] : sub == 1 ? mbits[1] : sub == 2 ? mbits[2] : mbits[3];
-  const int rmine = (int)__float_as_uint(safe_reciprocal(__uint_as_float(mine)));
-  const float rcp[4] = {__int_as_float(__builtin_amdgcn_mov_dpp(rmine, 0x00, 0xf, 0xf, true)),
-                        __int_as_float(__builtin_amdgcn_mov_dpp(rmine, 0x55, 0xf, 0xf, true)),
-                        __int_as_float(__builtin_amdgcn_mov_dpp(rmine, 0xAA, 0xf, 0xf, true)),
-                        __int_as_float(__builtin_amdgcn_mov_dpp(rmine, 0xFF, 0xf, 0xf, true))};
+  const float mine = __uint_as_float(block_reduce_dealt<QPB>(qmax, odd, high, [](uint32_t x, uint32_t y) { return x > y ? x : y; }));
+  const float rmine = safe_reciprocal(mine);
+  const float rcp[4] = {quad_lane<0>(rmine), quad_lane<1>(rmine), quad_lane<2>(rmine), quad_lane<3>(rmine)};
+  const float amax[4] = {quad_lane<0>(mine), quad_lane<1>(mine), quad_lane<2>(mine), quad_lane<3>(mine)};
+  float e2[4], eq[4], q2[4];
 #pragma unroll
   for (int u = 0; u < 4; ++u) {
-    const float amax = __uint_as_float(mbits[u]);
     uint32_t c[4];
-    float e2 = 0.f, eq = 0.f, q2 = 0.f;
+    e2[u] = eq[u] = q2[u] = 0.f;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       c[e] = search_code<BITS>(s_search, t[u][e] * rcp[u]);
-      if (WITH_ERR) {
-        const float w = a.rsc ? (e == 0 ? cw.x : e == 1 ? cw.y : e == 2 ? cw.z : cw.w) : 1.0f;
+      if constexpr (WITH_ERR) {
         const float q = s_code[c[e]];
-        const float err = t[u][e] - q * amax;
-        e2 = fmaf(w * err, err, e2);
-        eq = fmaf(w * err, q, eq);
-        q2 = fmaf(w * q, q, q2);
+        const float err = t[u][e] - q * amax[u];
+        float werr = err, wq = q;
+        if constexpr (WEIGHTED) {
+          const float w = e == 0 ? in.cw.x : e == 1 ? in.cw.y : e == 2 ? in.cw.z : in.cw.w;
+          werr = w * err; wq = w * q;
+        }
+        e2[u] = fmaf(werr, err, e2[u]);
+        eq[u] = fmaf(werr, q, eq[u]);
+        q2[u] = fmaf(wq, q, q2[u]);
       }
-    }
-    if (WITH_ERR) {
-      if (!live[u]) { e2 = 0.f; eq = 0.f; q2 = 0.f; }
-      e2 = group_sum_lanes<QPB>(e2); eq = group_sum_lanes<QPB>(eq); q2 = group_sum_lanes<QPB>(q2);
     }
     const int64_t quad_u = tq0 + (int64_t)u * quad_step;                   // uniform
-    store_quad_codes<BITS>(codes + ((quad_u * CODE_BYTES_X2) >> 1), lq, c, live[u]);
-    if (live[u] && (cq & (QPB - 1)) == 0) {
-      if (WITH_ERR) {
-        BlockRec rec; rec.s = amax; rec.e2 = e2; rec.eq = eq; rec.q2 = q2;
-        (blk + quad_u / QPB)[lq / QPB] = rec;
-      } else {
-        (reinterpret_cast<float*>(blk) + quad_u / QPB)[lq / QPB] = amax;   // without error sums a record is the absmax alone
-      }
-    }
+    store_quad_codes<BITS>(codes + ((quad_u * CODE_BYTES_X2) >> 1), lq, c, col_live && (NTHR1 / 32) * u < rows_left);
+  }
+  // lane i of a block's first hardware quad stores the record of quad i
+  const bool writes = col_live && (cq & (QPB - 1)) < 4 && (NTHR1 / 32) * sub < rows_left;
+  const uint32_t at = (uint32_t)sub * (quad_step / QPB) + lq / QPB;
+  if constexpr (WITH_ERR) {
+    auto add = [](float x, float y) { return x + y; };
+    BlockRec rec;
+    rec.s = mine;
+    rec.e2 = block_reduce_dealt<QPB>(e2, odd, high, add);
+    rec.eq = block_reduce_dealt<QPB>(eq, odd, high, add);
+    rec.q2 = block_reduce_dealt<QPB>(q2, odd, high, add);
+    if (writes) (blk + tq0 / QPB)[at] = rec;
+  } else {
+    if (writes) (reinterpret_cast<float*>(blk) + tq0 / QPB)[at] = mine;    // without error sums a record is the absmax alone
   }
 }
 
-template <int BITS, bool WITH_ERR>
+template <int BITS, bool WITH_ERR, bool WEIGHTED>
 __device__ __forceinline__ void phase1_dispatch_block(const PhaseArgs& a, int block, int z, const float* pt,
                                                       const SearchEntry* s_search, const float* s_code, int64_t r0,
-                                                      int64_t c0, const float4 (&wreg)[4]) {
+                                                      int64_t c0, const PhaseQuads& in) {
   switch (block) {
-    case 16: phase1_epilogue<BITS, 4, WITH_ERR>(a, z, pt, s_search, s_code, r0, c0, wreg); break;
-    case 32: phase1_epilogue<BITS, 8, WITH_ERR>(a, z, pt, s_search, s_code, r0, c0, wreg); break;
-    case 64: phase1_epilogue<BITS, 16, WITH_ERR>(a, z, pt, s_search, s_code, r0, c0, wreg); break;
-    default: phase1_epilogue<BITS, 32, WITH_ERR>(a, z, pt, s_search, s_code, r0, c0, wreg); break;
+    case 16: phase1_epilogue<BITS, 4, WITH_ERR, WEIGHTED>(a, z, pt, s_search, s_code, r0, c0, in); break;
+    case 32: phase1_epilogue<BITS, 8, WITH_ERR, WEIGHTED>(a, z, pt, s_search, s_code, r0, c0, in); break;
+    case 64: phase1_epilogue<BITS, 16, WITH_ERR, WEIGHTED>(a, z, pt, s_search, s_code, r0, c0, in); break;
+    default: phase1_epilogue<BITS, 32, WITH_ERR, WEIGHTED>(a, z, pt, s_search, s_code, r0, c0, in); break;
   }
+}
+template <bool WITH_ERR, bool WEIGHTED>
+__device__ __forceinline__ void phase1_dispatch(const PhaseArgs& a, const lq_config& cfg, int z, const float* pt, const SearchEntry* s_search,
+                                                const float* s_code, int64_t r0, int64_t c0, const PhaseQuads& in) {
+  switch (cfg.bits) {
+    case 2: phase1_dispatch_block<2, WITH_ERR, WEIGHTED>(a, cfg.block, z, pt, s_search, s_code, r0, c0, in); break;
+    case 3: phase1_dispatch_block<3, WITH_ERR, WEIGHTED>(a, cfg.block, z, pt, s_search, s_code, r0, c0, in); break;
+    case 4: phase1_dispatch_block<4, WITH_ERR, WEIGHTED>(a, cfg.block, z, pt, s_search, s_code, r0, c0, in); break;
+    default: phase1_dispatch_block<8, WITH_ERR, WEIGHTED>(a, cfg.block, z, pt, s_search, s_code, r0, c0, in); break;
+  }
+}
+
+// The quads of W and the row scales of the band of TM rows at r0, columns from c0; rows and columns past the matrix repeat the
+// last row and the first column of the stretch.  Addresses are a uniform base per quad plus a 32-bit lane offset (rows of a band are
+// at most 63 apart).
+template <bool WEIGHTED>
+__device__ __forceinline__ void fetch_phase_quads(const PhaseArgs& a, int64_t r0, int64_t c0, PhaseQuads& q) {
+  const int tr = threadIdx.x >> 5;
+  const uint32_t col = c0 + 4 * (threadIdx.x & 31) < a.k ? 4 * (threadIdx.x & 31) : 0;
+  int row[4] = {tr, tr, tr, tr};
+  uint32_t off[4];
+#pragma unroll
+  for (int u = 0; u < 4; ++u) off[u] = (uint32_t)((tr * a.k + col) * 4);
+  if (r0 + TM > a.d) {
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int64_t left = a.d - 1 - (r0 + (NTHR1 / 32) * u);
+      row[u] = left > 0 ? (tr < left ? tr : (int)left) : 0;
+      off[u] = (uint32_t)((row[u] * a.k + col) * 4);
+    }
+  }
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    const int64_t ru = r0 + (NTHR1 / 32) * u, row_u = ru < a.d ? ru : a.d - 1;              // uniform
+    q.w[u] = *reinterpret_cast<const float4*>(reinterpret_cast<const char*>(a.W + (size_t)row_u * a.k + c0) + off[u]);
+    if constexpr (WEIGHTED) q.rs[u] = (a.rsr + row_u)[row[u]];
+  }
+}
+template <bool WITH_ERR>
+__device__ __forceinline__ void fetch_phase_columns(const PhaseArgs& a, int64_t c0, PhaseQuads& q) {
+  const int64_t col = c0 + (c0 + 4 * (threadIdx.x & 31) < a.k ? 4 * (threadIdx.x & 31) : 0);
+  q.rc = *reinterpret_cast<const float4*>(a.rsc + col);
+  if constexpr (WITH_ERR) q.cw = *reinterpret_cast<const float4*>(a.col_w + col);
 }
 
 // SPLIT: L1 L2 from the packed bf16 hi/lo planes with three v_mfma_f32_32x32x16_bf16 per 16-deep group
@@ -270,7 +307,7 @@ __device__ __forceinline__ void phase1_dispatch_block(const PhaseArgs& a, int bl
 // Launch: one-dimensional, batch * tiles8 workgroups (tiles8 = number of 64 x 128 tiles rounded up to a multiple
 // of 8).  Workgroups go to the 8 XCDs round-robin by index; the index is decoded as (tile mod 8, problem, tile div 8),
 // so the problems of a batch that share a tile of W run on one XCD and fetch it into that XCD's L2 once.
-template <bool WITH_ERR, bool SPLIT>
+template <bool WITH_ERR, bool SPLIT, bool WEIGHTED>
 __global__ __launch_bounds__(NTHR1) void lowrank_blockquant_kernel(PhaseArgs a, int tiles, int tiles_n) {
   // The operand chunks and the product tile share one LDS buffer: the product is written after the last MFMA has
   // read its operands.  fp32: Y chunk KC x TM, B chunk KC x TN.  Split: four planes (Y hi, Y lo: TM rows; B hi, B lo:
@@ -295,21 +332,13 @@ __global__ __launch_bounds__(NTHR1) void lowrank_blockquant_kernel(PhaseArgs a, 
   // search table (and, for the error sums, the code book) of this problem's bit width, visible after the barriers of
   // the product stage
   const int slot = pr.cfg.bits == 2 ? 0 : pr.cfg.bits == 3 ? 1 : pr.cfg.bits == 4 ? 2 : 3;
-  build_search_nosync(a.tables, slot, s_search);
+  load_search_nosync(a.tables, slot, s_search);
   if constexpr (WITH_ERR)
     for (int i = tid; i < 256; i += NTHR1) s_code[i] = a.tables->code[slot][i];
-  // this lane's 4 quads of W, fetched now so that the loads overlap the MFMA stage.  Addresses are a uniform base per
-  // quad plus one 32-bit lane offset (rows of a tile are at most 63 apart).
-  float4 wreg[4];
-  const uint32_t w_lane = (uint32_t)(((tid >> 5) * a.k + 4 * (tid & 31)) * 4);
-  const bool w_col_live = c0 + 4 * (tid & 31) < a.k;
-#pragma unroll
-  for (int u = 0; u < 4; ++u) {
-    const int64_t row_u = r0 + (NTHR1 / 32) * u;                       // uniform
-    const char* base = reinterpret_cast<const char*>(a.W + (size_t)row_u * a.k + c0);
-    wreg[u] = (row_u + (tid >> 5) < a.d && w_col_live) ? *reinterpret_cast<const float4*>(base + w_lane)
-                                                         : make_float4(0.f, 0.f, 0.f, 0.f);
-  }
+  // this lane's 4 quads of W, fetched now so that the loads overlap the MFMA stage
+  PhaseQuads quads;
+  fetch_phase_quads<WEIGHTED>(a, r0, c0, quads);
+  if constexpr (WEIGHTED) fetch_phase_columns<WITH_ERR>(a, c0, quads);
 
   floatx16 acc;
 #pragma unroll
@@ -425,135 +454,353 @@ __global__ __launch_bounds__(NTHR1) void lowrank_blockquant_kernel(PhaseArgs a, 
     pt[row * PP + 32 * wc + ln] = acc[e];
   }
   __syncthreads();
-  switch (pr.cfg.bits) {
-    case 2: phase1_dispatch_block<2, WITH_ERR>(a, pr.cfg.block, z, pt, s_search, s_code, r0, c0, wreg); break;
-    case 3: phase1_dispatch_block<3, WITH_ERR>(a, pr.cfg.block, z, pt, s_search, s_code, r0, c0, wreg); break;
-    case 4: phase1_dispatch_block<4, WITH_ERR>(a, pr.cfg.block, z, pt, s_search, s_code, r0, c0, wreg); break;
-    default: phase1_dispatch_block<8, WITH_ERR>(a, pr.cfg.block, z, pt, s_search, s_code, r0, c0, wreg); break;
+  phase1_dispatch<WITH_ERR, WEIGHTED>(a, pr.cfg, z, pt, s_search, s_code, r0, c0, quads);
+}
+
+// ---- the form for split products of up to 64 ranks, used by default --------------------------------------------------
+// A workgroup keeps the planes of one 128-column stretch of B in LDS; its eight wavefronts walk over bands of 16 rows of W, each
+// for itself, without barriers.  v_mfma_f32_16x16x32_bf16 with the planes of B as its first operand leaves lane 16 q + n, in the accumulator of
+// column tile t, with columns 16 t + 4 q + 0..3 of row n: quads of W, subtracted where they are.  A block of B0 weights lies in
+// B0 / 16 tiles of the four lanes n, 16 + n, 32 + n, 48 + n, so block maxima and error sums are taken within a lane first;
+// for the rest v_permlane32_swap and v_permlane16_swap exchange a value for a value, so that every step halves
+// the number of blocks a lane has to do with.  The codes of 32 consecutive weights meet in one lane the same way and are
+// stored at once.  The loads of a band are in flight while the band before it is quantized.
+// Bound by instruction issue (vector ALU and LDS half busy each, matrix cores a sixth).  12 problems of 4096 x 4096, rank 64,
+// with error sums, per weight: tiles of 64 x 128 by the whole workgroup with the product turned into rows through LDS 38 vector
+// and 3.9 LDS instructions and four barriers per tile, 285 us; this form 19 and 3.0, 212 us.  One Fisher-weighted 4096 x 11008:
+// 102 -> 78 us.
+__device__ __forceinline__ void swap_halves(uint32_t& a, uint32_t& b) {      // upper 32 lanes of a <-> lower 32 lanes of b
+  const auto r = __builtin_amdgcn_permlane32_swap(a, b, false, false);
+  a = r[0]; b = r[1];
+}
+__device__ __forceinline__ void swap_rows(uint32_t& a, uint32_t& b) {        // lanes 16..31, 48..63 of a <-> 0..15, 32..47 of b
+  const auto r = __builtin_amdgcn_permlane16_swap(a, b, false, false);
+  a = r[0]; b = r[1];
+}
+// v[b]: what this lane has of block b < NB of its row -> y[i]: block (NB == 8 ? 2 q + i : q * NB / 4) from all four lanes.
+template <int NB, typename Op>
+__device__ __forceinline__ void quarter_reduce(uint32_t (&v)[8], uint32_t (&y)[2], Op op) {
+  constexpr int NX = NB > 1 ? NB / 2 : 1;
+  uint32_t x[NX];
+#pragma unroll
+  for (int b = 0; b < NX; ++b) {
+    uint32_t other = NB > 1 ? v[b + NX] : v[b];
+    swap_halves(v[b], other);
+    x[b] = op(v[b], other);
+  }
+#pragma unroll
+  for (int b = 0; b < (NX > 1 ? NX / 2 : 1); ++b) {
+    uint32_t other = NX > 1 ? x[b + NX / 2] : x[b];
+    swap_rows(x[b], other);
+    y[b] = op(x[b], other);
+  }
+}
+// Codes of 32 consecutive weights from the four lanes' quads: w[t] holds the codes of quad 4 t + q of the lane's row; out: weights
+// 32 q .. 32 q + 31 in order.
+template <int BITS>
+__device__ __forceinline__ void gather_codes(uint32_t (&w)[8], uint32_t (&out)[BITS]) {
+  if constexpr (BITS == 8) {
+#pragma unroll
+    for (int t = 0; t < 4; ++t) swap_halves(w[t], w[t + 4]);
+#pragma unroll
+    for (int t = 0; t < 8; t += 4) { swap_rows(w[t], w[t + 2]); swap_rows(w[t + 1], w[t + 3]); }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) { out[i] = w[2 * i]; out[4 + i] = w[2 * i + 1]; }
+  } else {
+    uint32_t p[4];
+#pragma unroll
+    for (int s = 0; s < 4; ++s) p[s] = w[2 * s] | (w[2 * s + 1] << 16);
+    swap_halves(p[0], p[2]); swap_halves(p[1], p[3]);
+    swap_rows(p[0], p[1]); swap_rows(p[2], p[3]);
+    if constexpr (BITS == 4) {
+      out[0] = __builtin_amdgcn_perm(p[1], p[0], 0x05040100); out[1] = __builtin_amdgcn_perm(p[3], p[2], 0x05040100);
+      out[2] = __builtin_amdgcn_perm(p[1], p[0], 0x07060302); out[3] = __builtin_amdgcn_perm(p[3], p[2], 0x07060302);
+    } else if constexpr (BITS == 2) {
+      const uint32_t a = __builtin_amdgcn_perm(p[1], p[0], 0x06020400), b = __builtin_amdgcn_perm(p[3], p[2], 0x06020400);
+      out[0] = __builtin_amdgcn_perm(b, a, 0x05040100); out[1] = __builtin_amdgcn_perm(b, a, 0x07060302);
+    } else {
+      uint32_t a[4], b[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) { a[i] = p[i] & 0xfffu; b[i] = p[i] >> 16; }
+      out[0] = a[0] | (a[1] << 12) | (a[2] << 24);
+      out[1] = (a[2] >> 8) | (a[3] << 4) | (b[0] << 16) | (b[1] << 28);
+      out[2] = (b[1] >> 4) | (b[2] << 8) | (b[3] << 20);
+    }
   }
 }
 
-// The split-precision variant used by default: a workgroup keeps the planes of one 128-column stretch of B in LDS and
-// walks `nb` consecutive 64-row bands of W with them, so the B planes (half of what a tile needs from memory) are
-// fetched once per `nb` tiles, and the W quads and Y planes of band i + 1 are fetched while band i is being quantized.
-// Launch: one-dimensional, batch * units8 workgroups, units = column stretches x groups of bands, rounded up to a
+constexpr int BAND = 16;
+struct BandShared {
+  __attribute__((aligned(16))) __bf16 b[2 * TN * KP];            // planes of B, hi then lo, zero past the rank
+  __attribute__((aligned(16))) SearchEntry search[SEARCH_ENTRIES];
+  __attribute__((aligned(16))) float rc[TN], cw[TN];             // 1/sqrt(col_w), col_w of the stretch
+  float code[256];
+};
+
+template <int BITS, int QPB, bool WITH_ERR, bool WEIGHTED>
+__device__ __forceinline__ void walk_bands(const PhaseArgs& a, int z, const BandShared& sh, int64_t c0, int band0, int band1) {
+  constexpr int TPB = QPB / 4, NB = 8 / TPB, NX = NB > 1 ? NB / 2 : 1, NY = NB == 8 ? 2 : 1;   // tiles per block, blocks per row
+  const int lane = threadIdx.x & 63, n = lane & 15, q = lane >> 4;
+  const int rk = (a.rank + 15) / 16 * 16;
+  const int64_t dpad = (a.d + TM - 1) / TM * TM;
+  const char* yhi = reinterpret_cast<const char*>(reinterpret_cast<const __bf16*>(a.packed) + (size_t)z * a.stridePacked);
+  const char* ylo = yhi + (size_t)dpad * rk * 2;
+  uint8_t* codes = a.codes + (size_t)z * a.strideCodes;
+  BlockRec* blk = a.blk + (size_t)z * a.strideBlk;
+  const int tiles = a.k - c0 < TN ? (int)((a.k - c0) / 16) : 8;             // of this stretch inside the matrix
+  const bool wide = a.k % 32 == 0;                                           // a lane's 32 codes lie inside or outside
+  const uint32_t y_lane = (uint32_t)((n * rk + 8 * q) * 2);
+  const uint32_t code_lane = (uint32_t)(n * (a.k / 16) + 2 * q) * (2 * BITS);
+  const int block0 = NB == 8 ? 2 * q : q * NB / 4;
+  const uint32_t blk_lane = (uint32_t)(n * (a.k / (4 * QPB)) + block0);
+  const bool blk_live = (NB >= 4 || q % (4 / NB) == 0) && 4 * QPB * block0 < 16 * tiles;
+
+  floatx4 wq[8], yv[2][2];
+  float rs = 1.0f;
+  auto fetch = [&](int band) {
+    const int64_t r0 = (int64_t)band * BAND;
+    int row = n;
+    if (r0 + BAND > a.d) row = n < (int)(a.d - 1 - r0) ? n : (int)(a.d - 1 - r0);          // rows past the end: the last one
+    const char* base = reinterpret_cast<const char*>(a.W + (size_t)r0 * a.k + c0);
+    const uint32_t off = (uint32_t)(row * a.k + 4 * q) * 4u;
+#pragma unroll
+    for (int t = 0; t < 8; ++t) wq[t] = *reinterpret_cast<const floatx4*>(base + (off + (t < tiles ? 64u * t : 0u)));
+    if constexpr (WEIGHTED) rs = (a.rsr + r0)[row];
+  };
+  auto fetch_y = [&](int band) {
+    const uint64_t at = (uint64_t)band * (BAND * 2 * rk);
+#pragma unroll
+    for (int g = 0; g < 2; ++g)
+      if (32 * g < rk) {
+        const uint32_t lane_at = y_lane + (32 * g + 8 * q < rk ? 64u * g : 0u);           // past the rank: anything
+        yv[g][0] = *reinterpret_cast<const floatx4*>(yhi + at + lane_at);
+        yv[g][1] = *reinterpret_cast<const floatx4*>(ylo + at + lane_at);
+      }
+  };
+  if (band0 < band1) { fetch(band0); fetch_y(band0); }
+  __syncthreads();                             // what the workgroup shares is in LDS
+  for (int band = band0; band < band1; band += 8) {
+    const int64_t r0 = (int64_t)band * BAND;
+    floatx4 t[8];
+    const __bf16* bop = sh.b + n * KP + 8 * q;
+    auto products = [&](int g) {
+      if (32 * g + 32 > rk && 32 * g + 8 * q >= rk) yv[g][0] = yv[g][1] = floatx4{0.f, 0.f, 0.f, 0.f};
+      const bf16x8 yh = __builtin_bit_cast(bf16x8, yv[g][0]), yl = __builtin_bit_cast(bf16x8, yv[g][1]);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const bf16x8 bh = *reinterpret_cast<const bf16x8*>(bop + 16 * i * KP + 32 * g);
+        const bf16x8 bl = *reinterpret_cast<const bf16x8*>(bop + (TN + 16 * i) * KP + 32 * g);
+        const floatx4 zero = {0.f, 0.f, 0.f, 0.f};
+        t[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bh, yl, g ? t[i] : zero, 0, 0, 0);
+        t[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bl, yh, t[i], 0, 0, 0);
+        t[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bh, yh, t[i], 0, 0, 0);
+      }
+    };
+    products(0);
+    if (rk > 32) products(1);
+    uint32_t m[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      if constexpr (WEIGHTED) t[i] *= rs * *reinterpret_cast<const floatx4*>(sh.rc + 16 * i + 4 * q);
+      t[i] = wq[i] - t[i];
+      const float e[4] = {t[i][0], t[i][1], t[i][2], t[i][3]};
+      const uint32_t mq = quad_absmax_bits(e);
+      if (i % TPB == 0) m[i / TPB] = mq;
+      else m[i / TPB] = m[i / TPB] > mq ? m[i / TPB] : mq;
+    }
+    const int following = band + 8 < band1 ? band + 8 : band;                 // past the end: the same band again
+    fetch(following);
+    fetch_y(following);
+    __builtin_amdgcn_sched_barrier(0);
+    uint32_t ymax[2];
+    quarter_reduce<NB>(m, ymax, [](uint32_t x, uint32_t y) { return x > y ? x : y; });
+    float mine[NY], inv[NY];
+#pragma unroll
+    for (int i = 0; i < NY; ++i) { mine[i] = __uint_as_float(ymax[i]); inv[i] = safe_reciprocal(mine[i]); }
+    // The way back for the reciprocals and maxima and, behind the weights, the sums' way in, pair by pair: what a pair needs
+    // does not stay in registers.
+    uint32_t w[8];
+    float y[NY][3];
+    auto add = [](uint32_t x, uint32_t other) { return __uint_as_float(x) + __uint_as_float(other); };
+    auto block_codes = [&](int b, float rcp, float amax, float (&sum)[3]) __attribute__((always_inline)) {
+      sum[0] = sum[1] = sum[2] = 0.f;
+#pragma unroll
+      for (int i = b * TPB; i < (b + 1) * TPB; ++i) {
+        if constexpr (WITH_ERR) asm volatile("" : "+v"(t[i]));            // tile by tile, or registers run out
+        floatx4 cw = {1.f, 1.f, 1.f, 1.f};
+        if constexpr (WITH_ERR && WEIGHTED) cw = *reinterpret_cast<const floatx4*>(sh.cw + 16 * i + 4 * q);
+        uint32_t c[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          c[e] = search_code<BITS>(sh.search, t[i][e] * rcp);
+          if constexpr (WITH_ERR) {
+            const float qv = sh.code[c[e]], err = t[i][e] - qv * amax;
+            float werr = err, wqv = qv;
+            if constexpr (WEIGHTED) { werr = cw[e] * err; wqv = cw[e] * qv; }
+            sum[0] = fmaf(werr, err, sum[0]);
+            sum[1] = fmaf(werr, qv, sum[1]);
+            sum[2] = fmaf(wqv, qv, sum[2]);
+          }
+        }
+        w[i] = c[0] | (c[1] << BITS) | (c[2] << (2 * BITS)) | (c[3] << (3 * BITS));
+      }
+    };
+#pragma unroll
+    for (int i = 0; i < NY; ++i) {
+      uint32_t xr[2] = {__float_as_uint(inv[i]), __float_as_uint(inv[i])}, xm[2] = {ymax[i], ymax[i]};
+      if constexpr (NX > 1) { swap_rows(xr[0], xr[1]); if constexpr (WITH_ERR) swap_rows(xm[0], xm[1]); }
+      float xs[2][3];
+#pragma unroll
+      for (int j = 0; j < (NX > 1 ? 2 : 1); ++j) {
+        const int b = i + j * (NX / 2);
+        uint32_t vr[2] = {xr[j], xr[j]}, vm[2] = {xm[j], xm[j]};
+        if constexpr (NB > 1) { swap_halves(vr[0], vr[1]); if constexpr (WITH_ERR) swap_halves(vm[0], vm[1]); }
+        float vs[2][3];
+#pragma unroll
+        for (int h = 0; h < (NB > 1 ? 2 : 1); ++h)
+          block_codes(b + h * NX, __uint_as_float(vr[h]), __uint_as_float(vm[h]), vs[h]);
+        if constexpr (WITH_ERR) {
+#pragma unroll
+          for (int e = 0; e < 3; ++e) {
+            uint32_t l = __float_as_uint(vs[0][e]), u = __float_as_uint(vs[NB > 1 ? 1 : 0][e]);
+            swap_halves(l, u);
+            xs[j][e] = add(l, u);
+          }
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+      if constexpr (WITH_ERR) {
+#pragma unroll
+        for (int e = 0; e < 3; ++e) {
+          uint32_t l = __float_as_uint(xs[0][e]), u = __float_as_uint(xs[NX > 1 ? 1 : 0][e]);
+          swap_rows(l, u);
+          y[i][e] = add(l, u);
+        }
+      }
+    }
+    uint32_t out[BITS];
+    gather_codes<BITS>(w, out);
+    const bool row_live = r0 + n < a.d;
+    uint8_t* to = codes + (((uint64_t)r0 * a.k + c0) / 16 * (2 * BITS)) + code_lane;
+    if (wide) {
+      if (row_live && 2 * q < tiles) {
+        if constexpr (BITS == 8) {
+          reinterpret_cast<uint4*>(to)[0] = make_uint4(out[0], out[1], out[2], out[3]);
+          reinterpret_cast<uint4*>(to)[1] = make_uint4(out[4], out[5], out[6], out[7]);
+        } else if constexpr (BITS == 4) {
+          *reinterpret_cast<uint4*>(to) = make_uint4(out[0], out[1], out[2], out[3]);
+        } else if constexpr (BITS == 3) {
+          *reinterpret_cast<uint3*>(to) = make_uint3(out[0], out[1], out[2]);
+        } else {
+          *reinterpret_cast<uint2*>(to) = make_uint2(out[0], out[1]);
+        }
+      }
+    } else {
+#pragma unroll
+      for (int h = 0; h < 2; ++h)                     // runs of 16 weights; 3 bits: 48 bits, 2-byte aligned
+        if (row_live && 2 * q + h < tiles) {
+          if constexpr (BITS == 3) {
+            uint16_t* p = reinterpret_cast<uint16_t*>(to + 6 * h);
+            p[0] = (uint16_t)(h ? out[1] >> 16 : out[0]);
+            p[1] = (uint16_t)(h ? out[2] : out[0] >> 16);
+            p[2] = (uint16_t)(h ? out[2] >> 16 : out[1]);
+          } else {
+#pragma unroll
+            for (int i = 0; i < BITS / 2; ++i) reinterpret_cast<uint32_t*>(to + 2 * BITS * h)[i] = out[h * (BITS / 2) + i];
+          }
+        }
+    }
+    if constexpr (WITH_ERR) {
+      BlockRec* at = blk + ((uint64_t)r0 * a.k + c0) / (4 * QPB) + blk_lane;
+      if (row_live && blk_live) {
+#pragma unroll
+        for (int i = 0; i < NY; ++i) {
+          BlockRec rec;
+          rec.s = mine[i]; rec.e2 = y[i][0]; rec.eq = y[i][1]; rec.q2 = y[i][2];
+          if (i == 0 || 4 * QPB * (block0 + i) < 16 * tiles) at[i] = rec;
+        }
+      }
+    } else {
+      float* at = reinterpret_cast<float*>(blk) + ((uint64_t)r0 * a.k + c0) / (4 * QPB) + blk_lane;    // the absmax alone
+      if (row_live && blk_live) {
+#pragma unroll
+        for (int i = 0; i < NY; ++i)
+          if (i == 0 || 4 * QPB * (block0 + i) < 16 * tiles) at[i] = mine[i];
+      }
+    }
+  }
+}
+
+template <int BITS, bool WITH_ERR, bool WEIGHTED>
+__device__ __forceinline__ void walk_bands_block(const PhaseArgs& a, int block, int z, const BandShared& sh, int64_t c0, int band0, int band1) {
+  switch (block) {
+    case 16: walk_bands<BITS, 4, WITH_ERR, WEIGHTED>(a, z, sh, c0, band0, band1); break;
+    case 32: walk_bands<BITS, 8, WITH_ERR, WEIGHTED>(a, z, sh, c0, band0, band1); break;
+    case 64: walk_bands<BITS, 16, WITH_ERR, WEIGHTED>(a, z, sh, c0, band0, band1); break;
+    default: walk_bands<BITS, 32, WITH_ERR, WEIGHTED>(a, z, sh, c0, band0, band1); break;
+  }
+}
+
+// Launch: one-dimensional, batch * units8 workgroups, units = column stretches x groups of 8 nb bands, rounded up to a
 // multiple of 8; index decoded as (unit mod 8, problem, unit div 8) so that the problems of a batch that share a
 // stretch of W run on one XCD at the same time.
-template <bool WITH_ERR>
-__global__ __launch_bounds__(NTHR1) void lowrank_blockquant_bands_kernel(PhaseArgs a, int units, int tiles_n, int nb) {
-  constexpr int BPLANE = 2 * TN * KP;                     // bf16 elements: B hi, B lo
-  constexpr int YPLANE = 2 * TM * KP;                     // Y hi, Y lo; shares its space with the product tile
-  constexpr int PT_BYTES = TM * PP * 4 > YPLANE * 2 ? TM * PP * 4 : YPLANE * 2;
-  __shared__ __attribute__((aligned(16))) __bf16 s_b[BPLANE];
-  __shared__ __attribute__((aligned(16))) char s_yp[PT_BYTES];
-  __shared__ __attribute__((aligned(16))) SearchEntry s_search[SEARCH_ENTRIES];
-  __shared__ float s_code[WITH_ERR ? 256 : 1];
-  __bf16* s_y = reinterpret_cast<__bf16*>(s_yp);
-  float* pt = reinterpret_cast<float*>(s_yp);
+template <bool WITH_ERR, bool WEIGHTED>
+__global__ __launch_bounds__(NTHR1, 4) void lowrank_blockquant_bands_kernel(PhaseArgs a, int units, int tiles_n, int nb) {
+  __shared__ BandShared sh;
   const int tid = threadIdx.x;
   const int slot8 = blockIdx.x >> 3;
   const int z = slot8 % a.batch;
   const int unit = (int)(blockIdx.x & 7) + 8 * (slot8 / a.batch);
   if (unit >= units) return;                   // padding of the unit count to a multiple of 8
-  const LoopProblem pr = a.prob[z];
-  const int nbands = (int)((a.d + TM - 1) / TM);
-  const int band0 = (unit / tiles_n) * nb;
-  const int band1 = band0 + nb < nbands ? band0 + nb : nbands;
+  const lq_config cfg = a.prob[z].cfg;
   const int64_t c0 = (int64_t)(unit % tiles_n) * TN;
-  const int wave = tid >> 6, lane = tid & 63, ln = lane & 31, lh = lane >> 5;
-  const int wr = wave >> 2, wc = wave & 3;      // 2 x 4 grid of 32x32 tiles
-
-  const int slot = pr.cfg.bits == 2 ? 0 : pr.cfg.bits == 3 ? 1 : pr.cfg.bits == 4 ? 2 : 3;
-  build_search_nosync(a.tables, slot, s_search);
+  const int slot = cfg.bits == 2 ? 0 : cfg.bits == 3 ? 1 : cfg.bits == 4 ? 2 : 3;
+  load_search_nosync(a.tables, slot, sh.search);
   if constexpr (WITH_ERR)
-    for (int i = tid; i < 256; i += NTHR1) s_code[i] = a.tables->code[slot][i];
-
-  const int rk = (a.rank + 15) / 16 * 16;
-  const int64_t dpad = (a.d + TM - 1) / TM * TM, kpad = (a.k + TN - 1) / TN * TN;
-  const __bf16* gy = reinterpret_cast<const __bf16*>(a.packed) + (size_t)z * a.stridePacked;
-  const __bf16* gb = gy + (size_t)2 * dpad * rk;
-  const floatx4 zero4 = {0.f, 0.f, 0.f, 0.f};
-  // lane parts of the addresses: 16-byte piece (tid & 7) of row tid / 8 of a plane; quad tid & 31 of row tid / 32 of W
-  const uint32_t p_lane = (uint32_t)(((tid >> 3) * rk + 8 * (tid & 7)) * 2);
-  const bool p_ok = 8 * (tid & 7) < rk;         // the rank fits one 64-deep chunk (checked by the launcher)
-  const uint32_t w_lane = (uint32_t)(((tid >> 5) * a.k + 4 * (tid & 31)) * 4);
-  const bool w_col_live = c0 + 4 * (tid & 31) < a.k;
-
-  // B planes of this column stretch: rows 0..63 and 64..127 of hi and of lo, one piece each per thread
+    for (int i = tid; i < (1 << cfg.bits); i += NTHR1) sh.code[i] = a.tables->code[slot][i];
+  if constexpr (WEIGHTED)
+    for (int i = tid; i < TN; i += NTHR1) {
+      const bool live = c0 + i < a.k;
+      sh.rc[i] = live ? a.rsc[c0 + i] : 1.0f;
+      if constexpr (WITH_ERR) sh.cw[i] = live ? a.col_w[c0 + i] : 1.0f;
+    }
   {
-    const char* bbase[4] = {reinterpret_cast<const char*>(gb + (size_t)c0 * rk),
-                            reinterpret_cast<const char*>(gb + (size_t)(c0 + 64) * rk),
-                            reinterpret_cast<const char*>(gb + (size_t)(kpad + c0) * rk),
-                            reinterpret_cast<const char*>(gb + (size_t)(kpad + c0 + 64) * rk)};
+    // planes of B: 16-byte piece tid & 7 of rows tid / 8 and tid / 8 + 64, of hi and of lo
+    const int rk = (a.rank + 15) / 16 * 16;
+    const int64_t dpad = (a.d + TM - 1) / TM * TM, kpad = (a.k + TN - 1) / TN * TN;
+    const __bf16* gb = reinterpret_cast<const __bf16*>(a.packed) + (size_t)z * a.stridePacked + (size_t)2 * dpad * rk;
+    const int piece = 8 * (tid & 7);
     floatx4 bp[4];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) bp[i] = p_ok ? *reinterpret_cast<const floatx4*>(bbase[i] + p_lane) : zero4;
+    for (int i = 0; i < 4; ++i) {
+      const __bf16* from = gb + (size_t)((i >> 1) * kpad + c0 + 64 * (i & 1) + (tid >> 3)) * rk;
+      bp[i] = piece < rk ? *reinterpret_cast<const floatx4*>(from + piece) : floatx4{0.f, 0.f, 0.f, 0.f};
+    }
 #pragma unroll
     for (int i = 0; i < 4; ++i)
-      *reinterpret_cast<floatx4*>(s_b + (size_t)((tid >> 3) + 64 * i) * KP + 8 * (tid & 7)) = bp[i];
+      *reinterpret_cast<floatx4*>(sh.b + (size_t)((tid >> 3) + 64 * i) * KP + piece) = bp[i];
   }
-
-  float4 wnext[4];
-  floatx4 ynext[2];
-  auto prefetch = [&](int band) {
-    const int64_t r0 = (int64_t)band * TM;
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int64_t row_u = r0 + (NTHR1 / 32) * u;                       // uniform
-      const char* base = reinterpret_cast<const char*>(a.W + (size_t)row_u * a.k + c0);
-      wnext[u] = (row_u + (tid >> 5) < a.d && w_col_live) ? *reinterpret_cast<const float4*>(base + w_lane)
-                                                           : make_float4(0.f, 0.f, 0.f, 0.f);
-    }
-    const char* ybase[2] = {reinterpret_cast<const char*>(gy + (size_t)r0 * rk),
-                            reinterpret_cast<const char*>(gy + (size_t)(dpad + r0) * rk)};
-#pragma unroll
-    for (int i = 0; i < 2; ++i) ynext[i] = p_ok ? *reinterpret_cast<const floatx4*>(ybase[i] + p_lane) : zero4;
-  };
-  prefetch(band0);
-
-  for (int band = band0; band < band1; ++band) {
-    const int64_t r0 = (int64_t)band * TM;
-    __syncthreads();          // the previous band's epilogue is done with the product tile (first band: nothing)
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-      *reinterpret_cast<floatx4*>(s_y + (size_t)((tid >> 3) + 64 * i) * KP + 8 * (tid & 7)) = ynext[i];
-    float4 wcur[4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) wcur[u] = wnext[u];
-    __syncthreads();          // Y planes (and, first band, B planes and tables) visible
-    if (band + 1 < band1) prefetch(band + 1);
-
-    floatx16 acc;
-#pragma unroll
-    for (int e = 0; e < 16; ++e) acc[e] = 0.0f;
-    const __bf16* yh = s_y + (size_t)(32 * wr + ln) * KP + 8 * lh;
-    const __bf16* yl = yh + (size_t)TM * KP;
-    const __bf16* bh = s_b + (size_t)(32 * wc + ln) * KP + 8 * lh;
-    const __bf16* bl = bh + (size_t)TN * KP;
-#pragma unroll
-    for (int kg = 0; kg < KC2 / 16; ++kg) {
-      if (16 * kg < rk) {
-        const bf16x8 ah = *reinterpret_cast<const bf16x8*>(yh + 16 * kg), al = *reinterpret_cast<const bf16x8*>(yl + 16 * kg);
-        const bf16x8 vh = *reinterpret_cast<const bf16x8*>(bh + 16 * kg), vl = *reinterpret_cast<const bf16x8*>(bl + 16 * kg);
-        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(al, vh, acc, 0, 0, 0);
-        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah, vl, acc, 0, 0, 0);
-        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah, vh, acc, 0, 0, 0);
-      }
-    }
-    __syncthreads();          // all reads of the Y planes done before the product overwrites them
-#pragma unroll
-    for (int e = 0; e < 16; ++e) {
-      const int row = 32 * wr + 8 * (e >> 2) + 4 * lh + (e & 3);
-      pt[row * PP + 32 * wc + ln] = acc[e];
-    }
-    __syncthreads();
-    switch (pr.cfg.bits) {
-      case 2: phase1_dispatch_block<2, WITH_ERR>(a, pr.cfg.block, z, pt, s_search, s_code, r0, c0, wcur); break;
-      case 3: phase1_dispatch_block<3, WITH_ERR>(a, pr.cfg.block, z, pt, s_search, s_code, r0, c0, wcur); break;
-      case 4: phase1_dispatch_block<4, WITH_ERR>(a, pr.cfg.block, z, pt, s_search, s_code, r0, c0, wcur); break;
-      default: phase1_dispatch_block<8, WITH_ERR>(a, pr.cfg.block, z, pt, s_search, s_code, r0, c0, wcur); break;
-    }
+  const int nbands = (int)((a.d + BAND - 1) / BAND), first = (unit / tiles_n) * (8 * nb);
+  const int band0 = first + __builtin_amdgcn_readfirstlane(tid >> 6), band1 = first + 8 * nb < nbands ? first + 8 * nb : nbands;
+  switch (cfg.bits) {
+    case 2: walk_bands_block<2, WITH_ERR, WEIGHTED>(a, cfg.block, z, sh, c0, band0, band1); break;
+    case 3: walk_bands_block<3, WITH_ERR, WEIGHTED>(a, cfg.block, z, sh, c0, band0, band1); break;
+    case 4: walk_bands_block<4, WITH_ERR, WEIGHTED>(a, cfg.block, z, sh, c0, band0, band1); break;
+    default: walk_bands_block<8, WITH_ERR, WEIGHTED>(a, cfg.block, z, sh, c0, band0, band1); break;
   }
+}
+
+// Steps of eight bands per workgroup: the fewest rounds of 512 resident workgroups times what one of them takes, a step each and
+// about as much as one more for the tables, the planes of B and the first loads.
+static int bands_per_wave(int64_t steps, int64_t stretches, int64_t batch) {
+  double least = 1e300;
+  int best = 1;
+  for (int64_t nb = 1; nb <= steps && nb <= 16; ++nb) {
+    const int64_t wgs = stretches * ((steps + nb - 1) / nb) * batch;
+    const double t = (double)((wgs + 511) / 512) * ((double)nb + 1.0);
+    if (t < least) { least = t; best = (int)nb; }
+  }
+  return best;
 }
 
 int launch_lowrank_blockquant(const PhaseArgs& a, bool with_err, hipStream_t st) {
@@ -568,25 +815,27 @@ int launch_lowrank_blockquant(const PhaseArgs& a, bool with_err, hipStream_t st)
                  (double)a.d * a.k * (4.0 * a.batch + a.quant_bytes_per_weight) + 4.0 * a.rank * (double)(a.d + a.k) * a.batch);
   const bool split = a.packed != nullptr;
   if (split && a.rank <= KC2) {
-    // bands per workgroup: as many as leave a few thousand workgroups, at most 8
-    int64_t nb = tiles * a.batch / 4096;
-    nb = nb < 1 ? 1 : (nb > 8 ? 8 : nb);
-    if (nb > nbands) nb = nbands;
-    const int64_t units = (int64_t)tiles_n * ((nbands + nb - 1) / nb);
+    const int64_t steps = ((a.d + BAND - 1) / BAND + 7) / 8;
+    const int nb = bands_per_wave(steps, tiles_n, a.batch);
+    const int64_t units = (int64_t)tiles_n * ((steps + nb - 1) / nb);
     const dim3 grid((unsigned)((units + 7) / 8 * 8 * a.batch));
-    if (with_err) hipLaunchKernelGGL(lowrank_blockquant_bands_kernel<true>, grid, dim3(NTHR1), 0, st, a, (int)units, tiles_n, (int)nb);
-    else hipLaunchKernelGGL(lowrank_blockquant_bands_kernel<false>, grid, dim3(NTHR1), 0, st, a, (int)units, tiles_n, (int)nb);
+    auto go = [&](auto err, auto weighted) {
+      hipLaunchKernelGGL((lowrank_blockquant_bands_kernel<decltype(err)::value, decltype(weighted)::value>), grid, dim3(NTHR1), 0, st, a,
+                         (int)units, tiles_n, nb);
+    };
+    if (a.rsc) { if (with_err) go(std::true_type{}, std::true_type{}); else go(std::false_type{}, std::true_type{}); }
+    else { if (with_err) go(std::true_type{}, std::false_type{}); else go(std::false_type{}, std::false_type{}); }
     LQ_HIP_TRY(hipGetLastError());
     return LQ_OK;
   }
   const dim3 grid((unsigned)((tiles + 7) / 8 * 8 * a.batch));
-  if (split) {
-    if (with_err) hipLaunchKernelGGL((lowrank_blockquant_kernel<true, true>), grid, dim3(NTHR1), 0, st, a, (int)tiles, tiles_n);
-    else hipLaunchKernelGGL((lowrank_blockquant_kernel<false, true>), grid, dim3(NTHR1), 0, st, a, (int)tiles, tiles_n);
-  } else {
-    if (with_err) hipLaunchKernelGGL((lowrank_blockquant_kernel<true, false>), grid, dim3(NTHR1), 0, st, a, (int)tiles, tiles_n);
-    else hipLaunchKernelGGL((lowrank_blockquant_kernel<false, false>), grid, dim3(NTHR1), 0, st, a, (int)tiles, tiles_n);
-  }
+  auto go = [&](auto err, auto weighted) {
+    constexpr bool E = decltype(err)::value, F = decltype(weighted)::value;
+    if (split) hipLaunchKernelGGL((lowrank_blockquant_kernel<E, true, F>), grid, dim3(NTHR1), 0, st, a, (int)tiles, tiles_n);
+    else hipLaunchKernelGGL((lowrank_blockquant_kernel<E, false, F>), grid, dim3(NTHR1), 0, st, a, (int)tiles, tiles_n);
+  };
+  if (a.rsc) { if (with_err) go(std::true_type{}, std::true_type{}); else go(std::false_type{}, std::true_type{}); }
+  else { if (with_err) go(std::true_type{}, std::false_type{}); else go(std::false_type{}, std::false_type{}); }
   LQ_HIP_TRY(hipGetLastError());
   return LQ_OK;
 }

@@ -44,10 +44,16 @@ int bits_slot(int bits);
 // lut[j], j = floor((x + 1) * 256) clamped to [0, 511]: number of thresholds that lie safely below bucket j,
 // built so that at most two further thresholds can be <= any x that lands in the bucket.  The code of x is
 // then lut[j] + (x >= thr[lut[j]]) + (x >= thr[lut[j] + 1]).  thr is padded with +inf.
+// search[slot]: the entries of the decomposition's own search (search_offset in nf_device.h): the code is below + (x >= thr).
+struct alignas(8) SearchEntry { float thr; uint32_t below; };
+constexpr int search_buckets(int bits) { return bits == 8 ? 256 : 16; }           // per unit of x
+constexpr int search_entries(int bits) { return 2 * search_buckets(bits) + 2; }
+constexpr int SEARCH_ENTRIES = search_entries(8);
 struct NfTables {
   float code[4][256];
   float thr[4][260];
   uint8_t lut[4][512];
+  alignas(16) SearchEntry search[4][SEARCH_ENTRIES];
 };
 typedef NfTables HostTables;
 const HostTables& host_tables();

@@ -165,14 +165,24 @@ int lq_test_bucket_code(int bits, float x) {
   const int slot = bits_slot(bits);
   if (slot < 0) return -1;
   const HostTables& t = host_tables();
-  // the search of the decomposition's quantize pass (search_code in fused_kernels.hip): bucket table, then one
-  // comparison (two for 8 bits); the stand-alone quantizer counts thresholds for 2 and 3 bits, which is the definition
+  // the search of the stand-alone quantizer for 4 and 8 bits: bucket table, then one comparison (two for 8 bits); for 2 and 3
+  // bits it counts thresholds, which is the definition
   int j = (int)std::fmaf(x, 256.0f, 256.0f);
   if (!(std::fmaf(x, 256.0f, 256.0f) >= 0.0f)) j = 0;   // NaN and negatives as the device's conversion treats them
   j = j < 0 ? 0 : (j > 513 ? 513 : j);
   const int c0 = t.lut[slot][j < 511 ? j : 511];
   if (bits <= 4) return c0 + (x >= t.thr[slot][c0]);          // one threshold per bucket at most
   return c0 + (x >= t.thr[slot][c0]) + (x >= t.thr[slot][c0 + 1]);
+}
+
+int lq_test_search_code(int bits, float x) {
+  const int slot = bits_slot(bits);
+  if (slot < 0) return -1;
+  const HostTables& t = host_tables();
+  const uint32_t offset = bits == 8 ? search_offset<8>(x) : search_offset<4>(x);
+  if ((int)offset / 8 >= search_entries(bits)) return -2;
+  const SearchEntry& e = t.search[slot][offset / 8];
+  return (int)e.below + (x >= e.thr);
 }
 
 float lq_test_sigma_by_reciprocal(float v, int levels) {

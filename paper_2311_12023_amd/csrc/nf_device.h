@@ -88,10 +88,22 @@ struct BucketSearch {
 template <> struct Thresholds<4> : BucketSearch<1> { __device__ Thresholds(const LdsTables& tt, const DevTables*) : BucketSearch<1>(tt) {} };
 template <> struct Thresholds<8> : BucketSearch<2> { __device__ Thresholds(const LdsTables& tt, const DevTables*) : BucketSearch<2>(tt) {} };
 
-// ---- reductions over the QPB = 4, 8, 16 or 32 consecutive lanes that hold one block (aligned groups) ----
-// Cross-lane moves by DPP: quad_perm for the two steps inside a quad; after those every quad is uniform, so the
-// mirror of a half row swaps the two quads of an 8-lane group and the mirror of a row the two halves of a 16-lane
-// group.  Only the last step of a 32-lane group goes through the LDS crossbar.
+// Code search of the decomposition's quantize pass: 16 buckets per unit, for 8 bits 256, and one comparison per weight.  The
+// entry of x is found by one fused product whose sum keeps the bucket number in the mantissa bits from the third on, so that a mask
+// leaves the entry's byte offset; NaN has none of these bits and takes the first entry, whose comparison it fails.  The sum
+// rounds to 1/8 of a bucket: entry j serves x from (j - 1/16) / buckets - 1 to the same of j + 1, ends included, and counts the
+// thresholds up to its lower end.  Thresholds are 1.27 (8 bits), 1.29 (4), 2.7 and 8 buckets apart at the least, so one at most is left
+// to compare.  |x| is at most 1 + 2^-20 (a weight by the reciprocal of its block's largest one, or by 0), which is the last entry
+// but one.  Up to 4 bits the 34 entries of 8 bytes lie in different LDS banks but for two pairs: with 256 buckets per unit for
+// every width the quantize pass spent half of its LDS cycles on bank conflicts.
+template <int BITS>
+__host__ __device__ __forceinline__ uint32_t search_offset(float x) {
+  constexpr float scale = (float)search_buckets(BITS), base = (float)(1 << 20) + scale;
+  return __builtin_bit_cast(uint32_t, fmaf(x, scale, base)) & ((4u * search_buckets(BITS) - 1u) << 3);
+}
+
+// ---- cross-lane moves by DPP: quad_perm inside a quad of lanes; where every quad is uniform the mirror of a half row swaps the
+// two quads of an 8-lane group and the mirror of a row the two halves of a 16-lane group ----
 constexpr int DPP_QUAD_XOR1 = 0xB1, DPP_QUAD_XOR2 = 0x4E, DPP_ROW_HALF_MIRROR = 0x141, DPP_ROW_MIRROR = 0x140;
 template <int CTRL>
 __device__ __forceinline__ float dpp_move(float x) {
@@ -100,25 +112,6 @@ __device__ __forceinline__ float dpp_move(float x) {
 template <int CTRL>
 __device__ __forceinline__ uint32_t dpp_move_u32(uint32_t x) {
   return (uint32_t)__builtin_amdgcn_mov_dpp((int)x, CTRL, 0xf, 0xf, true);
-}
-
-template <int QPB>
-__device__ __forceinline__ float group_max_lanes(float x) {
-  x = fmaxf(x, dpp_move<DPP_QUAD_XOR1>(x));
-  x = fmaxf(x, dpp_move<DPP_QUAD_XOR2>(x));
-  if constexpr (QPB >= 8) x = fmaxf(x, dpp_move<DPP_ROW_HALF_MIRROR>(x));
-  if constexpr (QPB >= 16) x = fmaxf(x, dpp_move<DPP_ROW_MIRROR>(x));
-  if constexpr (QPB >= 32) x = fmaxf(x, __shfl_xor(x, 16));
-  return x;
-}
-template <int QPB>
-__device__ __forceinline__ float group_sum_lanes(float x) {
-  x += dpp_move<DPP_QUAD_XOR1>(x);
-  x += dpp_move<DPP_QUAD_XOR2>(x);
-  if constexpr (QPB >= 8) x += dpp_move<DPP_ROW_HALF_MIRROR>(x);
-  if constexpr (QPB >= 16) x += dpp_move<DPP_ROW_MIRROR>(x);
-  if constexpr (QPB >= 32) x += __shfl_xor(x, 16);
-  return x;
 }
 
 __device__ inline float run_absmax(const float (&t)[16]) {

@@ -98,6 +98,12 @@ static void build_tables(HostTables& t) {
       if (upto - below > compares) below = upto - compares;
       t.lut[s][j] = (uint8_t)below;
     }
+    for (int j = 0; j < search_entries(widths[s]); ++j) {
+      const double edge = (j - 0.0625) / search_buckets(widths[s]) - 1.0;
+      uint32_t c0 = 0;
+      while (t.thr[s][c0] <= edge) ++c0;                    // past the last threshold they are infinite
+      t.search[s][j] = SearchEntry{t.thr[s][c0], c0};
+    }
   }
 }
 

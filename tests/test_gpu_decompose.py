@@ -157,7 +157,7 @@ def test_factorize_weighted(env, oracle):
     assert abs(werr - np.sum(ref[r:] ** 2)) < 1e-4 * np.sum(ref[r:] ** 2)
 
 
-def check_decomposition_consistency(oracle, w, out, ocfg, rank, row_w=None, col_w=None):
+def check_decomposition_consistency(oracle, w, out, ocfg, rank, row_w=None, col_w=None, product_error=0.0):
     """What must hold for the GPU's own outputs whatever the trajectory."""
     d, k = w.shape
     codes = oracle.unpack(out["codes"].cpu().numpy(), d * k, ocfg.bits)
@@ -169,7 +169,7 @@ def check_decomposition_consistency(oracle, w, out, ocfg, rank, row_w=None, col_
     t = w.astype(np.float64) - l1 @ l2
     wt = 1.0 if row_w is None else np.outer(row_w.astype(np.float64), col_w.astype(np.float64))
     eps = np.sqrt(np.sum(wt * (t - q) ** 2))
-    assert abs(eps - out["err"]) < 2e-5 * eps                      # reported error = error of the returned pieces
+    assert abs(eps - out["err"]) < 2e-5 * eps + product_error      # reported error = error of the returned pieces
     # the returned codes are the oracle's quantization of W - L1 L2 up to fp32 rounding of that residual
     ocodes, osidx, ov, _ = oracle.quantize(t.astype(np.float32).ravel(), ocfg)
     assert np.mean(ocodes != codes) < 2e-3
@@ -254,6 +254,26 @@ def test_decompose_quantized_initialisation(env, oracle, weighted):
     assert not np.allclose(plain["sigma"], one["sigma"], rtol=1e-3)
     with pytest.raises(lq.LqError):
         lq.error_table(wt, r, [lq.config(3, 32, 64)], 2, params=lq.SvdParams(init_quantized=1))
+
+
+# (d, k, rank): rows past a band of 16, columns past a stretch of 128, a lane's 32 columns cut by the edge (k = 16 mod 32), one
+# column run alone, ranks on both sides of the 32-deep products and of the kernel's 64
+@pytest.mark.parametrize("d,k,rank", [(129, 144, 16), (160, 272, 1), (177, 400, 17), (257, 128, 33), (208, 656, 64), (240, 384, 65)])
+@pytest.mark.parametrize("bits", [2, 3, 4, 8])
+@pytest.mark.parametrize("weighted", [False, True])
+def test_quantize_pass_edges(env, oracle, d, k, rank, bits, weighted):
+    torch, lq = env
+    blocks = [b for b in (16, 32, 64, 128) if k % b == 0]
+    w = gen.weight_matrix(d, k, 100 * d + bits, min(d, k) // 4, outlier_frac=0.004)
+    rw, cw = (gen.positive_weights(d, 5), gen.positive_weights(k, 6)) if weighted else (None, None)
+    fisher = dict(row_w=torch.from_numpy(rw).cuda(), col_w=torch.from_numpy(cw).cuda()) if weighted else {}
+    for block in blocks:
+        out = lq.decompose(torch.from_numpy(w).cuda(), rank, lq.config(bits, block, 16), 2, seed=3, want_dense=True, **fisher)
+        # L1 L2 in split products is off by 2^-16 of |L1| |L2| at most, which the error of an 8-bit quantizer is small enough to show
+        l1, l2 = (np.abs(out[n].cpu().numpy().astype(np.float64)) for n in ("L1", "L2"))
+        scale = 1.0 if rw is None else np.sqrt(np.outer(rw.astype(np.float64), cw.astype(np.float64)))
+        check_decomposition_consistency(oracle, w, out, oracle.config(bits, block, 16), rank, rw, cw,
+                                        product_error=2.0 ** -16 * np.linalg.norm(scale * (l1 @ l2)))
 
 
 def test_decompose_weighted(env, oracle):

@@ -7,6 +7,8 @@ import re
 import numpy as np
 import pytest
 
+import testing_lib
+
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 LIB = os.path.join(ROOT, "paper_2311_12023_amd", "liblq_hip.so")
 TEST_LIB = os.path.join(ROOT, "paper_2311_12023_amd", "liblq_hip_testing.so")
@@ -222,6 +224,33 @@ def test_code_search_equals_brute_force(L, oracle, bits):
     assert np.array_equal(got[inside], want[inside])
     assert L.lq_test_bucket_code(bits, float("nan")) == 0
     assert L.lq_test_bucket_code(5, 0.0) == -1
+
+
+@pytest.mark.parametrize("bits", [2, 3, 4, 8])
+def test_quantize_pass_search_equals_brute_force(oracle, bits):
+    """The search of the decomposition's quantize pass against the oracle's nearest code: every float within 3 ulp of a threshold
+    and of what bounds an entry (the edge of its bucket and an eighth, a sixteenth and a thirty-second below), a sweep
+    of [-1, 1], the most that rounding makes of a block's largest weight, and NaN."""
+    L = testing_lib.load()
+    q = oracle.codebook(bits)
+    buckets = 256 if bits == 8 else 16
+    j = np.arange(2 * buckets + 2, dtype=np.float64)
+    pts = [np.linspace(-1, 1, 20001).astype(np.float32)]
+    for base in (((q[:-1].astype(np.float64) + q[1:]) / 2), *((j - m) / buckets - 1 for m in (0, 1 / 16, 1 / 32, 1 / 8)), q):
+        up = dn = np.asarray(base, np.float32)
+        pts.append(up)
+        for _ in range(3):
+            up, dn = np.nextafter(up, np.float32(4)), np.nextafter(dn, np.float32(-4))
+            pts += [up, dn]
+    x = np.concatenate(pts)
+    x = x[np.abs(x) <= 1]
+    blocks = np.zeros((x.size, 16), np.float32)
+    blocks[:, 0], blocks[:, 1] = 1.0, x
+    want = oracle.quantize(blocks.ravel(), oracle.config(bits, 16, 16))[0].reshape(-1, 16)[:, 1]
+    assert np.array_equal([L.lq_test_search_code(bits, float(v)) for v in x], want)
+    for s in (-1, 1):
+        assert L.lq_test_search_code(bits, s * (1 + 2.0 ** -20)) == (2 ** bits - 1 if s > 0 else 0)
+    assert L.lq_test_search_code(bits, float("nan")) == L.lq_test_search_code(bits, -float("nan")) == 0
 
 
 @pytest.mark.parametrize("scale_bits", [2, 3, 4, 5, 6, 7, 8])

@@ -39,7 +39,7 @@ def load():
         L.lq_test_search_points.argtypes = [C.c_double, it, C.c_double, it, it, C.c_double, vp]
         L.lq_test_rows_finish.argtypes = [i64, i64, it]
         L.lq_test_lds_limit.restype = C.c_size_t
-        L.lq_test_bucket_code.argtypes = [C.c_int, C.c_float]
+        L.lq_test_bucket_code.argtypes = L.lq_test_search_code.argtypes = [C.c_int, C.c_float]
         L.lq_test_sigma_by_reciprocal.restype = C.c_float
         L.lq_test_sigma_by_reciprocal.argtypes = [C.c_float, it]
         L.lq_test_capture_iterate.argtypes = [it, it, vp, vp]
