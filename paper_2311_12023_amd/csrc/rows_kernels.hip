@@ -2,14 +2,22 @@
 // Y[m x N] = X dequant(codes) + (X L1) L2.  Two launches: the kernel below multiplies X with [Q | L1]
 // over ranges of the reduction, qmatvec_finish_kernel or rows_finish_kernel adds the ranges and the product (X L1) L2.
 //
-// Every weight is decoded (six vector instructions: extract, look up, scale, split into bf16 halves) for at most 48 rows,
-// where its matrix instructions take less time than the decode; the codes themselves are 0.25 to 1 byte per weight.  By
-// count the decode is a third of the kernel's 20 to 25 us at 24 rows x 4096 x 11008; what bounds it there is the latency of
-// loads one step ahead with two wavefronts per SIMD.  Nothing is staged: a lane fetches half a 16-weight run of eight reduction rows, decodes them straight into the
-// operand layout of v_mfma_f32_16x16x32_bf16 (8 column sets of 16 columns, column 8 c + j in set j) and multiplies them with
-// rows of X that it splits into bf16 halves on the way.  A workgroup owns 128 columns at a time; its eight wavefronts take
-// turns at the 32-deep reduction steps and their sums are added in order through LDS.
-// Whole call on 4096 x 11008, NF4, rank 64 (4096 x 4096): 24 rows 79 -> 32 us (45 -> 20), 64 rows 84 -> 50 us (47 -> 27),
+// A lane fetches half a 16-weight run of eight reduction rows, turns them straight into the operand layout of
+// v_mfma_f32_16x16x32_bf16 (8 column sets of 16 columns) and multiplies them with rows of X that it splits into bf16
+// halves on the way; only the sums are staged.  A workgroup owns 128 columns at a time; its eight wavefronts take
+// turns at the 32-deep reduction steps and their sums are added in order through LDS.  Every weight is turned into operands for at
+// most 48 rows, so that takes the time, not the products, and there are two forms of it:
+// - Blocks of 64 weights and more, three steps per wavefront or more.  The 64 or 128 columns of a row that a tile has in a block share one scale, so X Q is the
+//   product of X, its columns times these scales, with values of the code book, whose bf16 halves come from a table for
+//   two rows of Q at a time (QrTable).  A wavefront computes a step's scales one per lane and hands them out through LDS.
+// - Otherwise: six vector instructions per weight (extract, look up, scale, split), by count a third of the time.
+// Per wavefront and step of 4096 x 11008 at 24 rows the first form takes 260 vector instructions instead of 605; what is left is latency: two
+// wavefronts per SIMD, loads one step ahead, and the first fetch (behind the first segment: asked for with that one's last
+// step) and last sum of each workgroup.  Whole calls, NF4 64/256, rank 64, second form -> first (us): 4096 x 11008 at 9 rows 27.5 ->
+// 21.1, 24 rows 30.6 -> 27.7, 48 rows 40.5 -> 37.1, 4096 x 4096 at 128 rows 41.4 -> 36.3; 11008 x 4096, 3 bits, 16 rows 42.3 -> 33.6; the
+// error against 64 bits goes from 4.4e-6 to 3.6e-6 (3 bits 3.2e-6).  What did not help: a wavefront per 64 columns and
+// four per step, two steps in flight (twice the loads of X: 29 us at 24 rows, 42 at 48), one copy of the table (bank conflicts: 29.4).
+// Second form, whole call on 4096 x 11008, NF4, rank 64 (4096 x 4096): 24 rows 79 -> 32 us (45 -> 20), 64 rows 84 -> 50 us (47 -> 27),
 // 128 rows 94 -> 85 us (52 -> 42) against the kernel for large m, whose steps take 2 us whatever they multiply (256-row tiles
 // of X staged through LDS, a barrier per step).  At 192 rows that kernel is ahead on the wide matrix (95 against 111 us)
 // and level on the square one, so the line is drawn at 128; rows_kernel_ahead in lq_api_matmul.cpp has the large weights
@@ -99,12 +107,65 @@ __device__ __forceinline__ uint32_t code_offset(uint2 r) {
   else return (r.x >> (J * BITS)) & (((1u << BITS) - 1u) << 2);
 }
 
+// The table of the form with the scales in X: for codes of up to 4 bits, for every pair of them, a word of their bf16 high halves
+// (the first one's in the lower half) 32 times and a word of their low halves 32 times, for 8 bits a word of both halves of every
+// code 32 times: a lane reads its own copy, and no two of the 32 lanes that LDS serves at a time meet in a bank (a single copy of
+// the 256 pairs of 4-bit codes took 60 % of the reads' cycles for conflicts).
+template <int BITS> struct QrTable {
+  static constexpr int entries = BITS == 8 ? 256 : 1 << (2 * BITS), shift = BITS == 8 ? 7 : 8, words = entries << (shift - 2);
+};
+// Codes of this lane in one row: with NBLK = 1 columns 8 c + j in set j, with NBLK = 2 columns 4 c + j of the first 64 and then of the
+// second.  They stay as they come from memory until words() puts set j at bits [j BITS, + BITS): put together at once they would
+// be waited for at once.
+template <int BITS, int NBLK>
+struct RowCodes {
+  uint32_t lo, hi;
+  // byte offset of the lane's first code in a row
+  __device__ __forceinline__ static uint32_t lane_offset(int c) {
+    if constexpr (NBLK == 2) return (uint32_t)(4 * BITS * c) / 8u;
+    else return BITS == 3 ? (uint32_t)(c >> 1) * 6u + 2u * (c & 1) : (uint32_t)(BITS * c);
+  }
+  // `row` (of codes, uniform) + `lane`; `second`: bytes to the second 64 columns (uniform)
+  __device__ __forceinline__ void load(const uint8_t* row, uint32_t lane, uint32_t second) {
+    if constexpr (BITS == 8) {
+      lo = *reinterpret_cast<const uint32_t*>(row + lane);
+      hi = *reinterpret_cast<const uint32_t*>(row + (NBLK == 2 ? second : 4u) + lane);
+    } else if constexpr (BITS == 3) {        // 2-byte aligned but for the 12 bits from bit 12 c on
+      uint16_t w[2];
+      __builtin_memcpy(w, row + lane, 2);
+      __builtin_memcpy(w + 1, row + (NBLK == 2 ? second : 2u) + lane, 2);
+      lo = w[0]; hi = w[1];
+    } else if constexpr (NBLK == 1) {
+      hi = 0;
+      if constexpr (BITS == 4) lo = *reinterpret_cast<const uint32_t*>(row + lane);
+      else lo = *reinterpret_cast<const uint16_t*>(row + lane);
+    } else if constexpr (BITS == 4) {
+      lo = *reinterpret_cast<const uint16_t*>(row + lane);
+      hi = *reinterpret_cast<const uint16_t*>(row + second + lane);
+    } else {
+      lo = (row + lane)[0]; hi = (row + second + lane)[0];
+    }
+  }
+  __device__ __forceinline__ void words(int c, uint32_t (&w)[2]) const {
+    w[0] = lo; w[1] = hi;
+    if constexpr (BITS == 3 && NBLK == 1) w[0] = (lo | (hi << 16)) >> (8 * (c & 1));
+    else if constexpr (BITS == 3) {
+      const uint32_t sh = 4 * (c & 1);
+      w[0] = ((lo >> sh) & 0xfffu) | (((hi >> sh) & 0xfffu) << 12);
+    } else if constexpr (BITS != 8 && NBLK == 2) w[0] = lo | (hi << (4 * BITS));
+  }
+};
+
 // The steps of all column tiles, in order (tile, step), are dealt out in equal contiguous shares, so that every compute unit
 // gets the same work whatever the number of tiles; a workgroup's part of a tile is one segment, numbered within the tile.
-template <int BITS, int RT, bool SPLIT>
+// NBLK: 0 the form for small blocks, else the number of blocks of a tile's 128 columns.
+template <int BITS, int RT, bool SPLIT, int NBLK>
 __global__ __launch_bounds__(64 * QR_WAVES, 2) void qrows_kernel(QrArgs a) {
+  constexpr int TABLE = NBLK == 0 ? 1 << BITS : QrTable<BITS>::words;
+  typedef uint32_t uintx4 __attribute__((ext_vector_type(4)));
   __shared__ struct {
-    float code[1 << BITS];                   // first: a code's offset in the table is its LDS address
+    uint32_t code[TABLE];                    // first: a code's offset in the table is its LDS address
+    __attribute__((aligned(16))) float scale[NBLK == 0 ? 4 : QR_WAVES * NBLK * 32];
     __attribute__((aligned(16))) float sum[QR_WAVES][4][QR_SETS][64];
   } sh;
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
@@ -138,7 +199,7 @@ __global__ __launch_bounds__(64 * QR_WAVES, 2) void qrows_kernel(QrArgs a) {
     }
   };
   floatx4 acc[RT][QR_SETS];
-  auto multiply = [&](const float (&w)[8], auto set) {
+  auto multiply = [&](const float (&w)[8], auto set) __attribute__((always_inline)) {
     constexpr int j = decltype(set)::value;
     bf16x8 wh, wl;
     split8<SPLIT>(w, wh, wl);
@@ -152,7 +213,32 @@ __global__ __launch_bounds__(64 * QR_WAVES, 2) void qrows_kernel(QrArgs a) {
     for (int t = 0; t < RT; ++t) acc[t][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xh[t], wh, acc[t][j], 0, 0, 0);
   };
 
-  bool table = false;
+  // The form with the scales in X: what a step needs of X, codes and scales, one step ahead and across segments.
+  constexpr int NX = NBLK == 2 ? 2 : 1;
+  typedef RowCodes<BITS, NBLK == 0 ? 1 : NBLK> Row;
+  const uint32_t run_bytes = (uint32_t)(a.N / 16 * (2 * BITS)), row_blocks = (uint32_t)(a.N >> a.block_shift);   // of a row
+  const uint32_t row_lane = (uint32_t)(8 * q) * run_bytes + Row::lane_offset(c);
+  const uint32_t lane4 = 4u * (lane & 31);                              // this lane's copy of a table entry
+  float* const scales = sh.scale + (NBLK == 0 ? 0 : wave * (NX * 32));
+  Row cw[8];
+  uint32_t si = 0;
+  float vv = 0.f;
+  auto fetch_step = [&](int tile, int s) __attribute__((always_inline)) {
+    const int64_t col0 = (int64_t)tile * QR_COLS;
+    const bool two = NBLK == 2 && col0 + 64 < a.N;                      // N is a multiple of the block; else the first 64 columns again
+    const uint32_t second = two ? 8u * BITS : 0u;
+    uint64_t step = (uint64_t)(32 * (uint32_t)s) * run_bytes + (uint64_t)(col0 / 16) * (2 * BITS);
+    asm("" : "+s"(step));                                               // one lane offset for all rows instead of a pointer each
+#pragma unroll
+    for (int i = 0; i < 8; ++i) cw[i].load(a.codes + step + (uint64_t)((uint32_t)i * run_bytes), row_lane, second);
+    // one scale per lane: row lane % 32 of the step, block lane / 32
+    const uint32_t blk = (32 * (uint32_t)s + (uint32_t)(lane & 31)) * row_blocks + (uint32_t)((col0 + (two && lane >= 32 ? 64 : 0)) >> a.block_shift);
+    si = a.sidx[blk];
+    vv = a.v[blk >> a.group_shift];
+    fetch_x(s);
+  };
+
+  bool table = false, ready = false;
   for (int pos = wg * a.per_wg; pos < end;) {
     const int tile = pos / a.steps, s0 = pos - tile * a.steps;
     int s1 = a.steps - s0 < end - pos ? a.steps : s0 + (end - pos);
@@ -166,7 +252,108 @@ __global__ __launch_bounds__(64 * QR_WAVES, 2) void qrows_kernel(QrArgs a) {
 
     const bool dense = tile >= a.tiles_q;
     int s = s0 + wave;
-    if (!dense) {
+    if (!dense && NBLK > 0) {
+      if (!ready && s < s1) fetch_step(tile, s);
+      ready = false;
+      int next_s1 = 0;                         // steps of the next segment, if it is one of Q
+      if (pos < end && tile + 1 < a.tiles_q) next_s1 = end - pos < a.ksteps ? end - pos : a.ksteps;
+      if (!table) {
+        const float* book = a.tables->code[Slot<BITS>::value];
+#pragma unroll
+        for (int i = 0; i < (QrTable<BITS>::words / 4 + 64 * QR_WAVES - 1) / (64 * QR_WAVES); ++i) {
+          const int at = 16 * (tid + 64 * QR_WAVES * i), e = at >> QrTable<BITS>::shift;     // 16 bytes, entry
+          bf16x2 hi, lo;
+          uint32_t w;
+          if constexpr (BITS == 8) {
+            split_pair(book[e], 0.f, hi, lo);
+            w = __builtin_bit_cast(uint32_t, bf16x2{hi[0], lo[0]});
+          } else {
+            const int pr = e < QrTable<BITS>::entries ? e : 0;
+            split_pair(book[pr & ((1 << BITS) - 1)], book[pr >> BITS], hi, lo);
+            w = __builtin_bit_cast(uint32_t, at & 128 ? lo : hi);
+          }
+          if (e < QrTable<BITS>::entries) *reinterpret_cast<uint4*>(reinterpret_cast<char*>(sh.code) + at) = make_uint4(w, w, w, w);
+        }
+        __syncthreads();
+        table = true;
+      }
+      for (; s < s1; s += QR_WAVES) {
+        if (NBLK == 2 || lane < 32) scales[lane] = block_scale_by_reciprocal(si, vv, a.levels, a.inv_levels);
+        // fields of 2 BITS bits: the codes of rows 2 p and 2 p + 1 in set 2 f (pair[p][0]) and 2 f + 1 (pair[p][1])
+        uint32_t pair[4][2];
+        uint32_t codes[8][2];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) cw[i].words(c, codes[i]);
+        if constexpr (BITS != 8) {
+          constexpr uint32_t M = BITS == 4 ? 0x0f0f0f0fu : BITS == 3 ? 07070707u : 0x3333u;
+#pragma unroll
+          for (int p = 0; p < 4; ++p) {
+            const uint32_t u = codes[2 * p][0], d = codes[2 * p + 1][0];
+            pair[p][0] = (u & M) | ((d << BITS) & ~M);
+            pair[p][1] = ((u >> BITS) & M) | (d & ~M);
+          }
+        }
+        __builtin_amdgcn_wave_barrier();
+        bf16x8 sh_hi[NX][RT], sh_lo[NX][RT];
+#pragma unroll
+        for (int b = 0; b < NX; ++b) {
+          const floatx4 sl = *reinterpret_cast<const floatx4*>(scales + 32 * b + 8 * q), su = *reinterpret_cast<const floatx4*>(scales + 32 * b + 8 * q + 4);
+#pragma unroll
+          for (int t = 0; t < RT; ++t) {
+            float xs[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) xs[e] = xv[t][e >> 2][e & 3] * (e < 4 ? sl[e & 3] : su[e & 3]);
+            split8<SPLIT>(xs, sh_hi[b][t], sh_lo[b][t]);
+          }
+        }
+        // next: this tile's step, or the first one of the segment behind this one, or (nothing left) the same again
+        int next_tile = tile, next = s;
+        if (s + QR_WAVES < s1) next = s + QR_WAVES;
+        else if (wave < next_s1) { next_tile = tile + 1; next = wave; ready = true; }
+        fetch_step(next_tile, next);
+        __builtin_amdgcn_sched_barrier(0);
+        for_each_block<NX>([&](auto block) {
+          constexpr int b = decltype(block)::value;
+#pragma unroll
+          for (int t = 0; t < RT; ++t) { xh[t] = sh_hi[b][t]; xl[t] = sh_lo[b][t]; }
+          constexpr int SETS = RT < 2 ? 2 : 1;           // sets at a time: successive products are independent of one another
+          for_each_block<QR_SETS / NX / SETS>([&](auto set) {
+            constexpr int j0 = QR_SETS / NX * b + SETS * decltype(set)::value;
+            uintx4 h[SETS], l[SETS];
+#pragma unroll
+            for (int i = 0; i < SETS; ++i)
+#pragma unroll
+              for (int p = 0; p < 4; ++p) {
+                const int j = j0 + i;
+                const char* table = reinterpret_cast<const char*>(sh.code);
+                if constexpr (BITS == 8) {
+                  const uint32_t u = *reinterpret_cast<const uint32_t*>(table + ((__builtin_amdgcn_ubfe(codes[2 * p][j / 4], 8 * (j % 4), 8) << 7) | lane4));
+                  const uint32_t d = *reinterpret_cast<const uint32_t*>(table + ((__builtin_amdgcn_ubfe(codes[2 * p + 1][j / 4], 8 * (j % 4), 8) << 7) | lane4));
+                  h[i][p] = __builtin_amdgcn_perm(d, u, 0x05040100);
+                  l[i][p] = __builtin_amdgcn_perm(d, u, 0x07060302);
+                } else {
+                  const uint32_t f = pair[p][j % 2];
+                  const uint32_t at = BITS == 4 ? __builtin_amdgcn_perm(f, lane4, 0x0c0c0000u | ((4u + j / 2) << 8))
+                                                : (__builtin_amdgcn_ubfe(f, 2 * BITS * (j / 2), 2 * BITS) << 8) | lane4;
+                  h[i][p] = *reinterpret_cast<const uint32_t*>(table + at);
+                  l[i][p] = SPLIT ? *reinterpret_cast<const uint32_t*>(table + at + 128) : 0u;
+                }
+              }
+            auto product = [&](const bf16x8 (&x)[RT], const uintx4 (&w)[SETS]) __attribute__((always_inline)) {
+#pragma unroll
+              for (int i = 0; i < SETS; ++i)
+#pragma unroll
+                for (int t = 0; t < RT; ++t)
+                  acc[t][j0 + i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x[t], __builtin_bit_cast(bf16x8, w[i]), acc[t][j0 + i], 0, 0, 0);
+            };
+            // with scales in X neither side is exact for plain X, so the product of the low halves is not left out
+            if constexpr (SPLIT) { product(xl, l); product(xl, h); product(xh, l); }
+            product(xh, h);
+          });
+        });
+        __builtin_amdgcn_wave_barrier();
+      }
+    } else if (!dense) {
       const int64_t col = (int64_t)tile * QR_COLS + QR_SETS * c;
       const int64_t colc = col < a.N ? col : 0;                       // N is a multiple of 16
       const uint32_t run_bytes = (uint32_t)(a.N / 16 * (2 * BITS));   // of a row
@@ -190,7 +377,7 @@ __global__ __launch_bounds__(64 * QR_WAVES, 2) void qrows_kernel(QrArgs a) {
       };
       if (s < s1) { fetch_w(s); fetch_x(s); }
       if (!table) {
-        for (int i = tid; i < (1 << BITS); i += 64 * QR_WAVES) sh.code[i] = a.tables->code[Slot<BITS>::value][i];
+        for (int i = tid; i < (1 << BITS); i += 64 * QR_WAVES) sh.code[i] = __float_as_uint(a.tables->code[Slot<BITS>::value][i]);
         __syncthreads();
         table = true;
       }
@@ -259,7 +446,7 @@ __global__ __launch_bounds__(64 * QR_WAVES, 2) void qrows_kernel(QrArgs a) {
       if (row >= a.m) continue;
       const int64_t prow = (int64_t)segment * a.m + row;
       if (!dense) {
-        const int64_t col = (int64_t)tile * QR_COLS + QR_SETS * c + set0;
+        const int64_t col = (int64_t)tile * QR_COLS + (NBLK == 2 ? QR_COLS / 8 * set0 + 4 * c : QR_SETS * c + set0);
         if (col < a.N) *reinterpret_cast<floatx4*>(a.part + prow * a.N + col) = o;
       } else if (set0 == 0) {
         const int col = (tile - a.tiles_q) * QR_DCOLS + 4 * c;
@@ -303,11 +490,20 @@ size_t qrows_part_floats(int64_t m, int64_t K, int64_t N, int rank) {
   return (size_t)qrows_shares(m, K, N, rank).segments * (size_t)m * (size_t)(N + rank);
 }
 
-template <int BITS, bool SPLIT>
+template <int BITS, bool SPLIT, int NBLK>
 static void launch_rt(const QrArgs& a, int rt, dim3 grid, hipStream_t st) {
-  if (rt == 1) hipLaunchKernelGGL((qrows_kernel<BITS, 1, SPLIT>), grid, dim3(64 * QR_WAVES), 0, st, a);
-  else if (rt == 2) hipLaunchKernelGGL((qrows_kernel<BITS, 2, SPLIT>), grid, dim3(64 * QR_WAVES), 0, st, a);
-  else hipLaunchKernelGGL((qrows_kernel<BITS, 3, SPLIT>), grid, dim3(64 * QR_WAVES), 0, st, a);
+  if (rt == 1) hipLaunchKernelGGL((qrows_kernel<BITS, 1, SPLIT, NBLK>), grid, dim3(64 * QR_WAVES), 0, st, a);
+  else if (rt == 2) hipLaunchKernelGGL((qrows_kernel<BITS, 2, SPLIT, NBLK>), grid, dim3(64 * QR_WAVES), 0, st, a);
+  else hipLaunchKernelGGL((qrows_kernel<BITS, 3, SPLIT, NBLK>), grid, dim3(64 * QR_WAVES), 0, st, a);
+}
+template <int BITS, bool SPLIT>
+static void launch_blocks(const QrArgs& a, int rt, dim3 grid, hipStream_t st) {
+  // A workgroup of the form with the scales in X makes the table first, 64 KB for 4 bits, which one or two steps per wavefront do
+  // not pay back (24 rows: 2048 x 2048, one step 12.9 against 13.2 us; 4096 x 4096, three steps 17.5 against 17.3).
+  const bool scaled = a.per_wg > 2 * QR_WAVES;
+  if (scaled && a.block_shift >= 7) launch_rt<BITS, SPLIT, 1>(a, rt, grid, st);
+  else if (scaled && a.block_shift == 6) launch_rt<BITS, SPLIT, 2>(a, rt, grid, st);
+  else launch_rt<BITS, SPLIT, 0>(a, rt, grid, st);
 }
 
 int launch_qrows(const MvWeights& q, const float* X, int64_t ldx, int64_t K, const float* L1, const float* L2, int64_t ldl2,
@@ -341,8 +537,8 @@ int launch_qrows(const MvWeights& q, const float* X, int64_t ldx, int64_t K, con
     prof::Scope ps(prof::QROWS, st, 2.0 * m * (double)K * (double)(N + rank));
 #define LQ_QROWS(BITS)                                             \
   case BITS:                                                       \
-    if (precision == 0) launch_rt<BITS, true>(a, rt, grid, st);        \
-    else launch_rt<BITS, false>(a, rt, grid, st);                      \
+    if (precision == 0) launch_blocks<BITS, true>(a, rt, grid, st);    \
+    else launch_blocks<BITS, false>(a, rt, grid, st);                  \
     break;
     switch (q.bits) {
       LQ_QROWS(2) LQ_QROWS(3) LQ_QROWS(4) LQ_QROWS(8)

@@ -36,3 +36,36 @@ def test_rows_match_oracle(oracle, m, d, k, cfg, rank):
         y = y.cpu().numpy()
         assert np.all(np.isfinite(y))
         assert np.max(np.abs(y - ref) - tol * scale) <= 0, (precision, np.max(np.abs(y - ref) / scale))
+
+
+# (m, d, k, block) with three steps per wavefront: an odd number of 64 columns and one, two and three row tiles, blocks of a
+# tile's columns and more
+@pytest.mark.parametrize("m,d,k,block", [(9, 544, 16448, 64), (24, 544, 16448, 64), (40, 544, 16512, 128), (128, 544, 8256, 64), (17, 544, 16384, 1024)])
+@pytest.mark.parametrize("bits", [2, 3, 4, 8])
+def test_rows_with_scales_in_x(oracle, m, d, k, block, bits):
+    test_rows_match_oracle(oracle, m, d, k, (bits, block, 16), 33)
+
+
+def test_rows_shares_that_end_inside_a_tile(oracle):
+    """The next tile's first step is then asked for before this one's sums."""
+    test_rows_match_oracle(oracle, 48, 4096, 11072, (3, 64, 256), 33)
+
+
+@pytest.mark.parametrize("bits,block", [(3, 64), (4, 128)])
+def test_rows_zero_scales_and_infinite_x(oracle, bits, block):
+    """Blocks of zeros have scale 0 whatever X is multiplied with; a row of X that is not finite stays in its row."""
+    import torch
+    from paper_2311_12023_amd import lq
+    m, d, k = 20, 544, 16384
+    ocfg = oracle.config(bits, block, 16)
+    w = gen.weight_matrix(d, k, 77, 4)
+    w[:, :block] = 0
+    codes, sidx, v, _ = oracle.quantize(w.ravel(), ocfg)
+    x = gen.activations(m, d, 78)
+    x[3, 5], x[11, 200] = np.inf, np.nan
+    t = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    y = lq.matmul(t(x), t(oracle.pack(codes, bits)), t(sidx), t(v), lq.config(bits, block, 16), k).cpu().numpy()
+    ok = np.setdiff1d(np.arange(m), [3, 11])
+    ref, scale = oracle.matmul(x[ok], codes, sidx, v, ocfg, k, want_abs=True)
+    assert np.all(y[ok, :block] == 0) and np.all(np.abs(y[ok] - ref) <= 4e-5 * scale)
+    assert not np.any(np.isfinite(y[[3, 11]][:, block:]))
