@@ -14,7 +14,7 @@
 //  - X is split into its two bf16 planes once per call (every column tile needs the same halves); the tiles then
 //    travel from global memory straight into LDS (global_load_lds_dwordx4: each lane moves 16 bytes, a wavefront
 //    fills 1 KB = 16 rows), one step ahead.  No register or vector-ALU instruction touches X.  Rows are
-//    64 bytes without padding; the four 16-byte units of a row are stored in the order unit ^ ((row / 2) % 4), which
+//    64 bytes without padding; the four 16-byte units of a row are stored in the order unit ^ ((row / 4) % 4), which
 //    makes the 128-bit operand reads conflict-free.
 //  - The weight tile is decoded in registers: every thread fetches a 4 (reduction) x 4 (columns) patch a step or two
 //    ahead (four code words from four consecutive rows of Q and the reconstructed scales of their blocks, which are
@@ -427,14 +427,14 @@ __global__ __launch_bounds__(QM_THREADS, 2) void qmatmul_kernel(QmmArgs a) {
   t.col = col0 + 4 * t.quad;
   t.colc = t.col < a.N ? t.col : a.N - 4;          // in the quantized part N is a multiple of the block size, hence of 4
   // X transfer: the wavefront's row blocks are 16 * (8j + wave), j < 2; lane -> row lane / 4 of the block and the
-  // stored unit lane % 4, which holds the row's unit (lane % 4) ^ ((row / 2) % 4)
-  const int xr = lane >> 2, xu = (lane & 3) ^ ((xr >> 1) & 3);
+  // stored unit lane % 4, which holds the row's unit (lane % 4) ^ ((row / 4) % 4)
+  const int xr = lane >> 2, xu = (lane & 3) ^ ((xr >> 2) & 3);
   const int wave_s = __builtin_amdgcn_readfirstlane(wave);   // wavefront-uniform, kept in a scalar register
   t.xlds = (uint32_t)wave_s * 1024u;
-  // operands: row tile 0 of the wavefront's part, unit (2g + lh) ^ ((row / 2) % 4)
+  // operands: row tile 0 of the wavefront's part, unit (2g + lh) ^ ((row / 4) % 4)
   const int arow = 128 * wm + ln;
-  t.aoff[0] = (uint32_t)arow * 64u + (uint32_t)(((0 + lh) ^ ((arow >> 1) & 3)) << 4);
-  t.aoff[1] = (uint32_t)arow * 64u + (uint32_t)(((2 + lh) ^ ((arow >> 1) & 3)) << 4);
+  t.aoff[0] = (uint32_t)arow * 64u + (uint32_t)(((0 + lh) ^ ((arow >> 2) & 3)) << 4);
+  t.aoff[1] = (uint32_t)arow * 64u + (uint32_t)(((2 + lh) ^ ((arow >> 2) & 3)) << 4);
   t.boff = (uint32_t)((64 * wn + ln) * QM_PITCH + 8 * lh);
   const uint32_t lds_addr = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)s_raw;
   t.cwshift = 0;

@@ -6,11 +6,12 @@
 // 79, 197 -> 140, 168 -> 158.
 // The line is drawn above 512 rows: 513 rows, 4 bits, rank 64, with a plane 64, 137, 121 us (4096 x 4096, 4096 x 11008, 11008 x
 // 4096) against 72, 197, 138 without; 512 rows 65, 106, 110 against 66, 125, 110, but 8192 x 8192 146 against 132; 256 rows
-// 58, 80, 93 against 55, 74, 79.  Small weights: PLANE_M_SMALL in lq_api_matmul.cpp.  The product runs at 0.9 to 1.0 PFLOP/s
-// (138 us for 4096^3 in a trace); what holds it there is that reading operands from LDS and multiplying overlap poorly
-// (when it took 156 us: 110 without the MFMAs, 140 without the transfers).
+// 58, 80, 93 against 55, 74, 79.  Small weights: PLANE_M_SMALL in lq_api_matmul.cpp.  The product runs at 1.0 to 1.15 PFLOP/s
+// (120 us for 4096^3 in a trace, 60 % of its cycles in the matrix pipe, at a clock that has come down to 1.85 GHz by then; when it
+// took 156 us: 110 without the MFMAs, 140 without the transfers).
 #include <algorithm>
 
+#include "dense_device.h"
 #include "kernels.h"
 #include "lds_transfer.h"
 #include "nf_device.h"
@@ -100,7 +101,12 @@ __global__ __launch_bounds__(256) void weight_plane_kernel(WpArgs a) {
 // own transfers of the next step, the barrier makes that everyone's, and by then all have read the last operands of the
 // present stage, which is refilled.  So the operands of each half step are read while the other half multiplies (with the
 // barrier between the steps and reads before products the same tiles took 161 instead of 156 us at 4096^3; rows padded
-// to spread over the L2's channels changed nothing).  Rows are 64 bytes, unit u of a row stored at u ^ ((row / 2) % 4): conflict-free 128-bit operand reads.
+// to spread over the L2's channels changed nothing).  What a wavefront does between its products keeps the matrix pipe waiting,
+// since the barrier brings all of them there at once: the loop is unrolled over the stages, so that their addresses are
+// constants, the transfers' addresses are carried along instead of worked out (77 -> 30 scalar instructions per step), and the
+// transfers go out between the products (4096 x 4096 x 4160 131 -> 120 us, the call 169 -> 162).  Rows are 64 bytes, unit u of a
+// row stored at u ^ ((row / 4) % 4): 16 lanes' reads of 128 bits fall into different banks (with (row / 2) % 4 into half of
+// them, twice the LDS cycles; 0.6 % of the call, in qmatmul_kernel 0.3 %).
 constexpr int PG_T = 256, PG_STAGES = 4, PG_THREADS = 512;
 constexpr uint32_t PG_TILE = PG_T * 64, PG_STAGE = 2 * PG_TILE;            // bytes
 
@@ -129,21 +135,31 @@ __global__ __launch_bounds__(PG_THREADS) void plane_gemm_kernel(PgArgs a) {
   const int s0 = (int)((int64_t)a.nsteps * split / a.splits), s1 = (int)((int64_t)a.nsteps * (split + 1) / a.splits);
 
   // this wavefront's transfers: rows 16 wave .. + 15 and 128 further of both tiles; lane l brings unit l % 4 ^ swizzle of row l / 4
-  const int lrow = lane >> 2, unit = (lane & 3) ^ ((lrow >> 1) & 3);
+  const int lrow = lane >> 2, unit = (lane & 3) ^ ((lrow >> 2) & 3);
   const uint32_t voff1 = (uint32_t)(lrow * a.K * 2 + unit * 16), voff2 = (uint32_t)(lrow * a.K2 * 2 + unit * 16);
   const int64_t arow = (int64_t)tm * PG_T + 16 * wave, brow = (int64_t)tn * PG_T + 16 * wave;
-  auto issue = [&](int s) {                      // past the end: the last step again, into a stage that nobody reads any more
-    const uint32_t lds = (uint32_t)((s - s0) % PG_STAGES) * PG_STAGE + (uint32_t)wave * 1024u;
-    s = s < s1 ? s : s1 - 1;
-    const bool second = s >= a.nsteps1;
-    const int64_t K = second ? a.K2 : a.K, k = 32 * (int64_t)(second ? s - a.nsteps1 : s);
-    const uint16_t* A = (second ? a.A2 : a.A) + arow * K + k;
-    const uint16_t* B = (second ? a.B2 : a.B) + brow * K + k;
-    const uint32_t voff = second ? voff2 : voff1;
-    transfer_to_lds(A, voff, lds);
-    transfer_to_lds(A + 128 * K, voff, lds + 8192u);
-    transfer_to_lds(B, voff, lds + PG_TILE);
-    transfer_to_lds(B + 128 * K, voff, lds + PG_TILE + 8192u);
+  // Where the next step's transfers read: this wavefront's rows of the present pair of planes at the present reduction index.
+  const uint16_t *pa, *pb;
+  int64_t rows128;                               // elements to the rows 128 further
+  uint32_t voff;
+  int next = s0;                                 // the step that these belong to
+  auto plane_pair = [&](bool second, int64_t k) {
+    const int64_t K = second ? a.K2 : a.K;
+    pa = (second ? a.A2 : a.A) + arow * K + k;
+    pb = (second ? a.B2 : a.B) + brow * K + k;
+    rows128 = 128 * K;
+    voff = second ? voff2 : voff1;
+  };
+  plane_pair(s0 >= a.nsteps1, 32 * (int64_t)(s0 >= a.nsteps1 ? s0 - a.nsteps1 : s0));
+  auto transfer = [&](int part, int stage) {     // a quarter of a step's transfers
+    const uint32_t lds = (uint32_t)stage * PG_STAGE + (uint32_t)wave * 1024u + 8192u * part;
+    transfer_to_lds((part < 2 ? pa : pb) + (part & 1 ? rows128 : 0), voff, lds);
+  };
+  auto advance = [&]() {                         // past the end: the last step again, into a stage that nobody reads any more
+    if (next + 1 >= s1) return;
+    ++next;
+    if (next == a.nsteps1) plane_pair(true, 0);
+    else { pa += 32; pb += 32; }
   };
 
   floatx16 acc[4][2];
@@ -158,41 +174,53 @@ __global__ __launch_bounds__(PG_THREADS) void plane_gemm_kernel(PgArgs a) {
   uint32_t aoff[2], boff[2];
 #pragma unroll
   for (int g = 0; g < 2; ++g) {
-    const uint32_t u = (uint32_t)((2 * g + lh) ^ ((ln >> 1) & 3)) * 16u;
+    const uint32_t u = (uint32_t)((2 * g + lh) ^ ((ln >> 2) & 3)) * 16u;
     aoff[g] = (uint32_t)(128 * wm + ln) * 64u + u;
     boff[g] = PG_TILE + (uint32_t)(64 * wn + ln) * 64u + u;
   }
 
   bf16x8 x[2][4], b[2][2];                       // operands of the two halves of a step
-  auto read = [&](int s, int g) {
-    const unsigned char* stage = pg_lds + (uint32_t)((s - s0) % PG_STAGES) * PG_STAGE;
+  auto read = [&](int stage, int g) __attribute__((always_inline)) {
+    const unsigned char* from = pg_lds + (uint32_t)stage * PG_STAGE;
 #pragma unroll
-    for (int j = 0; j < 2; ++j) b[g][j] = *reinterpret_cast<const bf16x8*>(stage + boff[g] + 2048u * j);
+    for (int j = 0; j < 2; ++j) b[g][j] = *reinterpret_cast<const bf16x8*>(from + boff[g] + 2048u * j);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) x[g][i] = *reinterpret_cast<const bf16x8*>(stage + aoff[g] + 2048u * i);
+    for (int i = 0; i < 4; ++i) x[g][i] = *reinterpret_cast<const bf16x8*>(from + aoff[g] + 2048u * i);
     __builtin_amdgcn_sched_barrier(0);           // the reads go out before the products of the other half
   };
-  auto multiply = [&](int g) {
+  auto multiply = [&](int g, int i) __attribute__((always_inline)) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-      for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[g][i], b[g][j], acc[i][j], 0, 0, 0);
+    for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[g][i], b[g][j], acc[i][j], 0, 0, 0);
     __builtin_amdgcn_sched_barrier(0);
   };
 #pragma unroll
-  for (int p = 0; p < PG_STAGES; ++p) issue(s0 + p);
-  asm volatile("s_waitcnt vmcnt(12)\n\ts_barrier" ::: "memory");   // 4 transfers a step: the first step's are done
-  read(s0, 0);
-  for (int s = s0; s < s1; ++s) {
-    read(s, 1);
-    multiply(0);
-    // step s + 1 has arrived when at most the transfers of the two steps after it are outstanding; past the barrier that
-    // holds for every wavefront, and none reads stage s any more
-    asm volatile("s_waitcnt vmcnt(8) lgkmcnt(0)\n\ts_barrier" ::: "memory");
-    issue(s + PG_STAGES);
-    read(s + 1, 0);                              // past the end: never used (a branch here would cost exact waits)
-    multiply(1);
+  for (int p = 0; p < PG_STAGES; ++p) {
+#pragma unroll
+    for (int part = 0; part < 4; ++part) transfer(part, p);
+    advance();
   }
+  asm volatile("s_waitcnt vmcnt(12)\n\ts_barrier" ::: "memory");   // 4 transfers a step: the first step's are done
+  read(0, 0);
+  auto step = [&](auto stage) __attribute__((always_inline)) {
+    constexpr int u = decltype(stage)::value;
+    read(u, 1);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) multiply(0, i);
+    // the next step has arrived when at most the transfers of the two steps after it are outstanding; past the barrier that
+    // holds for every wavefront, and none reads this stage any more
+    asm volatile("s_waitcnt vmcnt(8) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    read((u + 1) % PG_STAGES, 0);                // past the end: never used (a branch here would cost exact waits)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      multiply(1, i);
+      transfer(i, u);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    advance();
+  };
+  int s = s0;
+  for (; s + PG_STAGES <= s1; s += PG_STAGES) for_each_block<PG_STAGES>(step);
+  for_each_block<PG_STAGES - 1>([&](auto stage) { if (s + decltype(stage)::value < s1) step(stage); });
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");                 // nothing lands in LDS after the workgroup is gone
 
   float* __restrict__ Y = a.Y + (size_t)split * (size_t)a.m * (size_t)a.ldy;
