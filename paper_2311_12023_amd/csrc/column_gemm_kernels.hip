@@ -13,14 +13,16 @@ namespace lq {
 // A workgroup owns l rows x 16 NT columns of the result and a range of the reduction, whose 32-deep steps its four wavefronts
 // take in turn.  Every operand goes from memory into the registers of the one wavefront that multiplies it, on
 // v_mfma_f32_16x16x32_bf16 (both sides split into bf16 hi + lo, three products each, fp32 accumulation): the loop has
-// neither barriers nor LDS traffic, two steps of A are in flight per wavefront, and a row of a step of A is one 128-byte
-// line.  X comes packed in operand layout, so that a step of it is one contiguous stretch (as rows 16 KB apart it took the
+// neither barriers nor LDS traffic, and a row of a step of A is one 128-byte line.  X comes packed in operand layout, so that a step of it is one contiguous stretch (as rows 16 KB apart it took the
 // kernel three times as long: the lines of a step then share an L2 channel).  The four partial results are added in LDS in
 // wavefront order.  Where the column tiles do not fill the chip the reduction is also cut into ranges, whose sums lie in
 // `part` (columns past the result are zero there) and are added, in order, by whoever reads the product next
 // (column_sum_kernel, filter_step_kernel): partial sums amount to a few results, where 256-column tiles needed 16.
 // What bounds it: L2, X being read once per tile (at 4096 columns and l = 128 half a megabyte beside a quarter of A per
-// compute unit), and below that the length of a single pass through memory.  Measured with the launches
+// compute unit), and below that the length of a single pass through memory.  With one wavefront per SIMD a load that waits for its
+// turn holds up the products behind it, so loads, split and products alternate row block by row block (24 loads, the split
+// and then 96 products per step took l = 128, 4096 x 4096 23.3 (X A) and 22.1 us, 4096 x 11008 56.4 and 48.1; now 18.5 and 21.4,
+// 44.3 and 44.6).  Beginning at another step in every tile, against rows of A that share an L2 channel, changed nothing.  Measured with the launches
 // that split X and add the ranges, against the kernel for batches and its fix-up (us, X A^T / X A): l = 64, 768 x 768 20.0 /
 // 17.5 -> 8.7 / 8.5; l = 96, 2500 x 4096 27.9 / 26.3 -> 23 / 22; l = 128, 4096 x 4096 40.2 / 38.5 -> 34.7 / 31.9, 4096 x 11008
 // 76.5 / 67.3 -> 71.5 / 59.8; where the neighbouring kernels split and add, 4 to 8 us less.  As the cold start runs them: l = 128,
@@ -85,31 +87,46 @@ __device__ __forceinline__ void col_fetch_x(const uintx4* X, int lane, int64_t k
     for (int p = 0; p < 2; ++p) x.v[i][p] = base[(2 * i + p) * 64 + lane];
 }
 
-template <int LB, int MODE, int NT>
-__device__ __forceinline__ void col_multiply(const ColA<MODE, NT>& a, const ColX<LB>& x, floatx4 (&acc)[LB][NT]) {
-  bf16x8 ah[NT], al[NT];
-#pragma unroll
-  for (int j = 0; j < NT; ++j)
-#pragma unroll
-    for (int e = 0; e < 8; e += 2) {
-      floatx2 v;
-      if constexpr (MODE == MODE_NT) v = floatx2{a.v[j][e >> 2][e & 3], a.v[j][e >> 2][(e & 3) + 1]};
-      else if constexpr (NT == 1) v = floatx2{a.v[e], a.v[e + 1]};
-      else v = floatx2{a.v[e][j], a.v[e + 1][j]};
-      bf16x2 h, l;
-      split_bf16(v, h, l);
-      ah[j][e] = h[0]; ah[j][e + 1] = h[1]; al[j][e] = l[0]; al[j][e + 1] = l[1];
-    }
-#pragma unroll
-  for (int i = 0; i < LB; ++i) {
-    const bf16x8 xh = __builtin_bit_cast(bf16x8, x.v[i][0]), xl = __builtin_bit_cast(bf16x8, x.v[i][1]);
-#pragma unroll
-    for (int j = 0; j < NT; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xl, ah[j], acc[i][j], 0, 0, 0);
-#pragma unroll
-    for (int j = 0; j < NT; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xh, al[j], acc[i][j], 0, 0, 0);
-#pragma unroll
-    for (int j = 0; j < NT; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xh, ah[j], acc[i][j], 0, 0, 0);
+// Load n of a step's A (NT mode: 2 NT of them, NN: 8); a step inside the reduction.
+template <int MODE, int NT> constexpr int COL_A_LOADS = MODE == MODE_NT ? 2 * NT : 8;
+template <int MODE, int NT>
+__device__ __forceinline__ void col_fetch_a_part(const float* A, int64_t lda, const uint32_t (&off)[MODE == MODE_NT ? NT : 1], int64_t k0, int n,
+                                                 ColA<MODE, NT>& a) {
+  if constexpr (MODE == MODE_NT) {
+    a.v[n >> 1][n & 1] = *reinterpret_cast<const floatx4*>(reinterpret_cast<const char*>(A + k0 + 16 * (n & 1)) + off[n >> 1]);
+  } else {
+    typedef typename Words<NT>::type Row;
+    a.v[n] = *reinterpret_cast<const Row*>(reinterpret_cast<const char*>(A + (size_t)(k0 + (n < 4 ? n : 12 + n)) * lda) + off[0]);
   }
+}
+
+// A's operands of a step: bf16 high and low halves.  Pair n (of 4 NT): elements 2 (n % 4), 2 (n % 4) + 1 of column n / 4.
+template <int NT> struct ColOps { bf16x8 h[NT], l[NT]; };
+template <int MODE, int NT>
+__device__ __forceinline__ void col_split_pair(const ColA<MODE, NT>& a, int n, ColOps<NT>& o) {
+  const int j = n >> 2, e = 2 * (n & 3);
+  floatx2 v;
+  if constexpr (MODE == MODE_NT) v = floatx2{a.v[j][e >> 2][e & 3], a.v[j][e >> 2][(e & 3) + 1]};
+  else if constexpr (NT == 1) v = floatx2{a.v[e], a.v[e + 1]};
+  else v = floatx2{a.v[e][j], a.v[e + 1][j]};
+  bf16x2 h, l;
+  split_bf16(v, h, l);
+  o.h[j][e] = h[0]; o.h[j][e + 1] = h[1]; o.l[j][e] = l[0]; o.l[j][e + 1] = l[1];
+}
+template <int MODE, int NT>
+__device__ __forceinline__ void col_split(const ColA<MODE, NT>& a, ColOps<NT>& o) {
+#pragma unroll
+  for (int n = 0; n < 4 * NT; ++n) col_split_pair<MODE, NT>(a, n, o);
+}
+template <int NT>
+__device__ __forceinline__ void col_multiply_row(const uintx4 (&x)[2], const ColOps<NT>& o, floatx4 (&acc)[NT]) {
+  const bf16x8 xh = __builtin_bit_cast(bf16x8, x[0]), xl = __builtin_bit_cast(bf16x8, x[1]);
+#pragma unroll
+  for (int j = 0; j < NT; ++j) acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xl, o.h[j], acc[j], 0, 0, 0);
+#pragma unroll
+  for (int j = 0; j < NT; ++j) acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xh, o.l[j], acc[j], 0, 0, 0);
+#pragma unroll
+  for (int j = 0; j < NT; ++j) acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xh, o.h[j], acc[j], 0, 0, 0);
 }
 
 // LB = l / 16.  Large accumulators: one wavefront per SIMD with all its registers.
@@ -141,29 +158,51 @@ __global__ __launch_bounds__(COL_THREADS, LB * NT <= 8 ? 2 : 1) void column_gemm
   for (int i = 0; i < LB; ++i)
 #pragma unroll
     for (int j = 0; j < NT; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
-  ColA<MODE, NT> a[3];
+  ColA<MODE, NT> a[2];
   ColX<LB> x[2];
+  ColOps<NT> o[2];
   if (count > 0) {
     auto at = [&](int t) { return kfirst + (int64_t)(t < count ? t : count - 1) * (4 * COL_BK); };
-    col_fetch_a<MODE, NT, false>(g.A, g.lda, g.K, off, q, at(0), a[0]);
-    col_fetch_x<LB>(g.X, lane, at(0), x[0]);
-    col_fetch_a<MODE, NT, false>(g.A, g.lda, g.K, off, q, at(1), a[1]);
-    auto step = [&](auto uc, int t) __attribute__((always_inline)) {
+    auto first = [&](auto uc) __attribute__((always_inline)) {
       constexpr int u = decltype(uc)::value;
-      col_fetch_x<LB>(g.X, lane, at(t + 1), x[(u + 1) % 2]);
-      col_fetch_a<MODE, NT, false>(g.A, g.lda, g.K, off, q, at(t + 2), a[(u + 2) % 3]);
-      __builtin_amdgcn_sched_barrier(0);                 // the next steps' loads are issued before this step's products
-      col_multiply<LB, MODE, NT>(a[u % 3], x[u % 2], acc);
+      col_fetch_a<MODE, NT, false>(g.A, g.lda, g.K, off, q, at(0), a[u]);
+      col_fetch_x<LB>(g.X, lane, at(0), x[u]);
+      col_fetch_a<MODE, NT, false>(g.A, g.lda, g.K, off, q, at(1), a[1 - u]);
       __builtin_amdgcn_sched_barrier(0);
+      col_split<MODE, NT>(a[u], o[u]);
     };
-    int t = 0;
-    for (; t + 6 <= count; t += 6) for_each_block<6>([&](auto uc) { step(uc, t + decltype(uc)::value); });
-    for_each_block<5>([&](auto uc) { if (t + decltype(uc)::value < count) step(uc, t + decltype(uc)::value); });
+    // Row block by row block: the products, between them the loads of X for the next step and of A for the one after it and the
+    // split of A for the next, so that the loads do not queue up in front of the products.
+    auto step = [&](auto uc, int t) __attribute__((always_inline)) {
+      constexpr int u = decltype(uc)::value, NA = COL_A_LOADS<MODE, NT>;
+      const int64_t k1 = at(t + 1), k2 = at(t + 2);
+      const uintx4* xnext = g.X + (size_t)(k1 / COL_BK) * (LB * 2 * 64) + lane;
+#pragma unroll
+      for (int i = 0; i < LB; ++i) {
+#pragma unroll
+        for (int p = 0; p < 2; ++p) x[(u + 1) % 2].v[i][p] = xnext[(2 * i + p) * 64];
+#pragma unroll
+        for (int n = i * NA / LB; n < (i + 1) * NA / LB; ++n) col_fetch_a_part<MODE, NT>(g.A, g.lda, off, k2, n, a[u % 2]);
+#pragma unroll
+        for (int n = i * 4 * NT / LB; n < (i + 1) * 4 * NT / LB; ++n) col_split_pair<MODE, NT>(a[(u + 1) % 2], n, o[(u + 1) % 2]);
+        col_multiply_row<NT>(x[u % 2].v[i], o[u % 2], acc[i]);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    };
+    // An odd step goes first: behind the loop the accumulators would be copied in every round of it.
+    const std::integral_constant<int, 0> even{};
+    const std::integral_constant<int, 1> odd{};
+    int t = count & 1;
+    if (t) { first(odd); step(odd, 0); }
+    else first(even);
+    for (; t < count; t += 2) { step(even, t); step(odd, t + 1); }
   }
   if (s1 == g.ns && full < g.ns && s0 <= full && (full - s0) % 4 == w) {
     col_fetch_a<MODE, NT, true>(g.A, g.lda, g.K, off, q, (int64_t)full * COL_BK, a[0]);
     col_fetch_x<LB>(g.X, lane, (int64_t)full * COL_BK, x[0]);
-    col_multiply<LB, MODE, NT>(a[0], x[0], acc);
+    col_split<MODE, NT>(a[0], o[0]);
+#pragma unroll
+    for (int i = 0; i < LB; ++i) col_multiply_row<NT>(x[0].v[i], o[0], acc[i]);
   }
 
   floatx4* mine = reinterpret_cast<floatx4*>(sums) + (size_t)w * (LB * NT * 64) + lane;
