@@ -242,7 +242,7 @@ __global__ __launch_bounds__(64 * QR_WAVES, 2) void qrows_kernel(QrArgs a) {
   for (int pos = wg * a.per_wg; pos < end;) {
     const int tile = pos / a.steps, s0 = pos - tile * a.steps;
     int s1 = a.steps - s0 < end - pos ? a.steps : s0 + (end - pos);
-    const int segment = wg - (int)((int64_t)tile * a.steps / a.per_wg);
+    const int segment = wg - tile * a.steps / a.per_wg;             // the steps of all tiles fit an int
     pos += s1 - s0;
     s1 = s1 < a.ksteps ? s1 : a.ksteps;
 #pragma unroll
