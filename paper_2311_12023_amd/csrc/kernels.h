@@ -103,9 +103,12 @@ struct BlockScales {
 };
 int split_project_splits(int64_t rows_pad, int64_t K);
 size_t split_project_part_floats(int64_t rows_pad, int64_t K);
+// What is left of T = X L1: the sum of its partial tiles, written as planes.  With `later` launch_split_project leaves that to
+// whoever is given it (launch_plane_product) before T is read.
+struct ProjectSum { const float* part; int splits; int64_t rows_pad; int Kd; uint16_t* th; uint16_t* tl; };
 int launch_split_project(const float* X, int64_t rows, int64_t K, int64_t ldx, int64_t rows_pad, const float* L1,
                          int rank, int precision, uint16_t* xh, uint16_t* xl, float* part, size_t part_floats,
-                         uint16_t* th, uint16_t* tl, int Kd, const BlockScales& bs, hipStream_t st);
+                         uint16_t* th, uint16_t* tl, int Kd, const BlockScales& bs, ProjectSum* later, hipStream_t st);
 // Quantized part of a product: X (planes of rows_pad x K) times the K x N matrix stored as NF codes (row-major
 // flattening, N a multiple of `block`, K * N below 2^31).  K is a multiple of 32; K == 0 leaves the part out.
 struct QmmPart {
@@ -181,7 +184,7 @@ int launch_qrows(const MvWeights& q, const float* X, int64_t ldx, int64_t K, con
 size_t weight_plane_elems(int64_t K, int64_t N);
 int launch_plane_product(const MvWeights& q, const uint16_t* Xh, int64_t K, const uint16_t* Th, int Kd, const float* L2,
                          int rank, int64_t m, int64_t rows_pad, int64_t N, uint16_t* Wt, uint16_t* Lt, float* Y, int64_t ldy,
-                         float* part, size_t part_floats, hipStream_t st);
+                         float* part, size_t part_floats, const ProjectSum& t, hipStream_t st);
 
 // ---- products of wide bases with l x l matrices (wide_kernels.hip) ------------------------------
 // C0[z] = U[z] A0[z] and, if A1 is given, C1[z] = U[z] A1[z] (U: l x l fp32 row-major, l = 32..128; A, C: l rows, leading

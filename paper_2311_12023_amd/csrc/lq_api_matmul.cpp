@@ -197,19 +197,20 @@ int lq_matmul(const float* X, int64_t m, int64_t d, int64_t k, const uint8_t* co
   uint16_t* lt = reinterpret_cast<uint16_t*>(w);
 
   if (route == ROUTE_PLANE) {
+    ProjectSum t{};
     if (p.fused)
       LQ_TRY(launch_split_project(X, m, d, d, p.rows_pad, L1, rank, precision, xh, xl, part, p.part_floats, th, tl,
-                                  (int)p.r32, BlockScales{}, st));
+                                  (int)p.r32, BlockScales{}, &t, st));
     else
       LQ_TRY(launch_split_planes(X, m, d, d, p.rows_pad, xh, xl, st));
     const MvWeights q{codes_packed, scale_idx, v, c.bits, c.block, c.scale_block, scale_levels(c)};
-    return launch_plane_product(q, xh, d, th, (int)p.r32, L2, rank, m, p.rows_pad, k, wt, lt, Y, k, part, p.part_floats, st);
+    return launch_plane_product(q, xh, d, th, (int)p.r32, L2, rank, m, p.rows_pad, k, wt, lt, Y, k, part, p.part_floats, t, st);
   }
   QmmPart none{};
   if (p.fused) {    // planes of X and of T = X L1 from one pass over X, the block scales of Q in the same launch
     const BlockScales bs{scale_idx, v, d * k / c.block, c.scale_block, scale_levels(c), bscale};
     LQ_TRY(launch_split_project(X, m, d, d, p.rows_pad, L1, rank, precision, xh, xl, part, p.part_floats, th, tl,
-                                (int)p.r32, bs, st));
+                                (int)p.r32, bs, nullptr, st));
   } else {
     LQ_TRY(launch_block_scales(scale_idx, v, d * k / c.block, c.scale_block, scale_levels(c), bscale, st));
     LQ_TRY(launch_split_planes(X, m, d, d, p.rows_pad, xh, xl, st));

@@ -16,17 +16,14 @@
 #include "lds_transfer.h"
 #include "nf_device.h"
 #include "profiler.h"
+#include "project_device.h"
 
 namespace lq {
 
-typedef float floatx16 __attribute__((ext_vector_type(16)));
-typedef float floatx2 __attribute__((ext_vector_type(2)));
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-
 // ------------------------------------------------------------------------------------------------
 // Wt[n][k] = bf16(Q[k][n]) and, in the last row of the grid, Lt[n][p] = bf16(L2[p][n]) (p >= rank: zero): a workgroup decodes
-// 64 rows x 128 columns, turns them in LDS and writes runs of 64 along k.
+// 64 rows x 128 columns, turns them in LDS and writes runs of 64 along k.  Behind these rows of the grid others add the partial
+// tiles of T = X L1, which a launch of their own took 5 us for.
 constexpr int WP_K = 64, WP_N = 128, WP_PITCH = 33;        // LDS pitch in pairs of bf16
 
 struct WpArgs {
@@ -37,10 +34,17 @@ struct WpArgs {
   int block_shift, group_shift, levels;
   float inv_levels;
   const DevTables* tables;
+  int sum_row;                       // first row of the grid that adds partial tiles of T
+  ProjectSum t;
 };
 
 template <int BITS>
 __global__ __launch_bounds__(256) void weight_plane_kernel(WpArgs a) {
+  if ((int)blockIdx.y >= a.sum_row) {
+    const int64_t wg = (int64_t)((int)blockIdx.y - a.sum_row) * gridDim.x + blockIdx.x;
+    project_sum(a.t, wg * 256 + threadIdx.x, (int64_t)(gridDim.y - a.sum_row) * gridDim.x * 256);
+    return;
+  }
   __shared__ float s_code[1 << BITS];
   __shared__ uint32_t s_w[WP_N][WP_PITCH];
   const int tid = threadIdx.x, run = tid & 7, pair = tid >> 3;      // two rows 2 pair, 2 pair + 1 of one 16-column run
@@ -247,7 +251,7 @@ static void launch_weight_plane(const WpArgs& a, dim3 grid, hipStream_t st) {
 
 int launch_plane_product(const MvWeights& q, const uint16_t* Xh, int64_t K, const uint16_t* Th, int Kd, const float* L2,
                          int rank, int64_t m, int64_t rows_pad, int64_t N, uint16_t* Wt, uint16_t* Lt, float* Y, int64_t ldy,
-                         float* part, size_t part_floats, hipStream_t st) {
+                         float* part, size_t part_floats, const ProjectSum& t, hipStream_t st) {
   if (m < 1 || rows_pad < m || rows_pad % PG_T || K < 32 || K % 32 || N < 16 || N % 16 || K * N >= (1ll << 31) ||
       rows_pad * K >= (1ll << 31))
     return LQ_ERR_SHAPE;
@@ -261,8 +265,12 @@ int launch_plane_product(const MvWeights& q, const uint16_t* Xh, int64_t K, cons
   w.levels = q.levels;
   w.inv_levels = 1.0f / (float)q.levels;
   LQ_TRY(device_tables(&w.tables));
-  const dim3 wgrid((unsigned)((N + WP_N - 1) / WP_N), (unsigned)((K + WP_K - 1) / WP_K + (rank > 0 ? 1 : 0)));
-  if (wgrid.y > 65535) return LQ_ERR_SHAPE;
+  const int64_t wx = (N + WP_N - 1) / WP_N, wy = (K + WP_K - 1) / WP_K + (rank > 0 ? 1 : 0);
+  const int64_t sum_wgs = t.splits > 0 ? (t.rows_pad * (t.Kd >> 2) + 255) / 256 : 0;
+  const int64_t sum_rows = std::min<int64_t>((std::min<int64_t>(sum_wgs, 4096) + wx - 1) / wx, 65535 - wy);
+  if (wy > 65535 || (sum_wgs > 0 && sum_rows < 1)) return LQ_ERR_SHAPE;
+  w.sum_row = (int)wy; w.t = t;
+  const dim3 wgrid((unsigned)wx, (unsigned)(wy + sum_rows));
   {
     prof::Scope ps(prof::WEIGHT_PLANE, st, (double)K * (double)N * (q.bits / 8.0 + 2.0));
     switch (q.bits) {

@@ -17,6 +17,7 @@
 #include <algorithm>
 
 #include "kernels.h"
+#include "project_device.h"
 #include "nf_device.h"
 #include "profiler.h"
 
@@ -27,7 +28,7 @@ typedef float floatx4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 
-constexpr int XP_ROWS = 64, XP_COLS = 64, XP_BK = 64, XP_THREADS = 256, XP_PITCH = 72;
+constexpr int XP_ROWS = 64, XP_BK = 64, XP_THREADS = 256, XP_PITCH = 72;
 
 struct XpArgs {
   const float* X; int64_t m, K, ldx;         // rows beyond m read as zero
@@ -39,12 +40,6 @@ struct XpArgs {
   // the reconstructed block scales of Q ride along in extra grid rows (nblocks == 0: none)
   const uint8_t* sidx; const float* v; float* bscale; int64_t nblocks; int group_shift, levels;
 };
-
-// hi = bf16(v), lo = bf16(v - hi): v = hi + lo + O(2^-17 v).
-__device__ __forceinline__ void xp_split(floatx4 v, bf16x4& hi, bf16x4& lo) {
-  hi = __builtin_convertvector(v, bf16x4);
-  lo = __builtin_convertvector(v - __builtin_convertvector(hi, floatx4), bf16x4);
-}
 
 // Registers of one step: the thread's four pieces of the X tile (rows tid / 16 + 16 i, reduction indices
 // 4 (tid % 16) ..) and its 4 x 4 patch of L1 (reduction indices 4 (tid / 16) + j, columns 4 (tid % 16) ..).
@@ -148,27 +143,8 @@ __global__ __launch_bounds__(XP_THREADS, 4) void split_project_kernel(XpArgs a) 
   for (int e = 0; e < 16; ++e) out[(size_t)(8 * (e >> 2) + 4 * lh + (e & 3)) * XP_COLS] = acc[e];
 }
 
-// T = sum of the partial tiles in range order, written as bf16 planes of rows_pad x Kd (the first Kd of the 64 columns).
-__global__ __launch_bounds__(256) void project_finish_kernel(const float* __restrict__ part, int splits, int64_t rows_pad,
-                                                             int Kd, uint16_t* __restrict__ th, uint16_t* __restrict__ tl) {
-  const int64_t q = Kd >> 2, total = rows_pad * q, stride = rows_pad * XP_COLS;
-  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < total; i += (int64_t)gridDim.x * 256) {
-    const int64_t row = i / q, c4 = (i % q) << 2;
-    const float* p = part + row * XP_COLS + c4;
-    floatx4 sum = {0.f, 0.f, 0.f, 0.f};
-    for (int s0 = 0; s0 < splits; s0 += 8) {       // the loads issued eight at a time
-      floatx4 v[8];
-#pragma unroll
-      for (int u = 0; u < 8; ++u)
-        v[u] = s0 + u < splits ? *reinterpret_cast<const floatx4*>(p + (int64_t)(s0 + u) * stride) : floatx4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int u = 0; u < 8; ++u) sum += v[u];
-    }
-    bf16x4 hi, lo;
-    xp_split(sum, hi, lo);
-    *reinterpret_cast<bf16x4*>(th + row * Kd + c4) = hi;
-    *reinterpret_cast<bf16x4*>(tl + row * Kd + c4) = lo;
-  }
+__global__ __launch_bounds__(256) void project_finish_kernel(ProjectSum t) {
+  project_sum(t, (int64_t)blockIdx.x * 256 + threadIdx.x, (int64_t)gridDim.x * 256);
 }
 
 int split_project_splits(int64_t rows_pad, int64_t K) {
@@ -183,7 +159,7 @@ size_t split_project_part_floats(int64_t rows_pad, int64_t K) {
 
 int launch_split_project(const float* X, int64_t m, int64_t K, int64_t ldx, int64_t rows_pad, const float* L1, int rank,
                          int precision, uint16_t* xh, uint16_t* xl, float* part, size_t part_floats, uint16_t* th,
-                         uint16_t* tl, int Kd, const BlockScales& bs, hipStream_t st) {
+                         uint16_t* tl, int Kd, const BlockScales& bs, ProjectSum* later, hipStream_t st) {
   if (m <= 0 || K <= 0 || (K & 3) != 0 || (ldx & 3) != 0 || rows_pad < m || (rows_pad % XP_ROWS) != 0) return LQ_ERR_SHAPE;
   if (rank < 1 || rank > SPLIT_PROJECT_MAX_RANK || (Kd != 32 && Kd != 64) || Kd < rank) return LQ_ERR_RANK;
   if (((uintptr_t)X & 15) != 0) return LQ_ERR_ARG;
@@ -212,10 +188,11 @@ int launch_split_project(const float* X, int64_t m, int64_t K, int64_t ldx, int6
     else hipLaunchKernelGGL(split_project_kernel<false>, grid, dim3(XP_THREADS), 0, st, a);
     LQ_HIP_TRY(hipGetLastError());
   }
+  const ProjectSum t{part, a.splits, rows_pad, Kd, th, tl};
+  if (later) { *later = t; return LQ_OK; }
   prof::Scope ps(prof::MISC, st, (double)(a.splits + 1) * (double)rows_pad * XP_COLS * 4.0);
   const int64_t total = rows_pad * (Kd >> 2);
-  hipLaunchKernelGGL(project_finish_kernel, dim3((unsigned)std::min<int64_t>((total + 255) / 256, 4096)), dim3(256), 0, st,
-                     part, a.splits, rows_pad, Kd, th, tl);
+  hipLaunchKernelGGL(project_finish_kernel, dim3((unsigned)std::min<int64_t>((total + 255) / 256, 4096)), dim3(256), 0, st, t);
   LQ_HIP_TRY(hipGetLastError());
   return LQ_OK;
 }
