@@ -791,7 +791,8 @@ __global__ __launch_bounds__(NTHR1, 4) void lowrank_blockquant_bands_kernel(Phas
 }
 
 // Steps of eight bands per workgroup: the fewest rounds of 512 resident workgroups times what one of them takes, a step each and
-// about as much as one more for the tables, the planes of B and the first loads.
+// about as much as one more for the tables, the planes of B and the first loads.  (At most 4 steps instead of 16: the passes of a
+// layer's sweep, 36 configurations at a time, 68.3 -> 76.1 ms.)
 static int bands_per_wave(int64_t steps, int64_t stretches, int64_t batch) {
   double least = 1e300;
   int best = 1;
