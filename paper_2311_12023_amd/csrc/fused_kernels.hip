@@ -123,12 +123,6 @@ __device__ __forceinline__ void load_search_nosync(const DevTables* __restrict__
   for (int j = threadIdx.x; j < n; j += blockDim.x) s_search[j] = tab->search[slot][j];
 }
 
-template <int BITS>
-__device__ __forceinline__ uint32_t search_code(const SearchEntry* s_search, float x) {
-  const SearchEntry e = *reinterpret_cast<const SearchEntry*>(reinterpret_cast<const char*>(s_search) + search_offset<BITS>(x));
-  return e.below + ((x >= e.thr) ? 1u : 0u);
-}
-
 // max |t| of a quad, as the bit pattern of a non-negative float (unsigned order = numeric order).
 __device__ __forceinline__ uint32_t quad_absmax_bits(const float (&t)[4]) {
   float m;

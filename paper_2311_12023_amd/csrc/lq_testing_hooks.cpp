@@ -179,10 +179,13 @@ int lq_test_search_code(int bits, float x) {
   const int slot = bits_slot(bits);
   if (slot < 0) return -1;
   const HostTables& t = host_tables();
-  const uint32_t offset = bits == 8 ? search_offset<8>(x) : search_offset<4>(x);
-  if ((int)offset / 8 >= search_entries(bits)) return -2;
-  const SearchEntry& e = t.search[slot][offset / 8];
-  return (int)e.below + (x >= e.thr);
+  // entries past the end of the width's table: found as if they held this code
+  constexpr uint32_t outside = 1u << 16;
+  SearchEntry table[4 * search_buckets(8)];
+  for (int j = 0; j < 4 * search_buckets(8); ++j)
+    table[j] = j < search_entries(bits) ? t.search[slot][j] : SearchEntry{HUGE_VALF, outside};
+  const uint32_t c = bits == 8 ? search_code<8>(table, x) : search_code<4>(table, x);
+  return c >= outside ? -2 : (int)c;
 }
 
 float lq_test_sigma_by_reciprocal(float v, int levels) {

@@ -90,16 +90,24 @@ template <> struct Thresholds<8> : BucketSearch<2> { __device__ Thresholds(const
 
 // Code search of the decomposition's quantize pass: 16 buckets per unit, for 8 bits 256, and one comparison per weight.  The
 // entry of x is found by one fused product whose sum keeps the bucket number in the mantissa bits from the third on, so that a mask
-// leaves the entry's byte offset; NaN has none of these bits and takes the first entry, whose comparison it fails.  The sum
+// leaves the entry's byte offset.  The sum
 // rounds to 1/8 of a bucket: entry j serves x from (j - 1/16) / buckets - 1 to the same of j + 1, ends included, and counts the
 // thresholds up to its lower end.  Thresholds are 1.27 (8 bits), 1.29 (4), 2.7 and 8 buckets apart at the least, so one at most is left
 // to compare.  |x| is at most 1 + 2^-20 (a weight by the reciprocal of its block's largest one, or by 0), which is the last entry
-// but one.  Up to 4 bits the 34 entries of 8 bytes lie in different LDS banks but for two pairs: with 256 buckets per unit for
-// every width the quantize pass spent half of its LDS cycles on bank conflicts.
+// but one; NaN, whose mantissa may hold anything, becomes -1 first and takes code 0 (one instruction more per weight, 36 cells of
+// 4096^2 31.3 ms with and without).  Up to 4 bits the 34 entries of 8 bytes lie
+// in different LDS banks but for two pairs: with 256 buckets per unit for every width the quantize pass spent half of its LDS
+// cycles on bank conflicts.
 template <int BITS>
 __host__ __device__ __forceinline__ uint32_t search_offset(float x) {
   constexpr float scale = (float)search_buckets(BITS), base = (float)(1 << 20) + scale;
   return __builtin_bit_cast(uint32_t, fmaf(x, scale, base)) & ((4u * search_buckets(BITS) - 1u) << 3);
+}
+template <int BITS>
+__host__ __device__ __forceinline__ uint32_t search_code(const SearchEntry* table, float x) {
+  x = fmaxf(x, -1.0f);
+  const SearchEntry e = *reinterpret_cast<const SearchEntry*>(reinterpret_cast<const char*>(table) + search_offset<BITS>(x));
+  return e.below + ((x >= e.thr) ? 1u : 0u);
 }
 
 // ---- cross-lane moves by DPP: quad_perm inside a quad of lanes; where every quad is uniform the mirror of a half row swaps the

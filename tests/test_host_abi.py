@@ -253,6 +253,19 @@ def test_quantize_pass_search_equals_brute_force(oracle, bits):
     assert L.lq_test_search_code(bits, float("nan")) == L.lq_test_search_code(bits, -float("nan")) == 0
 
 
+@pytest.mark.parametrize("bits", [2, 3, 4, 8])
+def test_quantize_pass_search_gives_every_nan_code_0(bits):
+    """Whatever a NaN carries in its mantissa (weights in memory filled with ones, say) takes code 0 and an entry of the table:
+    all patterns of the twelve lowest bits, which the entry's number comes from, and each of the others alone and with all below."""
+    L = testing_lib.load()
+    low = np.arange(1 << 12, dtype=np.uint32)
+    bit = np.uint32(1) << np.arange(12, 22, dtype=np.uint32)
+    quiet = np.uint32(0x7fc00000) | np.concatenate([low, bit, 2 * bit - 1, np.array([0x3fffff, 0x3ff000], np.uint32)])
+    x = np.concatenate([quiet, quiet | np.uint32(0x80000000)]).view(np.float32)
+    assert np.all(np.isnan(x))
+    assert not any(L.lq_test_search_code(bits, float(v)) for v in x)
+
+
 @pytest.mark.parametrize("scale_bits", [2, 3, 4, 5, 6, 7, 8])
 def test_division_free_block_scale_equals_the_division(L, scale_bits):
     """The forward product's kernels take v / levels from the reciprocal and a correction: equal to the division for normal
