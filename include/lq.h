@@ -263,8 +263,9 @@ int lq_fisher_row_col(const float* F, int64_t d, int64_t k, float* row_w, float*
  *   codes_packed, scale_idx, v    Quantize(Q, c) of the d x k matrix Q (row-major flattening); k % B0 == 0
  *   L1, L2   d x rank and rank x k fp32, or rank == 0 (then both may be NULL): Y = X Q
  *   precision  0: every operand is split into bf16 hi + lo and each product takes three bf16 MFMAs with fp32
- *                 accumulation (error of an output about 2^-16 of sum |x||w|);  1: bf16 operands, one MFMA
- *                 (about 2^-8), for callers that train in bf16
+ *                 accumulation (error of an output about 2^-16 of sum |x||w|; up to 128 rows, where block scales are taken
+ *                 into X, that has three parts and five MFMAs);  1: bf16 operands, one MFMA (about 2^-8; there X has two
+ *                 parts and two MFMAs), for callers that train in bf16
  *              Up to 128 rows (rank <= 512; 64 for weights of 2^24 and more, where more depends on the sizes) X is split
  *              on the fly and the workspace holds partial sums only.  Above 512 rows (rank <= 64) precision 1 decodes the
  *              weights into a bf16 plane in the workspace first.  A workspace that is too small for the way that is taken

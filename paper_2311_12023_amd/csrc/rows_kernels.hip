@@ -7,16 +7,22 @@
 // halves on the way; only the sums are staged.  A workgroup owns 128 columns at a time; its eight wavefronts take
 // turns at the 32-deep reduction steps and their sums are added in order through LDS.  Every weight is turned into operands for at
 // most 48 rows, so that takes the time, not the products, and there are two forms of it:
-// - Blocks of 64 weights and more, three steps per wavefront or more.  The 64 or 128 columns of a row that a tile has in a block share one scale, so X Q is the
-//   product of X, its columns times these scales, with values of the code book, whose bf16 halves come from a table for
-//   two rows of Q at a time (QrTable).  A wavefront computes a step's scales one per lane and hands them out through LDS.
-// - Otherwise: six vector instructions per weight (extract, look up, scale, split), by count a third of the time.
-// Per wavefront and step of 4096 x 11008 at 24 rows the first form takes 260 vector instructions instead of 605; what is left is latency: two
+// - Blocks of 64 weights and more, where some wavefront has three steps or more.  The 64 or 128 columns of a row that a tile has in
+//   a block share one scale, so X Q is the product of X, its columns times these scales, with values of the code book, whose bf16
+//   halves come from a table for two rows of Q at a time (QrTable).  A wavefront computes a step's scales one per lane and hands them
+//   out through LDS.  X times the scale goes in as three bf16 (precision 1: two): five products (two).
+// - Otherwise, and where two_scales_ahead says so: extract, look up, scale and split every weight into two bf16 (one): three
+//   products (one).
+// Per wavefront and step of 4096 x 11008 at 24 rows the loop has 349 vector instructions in the first form and 490 in the second; what
+// is left is latency: two
 // wavefronts per SIMD, loads one step ahead, and the first fetch (behind the first segment: asked for with that one's last
-// step) and last sum of each workgroup.  Whole calls, NF4 64/256, rank 64, second form -> first (us): 4096 x 11008 at 9 rows 27.5 ->
-// 21.1, 24 rows 30.6 -> 27.7, 48 rows 40.5 -> 37.1, 4096 x 4096 at 128 rows 41.4 -> 36.3; 11008 x 4096, 3 bits, 16 rows 42.3 -> 33.6; the
-// error against 64 bits goes from 4.4e-6 to 3.6e-6 (3 bits 3.2e-6).  What did not help: a wavefront per 64 columns and
-// four per step, two steps in flight (twice the loads of X: 29 us at 24 rows, 42 at 48), one copy of the table (bank conflicts: 29.4).
+// step) and last sum of each workgroup.  Whole calls, NF4 64/256, rank 64, precision 0, second form -> first (us): 4096 x 11008 at 9
+// rows 27.5 -> 21.5, 24 rows 29.2 -> 28.6; 8192 x 8192, 16 rows 34.5 -> 25.0; 11008 x 4096, 3 bits, 16 rows 41.3 -> 23.0.  With two parts
+// of X times the scale (four products) 24 rows took 26.2, but rows of X that are exact in bf16, which the second form does not
+// round, came out with an error of 3.2e-6 instead of 2.5e-6 (precision 1: 1.9e-3 instead of 1.7e-3); now 0.7e-6 (4 bits), 1.7e-6 (8)
+// and 1.1e-3, 1.2e-3, and for any fp32 X the same instead of 4.4e-6 and 2.3e-3.  What did not help: a wavefront per 64 columns and
+// four per step, two steps in flight (twice the loads of X: 29 us at 24 rows, 42 at 48, against 27 and 37 then), one copy of the
+// table (bank conflicts: 29.4).
 // Second form, whole call on 4096 x 11008, NF4, rank 64 (4096 x 4096): 24 rows 79 -> 32 us (45 -> 20), 64 rows 84 -> 50 us (47 -> 27),
 // 128 rows 94 -> 85 us (52 -> 42) against the kernel for large m, whose steps take 2 us whatever they multiply (256-row tiles
 // of X staged through LDS, a barrier per step).  At 192 rows that kernel is ahead on the wide matrix (95 against 111 us)
@@ -70,6 +76,21 @@ __device__ __forceinline__ void split8(const float (&w)[8], bf16x8& hi, bf16x8& 
     else { h = __builtin_convertvector(floatx2{w[i], w[i + 1]}, bf16x2); l = h; }
     hi[i] = h[0]; hi[i + 1] = h[1];
     if constexpr (SPLIT) { lo[i] = l[0]; lo[i + 1] = l[1]; }
+  }
+}
+
+// w as the sum of N bf16 parts, largest first: what they leave is about 2^-9 of the one before the last, each.
+template <int N>
+__device__ __forceinline__ void split_parts(const float (&w)[8], bf16x8 (&part)[N]) {
+#pragma unroll
+  for (int i = 0; i < 8; i += 2) {
+    floatx2 v = {w[i], w[i + 1]};
+#pragma unroll
+    for (int p = 0; p < N; ++p) {
+      const bf16x2 b = __builtin_convertvector(v, bf16x2);
+      part[p][i] = b[0]; part[p][i + 1] = b[1];
+      if (p + 1 < N) v -= __builtin_convertvector(b, floatx2);
+    }
   }
 }
 
@@ -214,7 +235,9 @@ __global__ __launch_bounds__(64 * QR_WAVES, 2) void qrows_kernel(QrArgs a) {
   };
 
   // The form with the scales in X: what a step needs of X, codes and scales, one step ahead and across segments.
-  constexpr int NX = NBLK == 2 ? 2 : 1;
+  constexpr int NX = NBLK == 2 ? 2 : 1, XPARTS = SPLIT ? 3 : 2;
+  // The code book times this is off by 5.0e-7 as a sum of two bf16, without it by 1.9e-6 (the other widths gain nothing by a factor).
+  constexpr float gain = BITS == 4 && SPLIT ? 1.828125f : 1.0f;
   typedef RowCodes<BITS, NBLK == 0 ? 1 : NBLK> Row;
   const uint32_t run_bytes = (uint32_t)(a.N / 16 * (2 * BITS)), row_blocks = (uint32_t)(a.N >> a.block_shift);   // of a row
   const uint32_t row_lane = (uint32_t)(8 * q) * run_bytes + Row::lane_offset(c);
@@ -269,7 +292,7 @@ __global__ __launch_bounds__(64 * QR_WAVES, 2) void qrows_kernel(QrArgs a) {
             w = __builtin_bit_cast(uint32_t, bf16x2{hi[0], lo[0]});
           } else {
             const int pr = e < QrTable<BITS>::entries ? e : 0;
-            split_pair(book[pr & ((1 << BITS) - 1)], book[pr >> BITS], hi, lo);
+            split_pair(gain * book[pr & ((1 << BITS) - 1)], gain * book[pr >> BITS], hi, lo);
             w = __builtin_bit_cast(uint32_t, at & 128 ? lo : hi);
           }
           if (e < QrTable<BITS>::entries) *reinterpret_cast<uint4*>(reinterpret_cast<char*>(sh.code) + at) = make_uint4(w, w, w, w);
@@ -278,7 +301,7 @@ __global__ __launch_bounds__(64 * QR_WAVES, 2) void qrows_kernel(QrArgs a) {
         table = true;
       }
       for (; s < s1; s += QR_WAVES) {
-        if (NBLK == 2 || lane < 32) scales[lane] = block_scale_by_reciprocal(si, vv, a.levels, a.inv_levels);
+        if (NBLK == 2 || lane < 32) scales[lane] = block_scale_by_reciprocal(si, vv, a.levels, a.inv_levels) * (1.0f / gain);
         // fields of 2 BITS bits: the codes of rows 2 p and 2 p + 1 in set 2 f (pair[p][0]) and 2 f + 1 (pair[p][1])
         uint32_t pair[4][2];
         uint32_t codes[8][2];
@@ -294,17 +317,14 @@ __global__ __launch_bounds__(64 * QR_WAVES, 2) void qrows_kernel(QrArgs a) {
           }
         }
         __builtin_amdgcn_wave_barrier();
-        bf16x8 sh_hi[NX][RT], sh_lo[NX][RT];
+        float xs[NX][RT][8];
 #pragma unroll
         for (int b = 0; b < NX; ++b) {
           const floatx4 sl = *reinterpret_cast<const floatx4*>(scales + 32 * b + 8 * q), su = *reinterpret_cast<const floatx4*>(scales + 32 * b + 8 * q + 4);
 #pragma unroll
-          for (int t = 0; t < RT; ++t) {
-            float xs[8];
+          for (int t = 0; t < RT; ++t)
 #pragma unroll
-            for (int e = 0; e < 8; ++e) xs[e] = xv[t][e >> 2][e & 3] * (e < 4 ? sl[e & 3] : su[e & 3]);
-            split8<SPLIT>(xs, sh_hi[b][t], sh_lo[b][t]);
-          }
+            for (int e = 0; e < 8; ++e) xs[b][t][e] = xv[t][e >> 2][e & 3] * (e < 4 ? sl[e & 3] : su[e & 3]);
         }
         // next: this tile's step, or the first one of the segment behind this one, or (nothing left) the same again
         int next_tile = tile, next = s;
@@ -314,8 +334,12 @@ __global__ __launch_bounds__(64 * QR_WAVES, 2) void qrows_kernel(QrArgs a) {
         __builtin_amdgcn_sched_barrier(0);
         for_each_block<NX>([&](auto block) {
           constexpr int b = decltype(block)::value;
+          // The values have one or two parts.  X times the scale has one more: rounding both sides alike would add an error that
+          // rounding the scaled weight does not make where X is exact in bf16.
+          if constexpr (b > 0) __builtin_amdgcn_sched_barrier(0);
+          bf16x8 xp[RT][XPARTS];
 #pragma unroll
-          for (int t = 0; t < RT; ++t) { xh[t] = sh_hi[b][t]; xl[t] = sh_lo[b][t]; }
+          for (int t = 0; t < RT; ++t) split_parts(xs[b][t], xp[t]);
           constexpr int SETS = RT < 2 ? 2 : 1;           // sets at a time: successive products are independent of one another
           for_each_block<QR_SETS / NX / SETS>([&](auto set) {
             constexpr int j0 = QR_SETS / NX * b + SETS * decltype(set)::value;
@@ -339,16 +363,16 @@ __global__ __launch_bounds__(64 * QR_WAVES, 2) void qrows_kernel(QrArgs a) {
                   l[i][p] = SPLIT ? *reinterpret_cast<const uint32_t*>(table + at + 128) : 0u;
                 }
               }
-            auto product = [&](const bf16x8 (&x)[RT], const uintx4 (&w)[SETS]) __attribute__((always_inline)) {
+            auto product = [&](int part, const uintx4 (&w)[SETS]) __attribute__((always_inline)) {
 #pragma unroll
               for (int i = 0; i < SETS; ++i)
 #pragma unroll
                 for (int t = 0; t < RT; ++t)
-                  acc[t][j0 + i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x[t], __builtin_bit_cast(bf16x8, w[i]), acc[t][j0 + i], 0, 0, 0);
+                  acc[t][j0 + i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xp[t][part], __builtin_bit_cast(bf16x8, w[i]), acc[t][j0 + i], 0, 0, 0);
             };
-            // with scales in X neither side is exact for plain X, so the product of the low halves is not left out
-            if constexpr (SPLIT) { product(xl, l); product(xl, h); product(xh, l); }
-            product(xh, h);
+            if constexpr (SPLIT) { product(2, h); product(1, l); product(0, l); }
+            product(1, h);
+            product(0, h);
           });
         });
         __builtin_amdgcn_wave_barrier();
@@ -490,20 +514,35 @@ size_t qrows_part_floats(int64_t m, int64_t K, int64_t N, int rank) {
   return (size_t)qrows_shares(m, K, N, rank).segments * (size_t)m * (size_t)(N + rank);
 }
 
-template <int BITS, bool SPLIT, int NBLK>
-static void launch_rt(const QrArgs& a, int rt, dim3 grid, hipStream_t st) {
-  if (rt == 1) hipLaunchKernelGGL((qrows_kernel<BITS, 1, SPLIT, NBLK>), grid, dim3(64 * QR_WAVES), 0, st, a);
-  else if (rt == 2) hipLaunchKernelGGL((qrows_kernel<BITS, 2, SPLIT, NBLK>), grid, dim3(64 * QR_WAVES), 0, st, a);
-  else hipLaunchKernelGGL((qrows_kernel<BITS, 3, SPLIT, NBLK>), grid, dim3(64 * QR_WAVES), 0, st, a);
-}
-template <int BITS, bool SPLIT>
-static void launch_blocks(const QrArgs& a, int rt, dim3 grid, hipStream_t st) {
+// Two scales per row of a tile: whether the form with the scales in X is ahead.  It keeps X times both scales, which with three row
+// tiles leaves 4 and 8 bits too few registers to have loads in flight, and 3-bit codes take a shift more to come apart (second form
+// -> first, us, 4096 x 11008: 48 rows, precision 0 / 1: 2 bits 39.4 / 31.1 -> 38.9 / 31.4, 3 bits 48.7 / 43.4 -> 43.8 / 35.0, 4 bits
+// 39.6 / 32.8 -> 42.7 / 31.5, 8 bits 40.8 / 33.5 -> 44.0 / 36.1; 24 rows: 2 bits 29.1 / 24.6 -> 27.6 / 22.9, 3 bits 31.3 / 26.3 ->
+// 31.1 / 26.8, 4 bits 29.2 / 23.9 -> 28.5 / 23.5, 8 bits 30.6 / 26.6 -> 30.5 / 25.7; one row tile: 5 to 60 % ahead for every width).
+template <int BITS, int RT, bool SPLIT>
+constexpr bool two_scales_ahead = RT == 1 || (RT == 2 ? BITS != 3 || SPLIT : BITS < 4 || (BITS == 4 && !SPLIT));
+
+template <int BITS, int RT, bool SPLIT>
+static void launch_blocks(const QrArgs& a, dim3 grid, hipStream_t st) {
   // A workgroup of the form with the scales in X makes the table first, 64 KB for 4 bits, which one or two steps per wavefront do
   // not pay back (24 rows: 2048 x 2048, one step 12.9 against 13.2 us; 4096 x 4096, three steps 17.5 against 17.3).
   const bool scaled = a.per_wg > 2 * QR_WAVES;
-  if (scaled && a.block_shift >= 7) launch_rt<BITS, SPLIT, 1>(a, rt, grid, st);
-  else if (scaled && a.block_shift == 6) launch_rt<BITS, SPLIT, 2>(a, rt, grid, st);
-  else launch_rt<BITS, SPLIT, 0>(a, rt, grid, st);
+  if (scaled && a.block_shift >= 7) {
+    hipLaunchKernelGGL((qrows_kernel<BITS, RT, SPLIT, 1>), grid, dim3(64 * QR_WAVES), 0, st, a);
+    return;
+  }
+  if constexpr (two_scales_ahead<BITS, RT, SPLIT>)
+    if (scaled && a.block_shift == 6) {
+      hipLaunchKernelGGL((qrows_kernel<BITS, RT, SPLIT, 2>), grid, dim3(64 * QR_WAVES), 0, st, a);
+      return;
+    }
+  hipLaunchKernelGGL((qrows_kernel<BITS, RT, SPLIT, 0>), grid, dim3(64 * QR_WAVES), 0, st, a);
+}
+template <int BITS, bool SPLIT>
+static void launch_rt(const QrArgs& a, int rt, dim3 grid, hipStream_t st) {
+  if (rt == 1) launch_blocks<BITS, 1, SPLIT>(a, grid, st);
+  else if (rt == 2) launch_blocks<BITS, 2, SPLIT>(a, grid, st);
+  else launch_blocks<BITS, 3, SPLIT>(a, grid, st);
 }
 
 int launch_qrows(const MvWeights& q, const float* X, int64_t ldx, int64_t K, const float* L1, const float* L2, int64_t ldl2,
@@ -537,8 +576,8 @@ int launch_qrows(const MvWeights& q, const float* X, int64_t ldx, int64_t K, con
     prof::Scope ps(prof::QROWS, st, 2.0 * m * (double)K * (double)(N + rank));
 #define LQ_QROWS(BITS)                                             \
   case BITS:                                                       \
-    if (precision == 0) launch_blocks<BITS, true>(a, rt, grid, st);    \
-    else launch_blocks<BITS, false>(a, rt, grid, st);                  \
+    if (precision == 0) launch_rt<BITS, true>(a, rt, grid, st);        \
+    else launch_rt<BITS, false>(a, rt, grid, st);                      \
     break;
     switch (q.bits) {
       LQ_QROWS(2) LQ_QROWS(3) LQ_QROWS(4) LQ_QROWS(8)

@@ -69,3 +69,24 @@ def test_rows_zero_scales_and_infinite_x(oracle, bits, block):
     ref, scale = oracle.matmul(x[ok], codes, sidx, v, ocfg, k, want_abs=True)
     assert np.all(y[ok, :block] == 0) and np.all(np.abs(y[ok] - ref) <= 4e-5 * scale)
     assert not np.any(np.isfinite(y[[3, 11]][:, block:]))
+
+
+@pytest.mark.parametrize("m,d,k,block", [(16, 544, 16448, 64), (24, 544, 16448, 64), (48, 544, 16512, 128)])
+@pytest.mark.parametrize("bits", [2, 3, 4, 8])
+def test_rows_bf16_x_is_not_rounded(oracle, m, d, k, block, bits):
+    """Rows of X with one element, exact in bf16, show every weight by itself.  Rounding the weight to the sum of two bf16
+    (precision 0) or to one (precision 1) is off by 2^-17 or 2^-8 of it at most; X times a block's scale must not be rounded
+    as coarsely on top of the values of the code book.  Beside that there are fp32 roundings of scale, product and sum and, for
+    precision 1, 2^-17 of X times the scale."""
+    import torch
+    from paper_2311_12023_amd import lq
+    ocfg = oracle.config(bits, block, 16)
+    codes, sidx, v, _ = oracle.quantize(gen.weight_matrix(d, k, 500 + bits, 4).ravel(), ocfg)
+    x = np.zeros((m, d), np.float32)
+    at = np.random.default_rng(bits).permutation(d)[:m]
+    x[np.arange(m), at] = torch.from_numpy(gen.activations(1, m, 501)[0]).bfloat16().float().numpy()
+    ref, scale = oracle.matmul(x, codes, sidx, v, ocfg, k, want_abs=True)
+    t = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    for precision, bound in ((0, 2.0 ** -17 + 2.0 ** -20), (1, 2.0 ** -8 + 2.0 ** -16)):
+        y = lq.matmul(t(x), t(oracle.pack(codes, bits)), t(sidx), t(v), lq.config(bits, block, 16), k, precision=precision).cpu().numpy()
+        assert np.max(np.abs(y - ref) - bound * scale) <= 0, (precision, np.max(np.abs(y - ref)[scale > 0] / scale[scale > 0]))
