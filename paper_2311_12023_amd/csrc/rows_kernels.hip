@@ -17,7 +17,7 @@
 // is left is latency: two
 // wavefronts per SIMD, loads one step ahead, and the first fetch (behind the first segment: asked for with that one's last
 // step) and last sum of each workgroup.  Whole calls, NF4 64/256, rank 64, precision 0, second form -> first (us): 4096 x 11008 at 9
-// rows 27.5 -> 21.5, 24 rows 29.2 -> 28.6; 8192 x 8192, 16 rows 34.5 -> 25.0; 11008 x 4096, 3 bits, 16 rows 41.3 -> 23.0.  With two parts
+// rows 27.5 -> 21.5, 24 rows 29.2 -> 28.5; 8192 x 8192, 16 rows 34.5 -> 25.0; 11008 x 4096, 3 bits, 16 rows 41.3 -> 23.0.  With two parts
 // of X times the scale (four products) 24 rows took 26.2, but rows of X that are exact in bf16, which the second form does not
 // round, came out with an error of 3.2e-6 instead of 2.5e-6 (precision 1: 1.9e-3 instead of 1.7e-3); now 0.7e-6 (4 bits), 1.7e-6 (8)
 // and 1.1e-3, 1.2e-3, and for any fp32 X the same instead of 4.4e-6 and 2.3e-3.  What did not help: a wavefront per 64 columns and
@@ -176,6 +176,36 @@ struct RowCodes {
     } else if constexpr (BITS != 8 && NBLK == 2) w[0] = lo | (hi << (4 * BITS));
   }
 };
+
+// Four columns from `col` (a multiple of 4) of row `row` of X times rows k0 .. k1 - 1 of Q, one element at a time; NaN at once where
+// X holds one.
+template <int BITS>
+__device__ __forceinline__ floatx4 plain_sum(const QrArgs& a, int row, int64_t col, int64_t k0, int64_t k1) {
+  const float* x = a.X + (int64_t)row * a.ldx;
+  bool nan = false;
+#pragma unroll 8
+  for (int64_t k = k0; k < k1; k += 4) {
+    const floatx4 v = *reinterpret_cast<const floatx4*>(x + k);
+    nan = nan || isnan(v[0]) || isnan(v[1]) || isnan(v[2]) || isnan(v[3]);
+  }
+  floatx4 o = {0.f, 0.f, 0.f, 0.f};
+  if (nan) return o + NAN;
+  const float* book = a.tables->code[Slot<BITS>::value];
+  const int quad = (int)(col & 15) >> 2;                             // of the 16-weight run
+#pragma unroll 1
+  for (int64_t k = k0; k < k1; ++k) {
+    const uint8_t* from = a.codes + (uint64_t)((k * a.N + col) >> 4) * (2 * BITS) + ((4 * BITS * quad) >> 3);
+    uint32_t w = from[0];
+    if constexpr (BITS > 2) w |= (uint32_t)from[1] << 8;
+    if constexpr (BITS == 8) w |= (uint32_t)from[2] << 16 | (uint32_t)from[3] << 24;
+    if constexpr (BITS == 3) w >>= 4 * (quad & 1);
+    const uint32_t blk = (uint32_t)((k * a.N + col) >> a.block_shift);
+    const float scale = block_scale_by_reciprocal(a.sidx[blk], a.v[blk >> a.group_shift], a.levels, a.inv_levels);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) o[j] = fmaf(x[k], book[__builtin_amdgcn_ubfe(w, BITS * j, BITS)] * scale, o[j]);
+  }
+  return o;
+}
 
 // The steps of all column tiles, in order (tile, step), are dealt out in equal contiguous shares, so that every compute unit
 // gets the same work whatever the number of tiles; a workgroup's part of a tile is one segment, numbered within the tile.
@@ -471,7 +501,15 @@ __global__ __launch_bounds__(64 * QR_WAVES, 2) void qrows_kernel(QrArgs a) {
       const int64_t prow = (int64_t)segment * a.m + row;
       if (!dense) {
         const int64_t col = (int64_t)tile * QR_COLS + (NBLK == 2 ? QR_COLS / 8 * set0 + 4 * c : QR_SETS * c + set0);
-        if (col < a.N) *reinterpret_cast<floatx4*>(a.part + prow * a.N + col) = o;
+        if (col < a.N) {
+          // X times a scale can leave the range of floats where X times the scaled weights does not (code 0 is 0 whatever the
+          // scale): sums that are not finite are formed again from these (24 rows x 4096 x 11008 28.3 -> 28.5 us for looking; a row
+          // with NaN 15 us, an infinite one 0.8 ms).
+          if constexpr (NBLK > 0)
+            if (__builtin_expect(!(fabsf(o[0]) + fabsf(o[1]) + fabsf(o[2]) + fabsf(o[3]) < HUGE_VALF), 0))
+              o = plain_sum<BITS>(a, row, col, 32 * (int64_t)s0, 32 * (int64_t)s1);
+          *reinterpret_cast<floatx4*>(a.part + prow * a.N + col) = o;
+        }
       } else if (set0 == 0) {
         const int col = (tile - a.tiles_q) * QR_DCOLS + 4 * c;
 #pragma unroll

@@ -90,3 +90,35 @@ def test_rows_bf16_x_is_not_rounded(oracle, m, d, k, block, bits):
     for precision, bound in ((0, 2.0 ** -17 + 2.0 ** -20), (1, 2.0 ** -8 + 2.0 ** -16)):
         y = lq.matmul(t(x), t(oracle.pack(codes, bits)), t(sidx), t(v), lq.config(bits, block, 16), k, precision=precision).cpu().numpy()
         assert np.max(np.abs(y - ref) - bound * scale) <= 0, (precision, np.max(np.abs(y - ref)[scale > 0] / scale[scale > 0]))
+
+
+@pytest.mark.parametrize("m", [12, 20, 48])
+@pytest.mark.parametrize("bits,block", [(2, 64), (3, 64), (4, 64), (8, 64), (3, 128), (4, 128), (8, 128)])
+def test_rows_scale_times_x_past_the_largest_float(oracle, m, bits, block):
+    """3e38 times a block's largest weight of 4 overflows, times its other weights (code 0, or small) it does not: columns whose
+    result fits are as close to the oracle's as any other, the rest are infinite.  A row with an infinite element is not finite
+    (split into bf16 it is NaN) and keeps to itself."""
+    import torch
+    from paper_2311_12023_amd import lq
+    d, k = 544, 16448 if block == 64 else 16512
+    ocfg = oracle.config(bits, block, 16)
+    w = gen.weight_matrix(d, k, 600 + bits, 4)
+    w[100], w[300] = 0, 0
+    w[100, 7::block] = 4
+    if bits == 8: w[100, 11::block] = -0.9
+    w[300, 3::block], w[300, 5::block] = 2, -2
+    codes, sidx, v, _ = oracle.quantize(w.ravel(), ocfg)
+    x = gen.activations(m, d, 601)
+    x[:, [100, 300]] = 0
+    x[1, 100] = x[m - 1, 100] = 3e38
+    x[4, 300] = np.inf
+    t = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    keep = np.arange(m) != 4
+    ref, scale = oracle.matmul(x[keep], codes, sidx, v, ocfg, k, want_abs=True)
+    fits = np.abs(ref) < 3.3e38
+    assert 0 < np.sum(~fits) <= 2 * k // block + k // block
+    for precision, tol in ((0, 4e-5), (1, 1e-2)):
+        y = lq.matmul(t(x), t(oracle.pack(codes, bits)), t(sidx), t(v), lq.config(bits, block, 16), k, precision=precision).cpu().numpy()
+        assert not np.any(np.isfinite(y[4]))
+        y = y[keep]
+        assert np.all(np.abs(y[fits] - ref[fits]) <= tol * scale[fits]) and np.all(np.isposinf(y[~fits]))
