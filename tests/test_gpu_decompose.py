@@ -157,7 +157,7 @@ def test_factorize_weighted(env, oracle):
     assert abs(werr - np.sum(ref[r:] ** 2)) < 1e-4 * np.sum(ref[r:] ** 2)
 
 
-def check_decomposition_consistency(oracle, w, out, ocfg, rank, row_w=None, col_w=None, product_error=0.0):
+def check_decomposition_consistency(oracle, w, out, ocfg, rank, row_w=None, col_w=None):
     """What must hold for the GPU's own outputs whatever the trajectory."""
     d, k = w.shape
     codes = oracle.unpack(out["codes"].cpu().numpy(), d * k, ocfg.bits)
@@ -169,7 +169,7 @@ def check_decomposition_consistency(oracle, w, out, ocfg, rank, row_w=None, col_
     t = w.astype(np.float64) - l1 @ l2
     wt = 1.0 if row_w is None else np.outer(row_w.astype(np.float64), col_w.astype(np.float64))
     eps = np.sqrt(np.sum(wt * (t - q) ** 2))
-    assert abs(eps - out["err"]) < 2e-5 * eps + product_error      # reported error = error of the returned pieces
+    assert abs(eps - out["err"]) < 2e-5 * eps                      # reported error = error of the returned pieces
     # the returned codes are the oracle's quantization of W - L1 L2 up to fp32 rounding of that residual
     ocodes, osidx, ov, _ = oracle.quantize(t.astype(np.float32).ravel(), ocfg)
     assert np.mean(ocodes != codes) < 2e-3
@@ -256,24 +256,90 @@ def test_decompose_quantized_initialisation(env, oracle, weighted):
         lq.error_table(wt, r, [lq.config(3, 32, 64)], 2, params=lq.SvdParams(init_quantized=1))
 
 
+def check_quantize_pass(oracle, w, out, ocfg, row_w=None, col_w=None):
+    """Every code, scale index and scale of the returned Q against W - L1 L2 in 64 bits, weight by weight, and the reported error.
+    The kernel's product is off by 2^-16 of |L1| |L2| at most (bf16 pairs, products of the low halves left out), the rest are
+    fp32 roundings: of the difference, the reciprocal and the quotient."""
+    d, k = w.shape
+    levels = 2 ** (ocfg.scale_bits - 1) - 1
+    codes = oracle.unpack(out["codes"].cpu().numpy(), d * k, ocfg.bits)
+    sidx, v = out["scale_idx"].cpu().numpy(), out["v"].cpu().numpy()
+    q = oracle.dequantize(codes, sidx, v, ocfg).reshape(d, k)
+    assert np.array_equal(out["Q"].cpu().numpy(), q)               # dense Q is the dequantized codes, bit for bit
+    l1, l2 = out["L1"].cpu().numpy().astype(np.float64), out["L2"].cpu().numpy().astype(np.float64)
+    t = w.astype(np.float64) - l1 @ l2
+    product = 2.0 ** -16 * (np.abs(l1) @ np.abs(l2))
+    blocks = lambda a: a.reshape(-1, ocfg.block)
+    absmax = np.abs(blocks(t)).max(1)
+    x = blocks(t) / absmax[:, None]
+    slack = blocks(product + 2.0 ** -23 * np.abs(w)) / absmax[:, None] + 2.0 ** -21
+    slack_max = slack.max(1, keepdims=True)                        # of a block's largest weight, at most
+    book = oracle.codebook(ocfg.bits).astype(np.float64)
+    edges = np.concatenate([[-np.inf], (book[1:] + book[:-1]) / 2, [np.inf]])
+    c = blocks(codes).astype(int)
+    slack = slack + np.abs(x) * slack_max
+    assert np.all((x >= edges[c] - slack) & (x <= edges[c + 1] + slack))
+    off = slack_max[:, 0] * absmax
+    groups = np.arange(absmax.size) // ocfg.scale_block
+    vmax = np.zeros(v.size)
+    np.maximum.at(vmax, groups, absmax)
+    voff = np.zeros(v.size)
+    np.maximum.at(voff, groups, off)
+    assert np.all(np.abs(v - vmax) <= voff + 2.0 ** -23 * vmax)
+    sigma = v.astype(np.float64)[groups] / levels
+    assert np.all(np.abs(sidx - absmax / sigma) <= 0.5 + off / sigma + 1e-5)
+    # What is wrong with the products of different weights has nothing to do with their quantization: in the sum it grows as the
+    # root of their number, by a sixth of the bound each at most (roundings are evenly spread), six standard deviations of which
+    # are allowed for; the squares stay.
+    wt = np.ones((d, k)) if row_w is None else np.outer(row_w.astype(np.float64), col_w.astype(np.float64))
+    eps, pe = np.sqrt(np.sum(wt * (t - q) ** 2)), np.linalg.norm(np.sqrt(wt) * product)
+    assert abs(eps - out["err"]) <= 1e-6 * eps + pe / np.sqrt(d * k) + pe ** 2 / (2 * eps)
+
+
 # (d, k, rank): rows past a band of 16, columns past a stretch of 128, a lane's 32 columns cut by the edge (k = 16 mod 32), one
-# column run alone, ranks on both sides of the 32-deep products and of the kernel's 64
-@pytest.mark.parametrize("d,k,rank", [(129, 144, 16), (160, 272, 1), (177, 400, 17), (257, 128, 33), (208, 656, 64), (240, 384, 65)])
+# column run alone, ranks on both sides of the 32-deep products and, with rows and columns past a tile, of the kernel's 64
+@pytest.mark.parametrize("d,k,rank", [(129, 144, 16), (160, 272, 1), (177, 400, 17), (257, 128, 33), (208, 656, 64), (240, 384, 65), (203, 208, 66)])
 @pytest.mark.parametrize("bits", [2, 3, 4, 8])
 @pytest.mark.parametrize("weighted", [False, True])
-def test_quantize_pass_edges(env, oracle, d, k, rank, bits, weighted):
+@pytest.mark.parametrize("gemm_mode", [1, 3])
+def test_quantize_pass_edges(env, oracle, d, k, rank, bits, weighted, gemm_mode):
     torch, lq = env
     blocks = [b for b in (16, 32, 64, 128) if k % b == 0]
     w = gen.weight_matrix(d, k, 100 * d + bits, min(d, k) // 4, outlier_frac=0.004)
     rw, cw = (gen.positive_weights(d, 5), gen.positive_weights(k, 6)) if weighted else (None, None)
     fisher = dict(row_w=torch.from_numpy(rw).cuda(), col_w=torch.from_numpy(cw).cuda()) if weighted else {}
     for block in blocks:
-        out = lq.decompose(torch.from_numpy(w).cuda(), rank, lq.config(bits, block, 16), 2, seed=3, want_dense=True, **fisher)
-        # L1 L2 in split products is off by 2^-16 of |L1| |L2| at most, which the error of an 8-bit quantizer is small enough to show
-        l1, l2 = (np.abs(out[n].cpu().numpy().astype(np.float64)) for n in ("L1", "L2"))
-        scale = 1.0 if rw is None else np.sqrt(np.outer(rw.astype(np.float64), cw.astype(np.float64)))
-        check_decomposition_consistency(oracle, w, out, oracle.config(bits, block, 16), rank, rw, cw,
-                                        product_error=2.0 ** -16 * np.linalg.norm(scale * (l1 @ l2)))
+        out = lq.decompose(torch.from_numpy(w).cuda(), rank, lq.config(bits, block, 16), 2, seed=3, want_dense=True,
+                           params=lq.SvdParams(gemm_mode=gemm_mode), **fisher)
+        check_quantize_pass(oracle, w, out, oracle.config(bits, block, 16), rw, cw)
+
+
+# More than 512 workgroups of eight bands, so each walks over sixteen: a last workgroup with one band of half its rows, a lane's 32
+# columns cut by the edge, a stretch of one 32-column run, blocks of a whole stretch
+@pytest.mark.parametrize("d,k,bits,block,weighted", [(4104, 2064, 3, 16, True), (4104, 2064, 8, 16, False), (2061, 4256, 2, 32, True),
+                                                     (2061, 4288, 4, 64, False), (4104, 2176, 4, 128, True), (4104, 2176, 8, 128, False)])
+def test_quantize_pass_walks_over_bands(env, oracle, d, k, bits, block, weighted):
+    torch, lq = env
+    w = gen.weight_matrix(d, k, d + k + bits, 4, outlier_frac=0.004)
+    rw, cw = (gen.positive_weights(d, 5), gen.positive_weights(k, 6)) if weighted else (None, None)
+    fisher = dict(row_w=torch.from_numpy(rw).cuda(), col_w=torch.from_numpy(cw).cuda()) if weighted else {}
+    out = lq.decompose(torch.from_numpy(w).cuda(), 8, lq.config(bits, block, 16), 2, seed=3, want_dense=True, **fisher)
+    check_quantize_pass(oracle, w, out, oracle.config(bits, block, 16), rw, cw)
+
+
+def test_quantize_pass_walks_over_bands_of_a_batch(env):
+    """Six configurations of a ragged matrix at once, two steps of bands per workgroup, with and without error sums.  The first
+    iteration's errors are those of each by itself, with one step per workgroup, bit for bit (later ones come from products that
+    batches and single problems add up in different orders)."""
+    torch, lq = env
+    w = torch.from_numpy(gen.weight_matrix(1033, 2064, 71, 8, outlier_frac=0.004)).cuda()
+    cfgs = [lq.config(b, 16, s) for b, s in ((2, 16), (3, 256), (8, 16), (4, 64), (3, 16), (8, 256))]
+    params = lq.SvdParams(streams=1)
+    e, _, trace = lq.error_table(w, 8, cfgs, 3, seed=5, params=params, want_trace=True)
+    assert np.array_equal(e, lq.error_table(w, 8, cfgs, 3, seed=5, params=params)[0])
+    for c, row in zip(cfgs, trace):
+        single = lq.decompose(w, 8, c, 3, seed=5)["trace"]
+        assert row[0] == single[0] and np.allclose(row, single, rtol=1e-4, atol=0)
 
 
 def test_decompose_weighted(env, oracle):
