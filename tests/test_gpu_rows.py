@@ -38,7 +38,7 @@ def test_rows_match_oracle(oracle, m, d, k, cfg, rank):
         assert np.max(np.abs(y - ref) - tol * scale) <= 0, (precision, np.max(np.abs(y - ref) / scale))
 
 
-# (m, d, k, block) with three steps per wavefront: an odd number of 64 columns and one, two and three row tiles, blocks of a
+# (m, d, k, block) with three steps for one wavefront and two for the others: an odd number of 64 columns and one, two and three row tiles, blocks of a
 # tile's columns and more
 @pytest.mark.parametrize("m,d,k,block", [(9, 544, 16448, 64), (24, 544, 16448, 64), (40, 544, 16512, 128), (128, 544, 8256, 64), (17, 544, 16384, 1024)])
 @pytest.mark.parametrize("bits", [2, 3, 4, 8])
@@ -46,9 +46,14 @@ def test_rows_with_scales_in_x(oracle, m, d, k, block, bits):
     test_rows_match_oracle(oracle, m, d, k, (bits, block, 16), 33)
 
 
-def test_rows_shares_that_end_inside_a_tile(oracle):
-    """The next tile's first step is then asked for before this one's sums."""
-    test_rows_match_oracle(oracle, 48, 4096, 11072, (3, 64, 256), 33)
+# Shares that end inside a tile: the next tile's first step is then asked for before this one's sums.  33 steps to a tile and 34 to
+# a share: every wavefront has four or more.
+@pytest.mark.parametrize("m,d,k,cfg", [
+    (48, 4096, 11072, (3, 64, 256)), (60, 1056, 16448, (8, 64, 16)), (60, 1056, 16512, (4, 128, 16)), (128, 1056, 11008, (3, 128, 16)),
+    (128, 1056, 11072, (2, 64, 16)),
+])
+def test_rows_shares_that_end_inside_a_tile(oracle, m, d, k, cfg):
+    test_rows_match_oracle(oracle, m, d, k, cfg, 33)
 
 
 @pytest.mark.parametrize("bits,block", [(3, 64), (4, 128)])
@@ -92,8 +97,8 @@ def test_rows_bf16_x_is_not_rounded(oracle, m, d, k, block, bits):
         assert np.max(np.abs(y - ref) - bound * scale) <= 0, (precision, np.max(np.abs(y - ref)[scale > 0] / scale[scale > 0]))
 
 
-@pytest.mark.parametrize("m", [12, 20, 48])
-@pytest.mark.parametrize("bits,block", [(2, 64), (3, 64), (4, 64), (8, 64), (3, 128), (4, 128), (8, 128)])
+@pytest.mark.parametrize("m,bits,block", [(12, 2, 64), (12, 3, 64), (20, 4, 64), (20, 8, 64), (48, 3, 64), (12, 4, 128), (20, 3, 128),
+                                          (48, 4, 128), (48, 8, 128)])
 def test_rows_scale_times_x_past_the_largest_float(oracle, m, bits, block):
     """3e38 times a block's largest weight of 4 overflows, times its other weights (code 0, or small) it does not: columns whose
     result fits are as close to the oracle's as any other, the rest are infinite.  A row with an infinite element is not finite
