@@ -14,15 +14,13 @@
 // - Otherwise, and where two_scales_ahead says so: extract, look up, scale and split every weight into two bf16 (one): three
 //   products (one).
 // Per wavefront and step of 4096 x 11008 at 24 rows the loop has 349 vector instructions in the first form and 490 in the second; what
-// is left is latency: two
-// wavefronts per SIMD, loads one step ahead, and the first fetch (behind the first segment: asked for with that one's last
-// step) and last sum of each workgroup.  Whole calls, NF4 64/256, rank 64, precision 0, second form -> first (us): 4096 x 11008 at 9
-// rows 27.5 -> 21.5, 24 rows 29.2 -> 28.5; 8192 x 8192, 16 rows 34.5 -> 25.0; 11008 x 4096, 3 bits, 16 rows 41.3 -> 23.0.  With two parts
-// of X times the scale (four products) 24 rows took 26.2, but rows of X that are exact in bf16, which the second form does not
-// round, came out with an error of 3.2e-6 instead of 2.5e-6 (precision 1: 1.9e-3 instead of 1.7e-3); now 0.7e-6 (4 bits), 1.7e-6 (8)
-// and 1.1e-3, 1.2e-3, and for any fp32 X the same instead of 4.4e-6 and 2.3e-3.  What did not help: a wavefront per 64 columns and
-// four per step, two steps in flight (twice the loads of X: 29 us at 24 rows, 42 at 48, against 27 and 37 then), one copy of the
-// table (bank conflicts: 29.4).
+// is left is latency: two wavefronts per SIMD, loads one step ahead, and the first fetch (behind the first segment: asked for with
+// that one's last step) and last sum of each workgroup.  scales_in_x_ahead has both sides' times.  With two parts of X times the scale
+// (four products) 24 rows took 26.2 us instead of 28.8, but rows of X that are exact in bf16, which the second form does not round,
+// came out with an error of 3.2e-6 instead of 2.5e-6 (precision 1: 1.9e-3 instead of 1.7e-3); now 0.7e-6 (4 bits), 1.7e-6 (8) and
+// 1.1e-3, 1.2e-3, and for any fp32 X the same instead of 4.4e-6 and 2.3e-3.  (X times the scale below 2^-112 loses bits: 1e-5 where
+// results are 1e-34.)  What did not help: a wavefront per 64 columns and four per step, two steps in flight (twice the loads of X: 29 us
+// at 24 rows, 42 at 48, against 27 and 37 then), one copy of the table (bank conflicts: 29.4).
 // Second form, whole call on 4096 x 11008, NF4, rank 64 (4096 x 4096): 24 rows 79 -> 32 us (45 -> 20), 64 rows 84 -> 50 us (47 -> 27),
 // 128 rows 94 -> 85 us (52 -> 42) against the kernel for large m, whose steps take 2 us whatever they multiply (256-row tiles
 // of X staged through LDS, a barrier per step).  At 192 rows that kernel is ahead on the wide matrix (95 against 111 us)
@@ -566,28 +564,40 @@ size_t qrows_part_floats(int64_t m, int64_t K, int64_t N, int rank) {
   return (size_t)qrows_shares(m, K, N, rank).segments * (size_t)m * (size_t)(N + rank);
 }
 
-// Two scales per row of a tile: whether the form with the scales in X is ahead.  It keeps X times both scales, which with three row
-// tiles leaves 4 and 8 bits too few registers to have loads in flight, and 3-bit codes take a shift more to come apart (second form
-// -> first, us, 4096 x 11008: 48 rows, precision 0 / 1: 2 bits 39.4 / 31.1 -> 38.9 / 31.4, 3 bits 48.7 / 43.4 -> 43.8 / 35.0, 4 bits
-// 39.6 / 32.8 -> 42.7 / 31.5, 8 bits 40.8 / 33.5 -> 44.0 / 36.1; 24 rows: 2 bits 29.1 / 24.6 -> 27.6 / 22.9, 3 bits 31.3 / 26.3 ->
-// 31.1 / 26.8, 4 bits 29.2 / 23.9 -> 28.5 / 23.5, 8 bits 30.6 / 26.6 -> 30.5 / 25.7; one row tile: 5 to 60 % ahead for every width).
-template <int BITS, int RT, bool SPLIT>
-constexpr bool two_scales_ahead = RT == 1 || (RT == 2 ? BITS != 3 || SPLIT : BITS < 4 || (BITS == 4 && !SPLIT));
+// Where the form with the scales in X is ahead: figures of whole calls, us, 4096 x 11008 (44 steps per workgroup), rank 64, second form
+// -> first, precision 0 / 1.
+//              2 bits                    3 bits                    4 bits                    8 bits
+//   blocks of 64 (two scales per row of a tile; with three row tiles X times both takes the registers that loads in flight need)
+//   12 rows    26.6->20.9 / 20.1->18.1   28.8->23.7 / 21.5->22.1   27.1->21.7 / 20.2->19.3   28.1->23.5 / 22.0->20.9
+//   24 rows    29.2->27.9 / 24.6->23.0   30.9->32.0 / 26.0->27.2   29.3->28.8 / 24.1->24.1   30.9->31.2 / 26.5->26.0
+//   48 rows    39.8->40.4 / 31.3->32.9   41.0->44.0 / 33.2->35.5   39.2->44.1 / 31.5->32.6   41.1->45.6 / 34.0->37.8
+//   blocks of 128 and more
+//   12 rows    26.5->19.5 / 20.1->17.2   28.5->21.2 / 21.3->19.6   26.7->20.2 / 20.0->18.4   28.0->22.6 / 21.7->20.2
+//   24 rows    29.1->25.6 / 24.5->22.0   30.6->28.1 / 25.9->24.6   28.9->26.9 / 24.0->22.9   30.6->28.8 / 26.3->24.7
+//   48 rows    39.3->35.2 / 31.2->29.6   41.1->37.9 / 32.9->33.0   39.2->37.3 / 31.3->31.0   41.0->40.5 / 33.7->32.5
+template <int BITS, int RT, bool SPLIT, int NBLK>
+constexpr bool scales_in_x_ahead = RT == 1   ? NBLK == 1 || BITS != 3 || SPLIT
+                                   : RT == 2 ? NBLK == 1 || BITS == 2 || BITS == 4 || (BITS == 8 && !SPLIT)
+                                             : NBLK == 1 && (BITS == 2 || (BITS == 8) != SPLIT);
+// A workgroup of that form makes its table first (4 KB for 2 bits, 16 for 3, 64 for 4, 32 for 8): the steps of all wavefronts that
+// do not pay it back (24 rows, 4 bits: 19 steps, 4096 x 4096, blocks of 64 16.8 -> 17.6, of 128 16.8 -> 16.6; 27 steps, 5120 x 5120,
+// 19.6 -> 20.1 and 19.6 -> 18.6; 2 bits at 19 steps 16.6 -> 16.6 and 16.8 -> 15.7).
+template <int BITS, int RT, int NBLK>
+constexpr int scaled_rounds = RT == 1 || BITS == 2 ? 2 : NBLK == 2 ? 5 : RT == 2 ? 3 : 4;
 
+template <int BITS, int RT, bool SPLIT, int NBLK>
+static bool launch_scaled(const QrArgs& a, dim3 grid, hipStream_t st) {
+  if constexpr (scales_in_x_ahead<BITS, RT, SPLIT, NBLK>)
+    if (a.per_wg > scaled_rounds<BITS, RT, NBLK> * QR_WAVES) {
+      hipLaunchKernelGGL((qrows_kernel<BITS, RT, SPLIT, NBLK>), grid, dim3(64 * QR_WAVES), 0, st, a);
+      return true;
+    }
+  return false;
+}
 template <int BITS, int RT, bool SPLIT>
 static void launch_blocks(const QrArgs& a, dim3 grid, hipStream_t st) {
-  // A workgroup of the form with the scales in X makes the table first, 64 KB for 4 bits, which one or two steps per wavefront do
-  // not pay back (24 rows: 2048 x 2048, one step 12.9 against 13.2 us; 4096 x 4096, three steps 17.5 against 17.3).
-  const bool scaled = a.per_wg > 2 * QR_WAVES;
-  if (scaled && a.block_shift >= 7) {
-    hipLaunchKernelGGL((qrows_kernel<BITS, RT, SPLIT, 1>), grid, dim3(64 * QR_WAVES), 0, st, a);
-    return;
-  }
-  if constexpr (two_scales_ahead<BITS, RT, SPLIT>)
-    if (scaled && a.block_shift == 6) {
-      hipLaunchKernelGGL((qrows_kernel<BITS, RT, SPLIT, 2>), grid, dim3(64 * QR_WAVES), 0, st, a);
-      return;
-    }
+  if (a.block_shift >= 7 && launch_scaled<BITS, RT, SPLIT, 1>(a, grid, st)) return;
+  if (a.block_shift == 6 && launch_scaled<BITS, RT, SPLIT, 2>(a, grid, st)) return;
   hipLaunchKernelGGL((qrows_kernel<BITS, RT, SPLIT, 0>), grid, dim3(64 * QR_WAVES), 0, st, a);
 }
 template <int BITS, bool SPLIT>
