@@ -73,7 +73,7 @@ static MatmulPlan plan_matmul(Route route, int64_t m, int64_t d, int64_t k, int 
   p.r32 = up32(rank);
   p.rows_pad = padded_rows(m);
   p.fused = rank > 0 && rank <= SPLIT_PROJECT_MAX_RANK;
-  p.xh = (size_t)p.rows_pad * (size_t)d;
+  p.xh = (size_t)p.rows_pad * (size_t)(route == ROUTE_PLANE ? plane_pitch(d) : d);
   p.xl = route == ROUTE_PLANE && p.fused ? 0 : p.xh;   // split_project_kernel leaves it alone for bf16 operands
   p.t_floats = rank > 0 && !p.fused ? (size_t)m * (size_t)p.r32 : 0;
   p.t_plane = rank > 0 ? (size_t)p.rows_pad * (size_t)p.r32 : 0;
@@ -82,7 +82,7 @@ static MatmulPlan plan_matmul(Route route, int64_t m, int64_t d, int64_t k, int 
   const size_t p2 = qmatmul_part_floats(m, k, (int)(d / 32 + p.r32 / 32));
   p.part_floats = p1 > p2 ? p1 : p2;
   if (route == ROUTE_PLANE) {
-    p.w_plane = weight_plane_elems(d, k);
+    p.w_plane = weight_plane_elems(plane_pitch(d), k);
     p.l_plane = rank > 0 ? weight_plane_elems(p.r32, k) : 0;
   } else {
     p.scale_floats = (size_t)(d * k / 16);          // one scale per block, block size at least 16
@@ -199,26 +199,26 @@ int lq_matmul(const float* X, int64_t m, int64_t d, int64_t k, const uint8_t* co
   if (route == ROUTE_PLANE) {
     ProjectSum t{};
     if (p.fused)
-      LQ_TRY(launch_split_project(X, m, d, d, p.rows_pad, L1, rank, precision, xh, xl, part, p.part_floats, th, tl,
+      LQ_TRY(launch_split_project(X, m, d, d, p.rows_pad, L1, rank, precision, plane_pitch(d), xh, xl, part, p.part_floats, th, tl,
                                   (int)p.r32, BlockScales{}, &t, st));
     else
-      LQ_TRY(launch_split_planes(X, m, d, d, p.rows_pad, xh, xl, st));
+      LQ_TRY(launch_split_planes(X, m, d, d, p.rows_pad, plane_pitch(d), xh, xl, st));
     const MvWeights q{codes_packed, scale_idx, v, c.bits, c.block, c.scale_block, scale_levels(c)};
     return launch_plane_product(q, xh, d, th, (int)p.r32, L2, rank, m, p.rows_pad, k, wt, lt, Y, k, part, p.part_floats, t, st);
   }
   QmmPart none{};
   if (p.fused) {    // planes of X and of T = X L1 from one pass over X, the block scales of Q in the same launch
     const BlockScales bs{scale_idx, v, d * k / c.block, c.scale_block, scale_levels(c), bscale};
-    LQ_TRY(launch_split_project(X, m, d, d, p.rows_pad, L1, rank, precision, xh, xl, part, p.part_floats, th, tl,
+    LQ_TRY(launch_split_project(X, m, d, d, p.rows_pad, L1, rank, precision, d, xh, xl, part, p.part_floats, th, tl,
                                 (int)p.r32, bs, nullptr, st));
   } else {
     LQ_TRY(launch_block_scales(scale_idx, v, d * k / c.block, c.scale_block, scale_levels(c), bscale, st));
-    LQ_TRY(launch_split_planes(X, m, d, d, p.rows_pad, xh, xl, st));
+    LQ_TRY(launch_split_planes(X, m, d, d, p.rows_pad, d, xh, xl, st));
   }
   if (rank > 0 && !p.fused) {   // T = X L1, m x r32 with zero columns beyond r, then its planes
     DensePart xl1{xh, xl, d, L1, rank, d, rank};
     LQ_TRY(launch_qmatmul(none, xl1, m, p.rows_pad, p.r32, T, p.r32, part, p.part_floats, precision, st));
-    LQ_TRY(launch_split_planes(T, m, p.r32, p.r32, p.rows_pad, th, tl, st));
+    LQ_TRY(launch_split_planes(T, m, p.r32, p.r32, p.rows_pad, p.r32, th, tl, st));
   }
   QmmPart q{xh, xl, d, codes_packed, bscale, c.bits, c.block};
   DensePart tl2{th, tl, rank > 0 ? p.r32 : 0, L2, k, rank, k};

@@ -69,9 +69,10 @@ __device__ __forceinline__ void split4(const float (&x)[4], bf16x4& hi, bf16x4& 
   lo = __builtin_convertvector(f - __builtin_convertvector(hi, floatx4), bf16x4);
 }
 
-// X (rows x K fp32, leading dimension ldx) -> bf16 planes hi, lo (rows_pad x K each); rows beyond `rows` are zero.
+// X (rows x K fp32, leading dimension ldx) -> bf16 planes hi, lo (rows_pad x K each, leading dimension pitch); rows beyond
+// `rows` are zero.
 __global__ __launch_bounds__(256) void split_planes_kernel(const float* __restrict__ X, int64_t rows, int64_t K,
-                                                           int64_t ldx, int64_t rows_pad, uint16_t* __restrict__ hi,
+                                                           int64_t ldx, int64_t rows_pad, int64_t pitch, uint16_t* __restrict__ hi,
                                                            uint16_t* __restrict__ lo) {
   const int64_t kq = K >> 2, total = rows_pad * kq;
   for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < total; i += (int64_t)gridDim.x * 256) {
@@ -83,18 +84,18 @@ __global__ __launch_bounds__(256) void split_planes_kernel(const float* __restri
     }
     bf16x4 h, l;
     split4(f, h, l);
-    *reinterpret_cast<bf16x4*>(hi + row * K + c4) = h;
-    *reinterpret_cast<bf16x4*>(lo + row * K + c4) = l;
+    *reinterpret_cast<bf16x4*>(hi + row * pitch + c4) = h;
+    *reinterpret_cast<bf16x4*>(lo + row * pitch + c4) = l;
   }
 }
 
-int launch_split_planes(const float* X, int64_t rows, int64_t K, int64_t ldx, int64_t rows_pad, uint16_t* hi,
+int launch_split_planes(const float* X, int64_t rows, int64_t K, int64_t ldx, int64_t rows_pad, int64_t pitch, uint16_t* hi,
                         uint16_t* lo, hipStream_t st) {
-  if (rows <= 0 || K <= 0 || (K & 3) != 0 || (ldx & 3) != 0 || rows_pad < rows) return LQ_ERR_SHAPE;
+  if (rows <= 0 || K <= 0 || (K & 3) != 0 || (ldx & 3) != 0 || rows_pad < rows || pitch < K || (pitch & 3) != 0) return LQ_ERR_SHAPE;
   const int64_t total = rows_pad * (K >> 2);
   const int64_t nwg = std::min<int64_t>((total + 255) / 256, 1 << 16);
   prof::Scope ps(prof::MISC, st, 4.0 * (double)rows * (double)K + 4.0 * (double)rows_pad * (double)K);
-  hipLaunchKernelGGL(split_planes_kernel, dim3((unsigned)nwg), dim3(256), 0, st, X, rows, K, ldx, rows_pad, hi, lo);
+  hipLaunchKernelGGL(split_planes_kernel, dim3((unsigned)nwg), dim3(256), 0, st, X, rows, K, ldx, rows_pad, pitch, hi, lo);
   LQ_HIP_TRY(hipGetLastError());
   return LQ_OK;
 }

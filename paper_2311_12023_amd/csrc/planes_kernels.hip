@@ -30,7 +30,7 @@ struct WpArgs {
   const uint8_t* codes; const uint8_t* sidx; const float* v;
   const float* L2; int rank, Kd;
   uint16_t* Wt; uint16_t* Lt;
-  int64_t K, N;
+  int64_t K, N, pitch;               // elements from row to row of Wt
   int block_shift, group_shift, levels;
   float inv_levels;
   const DevTables* tables;
@@ -88,9 +88,9 @@ __global__ __launch_bounds__(256) void weight_plane_kernel(WpArgs a) {
     s_w[16 * run + j][pair] = __builtin_bit_cast(uint32_t, __builtin_convertvector(floatx2{w[0][j], w[1][j]}, bf16x2));
   __syncthreads();
   uint32_t* out = reinterpret_cast<uint32_t*>(low_rank ? a.Lt : a.Wt);
-  const int64_t pitch = (low_rank ? a.Kd : a.K) / 2, at = low_rank ? 0 : k0 / 2;      // in pairs
+  const int64_t depth = (low_rank ? a.Kd : a.K) / 2, pitch = (low_rank ? a.Kd : a.pitch) / 2, at = low_rank ? 0 : k0 / 2;   // in pairs
   const int p = tid & 31;
-  if (at + p < pitch) {
+  if (at + p < depth) {
     for (int n = tid >> 5; n < WP_N; n += 8) {
       const int64_t row = (int64_t)blockIdx.x * WP_N + n;
       if (row < a.N) out[row * pitch + at + p] = s_w[n][p];
@@ -115,8 +115,8 @@ constexpr int PG_T = 256, PG_STAGES = 4, PG_THREADS = 512;
 constexpr uint32_t PG_TILE = PG_T * 64, PG_STAGE = 2 * PG_TILE;            // bytes
 
 struct PgArgs {
-  const uint16_t* A; const uint16_t* B; int64_t K;
-  const uint16_t* A2; const uint16_t* B2; int64_t K2;
+  const uint16_t* A; const uint16_t* B; int64_t pitch;      // elements from row to row
+  const uint16_t* A2; const uint16_t* B2; int64_t pitch2;
   float* Y; int64_t ldy;             // splits == 1: m x N; else range s at Y + s * m * ldy
   int64_t m, N;
   int nsteps1, nsteps, splits, tiles_m, tiles_n;
@@ -140,7 +140,7 @@ __global__ __launch_bounds__(PG_THREADS) void plane_gemm_kernel(PgArgs a) {
 
   // this wavefront's transfers: rows 16 wave .. + 15 and 128 further of both tiles; lane l brings unit l % 4 ^ swizzle of row l / 4
   const int lrow = lane >> 2, unit = (lane & 3) ^ ((lrow >> 2) & 3);
-  const uint32_t voff1 = (uint32_t)(lrow * a.K * 2 + unit * 16), voff2 = (uint32_t)(lrow * a.K2 * 2 + unit * 16);
+  const uint32_t voff1 = (uint32_t)(lrow * a.pitch * 2 + unit * 16), voff2 = (uint32_t)(lrow * a.pitch2 * 2 + unit * 16);
   const int64_t arow = (int64_t)tm * PG_T + 16 * wave, brow = (int64_t)tn * PG_T + 16 * wave;
   // Where the next step's transfers read: this wavefront's rows of the present pair of planes at the present reduction index.
   const uint16_t *pa, *pb;
@@ -148,10 +148,10 @@ __global__ __launch_bounds__(PG_THREADS) void plane_gemm_kernel(PgArgs a) {
   uint32_t voff;
   int next = s0;                                 // the step that these belong to
   auto plane_pair = [&](bool second, int64_t k) {
-    const int64_t K = second ? a.K2 : a.K;
-    pa = (second ? a.A2 : a.A) + arow * K + k;
-    pb = (second ? a.B2 : a.B) + brow * K + k;
-    rows128 = 128 * K;
+    const int64_t pitch = second ? a.pitch2 : a.pitch;
+    pa = (second ? a.A2 : a.A) + arow * pitch + k;
+    pb = (second ? a.B2 : a.B) + brow * pitch + k;
+    rows128 = 128 * pitch;
     voff = second ? voff2 : voff1;
   };
   plane_pair(s0 >= a.nsteps1, 32 * (int64_t)(s0 >= a.nsteps1 ? s0 - a.nsteps1 : s0));
@@ -242,7 +242,7 @@ __global__ __launch_bounds__(PG_THREADS) void plane_gemm_kernel(PgArgs a) {
   }
 }
 
-size_t weight_plane_elems(int64_t K, int64_t N) { return (size_t)((N + PG_T - 1) / PG_T * PG_T) * (size_t)K; }
+size_t weight_plane_elems(int64_t pitch, int64_t N) { return (size_t)((N + PG_T - 1) / PG_T * PG_T) * (size_t)pitch; }
 
 template <int BITS>
 static void launch_weight_plane(const WpArgs& a, dim3 grid, hipStream_t st) {
@@ -259,7 +259,7 @@ int launch_plane_product(const MvWeights& q, const uint16_t* Xh, int64_t K, cons
   if (q.block < 16 || (q.block & (q.block - 1)) || q.scale_block < 1 || (q.scale_block & (q.scale_block - 1)) || N % q.block)
     return LQ_ERR_CONFIG;
   WpArgs w{};
-  w.codes = q.codes; w.sidx = q.sidx; w.v = q.v; w.L2 = L2; w.rank = rank; w.Kd = Kd; w.Wt = Wt; w.Lt = Lt; w.K = K; w.N = N;
+  w.codes = q.codes; w.sidx = q.sidx; w.v = q.v; w.L2 = L2; w.rank = rank; w.Kd = Kd; w.Wt = Wt; w.Lt = Lt; w.K = K; w.N = N; w.pitch = plane_pitch(K);
   w.block_shift = __builtin_ctz((unsigned)q.block);
   w.group_shift = __builtin_ctz((unsigned)q.scale_block);
   w.levels = q.levels;
@@ -283,10 +283,10 @@ int launch_plane_product(const MvWeights& q, const uint16_t* Xh, int64_t K, cons
     LQ_HIP_TRY(hipGetLastError());
   }
   PgArgs a{};
-  a.A = Xh; a.B = Wt; a.K = K; a.A2 = Th; a.B2 = Lt; a.K2 = rank > 0 ? Kd : 0;
+  a.A = Xh; a.B = Wt; a.pitch = plane_pitch(K); a.A2 = Th; a.B2 = Lt; a.pitch2 = rank > 0 ? Kd : 0;
   a.m = m; a.N = N;
   a.nsteps1 = (int)(K / 32);
-  a.nsteps = a.nsteps1 + (int)(a.K2 / 32);
+  a.nsteps = a.nsteps1 + (int)(a.pitch2 / 32);
   a.tiles_m = (int)((m + PG_T - 1) / PG_T);
   a.tiles_n = (int)((N + PG_T - 1) / PG_T);
   a.splits = qmatmul_splits(m, N, a.nsteps);
@@ -299,7 +299,7 @@ int launch_plane_product(const MvWeights& q, const uint16_t* Xh, int64_t K, cons
   static LdsLimit limit;
   LQ_TRY(limit.raise(reinterpret_cast<const void*>(plane_gemm_kernel), lds));
   {
-    prof::Scope ps(prof::PLANE_GEMM, st, 2.0 * (double)m * (double)N * (double)(K + a.K2));
+    prof::Scope ps(prof::PLANE_GEMM, st, 2.0 * (double)m * (double)N * (double)(K + a.pitch2));
     hipLaunchKernelGGL(plane_gemm_kernel, dim3((unsigned)((tiles * a.splits + 7) / 8 * 8)), dim3(PG_THREADS), lds, st, a);
     LQ_HIP_TRY(hipGetLastError());
   }

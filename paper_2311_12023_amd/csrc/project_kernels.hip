@@ -34,7 +34,7 @@ struct XpArgs {
   const float* X; int64_t m, K, ldx;         // rows beyond m read as zero
   const float* L1; int rank;                 // K x rank, leading dimension rank
   int l1_vec;                                // rank % 4 == 0 and L1 16-byte aligned: whole float4 loads
-  uint16_t* xh; uint16_t* xl;                // planes, rows_pad x K
+  uint16_t* xh; uint16_t* xl; int64_t pitch; // planes, rows_pad x K, leading dimension pitch
   float* part; int64_t rows_pad;             // splits x rows_pad x 64
   int nsteps, splits;
   // the reconstructed block scales of Q ride along in extra grid rows (nblocks == 0: none)
@@ -106,8 +106,8 @@ __global__ __launch_bounds__(XP_THREADS, 4) void split_project_kernel(XpArgs a) 
       *reinterpret_cast<bf16x4*>(&s_a[0][row * XP_PITCH + 4 * (tid & 15)]) = hi;
       if constexpr (SPLIT) *reinterpret_cast<bf16x4*>(&s_a[1][row * XP_PITCH + 4 * (tid & 15)]) = lo;
       if (kx < a.K) {                        // rows up to rows_pad are written: zero beyond m
-        *reinterpret_cast<bf16x4*>(a.xh + (row0 + row) * a.K + kx) = hi;
-        if constexpr (SPLIT) *reinterpret_cast<bf16x4*>(a.xl + (row0 + row) * a.K + kx) = lo;
+        *reinterpret_cast<bf16x4*>(a.xh + (row0 + row) * a.pitch + kx) = hi;
+        if constexpr (SPLIT) *reinterpret_cast<bf16x4*>(a.xl + (row0 + row) * a.pitch + kx) = lo;
       }
     }
 #pragma unroll
@@ -158,16 +158,18 @@ size_t split_project_part_floats(int64_t rows_pad, int64_t K) {
 }
 
 int launch_split_project(const float* X, int64_t m, int64_t K, int64_t ldx, int64_t rows_pad, const float* L1, int rank,
-                         int precision, uint16_t* xh, uint16_t* xl, float* part, size_t part_floats, uint16_t* th,
+                         int precision, int64_t pitch, uint16_t* xh, uint16_t* xl, float* part, size_t part_floats, uint16_t* th,
                          uint16_t* tl, int Kd, const BlockScales& bs, ProjectSum* later, hipStream_t st) {
-  if (m <= 0 || K <= 0 || (K & 3) != 0 || (ldx & 3) != 0 || rows_pad < m || (rows_pad % XP_ROWS) != 0) return LQ_ERR_SHAPE;
+  if (m <= 0 || K <= 0 || (K & 3) != 0 || (ldx & 3) != 0 || rows_pad < m || (rows_pad % XP_ROWS) != 0 || pitch < K ||
+      (pitch & 3) != 0)
+    return LQ_ERR_SHAPE;
   if (rank < 1 || rank > SPLIT_PROJECT_MAX_RANK || (Kd != 32 && Kd != 64) || Kd < rank) return LQ_ERR_RANK;
   if (((uintptr_t)X & 15) != 0) return LQ_ERR_ARG;
   XpArgs a{};
   a.X = X; a.m = m; a.K = K; a.ldx = ldx;
   a.L1 = L1; a.rank = rank;
   a.l1_vec = ((rank & 3) == 0 && ((uintptr_t)L1 & 15) == 0) ? 1 : 0;
-  a.xh = xh; a.xl = xl; a.part = part; a.rows_pad = rows_pad;
+  a.xh = xh; a.xl = xl; a.pitch = pitch; a.part = part; a.rows_pad = rows_pad;
   a.nsteps = (int)((K + XP_BK - 1) / XP_BK);
   a.splits = split_project_splits(rows_pad, K);
   if (part_floats < (size_t)a.splits * (size_t)rows_pad * XP_COLS) return LQ_ERR_WORKSPACE;
