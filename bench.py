@@ -321,7 +321,8 @@ def matmul_roofline(prof: dict, precision: int, traffic: float | None) -> dict:
                              "unit": "TFLOP/s", "frac": ach / PEAK_BF16_MFMA_TFLOPS,
                              "traffic": traffic if name == "qmatmul_kernel" else None, "launches": launches,
                              "avg_us": 1e3 * kms / launches, "algorithmic_tflops": work / (kms * 1e-3) / 1e12},
-                "roofline_note": "achieved counts the bf16 MFMA flops the kernel executes (3 per product at precision 0) "
+                "roofline_note": "achieved counts bf16 MFMA flops, 3 per product at precision 0 and 1 at precision 1 (what the "
+                                 "kernels execute; qrows_kernel executes 5 and 2 where it takes scales into X), "
                                  "against the dense bf16 peak; algorithmic_tflops counts each product once.  " + timing,
                 "kernels": kernels}
     if "qmatvec_kernel" in prof:                             # few tokens: bound by reading the weights once

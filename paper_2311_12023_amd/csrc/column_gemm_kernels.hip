@@ -297,8 +297,10 @@ bool column_gemm_supported(int l) { return l % 32 == 0 && l >= 32 && l <= 128; }
 
 // Width of the tiles (16 nt columns) and number of ranges by what a launch is estimated to take, in us: per round of 256
 // workgroups what each reads (X out of L2 at 88 bytes per ns, A at 24, the share of one compute unit when all of them stream),
-// and with more than one range the partial sums, written and read at 2.5 TB/s, and 5 us for whoever adds them.  Compared with
-// all other choices on 84 shapes from 512 x 512 to 8192 x 8192 (l = 64, 96, 128): within 10 % of the fastest of them everywhere, 5 % in most.
+// and with more than one range the partial sums, written and read at 2.5 TB/s, and 5 us for whoever adds them.  The rates were fitted
+// when loads went out in one burst per step; with loads and products alternating the choice is still within 5 % of the fastest of
+// all others for 77 of 84 products from 512 x 512 to 8192 x 8192 (l = 64, 96, 128) and within 10 % for 83 (3072 x 3072, l = 64, X A: 19.9
+// against 15.5 us with four ranges).
 ColumnSplit column_gemm_split(int l, int64_t big, int64_t K) {
   const int64_t ns = (K + COL_BK - 1) / COL_BK;
   ColumnSplit best{1, 1};

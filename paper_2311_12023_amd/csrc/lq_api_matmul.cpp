@@ -15,18 +15,21 @@ static int64_t up32(int64_t x) { return (x + 31) & ~(int64_t)31; }
 constexpr int64_t SMALL_M = QMATVEC_MAX_ROWS;
 constexpr int SMALL_RANK = 512;
 // Above this many rows precision 1 decodes the weights into a bf16 plane first (see planes_kernels.hip for both sides).
-// On small weights without a low-rank part of more than 32 the launch more costs what it gains up to 1024 rows (1024 x 1024, rank
-// 16, 640 rows: 37.8 us against 34.7 without a plane; rank 64: 37.3 against 38.7; 1500 rows, rank 16: level).
+// On small weights without a low-rank part of more than 32 the launch more cost what it gained up to 1024 rows when the line was
+// drawn.  Since the launch that adds T's partial tiles is gone it gains a little there too (1024 x 1024, 640 rows, with a plane
+// against without: rank 0 32.4 and 29.2 us, rank 16 34.8 and 35.1, rank 32 34.7 and 37.3; 1024 rows, rank 16: 34.9 and 38.3).
 constexpr int64_t PLANE_M = 512, PLANE_M_SMALL = 1024;
 
 // Between 9 and 128 rows: whether qrows_kernel is ahead of qmatmul_kernel, whose time is that of 256 rows whatever m is.
 // qrows_kernel decodes the weights once for every group of up to 48 rows, so it loses on large weights where it has three
-// groups (97 rows and more; qrows against qmatmul in us at 112 rows, whole calls, precision 0 / 1):
-//   3-bit codes, the dearest to decode        4096 x 11008, rank 64   112 / 89 against 98 / 75    (4096^2: 56 / 44 against 57 / 47)
-//   rows of L1 that cannot be read as float4  8192^2, rank 65         139 / 140 against 141 / 99
-//   T L2, on the vector ALU, for high ranks   4096 x 11008, rank 512  155 / 133 against 132 / 112  (11008 x 4096: 112 / 88 against 163 / 139)
-//   bf16 operands and the largest weights     8192^2, rank 64         - / 89 against - / 83
-// and elsewhere wins (4096 x 11008, 4 bits, rank 64: 82 / 61 against 86 / 67; rank 256: 110 / 89 against 125 / 104).
+// groups (97 rows and more; qrows against qmatmul in us at 112 rows, whole calls, precision 0 / 1, blocks of 64, with 32 within 4 %
+// but for the largest):
+//   rows of L1 that cannot be read as float4  8192^2, rank 65         135 / 139 against 142 / 98
+//   T L2, on the vector ALU, for high ranks   4096 x 11008, rank 512  143 / 120 against 134 / 111  (11008 x 4096: 109 / 85 against 164 / 136)
+//   bf16 operands and the largest weights     8192^2, rank 64         - / 83 against - / 80        (blocks of 32: 94 against 81)
+// and elsewhere wins (4096 x 11008, 4 bits, rank 64: 79 / 58 against 88 / 67; rank 256: 103 / 81 against 124 / 103).  3-bit codes were
+// 112 / 89 against 98 / 75 (4096 x 11008, rank 64) while each of their loads was waited for and are kept from it from 97 rows on; they
+// are 87 / 64 against 96 / 71 now (4096^2 42 / 32 against 58 / 46), so that line could be taken out.
 static bool rows_kernel_ahead(int64_t m, int64_t d, int64_t k, int rank, int bits, int precision) {
   const int64_t weights = d * k;
   const bool wide = k > d, odd = rank % 4 != 0;

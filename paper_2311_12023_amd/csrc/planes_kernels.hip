@@ -1,14 +1,13 @@
 // Forward product with a decomposed weight in bf16 for many rows of X (lq_matmul, precision 1):  Y = X Q + (X L1) L2  with
 // every operand rounded to bf16 and fp32 accumulation.  The weights are decoded once per call into a bf16 plane that the
 // product then reads like any other operand, where qmatmul_kernel decodes a weight again for every 256 rows of X: with one
-// MFMA per product that decode cannot hide behind the matrix pipe.  4096 rows, rank 64, whole call without and with a plane:
-// 4096 x 4096 213 -> 163 us (4 bits; 239 -> 163 with 3), 4096 x 11008 592 -> 419, 11008 x 4096 595 -> 414; 1024 rows, 4 bits 87 ->
-// 79, 197 -> 140, 168 -> 158.
-// The line is drawn above 512 rows: 513 rows, 4 bits, rank 64, with a plane 64, 137, 121 us (4096 x 4096, 4096 x 11008, 11008 x
-// 4096) against 72, 197, 138 without; 512 rows 65, 106, 110 against 66, 125, 110, but 8192 x 8192 146 against 132; 256 rows
-// 58, 80, 93 against 55, 74, 79.  Small weights: PLANE_M_SMALL in lq_api_matmul.cpp.  The product runs at 1.0 to 1.15 PFLOP/s
-// (120 us for 4096^3 in a trace, 60 % of its cycles in the matrix pipe, at a clock that has come down to 1.85 GHz by then; when it
-// took 156 us: 110 without the MFMAs, 140 without the transfers).
+// MFMA per product that decode cannot hide behind the matrix pipe.  Whole calls, 4 bits, rank 64, without and with a plane: 1500 rows
+// x 4096 x 4096 128 -> 92 us, 4096 x 11008 382 -> 229, 11008 x 4096 277 -> 200; 1024 rows 88 -> 75, 199 -> 127, 168 -> 151.
+// The line is drawn above 512 rows: 513 rows, with a plane 61, 117, 115 us (4096 x 4096, 4096 x 11008, 11008 x 4096) against 73,
+// 196, 137 without; 512 rows 61, 98, 107 against 67, 124, 109, but 8192 x 8192 140 against 133; 256 rows 56, 79, 87 against 56,
+// 75, 80 (8192 x 8192 115 against 94).  Small weights: PLANE_M_SMALL in lq_api_matmul.cpp.  The product runs at 1.05 to 1.15 PFLOP/s
+// (4096^3 with rank 64: 120 us in a short run, 131 to 133 call after call, at a clock that has come down to 1.8 GHz and 60 % of
+// the cycles in the matrix pipe; when it took 156 us: 110 without the MFMAs, 140 without the transfers).
 #include <algorithm>
 
 #include "dense_device.h"
@@ -108,7 +107,8 @@ __global__ __launch_bounds__(256) void weight_plane_kernel(WpArgs a) {
 // to spread over the L2's channels changed nothing).  What a wavefront does between its products keeps the matrix pipe waiting,
 // since the barrier brings all of them there at once: the loop is unrolled over the stages, so that their addresses are
 // constants, the transfers' addresses are carried along instead of worked out (77 -> 30 scalar instructions per step), and the
-// transfers go out between the products (4096 x 4096 x 4160 131 -> 120 us, the call 169 -> 162).  Rows are 64 bytes, unit u of a
+// transfers go out between the products (4096 x 4096 x 4160 131 -> 120 us, the call 169 -> 162; all four before the operand reads:
+// 2 to 4 % more, but less where the weights come from memory and rows begin inside a line, which they no longer do).  Rows are 64 bytes, unit u of a
 // row stored at u ^ ((row / 4) % 4): 16 lanes' reads of 128 bits fall into different banks (with (row / 2) % 4 into half of
 // them, twice the LDS cycles; 0.6 % of the call, in qmatmul_kernel 0.3 %).
 constexpr int PG_T = 256, PG_STAGES = 4, PG_THREADS = 512;
