@@ -7,16 +7,16 @@
 // halves on the way; only the sums are staged.  A workgroup owns 128 columns at a time; its eight wavefronts take
 // turns at the 32-deep reduction steps and their sums are added in order through LDS.  Every weight is turned into operands for at
 // most 48 rows, so that takes the time, not the products, and there are two forms of it:
-// - Blocks of 64 weights and more, where some wavefront has three steps or more.  The 64 or 128 columns of a row that a tile has in
+// - Blocks of 64 weights and more, where scales_in_x_ahead and scaled_rounds say so.  The 64 or 128 columns of a row that a tile has in
 //   a block share one scale, so X Q is the product of X, its columns times these scales, with values of the code book, whose bf16
 //   halves come from a table for two rows of Q at a time (QrTable).  A wavefront computes a step's scales one per lane and hands them
 //   out through LDS.  X times the scale goes in as three bf16 (precision 1: two): five products (two).
-// - Otherwise, and where two_scales_ahead says so: extract, look up, scale and split every weight into two bf16 (one): three
+// - Otherwise: extract, look up, scale and split every weight into two bf16 (one): three
 //   products (one).
 // Per wavefront and step of 4096 x 11008 at 24 rows the loop has 349 vector instructions in the first form and 490 in the second; what
 // is left is latency: two wavefronts per SIMD, loads one step ahead, and the first fetch (behind the first segment: asked for with
 // that one's last step) and last sum of each workgroup.  scales_in_x_ahead has both sides' times.  With two parts of X times the scale
-// (four products) 24 rows took 26.2 us instead of 28.8, but rows of X that are exact in bf16, which the second form does not round,
+// (four products) 24 rows took 26.2 us instead of 28.5, but rows of X that are exact in bf16, which the second form does not round,
 // came out with an error of 3.2e-6 instead of 2.5e-6 (precision 1: 1.9e-3 instead of 1.7e-3); now 0.7e-6 (4 bits), 1.7e-6 (8) and
 // 1.1e-3, 1.2e-3, and for any fp32 X the same instead of 4.4e-6 and 2.3e-3.  (X times the scale below 2^-112 loses bits: 1e-5 where
 // results are 1e-34.)  What did not help: a wavefront per 64 columns and four per step, two steps in flight (twice the loads of X: 29 us

@@ -38,8 +38,8 @@ def test_rows_match_oracle(oracle, m, d, k, cfg, rank):
         assert np.max(np.abs(y - ref) - tol * scale) <= 0, (precision, np.max(np.abs(y - ref) / scale))
 
 
-# (m, d, k, block) with three steps for one wavefront and two for the others: an odd number of 64 columns and one, two and three row tiles, blocks of a
-# tile's columns and more
+# (m, d, k, block) with three steps for one wavefront and two for the others, from which one row tile and 2-bit codes take the scales into
+# X and the others do not: an odd number of 64 columns and one, two and three row tiles, blocks of a tile's columns and more
 @pytest.mark.parametrize("m,d,k,block", [(9, 544, 16448, 64), (24, 544, 16448, 64), (40, 544, 16512, 128), (128, 544, 8256, 64), (17, 544, 16384, 1024)])
 @pytest.mark.parametrize("bits", [2, 3, 4, 8])
 def test_rows_with_scales_in_x(oracle, m, d, k, block, bits):
